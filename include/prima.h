@@ -385,8 +385,8 @@ prima_status prima_layer_window_prefill(const prima_dims *d, const prima_layer *
                                         const float *x_in, float *x_out,
                                         void *workspace, size_t workspace_bytes, void *hip_stream);
 /* The same with every matrix in a format of its own (formats[l], as for prima_layer_window_decode_mixed; null: all
- * Q4_K).  Q4_K matrices go through the matrix product; a matrix in another format is multiplied PRIMA_MAX_TOK tokens a
- * launch by the format mat-vec, so its bytes are read once per 16 prompt tokens.  Same scratch size. */
+ * Q4_K).  Each matrix goes through the matrix product of its format; only FP32, whose weights are not exact in the product's
+ * binary16 operands, is multiplied PRIMA_MAX_TOK tokens a launch by the format mat-vec.  Same scratch size. */
 prima_status prima_layer_window_prefill_mixed(const prima_dims *d, const prima_layer *layers, const prima_layer_formats *formats,
                                               int32_t L, int32_t kv_cap, int32_t n_past, int32_t T,
                                               const float *x_in, float *x_out,

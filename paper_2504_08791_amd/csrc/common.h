@@ -115,6 +115,12 @@ struct GemmMat {
 prima_status launch_q4k_gemm_multi(const GemmMat *mats, int n_mats, bool pair, int64_t n_cols, const float *x, int64_t ldx, int T,
                                    const float *gain, float eps, const float *resid, int64_t ldr, void *ws, hipStream_t st,
                                    bool split_ready = false, void *part = nullptr, size_t part_bytes = 0);
+// the same for one matrix in another format (fmt_gemm.hip), where fmt_gemm_takes(fmt) (all of them but FP32, whose weights
+// are not exact in binary16); split_ready as above: ws may hold the split a Q4_K product of the group made, and vice versa
+bool fmt_gemm_takes(int fmt);
+prima_status launch_fmt_gemm(int fmt, const uint8_t *W, int64_t n_rows, int64_t n_cols, const float *x, int64_t ldx, int T,
+                             const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy,
+                             void *ws, hipStream_t st, bool split_ready, void *part, size_t part_bytes);
 // RoPE table [T][D/2] of (cos, sin) for the positions n_past .. n_past + T - 1 (any T)
 prima_status launch_rope_table(float *tab, int T, int D, int n_past, float theta, hipStream_t st);
 

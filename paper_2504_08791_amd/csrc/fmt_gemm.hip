@@ -1,0 +1,502 @@
+// Matrix product for many tokens with weights in the other formats (Q5_K, Q6_K, Q8_0, FP16): what q4k_gemm.hip is for Q4_K.
+//
+//     y[t][r] = sum_c W[r][c] * a[t][c],   a = x (or RMSNorm(x; gain)),   + resid[t][r] (optional)
+//
+// The activations are those of the Q4_K product (gemm_common.h: two binary16 parts, split once per activation tensor and
+// shared with the group's Q4_K matrices).  The B operand is, per sub-block of 32 weights, as binary16 numbers:
+//   Q5_K  sc_s (q - 16), exact.  The 16 sc_s come back, and the min term is formed, as one MFMA step each on the sub-block
+//         sums of the activations (uncentred, the two sums that nearly cancel are twice as large: error 3.4e-7 against 1.9e-7);
+//   Q6_K  sc_s (q - 32), up to 4096 in magnitude: 13 bits.  Rounded to 11 bits, and the remainder (-1, 0 or 1) as a second
+//         operand that meets the hi parts of the activations alone (its product with the lo parts is 2^-23 of the largest
+//         term and is left out): three MFMAs per step, d per super-block;
+//   Q8_0  q: exact; the sum of a sub-block is multiplied by its d and added;
+//   FP16  the weight itself.
+// Roundings.  A sub-block's MFMAs start from zero, small terms first, and their sum is added to the super-block's: 8 roundings
+// per super-block at its magnitude where one accumulator through all of them would have 16 or 24.  The matrix cores round
+// their fp32 sums towards minus infinity, which over 28672 columns adds up to -2e-7 of the outputs' rms in every output: odd
+// sub-blocks are multiplied as their negatives and subtracted, and it cancels.  The chain of super-blocks is compensated (Kahan;
+// the compensation as bfloat16, two to a register) in all but Q6_K, whose registers are full.
+// Error against 64 bits (2-norm, 256 to 28672 columns, 17 to 1024 tokens) beside that of the fp32 mat-vec: Q5_K 1.4-1.6e-7
+// (2.1-2.3e-7), Q6_K 1.1-2.2e-7 (2.2-2.3e-7), Q8_0 1.0-1.3e-7 (1.1-1.4e-7), FP16 1.0-1.3e-7 (1.1-1.4e-7).
+// What bounds it: at many tokens the matrix cores and the LDS reads that feed them, as in the Q4_K product; at few the weight
+// stream and the length of the position chain.  Before, the prompt call streamed these matrices once per 8 tokens through the
+// fp32 multiply-adds of the mat-vec.  us, this kernel / that: 4096 x 14336 at 17 tokens 52-56 / 148-182, at 64 60 / 570-650, at
+// 333 220-250 / 2800-3250; 8192 x 28672 at 1024 tokens 1360-1570 (307-355 TFLOP/s) / 17700-20500.
+//
+// A workgroup of 4 waves owns 128 rows x 32 WT tokens, a wave 64 rows x 16 WT tokens.  Per position (sub-block) a thread
+// decodes 16 weights of one row for the next position into LDS, where both row halves of the workgroup's waves read them
+// as operands: a weight is decoded once per workgroup, not once per wave.  Activations come by 16-byte global->LDS loads.  Both
+// are double-buffered with one barrier per position; 54 to 74 KiB of LDS, so that two workgroups share a compute unit and one's
+// waits run under the other's matrix instructions.
+#include <algorithm>
+#include <atomic>
+
+#include "gemm_common.h"
+
+namespace prima {
+namespace {
+
+constexpr int FM_THREADS = 256;
+constexpr int FM_ROWS = 128;
+constexpr int FM_RT = 4; // 16-row tiles per wave
+
+struct FmtGemmArgs {
+    const uint8_t *W;
+    int64_t n_rows, n_cols;
+    const uint8_t *A;   // split activations
+    const float2 *stat; // per token: (2^p [* 1/rms], 2^-p)
+    const float *resid;
+    int64_t ldr;
+    float *y;
+    int64_t ldy;
+    int T, n_tiles, n_rb, n_tb;
+    int ksplit; // as in q4k_gemm.hip: shares of K, each share's sums in part[share][token][n_rows]
+    float *part;
+};
+
+// value of the neighbouring lane (lane ^ 1)
+__device__ __forceinline__ unsigned swap1(unsigned v) { return __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0xB1, 0xf, 0xf, true); }
+
+// bytes of the 4-byte words u (weights 0..3) and v (weights 4..7) -> four binary16 pairs (0,4) (1,5) (2,6) (3,7) of 1024 + byte
+__device__ __forceinline__ void bytes_to_pairs(unsigned u, unsigned v, half2v *p)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const unsigned sel = 0x0c040c00u + 0x00010001u * i; // {0, byte i of v, 0, byte i of u}
+        p[i] = __builtin_bit_cast(half2v, __builtin_amdgcn_perm(v, u, sel) | 0x64006400u);
+    }
+}
+
+// what a thread holds of its row's weights: a pair of sub-blocks (2 i, 2 i + 1), of which thread h of the row's two
+// threads loads sub-block 2 i + h (Q5_K, Q6_K: the neighbours exchange halves), or its 16 weights of one sub-block
+template <int FMT> struct Quants;
+template <> struct Quants<PRIMA_FMT_Q5_K> { uint4 lo; unsigned hi; };
+template <> struct Quants<PRIMA_FMT_Q6_K> { uint4 lo; uint2 hi; };
+template <> struct Quants<PRIMA_FMT_Q8_0> { uint4 q; };
+template <> struct Quants<PRIMA_FMT_F16> { uint4 a, b; };
+template <int FMT> constexpr bool fm_pairwise = FMT == PRIMA_FMT_Q5_K || FMT == PRIMA_FMT_Q6_K;
+
+template <int FMT, int WT>
+struct FmLds {
+    static constexpr int A_SLOT = 2 * WT * 2048;            // 2 WT token tiles x (hi, lo) of a sub-block
+    static constexpr int B_PARTS = FMT == PRIMA_FMT_Q6_K ? 2 : 1;
+    static constexpr int B_SLOT = B_PARTS * FM_ROWS * 64;   // [part][16-row tile][lane][16 bytes]
+    static constexpr int B0 = 2 * A_SLOT;
+    static constexpr int D0 = B0 + 2 * B_SLOT;              // d: [2][128] floats (Q8_0: per position; Q5_K: d, dmin)
+    static constexpr int M0 = D0 + 2 * FM_ROWS * 4;         // Q5_K: sums slabs of the tokens, then the m_s and the 16 sc_s of every row
+    static constexpr int TOTAL = FMT == PRIMA_FMT_Q5_K ? M0 + 2 * WT * 1024 + 2 * FM_ROWS * 16 : M0;
+    static_assert(TOTAL <= 81920, "two workgroups per compute unit");
+};
+
+template <int FMT, int WT>
+__global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    typedef FmLds<FMT, WT> L;
+    constexpr bool Q5 = FMT == PRIMA_FMT_Q5_K, Q6 = FMT == PRIMA_FMT_Q6_K, Q8 = FMT == PRIMA_FMT_Q8_0, H = FMT == PRIMA_FMT_F16;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, g = lane >> 4;
+    // consecutive workgroup numbers go to consecutive XCDs: an XCD owns the row blocks xcd, xcd + 8, ... and takes all token
+    // blocks of a row block one after the other, so that the weights come into one L2 only
+    const int xcd = blockIdx.x % GM_XCDS, seq = blockIdx.x / GM_XCDS;
+    const int rb = seq / a.n_tb * GM_XCDS + xcd, tb = seq % a.n_tb;
+    if (rb >= a.n_rb) return; // the whole workgroup, before any barrier
+    const int nb = static_cast<int>(a.n_cols >> 8);
+    const int b_lo = static_cast<int>(static_cast<int64_t>(blockIdx.y) * nb / a.ksplit);
+    const int b_hi = static_cast<int>(static_cast<int64_t>(blockIdx.y + 1) * nb / a.ksplit); // > b_lo: the host keeps ksplit <= nb
+    const int tile0 = tb * 2 * WT;
+    const int wr = wave & 1, wt = wave >> 1; // this wave's half of the rows and of the token tiles
+
+    // ---- this thread's row of the workgroup's weights and its half h (16 weights) of every sub-block ----
+    const int drow = threadIdx.x >> 1, h = threadIdx.x & 1;
+    const int64_t grow = min<int64_t>(static_cast<int64_t>(rb) * FM_ROWS + drow, a.n_rows - 1); // past the end: a valid row, not stored
+    const int64_t blk0 = grow * nb, nblk = a.n_rows * nb;
+    // where its decoded weights go: operand lane (row % 16, g = 2 h and 2 h + 1) of the row's tile
+    uint8_t *const bdst = smem + L::B0 + (drow >> 4) * 1024 + (2 * h * 16 + (drow & 15)) * 16;
+    float *const l_d = reinterpret_cast<float *>(smem + L::D0);
+    uint8_t *const l_xs = smem + L::M0, *const l_m = l_xs + 2 * WT * 1024;
+
+    auto load_quants = [&](Quants<FMT> &q, int b, int s) __attribute__((always_inline)) { // s even where a pair is loaded
+        const int64_t blk = blk0 + b;
+        if constexpr (Q6) {
+            q.lo = *reinterpret_cast<const uint4 *>(a.W + blk * 128 + (s + h) * 16);
+            q.hi = *reinterpret_cast<const uint2 *>(a.W + nblk * 128 + blk * 64 + (s + h) * 8);
+        } else if constexpr (Q5) {
+            q.lo = *reinterpret_cast<const uint4 *>(a.W + nblk * 16 + blk * 128 + (s + h) * 16);
+            q.hi = *reinterpret_cast<const unsigned *>(a.W + nblk * 144 + blk * 32 + (s + h) * 4);
+        } else if constexpr (Q8) {
+            q.q = *reinterpret_cast<const uint4 *>(a.W + blk * 256 + s * 32 + h * 16);
+        } else {
+            q.a = *reinterpret_cast<const uint4 *>(a.W + blk * 512 + s * 64 + h * 32);
+            q.b = *reinterpret_cast<const uint4 *>(a.W + blk * 512 + s * 64 + h * 32 + 16);
+        }
+    };
+    // scales of a super-block: Q5_K its header, Q6_K sixteen sub-scales (and d beside them), Q8_0 eight d
+    auto load_header = [&](uint4 &hd, unsigned &hx, int b) __attribute__((always_inline)) {
+        const int64_t blk = blk0 + b;
+        if constexpr (Q5) hd = *reinterpret_cast<const uint4 *>(a.W + blk * 16);
+        if constexpr (Q6) {
+            hd = *reinterpret_cast<const uint4 *>(a.W + nblk * 192 + blk * 16);
+            hx = *reinterpret_cast<const unsigned short *>(a.W + nblk * 208 + blk * 2);
+        }
+        if constexpr (Q8) hd = *reinterpret_cast<const uint4 *>(a.W + nblk * 256 + blk * 16);
+    };
+    auto h2f = [](unsigned v) { return __half2float(__ushort_as_half(static_cast<unsigned short>(v & 0xffffu))); };
+    auto word = [](const uint4 &v, int i) __attribute__((always_inline)) { return i == 0 ? v.x : (i == 1 ? v.y : (i == 2 ? v.z : v.w)); };
+
+    // this thread's 16 weights of sub-block s as operand bytes in buffer `buf`; of an odd sub-block their negatives, whose sums
+    // are subtracted (see the top of the file)
+    auto decode = [&](const Quants<FMT> &q, const uint4 &hd, unsigned hx, int s, int buf) __attribute__((always_inline)) {
+        half2v hi[8], lo[8];
+        if constexpr (Q5 || Q6) {
+            // thread s & 1 of the row holds the sub-block; its neighbour takes its own half from there
+            const bool own = (s & 1) == h;
+            unsigned w0, w1;
+            if ((s & 1) == 0) {
+                const unsigned t0 = swap1(q.lo.z), t1 = swap1(q.lo.w);
+                w0 = own ? q.lo.x : t0; w1 = own ? q.lo.y : t1;
+            } else {
+                const unsigned t0 = swap1(q.lo.x), t1 = swap1(q.lo.y);
+                w0 = own ? q.lo.z : t0; w1 = own ? q.lo.w : t1;
+            }
+            unsigned u[4];
+            if constexpr (Q6) {
+                unsigned hb;
+                if ((s & 1) == 0) { const unsigned t = swap1(q.hi.y); hb = own ? q.hi.x : t; }
+                else { const unsigned t = swap1(q.hi.x); hb = own ? q.hi.y : t; }
+                u[0] = (w0 & 0x0F0F0F0Fu) | ((hb << 4) & 0x30303030u);
+                u[1] = ((w0 >> 4) & 0x0F0F0F0Fu) | ((hb << 2) & 0x30303030u);
+                u[2] = (w1 & 0x0F0F0F0Fu) | (hb & 0x30303030u);
+                u[3] = ((w1 >> 4) & 0x0F0F0F0Fu) | ((hb >> 2) & 0x30303030u);
+            } else {
+                const unsigned t = swap1(q.hi);
+                const unsigned hb = (own ? q.hi : t) >> (4 * h); // bits 4 h .. 4 h + 3 of every byte: this half's groups of four
+                u[0] = (w0 & 0x0F0F0F0Fu) | ((hb << 4) & 0x10101010u);
+                u[1] = ((w0 >> 4) & 0x0F0F0F0Fu) | ((hb << 3) & 0x10101010u);
+                u[2] = (w1 & 0x0F0F0F0Fu) | ((hb << 2) & 0x10101010u);
+                u[3] = ((w1 >> 4) & 0x0F0F0F0Fu) | ((hb << 1) & 0x10101010u);
+            }
+            bytes_to_pairs(u[0], u[1], hi);
+            bytes_to_pairs(u[2], u[3], hi + 4);
+            if constexpr (Q6) {
+                const unsigned w = word(hd, s >> 1);
+                const int sc = static_cast<int>(w << (24 - 16 * (s & 1) - 8 * h)) >> 24; // byte 2 s + h, signed
+                const _Float16 f = static_cast<_Float16>(static_cast<float>(s & 1 ? -sc : sc));
+                const half2v sc2 = {f, f}, off = {static_cast<_Float16>(-1056.f), static_cast<_Float16>(-1056.f)};
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const half2v v = hi[i] + off; // q - 32, exact
+                    hi[i] = v * sc2;              // rounded to 11 bits
+                    lo[i] = __builtin_elementwise_fma(v, sc2, -hi[i]); // the remainder, exact
+                }
+            } else {
+                const float fs = static_cast<float>(hdr_field(hd, s));
+                const _Float16 f = static_cast<_Float16>(s & 1 ? -fs : fs);
+                const half2v sc2 = {f, f}, off = {static_cast<_Float16>(-1040.f), static_cast<_Float16>(-1040.f)};
+#pragma unroll
+                for (int i = 0; i < 8; ++i) hi[i] = (hi[i] + off) * sc2; // (q - 16) sc: both steps exact
+            }
+        } else if constexpr (Q8) {
+            bytes_to_pairs(q.q.x ^ 0x80808080u, q.q.y ^ 0x80808080u, hi);
+            bytes_to_pairs(q.q.z ^ 0x80808080u, q.q.w ^ 0x80808080u, hi + 4);
+            const half2v off = {static_cast<_Float16>(-1152.f), static_cast<_Float16>(-1152.f)};
+#pragma unroll
+            for (int i = 0; i < 8; ++i) hi[i] = s & 1 ? -off - hi[i] : hi[i] + off;
+        } else {
+            // numbers 0..7 as pairs (0,4) (1,5) (2,6) (3,7)
+            const unsigned neg = s & 1 ? 0x80008000u : 0u;
+            const unsigned v[8] = {q.a.x ^ neg, q.a.y ^ neg, q.a.z ^ neg, q.a.w ^ neg, q.b.x ^ neg, q.b.y ^ neg, q.b.z ^ neg, q.b.w ^ neg};
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    hi[4 * c + i] = __builtin_bit_cast(half2v, __builtin_amdgcn_perm(v[4 * c + 2 + (i >> 1)], v[4 * c + (i >> 1)],
+                                                                                     (i & 1) ? 0x07060302u : 0x05040100u));
+        }
+        uint8_t *dst = bdst + buf * L::B_SLOT;
+        auto store = [&](uint8_t *to, const half2v *p) __attribute__((always_inline)) {
+            *reinterpret_cast<uint4 *>(to) = make_uint4(__builtin_bit_cast(unsigned, p[0]), __builtin_bit_cast(unsigned, p[1]),
+                                                        __builtin_bit_cast(unsigned, p[2]), __builtin_bit_cast(unsigned, p[3]));
+        };
+        store(dst, hi);
+        store(dst + 256, hi + 4);
+        if constexpr (Q6) {
+            store(dst + FM_ROWS * 64, lo);
+            store(dst + FM_ROWS * 64 + 256, lo + 4);
+        }
+        if constexpr (Q8) {
+            const unsigned w = word(hd, s >> 1);
+            if (h == 0) l_d[buf * FM_ROWS + drow] = h2f(s & 1 ? w >> 16 : w);
+        }
+    };
+    // what the fold of a super-block needs of its rows: d (Q6_K), d, dmin and the m_s (Q5_K)
+    auto put_scales = [&](const uint4 &hd, unsigned hx) __attribute__((always_inline)) {
+        if constexpr (Q6) {
+            if (h == 0) l_d[drow] = h2f(hx);
+        }
+        if constexpr (Q5) {
+            if (h == 0) {
+                l_d[drow] = hdr_d(hd);
+                l_d[FM_ROWS + drow] = hdr_dmin(hd);
+                half8 m, c;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    m[i] = static_cast<_Float16>(static_cast<float>(hdr_field(hd, 8 + i)));
+                    c[i] = static_cast<_Float16>(static_cast<float>(16 * hdr_field(hd, i)));
+                }
+                *reinterpret_cast<half8 *>(l_m + drow * 16) = m;
+                *reinterpret_cast<half8 *>(l_m + (FM_ROWS + drow) * 16) = c;
+            }
+        }
+    };
+
+    // ---- activation requests: 4 WT slabs of 1 KiB per position, WT per wave; a sums slab per token tile (Q5_K) ----
+    const uint32_t lds0 = lds_address(smem), lane16 = lane * 16;
+    const uint8_t *abase[WT];
+#pragma unroll
+    for (int j = 0; j < WT; ++j) {
+        const int slab = wave * WT + j, tile = min(tile0 + (slab >> 1), a.n_tiles - 1); // past the last tile: a valid one, not stored
+        abase[j] = a.A + (static_cast<int64_t>(tile) * nb * GM_SLABS + (slab & 1)) * 1024;
+    }
+    auto issue = [&](int b, int s, int buf) __attribute__((always_inline)) {
+        const int64_t off = (static_cast<int64_t>(b) * GM_SLABS + 2 * s) * 1024;
+#pragma unroll
+        for (int j = 0; j < WT; ++j) dma16_base(abase[j] + off, lane16, lds0 + buf * L::A_SLOT + (wave * WT + j) * 1024);
+    };
+    auto issue_sums = [&](int b) __attribute__((always_inline)) {
+        if constexpr (Q5) {
+#pragma unroll
+            for (int j = wave; j < 2 * WT; j += 4) {
+                const int tile = min(tile0 + j, a.n_tiles - 1);
+                dma16_base(a.A + ((static_cast<int64_t>(tile) * nb + b) * GM_SLABS + 16) * 1024, lane16, lds0 + L::M0 + j * 1024);
+            }
+        }
+    };
+
+    gm_v4f acc[WT][FM_RT], ysum[WT][FM_RT];
+    const gm_v4f zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int tt = 0; tt < WT; ++tt)
+#pragma unroll
+        for (int rt = 0; rt < FM_RT; ++rt) acc[tt][rt] = ysum[tt][rt] = zero;
+    unsigned comp[Q6 ? 1 : WT][FM_RT][2] = {}; // Kahan's compensation of ysum, bfloat16 pairs
+
+    // prologue: position 0's activations and decoded weights, the quants after it, the header
+    uint4 hd, hd_next;
+    unsigned hx = 0, hx_next = 0;
+    Quants<FMT> qc, qn;
+    issue(b_lo, 0, 0);
+    load_header(hd, hx, b_lo);
+    load_quants(qc, b_lo, 0);
+    if constexpr (fm_pairwise<FMT>) load_quants(qn, b_lo, 2);
+    else load_quants(qn, b_lo, 1);
+    decode(qc, hd, hx, 0, 0);
+    hd_next = hd; hx_next = hx;
+
+    for (int b = b_lo; b < b_hi; ++b) {
+        const bool more = b + 1 < b_hi;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const int buf = s & 1;
+            // everything requested at the position before has landed; everyone has written its operands of this position
+            // and is done with the buffers of the one before
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            gm_barrier();
+            if (s < 7 || more) issue(s < 7 ? b : b + 1, (s + 1) & 7, buf ^ 1);
+            if (s == 6) issue_sums(b);
+            if (s == 0) put_scales(hd, hx);
+            // quants of the next position (requested a pair, or a position, ahead), and the request after them
+            if constexpr (fm_pairwise<FMT>) {
+                if (s & 1) {
+                    qc = qn;
+                    const int s2 = (s + 3) & 7; // the pair behind the one that is decoded next
+                    if (s + 3 < 8 || more) load_quants(qn, s + 3 < 8 ? b : b + 1, s2);
+                }
+            } else {
+                qc = qn;
+                if (s + 2 < 8 || more) load_quants(qn, s + 2 < 8 ? b : b + 1, (s + 2) & 7);
+            }
+            if (s == 5 && more) load_header(hd_next, hx_next, b + 1);
+            if (s < 7) decode(qc, hd, hx, s + 1, buf ^ 1);
+            else if (more) decode(qc, hd_next, hx_next, 0, buf ^ 1);
+
+            const uint8_t *ab = smem + buf * L::A_SLOT + wt * (WT * 2048) + lane * 16;
+            const uint8_t *bb = smem + L::B0 + buf * L::B_SLOT + wr * 4096 + lane * 16;
+            half8 B[FM_RT], Bl[FM_RT];
+#pragma unroll
+            for (int rt = 0; rt < FM_RT; ++rt) {
+                B[rt] = *reinterpret_cast<const half8 *>(bb + rt * 1024);
+                if constexpr (Q6) Bl[rt] = *reinterpret_cast<const half8 *>(bb + FM_ROWS * 64 + rt * 1024);
+            }
+            float ds[FM_RT];
+            if constexpr (Q8) {
+#pragma unroll
+                for (int rt = 0; rt < FM_RT; ++rt) ds[rt] = l_d[buf * FM_ROWS + wr * 64 + rt * 16 + n];
+            }
+#pragma unroll
+            for (int tt = 0; tt < WT; ++tt) {
+                const half8 ah = *reinterpret_cast<const half8 *>(ab + tt * 2048);
+                const half8 al = *reinterpret_cast<const half8 *>(ab + tt * 2048 + 1024);
+#pragma unroll
+                for (int rt = 0; rt < FM_RT; ++rt) {
+                    gm_v4f c = zero;
+                    if constexpr (Q6) c = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, Bl[rt], c, 0, 0, 0);
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, B[rt], c, 0, 0, 0);
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, B[rt], c, 0, 0, 0);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float ci = s & 1 ? -c[i] : c[i];
+                        if constexpr (Q8) acc[tt][rt][i] = s == 0 ? ds[rt] * ci : fmaf(ds[rt], ci, acc[tt][rt][i]);
+                        else acc[tt][rt][i] = s == 0 ? ci : acc[tt][rt][i] + ci;
+                    }
+                }
+                // the sums are made here (the compiler would move products and additions into the next position's block, where
+                // they are used, and spill their operands), tile by tile
+#pragma unroll
+                for (int rt = 0; rt < FM_RT; ++rt) asm volatile("" : "+v"(acc[tt][rt]));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (s == 7) { // the super-block's term is formed at its own magnitude and added in one step
+#pragma unroll
+                for (int rt = 0; rt < FM_RT; ++rt) {
+                    const int r = wr * 64 + rt * 16 + n;
+                    float d = 1.f, dm = 0.f;
+                    half8 m = {}, sc16 = {};
+                    if constexpr (Q5 || Q6) d = l_d[r];
+                    if constexpr (Q5) {
+                        dm = l_d[FM_ROWS + r];
+                        m = *reinterpret_cast<const half8 *>(l_m + r * 16);
+                        sc16 = *reinterpret_cast<const half8 *>(l_m + (FM_ROWS + r) * 16);
+                    }
+#pragma unroll
+                    for (int tt = 0; tt < WT; ++tt) {
+                        gm_v4f am = zero, t = acc[tt][rt];
+                        if constexpr (Q5) {
+                            // the sums slabs were requested a position ago by all waves and have landed before this position's barrier
+                            const half8 ax = *reinterpret_cast<const half8 *>(l_xs + (wt * WT + tt) * 1024 + lane * 16);
+                            am = __builtin_amdgcn_mfma_f32_16x16x32_f16(ax, m, zero, 0, 0, 0);
+                            t = __builtin_amdgcn_mfma_f32_16x16x32_f16(ax, sc16, t, 0, 0, 0);
+                        }
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            if constexpr (Q6) {
+                                ysum[tt][rt][i] = fmaf(d, t[i], ysum[tt][rt][i]);
+                            } else {
+                                const float term = Q5 ? fmaf(d, t[i], -(dm * am[i])) : t[i];
+                                unsigned &cw = comp[tt][rt][i >> 1];
+                                const float c0 = __builtin_bit_cast(float, i & 1 ? cw & 0xffff0000u : cw << 16);
+                                const float v = term - c0, yn = ysum[tt][rt][i] + v;
+                                const unsigned cn = __builtin_bit_cast(unsigned, (yn - ysum[tt][rt][i]) - v); // (cut off: its error is 2^-8 of it)
+                                cw = i & 1 ? (cw & 0xffffu) | (cn & 0xffff0000u) : (cw & 0xffff0000u) | cn >> 16;
+                                ysum[tt][rt][i] = yn;
+                            }
+                        }
+                    }
+                }
+            }
+        }
+        hd = hd_next;
+        hx = hx_next;
+    }
+
+#pragma unroll
+    for (int rt = 0; rt < FM_RT; ++rt) {
+        const int64_t row = static_cast<int64_t>(rb) * FM_ROWS + wr * 64 + rt * 16 + n;
+        if (row >= a.n_rows) continue;
+#pragma unroll
+        for (int tt = 0; tt < WT; ++tt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int t = (tile0 + wt * WT + tt) * 16 + 4 * g + i;
+                if (t < a.T) {
+                    float v = ysum[tt][rt][i] * a.stat[t].y;
+                    if (a.ksplit > 1) {
+                        a.part[(static_cast<int64_t>(blockIdx.y) * a.T + t) * a.n_rows + row] = v;
+                    } else {
+                        if (a.resid) v += a.resid[t * a.ldr + row];
+                        a.y[t * a.ldy + row] = v;
+                    }
+                }
+            }
+    }
+}
+
+// y = the shares of K added in order (+ resid)
+__global__ void __launch_bounds__(256) fmt_gemm_reduce_kernel(FmtGemmArgs a)
+{
+    const int64_t row = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const int t = blockIdx.y;
+    if (row >= a.n_rows) return;
+    float v = a.part[static_cast<int64_t>(t) * a.n_rows + row];
+    for (int ks = 1; ks < a.ksplit; ++ks) v += a.part[(static_cast<int64_t>(ks) * a.T + t) * a.n_rows + row];
+    if (a.resid) v += a.resid[t * a.ldr + row];
+    a.y[t * a.ldy + row] = v;
+}
+
+template <int FMT, int WT>
+prima_status launch_wt(const FmtGemmArgs &a, unsigned grid, hipStream_t st)
+{
+    static std::atomic<bool> attr_set{false}; // set twice by two threads at worst: the attribute call is idempotent
+    if (!attr_set) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(fmt_gemm_kernel<FMT, WT>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                FmLds<FMT, WT>::TOTAL) != hipSuccess)
+            return PRIMA_E_DEVICE;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL((fmt_gemm_kernel<FMT, WT>), dim3(grid, a.ksplit), dim3(FM_THREADS), (FmLds<FMT, WT>::TOTAL), st, a);
+    return last_launch_status();
+}
+
+template <int FMT>
+prima_status launch_fm(FmtGemmArgs a, void *part, size_t part_bytes, hipStream_t st)
+{
+    // 128 tokens per workgroup, 64 where that leaves fewer tokens of padding or twice the workgroups on an idle device
+    const bool narrow = (a.n_tiles + 3) / 4 * 4 < (a.n_tiles + 7) / 8 * 8 || static_cast<int64_t>(a.n_rb) * ((a.n_tiles + 7) / 8) * 2 <= 2 * GM_CUS;
+    a.n_tb = narrow ? (a.n_tiles + 3) / 4 : (a.n_tiles + 7) / 8;
+    const int64_t wgs = static_cast<int64_t>(a.n_rb) * a.n_tb, slots = 2 * GM_CUS;
+    const int64_t nb = a.n_cols / QK;
+    // shares of K: as the Q4_K product divides it (at least 4 super-blocks each), as far as the scratch holds the shares
+    a.ksplit = 1;
+    if (part && a.T <= 65535 && wgs * 2 <= slots) {
+        const int64_t room = static_cast<int64_t>(part_bytes / (static_cast<size_t>(a.T) * static_cast<size_t>(a.n_rows) * sizeof(float)));
+        a.ksplit = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({slots / wgs, nb / 4, 16, room})));
+    }
+    a.part = static_cast<float *>(part);
+    const int64_t grid = (a.n_rb + GM_XCDS - 1) / GM_XCDS * static_cast<int64_t>(GM_XCDS) * a.n_tb;
+    if (grid >= (int64_t{1} << 31)) return PRIMA_E_SHAPE;
+    const prima_status s = narrow ? launch_wt<FMT, 2>(a, static_cast<unsigned>(grid), st) : launch_wt<FMT, 4>(a, static_cast<unsigned>(grid), st);
+    if (s != PRIMA_OK || a.ksplit == 1) return s;
+    hipLaunchKernelGGL(fmt_gemm_reduce_kernel, dim3(static_cast<unsigned>((a.n_rows + 255) / 256), a.T), dim3(256), 0, st, a);
+    return last_launch_status();
+}
+
+} // namespace
+
+bool fmt_gemm_takes(int fmt) { return fmt == PRIMA_FMT_Q5_K || fmt == PRIMA_FMT_Q6_K || fmt == PRIMA_FMT_Q8_0 || fmt == PRIMA_FMT_F16; }
+
+prima_status launch_fmt_gemm(int fmt, const uint8_t *W, int64_t n_rows, int64_t n_cols, const float *x, int64_t ldx, int T,
+                             const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy,
+                             void *ws, hipStream_t st, bool split_ready, void *part, size_t part_bytes)
+{
+    if (T == 0 || n_rows == 0) return PRIMA_OK;
+    const int64_t n_rb = (n_rows + FM_ROWS - 1) / FM_ROWS;
+    const int n_tiles = (T + 15) / 16;
+    if (n_rb >= (int64_t{1} << 30) || n_tiles > 65535 || n_cols / QK >= (int64_t{1} << 31)) return PRIMA_E_SHAPE;
+    if (!split_ready) {
+        const prima_status s = launch_gemm_split(n_cols, x, ldx, T, gain, eps, ws, st);
+        if (s != PRIMA_OK) return s;
+    }
+    FmtGemmArgs a{};
+    a.W = W; a.n_rows = n_rows; a.n_cols = n_cols; a.A = gemm_split(ws, T); a.stat = gemm_stat(ws);
+    a.resid = resid; a.ldr = ldr; a.y = y; a.ldy = ldy; a.T = T; a.n_tiles = n_tiles; a.n_rb = static_cast<int>(n_rb);
+    switch (fmt) {
+    case PRIMA_FMT_Q5_K: return launch_fm<PRIMA_FMT_Q5_K>(a, part, part_bytes, st);
+    case PRIMA_FMT_Q6_K: return launch_fm<PRIMA_FMT_Q6_K>(a, part, part_bytes, st);
+    case PRIMA_FMT_Q8_0: return launch_fm<PRIMA_FMT_Q8_0>(a, part, part_bytes, st);
+    case PRIMA_FMT_F16: return launch_fm<PRIMA_FMT_F16>(a, part, part_bytes, st);
+    default: return PRIMA_E_SHAPE;
+    }
+}
+
+} // namespace prima

@@ -1,0 +1,44 @@
+// What the matrix products for many tokens share (q4k_gemm.hip, fmt_gemm.hip): the layout of the split activations and
+// the loads and barriers of their pipelines.
+#pragma once
+#include "common.h"
+
+namespace prima {
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef float gm_v4f __attribute__((ext_vector_type(4)));
+
+// Split activations: [token tile of 16][super-block][17 slabs][64 lanes] x 16 bytes; slabs 2 s and 2 s + 1 are the hi and lo
+// parts of sub-block s (lane (m, g): token m, columns 8g .. 8g+7 of the sub-block in the order 0 4 1 5 2 6 3 7), slab 16
+// the sub-block sums (lane (m, 0) their hi parts, lane (m, 1) their lo parts).
+constexpr int GM_SLABS = 17;
+constexpr int GM_TILE_BYTES = GM_SLABS * 1024;
+constexpr size_t GM_STAT_ALIGN = 1024;
+constexpr int GM_XCDS = 8;
+constexpr int GM_CUS = 256;
+
+// the split activations and the per-token (2^p [* 1/rms], 2^-p) inside the scratch of gemm_ws_bytes(T, n_cols)
+inline float2 *gemm_stat(void *ws) { return static_cast<float2 *>(ws); }
+inline uint8_t *gemm_split(void *ws, int T)
+{
+    return static_cast<uint8_t *>(ws) + round_up(static_cast<size_t>(T) * sizeof(float2), GM_STAT_ALIGN);
+}
+// fills both (two launches)
+prima_status launch_gemm_split(int64_t n_cols, const float *x, int64_t ldx, int T, const float *gain, float eps, void *ws, hipStream_t st);
+
+// 16 bytes per lane from global memory straight into LDS (as dma16), with the address as a wave-uniform base plus a
+// 32-bit lane offset: the bases live in scalar registers and cost no vector register per request in flight
+__device__ __forceinline__ void dma16_base(const void *sbase, uint32_t lane_off, uint32_t lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_off), "s"(sbase), "s"(lds_addr) : "memory");
+}
+
+// workgroup barrier that orders LDS traffic only (__syncthreads() would also wait for every global load in flight,
+// that is, for the whole ring of requests)
+__device__ __forceinline__ void gm_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+} // namespace prima

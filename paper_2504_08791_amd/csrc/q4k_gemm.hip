@@ -30,14 +30,12 @@
 #include <atomic>
 #include <type_traits>
 
-#include "common.h"
+#include "gemm_common.h"
 
 namespace prima {
 namespace {
 
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-typedef float v4f __attribute__((ext_vector_type(4)));
+typedef gm_v4f v4f;
 
 constexpr int GM_THREADS = 256;
 constexpr int GM_WAVES = GM_THREADS / 64;       // one wave per SIMD and workgroup
@@ -45,22 +43,17 @@ constexpr int GM_RT = 4;                        // 16-row tiles per wave
 constexpr int GM_TT = 4;                        // 16-token tiles per workgroup
 constexpr int GM_ROWS = 16 * GM_RT * GM_WAVES;  // rows per workgroup
 constexpr int GM_TM = 16 * GM_TT;               // tokens per workgroup
-constexpr int GM_SLABS = 17;                    // per (token tile, super-block): 8 sub-blocks x (hi, lo), sums
-constexpr int GM_TILE_BYTES = GM_SLABS * 1024;
 constexpr int GM_NS = 3;                        // ring slots: positions whose activations are in LDS or on their way (a divisor
                                                 // of the 9 positions of a super-block: the slot of a position is a constant; 4
                                                 // and 5 slots measured the same)
 constexpr int GM_SLOT = GM_TT * 2048;                                     // 8 KiB of activations
 constexpr int GM_WQ = 2 * 4096;                                           // per wave: the quants of half a super-block, twice
 constexpr int GM_LDS_BYTES = GM_NS * GM_SLOT + GM_WAVES * (GM_WQ + 2 * 1024); // 64 KiB: two workgroups per compute unit
-constexpr int GM_XCDS = 8;
-constexpr int GM_CUS = 256;
 // Workgroups that share an XCD at a time: a patch of 4 row blocks x 8 token blocks; with fewer than 8 token blocks all of
 // them and more row blocks, with few row blocks per XCD only those.  A workgroup number that falls outside the matrix
 // costs its dispatch (about 0.1 us): with one token block and patches of 4 x 8, seven numbers in eight were idle and a
 // launch took no less than 260 us whatever its work.
 constexpr int GM_PATCH = 32, GM_PATCH_C = 8;
-constexpr size_t GM_STAT_ALIGN = 1024;
 
 struct GemmSegDev {
     const uint8_t *W;
@@ -193,13 +186,7 @@ __global__ void __launch_bounds__(256) gemm_split_kernel(const float *__restrict
     }
 }
 
-// 16 bytes per lane from global memory straight into LDS (as dma16), with the address as a wave-uniform base plus a
-// 32-bit lane offset: the bases live in scalar registers and cost no vector register per request in flight
-__device__ __forceinline__ void dma16_base(const void *sbase, uint32_t lane_off, uint32_t lds_addr)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_off), "s"(sbase), "s"(lds_addr) : "memory");
-}
-// ... and with a per-lane pointer plus a constant byte offset (0 .. 4095) in the instruction.  The instruction adds
+// dma16_base with a per-lane pointer plus a constant byte offset (0 .. 4095) in the instruction instead.  The instruction adds
 // its offset to the LDS address as well as to the global one, so M0 gets the LDS address less the offset.
 template <int OFF>
 __device__ __forceinline__ void dma16_off(const void *gptr, uint32_t lds_addr)
@@ -229,13 +216,6 @@ static_assert(GM_AHEAD != 4 ||
                    requests_behind(7, true) == 6 && requests_behind(8, true) == 10 && requests_behind(8, false) == 6),
               "request counts of the product kernel's schedule");
 static_assert(GM_AHEAD >= 2 && GM_AHEAD <= 4, "the weight requests at s == 3, 4, 7 must be older than the activation requests a wait lets pass");
-
-// workgroup barrier that orders LDS traffic only (__syncthreads() would also wait for every global load in flight,
-// that is, for the whole ring of requests below)
-__device__ __forceinline__ void gm_barrier()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
 
 // One workgroup: 4 waves, one per SIMD; a wave owns 64 rows (four B tiles) x 64 tokens, i.e. 16 accumulator tiles for the
 // super-block in hand and as many running sums; two workgroups share a compute unit (237 registers per wave, 64 KiB of
@@ -646,6 +626,17 @@ size_t gemm_ws_bytes(int T, int64_t n_cols)
     return round_up(static_cast<size_t>(T) * sizeof(float2), GM_STAT_ALIGN) + tiles * static_cast<size_t>(n_cols / QK) * GM_TILE_BYTES;
 }
 
+prima_status launch_gemm_split(int64_t n_cols, const float *x, int64_t ldx, int T, const float *gain, float eps, void *ws, hipStream_t st)
+{
+    const int64_t nb = n_cols / QK;
+    const int n_tiles = (T + 15) / 16;
+    if (n_tiles > 65535 || nb >= (int64_t{1} << 31)) return PRIMA_E_SHAPE;
+    hipLaunchKernelGGL(gemm_token_scale_kernel, dim3(T), dim3(256), 0, st, x, ldx, n_cols, gain, eps, gemm_stat(ws));
+    hipLaunchKernelGGL(gemm_split_kernel, dim3(static_cast<unsigned>(nb), n_tiles), dim3(256), 0, st, x, ldx, gain, gemm_stat(ws), T, nb,
+                       gemm_split(ws, T));
+    return last_launch_status();
+}
+
 prima_status launch_q4k_gemm_multi(const GemmMat *mats, int n_mats, bool pair, int64_t n_cols, const float *x, int64_t ldx, int T,
                                    const float *gain, float eps, const float *resid, int64_t ldr, void *ws, hipStream_t st, bool split_ready,
                                    void *part, size_t part_bytes)
@@ -679,12 +670,12 @@ prima_status launch_q4k_gemm_multi(const GemmMat *mats, int n_mats, bool pair, i
             return PRIMA_E_DEVICE;
         attr_set = true;
     }
-    float2 *stat = static_cast<float2 *>(ws);
-    uint8_t *A = static_cast<uint8_t *>(ws) + round_up(static_cast<size_t>(T) * sizeof(float2), GM_STAT_ALIGN);
+    const float2 *stat = gemm_stat(ws);
+    const uint8_t *A = gemm_split(ws, T);
     // split_ready: ws holds the split of these very activations (the call before this one had the same x, gain, eps, T)
     if (!split_ready) {
-        hipLaunchKernelGGL(gemm_token_scale_kernel, dim3(T), dim3(256), 0, st, x, ldx, n_cols, gain, eps, stat);
-        hipLaunchKernelGGL(gemm_split_kernel, dim3(static_cast<unsigned>(nb), n_tiles), dim3(256), 0, st, x, ldx, gain, stat, T, nb, A);
+        const prima_status ps = launch_gemm_split(n_cols, x, ldx, T, gain, eps, ws, st);
+        if (ps != PRIMA_OK) return ps;
     }
     a.pair = pair ? 1 : 0;
     a.n_cols = n_cols; a.A = A; a.stat = stat; a.resid = resid; a.ldr = ldr;

@@ -268,9 +268,8 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
                                const float *x, float *y, void *ws, const PrefillWs &w, hipStream_t st,
                                const prima_layer_formats *fm = nullptr)
 {
-    // fm: formats of the seven matrices (null: all Q4_K).  Q4_K matrices go through the matrix product; a matrix in
-    // another format through the format mat-vec, PRIMA_MAX_TOK tokens a launch (there is no matrix-core kernel for those
-    // formats: a model that keeps a few tensors in them pays their weight stream once per 16 tokens)
+    // fm: formats of the seven matrices (null: all Q4_K).  Each goes through the matrix product of its format; FP32 (whose
+    // weights are not exact in the product's binary16 operands) through the format mat-vec, PRIMA_MAX_TOK tokens a launch
     const int f_q = fm ? fm->wq : 0, f_k = fm ? fm->wk : 0, f_v = fm ? fm->wv : 0, f_o = fm ? fm->wo : 0;
     const int f_g = fm ? fm->wgate : 0, f_u = fm ? fm->wup : 0, f_d = fm ? fm->wdown : 0;
     const int64_t e = d.e, qd = static_cast<int64_t>(d.n_q_heads) * d.head_dim, kvd = static_cast<int64_t>(d.n_kv_heads) * d.head_dim, F = d.ffn;
@@ -286,6 +285,9 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
         if (fmt == PRIMA_FMT_Q4_K)
             return launch_q4k_gemm(W(Wm), rows, cols, xin, cols, T, gain, d.rms_eps, resid, rows, out, rows, stat, st, split_ready, part,
                                    w.part_bytes);
+        if (fmt_gemm_takes(fmt))
+            return launch_fmt_gemm(fmt, W(Wm), rows, cols, xin, cols, T, gain, d.rms_eps, resid, rows, out, rows, stat, st, split_ready, part,
+                                   w.part_bytes);
         for (int t0 = 0; t0 < T; t0 += PRIMA_MAX_TOK) {
             const int Tc = std::min<int>(PRIMA_MAX_TOK, T - t0);
             const prima_status ps = launch_fmt_gemv(fmt, W(Wm), rows, cols, xin + t0 * cols, cols, Tc, gain, d.rms_eps,
@@ -299,11 +301,12 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
         const GemmMat qkv[3] = {{W(L.wq), q, qd, qd}, {W(L.wk), k, kvd, kvd}, {W(L.wv), v, kvd, kvd}};
         PRIMA_TRY(launch_q4k_gemm_multi(qkv, 3, false, e, x, e, T, g_attn, d.rms_eps, nullptr, 0, stat, st, false, part, w.part_bytes));
     } else {
-        bool ready = false; // the first Q4_K matrix of the group splits the activations for the others
+        auto splits = [](int f) { return f == PRIMA_FMT_Q4_K || fmt_gemm_takes(f); };
+        bool ready = false; // the first matrix of the group that goes through a matrix product splits the activations for the others
         PRIMA_TRY(product(f_q, L.wq, qd, e, x, g_attn, nullptr, q, ready));
-        ready = ready || f_q == PRIMA_FMT_Q4_K;
+        ready = ready || splits(f_q);
         PRIMA_TRY(product(f_k, L.wk, kvd, e, x, g_attn, nullptr, k, ready));
-        ready = ready || f_k == PRIMA_FMT_Q4_K;
+        ready = ready || splits(f_k);
         PRIMA_TRY(product(f_v, L.wv, kvd, e, x, g_attn, nullptr, v, ready));
     }
     // RoPE and the cache rows of all T tokens first; then the full pieces of PRIMA_MAX_TOK tokens in one launch and the
@@ -322,7 +325,7 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
     } else {
         float *up = at<float>(ws, w.u);
         PRIMA_TRY(product(f_g, L.wgate, F, e, h, g_ffn, nullptr, act, false));
-        PRIMA_TRY(product(f_u, L.wup, F, e, h, g_ffn, nullptr, up, f_g == PRIMA_FMT_Q4_K));
+        PRIMA_TRY(product(f_u, L.wup, F, e, h, g_ffn, nullptr, up, f_g == PRIMA_FMT_Q4_K || fmt_gemm_takes(f_g)));
         PRIMA_TRY(launch_swiglu(act, up, static_cast<int64_t>(T) * F, st));
     }
     PRIMA_TRY(product(f_d, L.wdown, e, F, act, nullptr, h, y, false));

@@ -133,6 +133,51 @@ def test_prefill_with_mixed_formats(gpu_lib, route, mix, name, T, n_past):
     assert rel_err(g[:, n_past:n_past + T].reshape(1, -1), r[:, n_past:n_past + T].reshape(1, -1)) < 1e-3
 
 
+def _centred(rng, fmt, rows, cols):
+    """A matrix of mean about zero and standard deviation about 0.02: every quant uniform, Q4_K / Q5_K sub-mins that put the
+    middle of the quants' range at zero on average."""
+    W = synth.fmt_tensor(7, 0, int(rng.integers(1 << 20)), fmt, rows, cols)
+    n = rows * cols // 256
+    if fmt == "f16":
+        return (0.02 * rng.standard_normal(rows * cols)).astype(np.float16).view(np.uint8)
+    size, mean = {"q4_k": (n, 4e-5), "q5_k": (n, 2e-5), "q6_k": (n, 1.5e-5), "q8_0": (8 * n, 2.7e-4)}[fmt]
+    d = (mean * (0.5 + rng.random(size))).astype(np.float16)
+    if fmt in ("q4_k", "q5_k"):
+        head = W.reshape(n, 144) if fmt == "q4_k" else W[:16 * n].reshape(n, 16)
+        head[:, 0:2] = d.view(np.uint8).reshape(n, 2)
+        head[:, 2:4] = (d.astype(np.float32) * (7.5 if fmt == "q4_k" else 15.5)).astype(np.float16).view(np.uint8).reshape(n, 2)
+    else:
+        W[-2 * size:] = d.view(np.uint8)
+    return W
+
+
+@pytest.mark.parametrize("T", [17, 64, 65, 129, 490])
+@pytest.mark.parametrize("fmt", ["q5_k", "q6_k", "q8_0", "f16"])
+def test_products_of_the_other_formats_agree_with_the_mat_vec(gpu_lib, fmt, T):
+    """One layer with all seven matrices in one format, as one prompt call (matrix product: 64- and 128-token workgroups, ragged
+    last ones, rows ragged against 128, K divided and whole) and as decode calls of 16 tokens (fp32 mat-vec, which the oracle
+    tests cover).  The products are within 2.3e-7 of 64 bits either way; a token that appends a K / V value which rounds to the
+    other fp16 neighbour may move by up to the hidden-state bar, the others must not."""
+    from workloads.configs import ModelDims
+    d = ModelDims(2560, 20, 5, 128, 8448, 1e5)
+    rng = np.random.default_rng(T)
+    shapes = {"wq": (d.qd, d.e), "wk": (d.kvd, d.e), "wv": (d.kvd, d.e), "wo": (d.e, d.qd), "wgate": (d.ffn, d.e), "wup": (d.ffn, d.e),
+              "wdown": (d.e, d.ffn)}
+    t = {k: _dev(_centred(rng, fmt, *shapes[k])) for k in shapes}
+    n_past, cap = 64, 64 + T
+    t["g_attn"], t["g_ffn"] = (_dev((1 + 0.1 * rng.standard_normal(d.e)).astype(np.float32)) for _ in range(2))
+    kv = [_dev(rng.standard_normal((d.n_kv_heads, cap, d.head_dim)).astype(np.float16)) for _ in range(2)]
+    x = _dev(rng.standard_normal((T, d.e)).astype(np.float32))
+    fm = [{k: fmt for k in shapes}]
+    wins = [gpu_lib.Window(d, [dict(t, k_cache=kv[0].clone(), v_cache=kv[1].clone())], cap, formats=fm) for _ in range(2)]
+    print("case", fmt, T, flush=True)
+    got = wins[0].prefill(x, n_past)
+    assert torch.equal(got, wins[0].prefill(x, n_past))
+    ref = torch.cat([wins[1].decode(x[i:i + 16].contiguous(), n_past + i) for i in range(0, T, 16)]).cpu().numpy().astype(np.float64)
+    per_token = [rel_err(got[i].cpu().numpy(), ref[i]) for i in range(T)]
+    assert max(per_token) < HID_TOL and float(np.median(per_token)) < 2e-5, (max(per_token), float(np.median(per_token)))
+
+
 def test_prefill_then_decode_continues(gpu_lib, route):
     """A prompt through the prefill call, the next token through the decode call: against the oracle doing the same."""
     cfg = TINY["t1"].with_(T=40, n_past=0)
