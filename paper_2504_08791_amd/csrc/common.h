@@ -83,6 +83,11 @@ prima_status launch_fmt_dequant(int fmt, const uint8_t *W, int64_t n_rows, int64
 prima_status launch_fmt_gemv(int fmt, const uint8_t *W, int64_t n_rows, int64_t n_cols, const float *x, int64_t ldx, int T,
                              const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy, hipStream_t st);
 
+// 2 to 16 tokens in the formats whose weights are exact in binary16 operands (tok_gemv.hip); launch_fmt_gemv goes there
+bool tok_gemv_takes(int fmt, int64_t n_rows, int64_t n_cols, int T);
+prima_status launch_tok_gemv(int fmt, const uint8_t *W, int64_t n_rows, int64_t n_cols, const float *x, int64_t ldx, int T,
+                             const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy, hipStream_t st);
+
 prima_status launch_dequant(const uint8_t *W, int64_t n_rows, int64_t n_cols, float *out, hipStream_t st);
 // ws: scratch; its first arrivals_region bytes (>= gemv_arrivals_bytes(rows)) are counters that must be
 // zero before the first launch (launch_zero_arrivals) and are left zero by every launch; the partial

@@ -16,8 +16,8 @@
 // With the fields in planes every lane's load is aligned to its size and a wave's loads are contiguous,
 // whatever the block size (210 and 34 bytes per block otherwise); the bytes per weight are the formats' own.
 //
-// Mat-vec design: HBM-bound streaming with fp32 vector arithmetic (no matrix cores: one to eight tokens leave
-// them nothing to contract).  One workgroup of 16 waves per compute unit keeps the activations in LDS (up to
+// Mat-vec design: HBM-bound streaming with fp32 vector arithmetic, for one token and where tok_gemv_takes() leaves several to
+// it (few tokens or few rows; FP32 always).  One workgroup of 16 waves per compute unit keeps the activations in LDS (up to
 // 128 KB: all of K for one token up to K = 32768; otherwise K is walked in chunks and y accumulates chunk by
 // chunk), with the RMSNorm gain already applied: read from L2 by every wave they cost as much bandwidth as
 // the weights (measured: every quantised format stuck at the same 4.6 T weights/s, FP16 alone reached the
@@ -400,23 +400,26 @@ prima_status launch_fmt(FmtArgs a, hipStream_t st)
     const float *x = a.x, *resid = a.resid;
     float *y = a.y;
     const int T = a.T;
-    for (int t0 = 0; t0 < T; t0 += FG_MAX_T) {
-        const int Tp = T - t0 < FG_MAX_T ? T - t0 : FG_MAX_T;
+    constexpr int PASS = FMT == PRIMA_FMT_F32 ? FG_MAX_T : 4; // (5 and more tokens: FP32 only, the others go to tok_gemv.hip)
+    for (int t0 = 0; t0 < T; t0 += PASS) {
+        const int Tp = T - t0 < PASS ? T - t0 : PASS;
         a.x = x + t0 * a.ldx;
         a.resid = resid ? resid + t0 * a.ldr : nullptr;
         a.y = y + t0 * a.ldy;
         a.T = Tp;
         prima_status s;
-        switch (Tp) {
-        case 1: s = launch_tt<FMT, 1>(a, st); break;
-        case 2: s = launch_tt<FMT, 2>(a, st); break;
-        case 3: s = launch_tt<FMT, 3>(a, st); break;
-        case 4: s = launch_tt<FMT, 4>(a, st); break;
-        case 5: s = launch_tt<FMT, 5>(a, st); break;
-        case 6: s = launch_tt<FMT, 6>(a, st); break;
-        case 7: s = launch_tt<FMT, 7>(a, st); break;
-        default: s = launch_tt<FMT, 8>(a, st); break;
-        }
+        if (Tp == 1) s = launch_tt<FMT, 1>(a, st);
+        else if (Tp == 2) s = launch_tt<FMT, 2>(a, st);
+        else if (Tp == 3) s = launch_tt<FMT, 3>(a, st);
+        else if (Tp == 4) s = launch_tt<FMT, 4>(a, st);
+        else if constexpr (FMT == PRIMA_FMT_F32) {
+            switch (Tp) {
+            case 5: s = launch_tt<FMT, 5>(a, st); break;
+            case 6: s = launch_tt<FMT, 6>(a, st); break;
+            case 7: s = launch_tt<FMT, 7>(a, st); break;
+            default: s = launch_tt<FMT, 8>(a, st); break;
+            }
+        } else s = PRIMA_E_SHAPE; // (not reached)
         if (s != PRIMA_OK) return s;
     }
     return PRIMA_OK;
@@ -460,6 +463,7 @@ prima_status launch_fmt_gemv(int fmt, const uint8_t *W, int64_t n_rows, int64_t 
                              const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy, hipStream_t st)
 {
     if (n_rows == 0) return PRIMA_OK;
+    if (tok_gemv_takes(fmt, n_rows, n_cols, T)) return launch_tok_gemv(fmt, W, n_rows, n_cols, x, ldx, T, gain, eps, resid, ldr, y, ldy, st);
     FmtArgs a{W, n_rows, n_cols, x, ldx, gain, eps, resid, ldr, y, ldy, T, 0};
     switch (fmt) {
     case PRIMA_FMT_Q5_K: return launch_fmt<PRIMA_FMT_Q5_K>(a, st);

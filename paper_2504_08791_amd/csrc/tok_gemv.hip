@@ -1,0 +1,324 @@
+// Mat-vec of 2 to 16 tokens for weights in the other formats (Q5_K, Q6_K, Q8_0, FP16), without scratch: the kernel behind
+// prima_fmt_gemv and prima_lm_head_fmt for several tokens (one token: fmt_gemv.hip).  Arithmetic and layouts: tok_common.h.
+//
+// One workgroup of 8 waves per compute unit.  It owns a share of the 16-row tiles and walks all of K in chunks: the
+// activations of a chunk (all tokens) are normalised, split and laid out in LDS by the workgroup, then the waves stream
+// their units (a tile, or with few tiles a part of the chunk of one) against them; a unit's sums stay in LDS from chunk to
+// chunk.  The weight stream runs ahead by two stages in registers and does not stop between chunks.  1 / rms multiplies the
+// finished sums, so that no pass over the activations is needed in front.
+//
+// What bounds it: the output layer 128256 x 8192 in Q6_K at 8 tokens takes 203 us (4.2 TB/s of weights; the fp32 mat-vec took
+// 514 to 578): its stream alone, products left out, 156 us; its products alone, requests left out, 178 us (200 vector
+// instructions a super-block and tile, and the latencies of its LDS reads and matrix instructions under two waves a SIMD).
+// FP16 and Q8_0, with little to unpack, run at 6.1 and 5.9 TB/s.  Sixteen waves of half the stage were slower (253 us: fields
+// of 2 to 64 bytes a row and stage are then fetched twice as often).
+#include <algorithm>
+#include <atomic>
+#include <type_traits>
+
+#include "tok_common.h"
+
+namespace prima {
+namespace {
+
+struct TokArgs {
+    const uint8_t *W;
+    int64_t n_rows;
+    int nb; // super-blocks of a row
+    const float *x;
+    int64_t ldx;
+    const float *gain; // null: plain activations
+    float eps;
+    const float *resid; // null: none
+    int64_t ldr;
+    float *y;
+    int64_t ldy;
+    int T;
+    int n_tiles;  // 16-row tiles
+    int chunk;    // super-blocks per chunk of K (a multiple of the stage's)
+    int ks_shift; // a unit is one of 2^ks_shift parts of a (tile, chunk)
+    // Rounds: in each every wave has one unit at most.  Round k covers tiles [n_tiles k / rounds, n_tiles (k + 1) / rounds), dealt
+    // to the workgroups one by one (a run of neighbouring tiles for each was measured 3 to 10 % slower: the requests of the
+    // device then crowd on fewer memory channels).
+    int rounds, blk_rounds; // in all; whose sums are in LDS at a time
+};
+
+// LDS: the waves' stage buffers | operands [chunk] | sums [chunk] | 2^-p [chunk][NT] | sums of squares [chunk][NT] | 1/rms [NT] |
+// units' sums [blk_rounds][waves][NT][16]
+template <int FMT, int NT>
+__global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64, TkFmt<FMT>::WAVES / 4) tok_gemv_kernel(TokArgs a)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    constexpr int SBS = TkFmt<FMT>::SBS, WAVES = TkFmt<FMT>::WAVES, THREADS = WAVES * 64;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, g = lane >> 4;
+    uint8_t *const l_stage = smem + wave * tk_stage_bytes<FMT>;
+    uint8_t *const l_a = smem + WAVES * tk_stage_bytes<FMT>;
+    uint8_t *const l_sums = l_a + a.chunk * tk_a_bytes(NT);
+    float *const l_inv = reinterpret_cast<float *>(l_sums + a.chunk * tk_sum_bytes(NT));
+    float *const l_ss = l_inv + a.chunk * NT;
+    float *const l_rms = l_ss + a.chunk * NT;
+    float *const l_acc = l_rms + NT;
+
+    const int ks_shift = a.ks_shift, ks = 1 << ks_shift, nb = a.nb, chunk = a.chunk;
+    const int my_l = wave >> ks_shift, part = wave & (ks - 1); // this wave's tile of a round's and its part
+    // tiles of round k: this workgroup's are first + i * gridDim.x, i < count
+    auto share = [&](int k, int &first, int &count) __attribute__((always_inline)) {
+        const int t0 = static_cast<int>(static_cast<int64_t>(a.n_tiles) * k / a.rounds), nt = static_cast<int>(static_cast<int64_t>(a.n_tiles) * (k + 1) / a.rounds) - t0;
+        first = t0 + static_cast<int>(blockIdx.x);
+        count = (nt + static_cast<int>(gridDim.x) - 1 - static_cast<int>(blockIdx.x)) / static_cast<int>(gridDim.x);
+    };
+    // the first round from k on in which this wave has a tile (k_end: none), and the tile
+    auto next_round = [&](int k, int k_end, int &tile) __attribute__((always_inline)) {
+        for (; k < k_end; ++k) {
+            int first, count;
+            share(k, first, count);
+            if (my_l < count) { tile = first + my_l * static_cast<int>(gridDim.x); break; }
+        }
+        return k;
+    };
+    // stages [s0, s1) of the chunk of `len` super-blocks are this wave's part (never empty: the host keeps ks <= a chunk's stages)
+    auto part_of = [&](int len, int &s0, int &s1) __attribute__((always_inline)) {
+        const int stages = (len + SBS - 1) / SBS;
+        s0 = (stages * part) >> ks_shift;
+        s1 = (stages * (part + 1)) >> ks_shift;
+    };
+
+    for (int k0 = 0; k0 < a.rounds; k0 += a.blk_rounds) {
+        const int k_end = min(k0 + a.blk_rounds, a.rounds);
+        int n_active = 0; // rounds in which this wave has a tile
+        {
+            int tile;
+            for (int k = next_round(k0, k_end, tile); k < k_end; k = next_round(k + 1, k_end, tile)) ++n_active;
+        }
+        // The requesting side of the wave's stream of stages: chunk by chunk, round by round, stage by stage.  A wave's stages of
+        // a chunk come in pairs, one for each of its two sets of registers (so that the loads in flight behind a set are the
+        // same on every path and the compiler's wait in front of its use leaves them out): an odd number is padded with a
+        // stage that is requested again and not used; so is whatever is requested past the end.
+        TkSrc<FMT> src;
+        int ld_sb0 = 0, ld_len = min(chunk, nb), ld_k = k0 - 1, ld_b = 0, ld_left = 0, ld_step = SBS;
+        bool ld_padded = false;
+        auto ld_next = [&]() __attribute__((always_inline)) { // a unit has been requested to its end
+            for (;;) {
+                int s0, s1;
+                part_of(ld_len, s0, s1);
+                if (!ld_padded) {
+                    int tile;
+                    const int k = next_round(ld_k + 1, k_end, tile);
+                    if (k < k_end) {
+                        ld_k = k;
+                        ld_b = ld_sb0 + s0 * SBS;
+                        ld_left = s1 - s0;
+                        tk_tile<FMT>(src, a.W, a.n_rows, nb, static_cast<int64_t>(tile) * 16, lane);
+                        return;
+                    }
+                    if (((s1 - s0) * n_active) & 1) { ld_padded = true; ld_b -= ld_step; ld_left = 1; return; }
+                }
+                if (ld_sb0 + ld_len >= nb) { ld_b -= ld_step; ld_step = 0; ld_left = 0x7fffffff; return; }
+                ld_sb0 += ld_len;
+                ld_len = min(chunk, nb - ld_sb0);
+                ld_k = k0 - 1;
+                ld_padded = false;
+            }
+        };
+        TkRegs<FMT> r0, r1;
+        auto request = [&](TkRegs<FMT> &r) __attribute__((always_inline)) {
+            tk_load<FMT>(r, src, max(min(ld_b, nb - SBS), 0)); // (the last stage of an odd number of super-blocks: its second one)
+            ld_b += ld_step;
+            if (--ld_left == 0) ld_next();
+        };
+
+        float ss_run = 0.f; // sum of squares of token threadIdx.x
+        for (int i = threadIdx.x; i < (k_end - k0) * WAVES * NT * 16; i += THREADS) l_acc[i] = 0.f;
+        if (n_active != 0) { // (else this wave has nothing to request in any chunk)
+            ld_next();
+            request(r0);
+            request(r1);
+        }
+
+        for (int sb0 = 0; sb0 < nb; sb0 += chunk) {
+            const int nsb = min(chunk, nb - sb0);
+            __syncthreads(); // the previous chunk's operands have been used (and the sums' region is clear)
+            for (int p0 = 0; p0 < nsb * NT; p0 += WAVES * 4) {
+                const int pi = p0 + wave * 4 + g;
+                const int t = pi & (NT - 1), b = pi / NT;
+                if (b < nsb) {
+                    float v[16], ss = 0.f;
+                    const bool real = t < a.T;
+                    const int64_t col = static_cast<int64_t>(sb0 + b) * 256 + n * 16;
+                    const float *xp = a.x + (real ? t : 0) * a.ldx + col;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const float4 q = *reinterpret_cast<const float4 *>(xp + 4 * k);
+                        v[4 * k] = q.x; v[4 * k + 1] = q.y; v[4 * k + 2] = q.z; v[4 * k + 3] = q.w;
+                    }
+                    if (!real) {
+#pragma unroll
+                        for (int k = 0; k < 16; ++k) v[k] = 0.f;
+                    }
+                    if (a.gain) {
+#pragma unroll
+                        for (int k = 0; k < 16; ++k) ss += v[k] * v[k];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const float4 q = *reinterpret_cast<const float4 *>(a.gain + col + 4 * k);
+                            v[4 * k] *= q.x; v[4 * k + 1] *= q.y; v[4 * k + 2] *= q.z; v[4 * k + 3] *= q.w;
+                        }
+                        ss = row_sum16(ss);
+                        if (n == 0) l_ss[b * NT + t] = ss;
+                    }
+                    tk_split<NT, TkFmt<FMT>::ORD>(v, n, t, l_a + b * tk_a_bytes(NT), l_sums + b * tk_sum_bytes(NT), l_inv + b * NT + t);
+                }
+            }
+            __syncthreads();
+            if (a.gain && threadIdx.x < NT) {
+                for (int b = 0; b < nsb; ++b) ss_run += l_ss[b * NT + threadIdx.x];
+                if (sb0 + nsb == nb) l_rms[threadIdx.x] = 1.0f / sqrtf(ss_run / (static_cast<float>(nb) * 256.f) + a.eps);
+            }
+            // ---- this wave's stages of the chunk ----
+            int s0, s1;
+            part_of(nsb, s0, s1);
+            const int total = (s1 - s0) * n_active;
+            int tile, k = next_round(k0, k_end, tile), s = s0;
+            float y[4] = {0.f, 0.f, 0.f, 0.f};
+            auto consume = [&](TkRegs<FMT> &r, bool real, auto second) __attribute__((always_inline)) {
+                tk_put<FMT>(r, l_stage, lane);
+                request(r);
+                if (real) {
+                    auto mul = [&](int slot, int b, auto odd) __attribute__((always_inline)) {
+                        tk_mul<FMT, NT, decltype(odd)::value>(l_stage, slot, l_a + b * tk_a_bytes(NT), l_sums + b * tk_sum_bytes(NT), l_inv + b * NT, lane, y);
+                    };
+                    if constexpr (SBS == 1) {
+                        mul(0, s, second);
+                    } else if (2 * s + 1 < nsb) {
+                        mul(0, 2 * s, std::false_type{});
+                        mul(1, 2 * s + 1, std::true_type{});
+                    } else {
+                        mul(nb == 1 ? 0 : 1, 2 * s, std::false_type{});
+                    }
+                    if (++s == s1) { // the unit ends: its sums of this chunk (lanes past the token slots repeat others)
+                        float *dst = l_acc + ((k - k0) * WAVES + wave) * (NT * 16) + n;
+                        constexpr int NY = NT <= 8 ? 2 : 4;
+                        if (NT >= 8 || g < NT / 2) {
+#pragma unroll
+                            for (int i = 0; i < NY; ++i) dst[(NY * g + i) * 16] += y[i];
+                        }
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) y[i] = 0.f;
+                        s = s0;
+                        k = next_round(k + 1, k_end, tile);
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+                asm volatile("" ::: "memory");
+            };
+            for (int i = 0; i < total; i += 2) {
+                consume(r0, true, std::false_type{});
+                consume(r1, i + 1 < total, std::true_type{});
+            }
+        }
+        __syncthreads();
+        // ---- a unit's parts in order, 1/rms, the residual ----
+        for (int k = k0; k < k_end; ++k) {
+            int first, count;
+            share(k, first, count);
+            const int n_out = count * 16 * a.T;
+            for (int idx = threadIdx.x; idx < n_out; idx += THREADS) {
+                const int l = idx / (16 * a.T), rem = idx - l * (16 * a.T), t = rem >> 4, j = rem & 15;
+                const int64_t row = (first + static_cast<int64_t>(l) * gridDim.x) * 16 + j;
+                if (row >= a.n_rows) continue;
+                const float *u = l_acc + ((k - k0) * WAVES + (l << ks_shift)) * (NT * 16) + t * 16 + j;
+                float v = u[0];
+                for (int p = 1; p < ks; ++p) v += u[p * (NT * 16)];
+                if (a.gain) v *= l_rms[t];
+                if (a.resid) v += a.resid[t * a.ldr + row];
+                a.y[t * a.ldy + row] = v;
+            }
+        }
+        __syncthreads(); // the sums' region and 1/rms are used again
+    }
+}
+
+template <int FMT, int NT>
+prima_status launch_nt(TokArgs a, hipStream_t st)
+{
+    static std::atomic<bool> attr_set{false}; // set twice by two threads at worst: the attribute call is idempotent
+    if (!attr_set) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(tok_gemv_kernel<FMT, NT>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                static_cast<int>(TK_LDS)) != hipSuccess)
+            return PRIMA_E_DEVICE;
+        attr_set = true;
+    }
+    constexpr int SBS = TkFmt<FMT>::SBS, WAVES = TkFmt<FMT>::WAVES;
+    constexpr size_t per_sb = tk_a_bytes(NT) + tk_sum_bytes(NT) + 8 * NT, fixed = WAVES * tk_stage_bytes<FMT> + NT * 4;
+    const int grid = std::min(a.n_tiles, TK_CUS);
+    // Parts of a unit: with few tiles the waves share them (what the longest wave has to do counts); the sums of a workgroup's
+    // units take at most 32 KiB, more rounds than that are worked off in blocks, each with a walk over K of its own.
+    constexpr int ROUND_BYTES = WAVES * NT * 64, MAX_BLK = 32 * 1024 / ROUND_BYTES;
+    double best = 0.;
+    for (int sh = 0; (1 << sh) <= WAVES; ++sh) {
+        const int64_t per_round = static_cast<int64_t>(grid) * (WAVES >> sh);
+        const int rounds = static_cast<int>((a.n_tiles + per_round - 1) / per_round), blk = std::min(rounds, MAX_BLK);
+        int chunk = static_cast<int>((TK_LDS - fixed - static_cast<size_t>(blk) * ROUND_BYTES) / per_sb) / SBS * SBS;
+        const int n_chunks = (a.nb + chunk - 1) / chunk;
+        chunk = ((a.nb + n_chunks - 1) / n_chunks + SBS - 1) / SBS * SBS;
+        const int last = a.nb - (a.nb - 1) / chunk * chunk; // super-blocks of the last chunk
+        if (sh > 0 && (1 << sh) > (last + SBS - 1) / SBS) continue; // every part of every chunk has a stage
+        // a chunk costs its operands (about two stages' time) and, round by round, the longest part
+        const double t = static_cast<double>(n_chunks) * (2.0 * ((rounds + blk - 1) / blk) + rounds * static_cast<double>((chunk / SBS + (1 << sh) - 1) >> sh));
+        if (sh == 0 || t < best * 0.999) {
+            best = t;
+            a.ks_shift = sh;
+            a.rounds = rounds;
+            a.blk_rounds = blk;
+            a.chunk = chunk;
+        }
+    }
+    const size_t lds = fixed + static_cast<size_t>(a.chunk) * per_sb + static_cast<size_t>(a.blk_rounds) * ROUND_BYTES;
+    if (lds > TK_LDS || a.chunk < SBS) return PRIMA_E_SHAPE; // (does not happen: the smallest chunk fits beside the largest sums)
+    hipLaunchKernelGGL((tok_gemv_kernel<FMT, NT>), dim3(grid), dim3(WAVES * 64), lds, st, a);
+    return last_launch_status();
+}
+
+template <int FMT>
+prima_status launch_fmt(const TokArgs &a, hipStream_t st)
+{
+    if (a.T <= 2) return launch_nt<FMT, 2>(a, st);
+    if (a.T <= 4) return launch_nt<FMT, 4>(a, st);
+    if (a.T <= 8) return launch_nt<FMT, 8>(a, st);
+    return launch_nt<FMT, 16>(a, st);
+}
+
+} // namespace
+
+// Where the line lies, us, this kernel / the fp32 mat-vec (start of the measurement: 128256 x 8192 with the norm in front):
+//   Q6_K 128256 x 8192   2 tokens 204 / 201, 3: 197 / 223, 4: 195 / 266, 8: 203 / 578, 16: 297 / 1113
+//   Q8_0 128256 x 8192   2 tokens 183 / 181, 3: 183 / 201, 4: 182 / 246, 8: 191 / 506, 16: 264 / 972
+//   Q6_K 8192 x 28672    2 tokens  61 / 60,  3: 71 / 66,   4: 71 / 80,   8: 106 / 150, 16: 179 / 312
+//   Q8_0 8192 x 28672    2 tokens  58 / 50,  3: 72 / 58,   4: 71 / 70,   8: 118 / 126, 16: 153 / 264
+//   Q6_K 5120 x 13824    2 tokens  33 / 30,  3: 41 / 33,   4: 41 / 38,   8: 52 / 71,   16: 106 / 141
+// With few rows every workgroup prepares all of the activations for a tile or two; the mat-vec keeps what it is faster at.
+bool tok_gemv_takes(int fmt, int64_t n_rows, int64_t n_cols, int T)
+{
+    if (fmt != PRIMA_FMT_Q5_K && fmt != PRIMA_FMT_Q6_K && fmt != PRIMA_FMT_Q8_0 && fmt != PRIMA_FMT_F16) return false;
+    if (T < 2 || T > PRIMA_MAX_TOK || n_cols / QK >= (1 << 18) || n_rows >= (int64_t{1} << 34)) return false; // (32-bit offsets in a tile's 16 rows, 32-bit tile numbers)
+    return T >= 5 || n_rows >= 65536 || (T == 4 && n_rows >= 8192);
+}
+
+prima_status launch_tok_gemv(int fmt, const uint8_t *W, int64_t n_rows, int64_t n_cols, const float *x, int64_t ldx, int T,
+                             const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy, hipStream_t st)
+{
+    TokArgs a{};
+    a.W = W; a.n_rows = n_rows; a.nb = static_cast<int>(n_cols / QK); a.x = x; a.ldx = ldx; a.gain = gain; a.eps = eps;
+    a.resid = resid; a.ldr = ldr; a.y = y; a.ldy = ldy; a.T = T; a.n_tiles = static_cast<int>((n_rows + 15) / 16);
+    switch (fmt) {
+    case PRIMA_FMT_Q5_K: return launch_fmt<PRIMA_FMT_Q5_K>(a, st);
+    case PRIMA_FMT_Q6_K: return launch_fmt<PRIMA_FMT_Q6_K>(a, st);
+    case PRIMA_FMT_Q8_0: return launch_fmt<PRIMA_FMT_Q8_0>(a, st);
+    case PRIMA_FMT_F16: return launch_fmt<PRIMA_FMT_F16>(a, st);
+    default: return PRIMA_E_SHAPE;
+    }
+}
+
+} // namespace prima

@@ -241,3 +241,24 @@ def test_batch_of_sequences_with_mixed_formats(gpu_lib, name):
                 got = dev_caches[l][b][i][:, lens[b]].float().cpu().numpy().reshape(1, -1)
                 want = caches[l][b][i][:, lens[b]].astype(np.float64).reshape(1, -1)
                 assert rel_err(got, want) < 2e-3
+
+
+@pytest.mark.parametrize("fmt", ["q5_k", "q6_k", "q8_0", "f16"])
+@pytest.mark.parametrize("rows,cols,tokens", [(65551, 256, (2, 3)),   # a tile of 15 rows at the end, rows of one super-block
+                                              (8199, 1280, (4,)),     # an odd number of super-blocks, 7 rows over
+                                              (17, 9 * 256, (5, 8)),  # two tiles: parts of a unit
+                                              (131105, 256, (9, 16))])  # more rounds than sums fit LDS
+def test_matrix_core_matvec_edges(gpu_lib, fmt, rows, cols, tokens):
+    """The several-token kernel at the edges of its tiles, parts, chunks and rounds, rows sampled from both ends and between."""
+    rng = np.random.default_rng(11)
+    W = _rand_tensor(rng, fmt, rows, cols)
+    Wd = _dev(W)
+    pick = np.unique(np.concatenate([np.arange(min(rows, 40)), np.arange(max(0, rows - 40), rows), rng.integers(0, rows, 40)]))
+    w = gpu_lib.fmt_dequant(fmt, Wd, rows, cols)[torch.from_numpy(pick).cuda()].cpu().numpy().astype(np.float64)
+    for T in tokens:
+        x = rng.standard_normal((T, cols)).astype(np.float32) * np.logspace(-3, 3, T, dtype=np.float32)[:, None]
+        got = gpu_lib.fmt_gemv(fmt, Wd, rows, cols, _dev(x)).cpu().numpy()
+        again = gpu_lib.fmt_gemv(fmt, Wd, rows, cols, _dev(x)).cpu().numpy()
+        assert np.array_equal(got, again)
+        ref = x.astype(np.float64) @ w.T
+        assert rel_err(got[:, pick], ref) <= GEMV_TOL, (fmt, rows, T)
