@@ -1,4 +1,4 @@
-// Mat-vecs of 2 to 16 tokens on the matrix cores: what their kernels share (tok_gemv.hip).  The activations as binary16
+// Mat-vecs of 2 to 16 tokens on the matrix cores: what their kernels share (tok_gemv.hip, tok_stream.hip).  The activations as binary16
 // operands in LDS, the weight stream of a wave, and the products of one super-block of 16 rows with all tokens.
 //
 // Arithmetic.  A weight becomes a binary16 number in a register (sub-scale times quant, exact; Q6_K, 13 bits: two numbers, the
@@ -33,18 +33,21 @@ typedef unsigned tk_v4u __attribute__((ext_vector_type(4)));
 constexpr int TK_CUS = 256;
 constexpr size_t TK_LDS = 160 * 1024;
 
-// LDS bytes of the activations of one super-block for NT token slots: operands | sub-block sums | 2^-p per token
-constexpr int tk_a_bytes(int nt) { return nt * 1024; }
-constexpr int tk_sum_bytes(int nt) { return nt * 32; }
+// The activations of one super-block for NT token slots, a record: operands | sub-block sums | 2^-p per token
+constexpr int tk_sums_at(int nt) { return nt * 1024; }
+constexpr int tk_inv_at(int nt) { return nt * 1056; }
+constexpr int tk_rec(int nt) { return nt * 1056 + (nt < 4 ? 16 : nt * 4); }
+constexpr int tk_slots(int T) { return T <= 2 ? 2 : (T <= 4 ? 4 : (T <= 8 ? 8 : 16)); }
 
 // ---- activations -> operands ----------------------------------------------------------------------------------------
-// Sixteen lanes hold one token's super-block, lane i columns 16 i .. 16 i + 15 in v (RMSNorm gain applied).  ORD: the order of
+// Sixteen lanes hold one token's super-block, lane i columns 16 i .. 16 i + 15 in v (RMSNorm gain applied); into the record.  ORD: the order of
 // a slice's 8 columns in the operand: 0: 0 4 1 5 2 6 3 7 (Q4_K's nibbles), 1: 0 2 1 3 4 6 5 7 (bytes).
 // A 16-byte piece (8 columns of one row) c = 4 S + j, S the sub-block, j the slice, lies at a[c][row ^ f(c)], f(c) = (c >> 1) & 15:
 // the sixteen lanes write pieces whose rows would otherwise share their banks.
 template <int NT, int ORD>
-__device__ __forceinline__ void tk_split(const float (&v)[16], int i, int t, uint8_t *a, uint8_t *sums, float *inv)
+__device__ __forceinline__ void tk_split(const float (&v)[16], int i, int t, uint8_t *rec)
 {
+    uint8_t *const a = rec, *const sums = rec + tk_sums_at(NT);
     constexpr int MR = NT <= 8 ? 2 * NT : 16; // rows (of one part with 16 tokens)
     float amax = 0.f;
 #pragma unroll
@@ -56,14 +59,16 @@ __device__ __forceinline__ void tk_split(const float (&v)[16], int i, int t, uin
     p = p > 120 ? 120 : (p < -120 ? -120 : p);
     const float S = ldexpf(1.0f, p);
     _Float16 hh[16], ll[16];
-    float sum = 0.f;
+    // The sum of what the products will see: hi parts (whose sum is exact or nearly so) and lo parts on their own
+    float sum = 0.f, suml = 0.f;
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
         float sv = v[k] * S;
         asm volatile("" : "+v"(sv)); // one rounded number for hi and lo (see gemm_split_kernel)
         hh[k] = static_cast<_Float16>(sv);
         ll[k] = static_cast<_Float16>(sv - static_cast<float>(hh[k]));
-        sum += static_cast<float>(hh[k]) + static_cast<float>(ll[k]); // what the products will see
+        sum += static_cast<float>(hh[k]);
+        suml += static_cast<float>(ll[k]);
     }
 #pragma unroll
     for (int gi = 0; gi < 2; ++gi) {
@@ -86,9 +91,10 @@ __device__ __forceinline__ void tk_split(const float (&v)[16], int i, int t, uin
     }
     // the sub-block's sum (this lane and its neighbour), as hi + lo; [part (16 tokens)][S & 3][row][S >> 2]
     sum += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sum), 0xB1, 0xf, 0xf, true));
+    suml += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, suml), 0xB1, 0xf, 0xf, true));
     if ((i & 1) == 0) {
         const int S8 = i >> 1;
-        const _Float16 sh = static_cast<_Float16>(sum), sl = static_cast<_Float16>(sum - static_cast<float>(sh));
+        const _Float16 sh = static_cast<_Float16>(sum + suml), sl = static_cast<_Float16>((sum - static_cast<float>(sh)) + suml);
         _Float16 *q = reinterpret_cast<_Float16 *>(sums);
         if constexpr (NT <= 8) {
             q[((S8 & 3) * MR + 2 * t) * 2 + (S8 >> 2)] = sh;
@@ -98,7 +104,7 @@ __device__ __forceinline__ void tk_split(const float (&v)[16], int i, int t, uin
             q[((4 + (S8 & 3)) * 16 + t) * 2 + (S8 >> 2)] = sl;
         }
     }
-    if (i == 0) *inv = ldexpf(1.0f, -p);
+    if (i == 0) reinterpret_cast<float *>(rec + tk_inv_at(NT))[t] = ldexpf(1.0f, -p);
 }
 
 // ---- the weight stream of a wave --------------------------------------------------------------------------------------
@@ -301,10 +307,12 @@ __device__ __forceinline__ float tk_h2f(unsigned v) { return __half2float(__usho
 __device__ __forceinline__ unsigned tk_sel(unsigned m, unsigned a, unsigned b) { return (a & m) | (b & ~m); }
 
 // y[i] += the super-block's share: tokens 2 g' + i (NT <= 8, g' = g modulo the token pairs) or 4 g + i of row n.
-// stage: the wave's buffer; b: super-block of the stage; ODD: multiplied as its negative; a, sums, inv: the activations
+// stage: the wave's buffer; b: super-block of the stage; ODD: multiplied as its negative; a: the activations' record
 template <int FMT, int NT, bool ODD>
-__device__ __forceinline__ void tk_mul(const uint8_t *stage, int b, const uint8_t *a, const uint8_t *sums, const float *inv, int lane, float *y)
+__device__ __forceinline__ void tk_mul(const uint8_t *stage, int b, const uint8_t *a, int lane, float *y)
 {
+    const uint8_t *const sums = a + tk_sums_at(NT);
+    const float *const inv = reinterpret_cast<const float *>(a + tk_inv_at(NT));
     constexpr int RS = TkFmt<FMT>::RS, SBS = TkFmt<FMT>::SBS;
     constexpr int MR = NT <= 8 ? 2 * NT : 16, PS = NT <= 8 ? MR : 32; // rows of a part, rows between pieces
     constexpr int NY = NT <= 8 ? 2 : 4;
@@ -468,18 +476,23 @@ __device__ __forceinline__ void tk_mul(const uint8_t *stage, int b, const uint8_
             }
         }
     }
-    tk_v4f am = zero;
+    tk_v4f ac = zero, am = zero;
     if constexpr (Q4 || Q5) {
         tk_v4u xs = {0u, 0u, 0u, 0u};
-        xs[0] = *reinterpret_cast<const unsigned *>(sums + (g * MR + (n & (MR - 1))) * 4);
-        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(tk_half8, xs), Bc, acc[0], 0, 0, 0);
-        am = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(tk_half8, xs), Bm, am, 0, 0, 0);
         if constexpr (NT > 8) {
             xs[0] = *reinterpret_cast<const unsigned *>(sums + ((4 + g) * MR + n) * 4);
-            lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(tk_half8, xs), Bc, lo, 0, 0, 0);
+            ac = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(tk_half8, xs), Bc, ac, 0, 0, 0);
             am = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(tk_half8, xs), Bm, am, 0, 0, 0);
         }
+        xs[0] = *reinterpret_cast<const unsigned *>(sums + (g * MR + (n & (MR - 1))) * 4);
+        ac = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(tk_half8, xs), Bc, ac, 0, 0, 0);
+        am = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(tk_half8, xs), Bm, am, 0, 0, 0);
     }
+    // d s + (d ac - dmin am): the two in brackets are larger than their difference, the second's rounding is taken back
+    auto finish = [&](float v, float vc, float vm) __attribute__((always_inline)) {
+        const float p = __fmul_rn(dmin, vm), e = __fmaf_rn(dmin, vm, -p);
+        return fmaf(d, v, __fmaf_rn(d, vc, -p) - e);
+    };
 #pragma unroll
     for (int i = 0; i < NY; ++i) {
         float s;
@@ -487,11 +500,11 @@ __device__ __forceinline__ void tk_mul(const uint8_t *stage, int b, const uint8_
             const float s0 = acc[0][2 * i] + acc[1][2 * i], s1 = acc[0][2 * i + 1] + acc[1][2 * i + 1];
             s = s0 + s1;
             if constexpr (Q6) s = fmaf(16.f, s, rem[2 * i] + rem[2 * i + 1]);
-            if constexpr (Q4 || Q5) s = fmaf(d, s, -(dmin * (am[2 * i] + am[2 * i + 1])));
+            if constexpr (Q4 || Q5) s = finish(s, ac[2 * i] + ac[2 * i + 1], am[2 * i] + am[2 * i + 1]);
         } else {
             s = (acc[0][i] + acc[1][i]) + lo[i];
             if constexpr (Q6) s = fmaf(16.f, s, rem[i]);
-            if constexpr (Q4 || Q5) s = fmaf(d, s, -(dmin * am[i]));
+            if constexpr (Q4 || Q5) s = finish(s, ac[i], am[i]);
         }
         if constexpr (Q6) s *= d;
         y[i] = fmaf(s, ODD ? -iv[i] : iv[i], y[i]);

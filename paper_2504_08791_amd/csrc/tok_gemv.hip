@@ -43,10 +43,10 @@ struct TokArgs {
     int rounds, blk_rounds; // in all; whose sums are in LDS at a time
 };
 
-// LDS: the waves' stage buffers | operands [chunk] | sums [chunk] | 2^-p [chunk][NT] | sums of squares [chunk][NT] | 1/rms [NT] |
+// LDS: the waves' stage buffers | activations [chunk] | sums of squares [chunk][NT] | 1/rms [NT] |
 // units' sums [blk_rounds][waves][NT][16]
 template <int FMT, int NT>
-__global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64, TkFmt<FMT>::WAVES / 4) tok_gemv_kernel(TokArgs a)
+__global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) tok_gemv_kernel(TokArgs a)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     constexpr int SBS = TkFmt<FMT>::SBS, WAVES = TkFmt<FMT>::WAVES, THREADS = WAVES * 64;
@@ -55,9 +55,7 @@ __global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64, TkFmt<FMT>::WAVES / 4)
     const int n = lane & 15, g = lane >> 4;
     uint8_t *const l_stage = smem + wave * tk_stage_bytes<FMT>;
     uint8_t *const l_a = smem + WAVES * tk_stage_bytes<FMT>;
-    uint8_t *const l_sums = l_a + a.chunk * tk_a_bytes(NT);
-    float *const l_inv = reinterpret_cast<float *>(l_sums + a.chunk * tk_sum_bytes(NT));
-    float *const l_ss = l_inv + a.chunk * NT;
+    float *const l_ss = reinterpret_cast<float *>(l_a + a.chunk * tk_rec(NT));
     float *const l_rms = l_ss + a.chunk * NT;
     float *const l_acc = l_rms + NT;
 
@@ -168,7 +166,7 @@ __global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64, TkFmt<FMT>::WAVES / 4)
                         ss = row_sum16(ss);
                         if (n == 0) l_ss[b * NT + t] = ss;
                     }
-                    tk_split<NT, TkFmt<FMT>::ORD>(v, n, t, l_a + b * tk_a_bytes(NT), l_sums + b * tk_sum_bytes(NT), l_inv + b * NT + t);
+                    tk_split<NT, TkFmt<FMT>::ORD>(v, n, t, l_a + b * tk_rec(NT));
                 }
             }
             __syncthreads();
@@ -187,7 +185,7 @@ __global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64, TkFmt<FMT>::WAVES / 4)
                 request(r);
                 if (real) {
                     auto mul = [&](int slot, int b, auto odd) __attribute__((always_inline)) {
-                        tk_mul<FMT, NT, decltype(odd)::value>(l_stage, slot, l_a + b * tk_a_bytes(NT), l_sums + b * tk_sum_bytes(NT), l_inv + b * NT, lane, y);
+                        tk_mul<FMT, NT, decltype(odd)::value>(l_stage, slot, l_a + b * tk_rec(NT), lane, y);
                     };
                     if constexpr (SBS == 1) {
                         mul(0, s, second);
@@ -251,7 +249,7 @@ prima_status launch_nt(TokArgs a, hipStream_t st)
         attr_set = true;
     }
     constexpr int SBS = TkFmt<FMT>::SBS, WAVES = TkFmt<FMT>::WAVES;
-    constexpr size_t per_sb = tk_a_bytes(NT) + tk_sum_bytes(NT) + 8 * NT, fixed = WAVES * tk_stage_bytes<FMT> + NT * 4;
+    constexpr size_t per_sb = tk_rec(NT) + 4 * NT, fixed = WAVES * tk_stage_bytes<FMT> + NT * 4;
     const int grid = std::min(a.n_tiles, TK_CUS);
     // Parts of a unit: with few tiles the waves share them (what the longest wave has to do counts); the sums of a workgroup's
     // units take at most 32 KiB, more rounds than that are worked off in blocks, each with a walk over K of its own.

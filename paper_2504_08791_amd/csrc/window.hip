@@ -2,9 +2,11 @@
 // launch sequence of a layer window (arXiv 2504.08791, Sec. 3.1: a device advances its window
 // of consecutive layers and hands e FP32 values per token to its successor).
 #include <algorithm>
+#include <initializer_list>
 #include <mutex>
 
 #include "attn_common.h"
+#include "tok_stream.h"
 
 using namespace prima;
 
@@ -12,6 +14,8 @@ namespace {
 
 struct WindowWs {
     size_t q, k, v, o, h, a, u, xb0, xb1, rope, attn, gemv, gemv_bytes, arrivals_bytes, sync, total;
+    // 9 and more tokens: activations laid out for Q4_K and for the other formats, their sums of squares, the shares of K
+    size_t tok_rec[2], tok_ss, tok_part, tok_part_floats;
 };
 
 bool dims_ok(const prima_dims *d)
@@ -19,6 +23,16 @@ bool dims_ok(const prima_dims *d)
     return d->e > 0 && d->e % QK == 0 && d->ffn > 0 && d->ffn % QK == 0 && d->n_kv_heads > 0 &&
            d->n_q_heads > 0 && d->n_q_heads % d->n_kv_heads == 0 && (d->head_dim == 64 || d->head_dim == 128) &&
            (static_cast<int64_t>(d->n_q_heads) * d->head_dim) % QK == 0 && (d->rope_mode == 0 || d->rope_mode == 1);
+}
+
+// Windows of 9 to 16 tokens go through tok_stream.hip, in one pass over the weights (16 sequences through three 14B-shaped layers
+// 585 -> 371 us; at 8 tokens and fewer run_layer()'s one pass is faster, 364 us against 379 for two 70B-shaped layers).  K long
+// enough to need hundreds of slabs and layers with an FP32 matrix go through run_layer() too.
+bool tok_takes(const prima_dims &d, int T)
+{
+    const int64_t qd = static_cast<int64_t>(d.n_q_heads) * d.head_dim, widest = std::max<int64_t>({d.e, qd, d.ffn});
+    return T > 8 && widest / QK <= 1024 && tok_max_parts(static_cast<int>(widest / QK), tok_slots(T)) <= 256 &&
+           (2 * static_cast<int64_t>(d.ffn) + qd + 2 * static_cast<int64_t>(d.n_kv_heads) * d.head_dim) < (int64_t{1} << 30);
 }
 
 WindowWs carve(const prima_dims &d, int kv_cap, int T)
@@ -51,6 +65,14 @@ WindowWs carve(const prima_dims &d, int kv_cap, int T)
     w.gemv_bytes += w.arrivals_bytes; // the counter region is sized for the tallest matrix
     w.gemv = take(w.gemv_bytes);
     w.sync = take(WAIT_FLAG_BYTES);
+    if (tok_takes(d, T)) {
+        const int64_t widest = std::max<int64_t>({d.e, static_cast<int64_t>(qd), d.ffn});
+        for (size_t &r : w.tok_rec) r = take(tok_rec_bytes(widest, T));
+        w.tok_ss = take(tok_ss_bytes(d.e, T));
+        w.tok_part_floats = std::max({tok_part_floats(static_cast<int64_t>(qd + 2 * kvd), d.e, T), tok_part_floats(d.e, static_cast<int64_t>(qd), T),
+                                      tok_part_floats(2 * static_cast<int64_t>(d.ffn), d.e, T), tok_part_floats(d.e, d.ffn, T)});
+        w.tok_part = take(w.tok_part_floats * sizeof(float));
+    }
     w.total = off;
     return w;
 }
@@ -188,6 +210,146 @@ prima_status run_layer(const prima_dims &d, const prima_layer &L, int kv_cap, in
     }
 #undef PRIMA_WANT
 #undef PRIMA_TRY
+    return PRIMA_OK;
+}
+
+// One decoder layer for 9 to 16 tokens (tok_stream.hip), x -> y.  Launches: the weight streams (one per format in a group), and
+// between them one that adds their shares, finishes the vector and lays it out for the next stream.  prepared: the layer
+// before this one has laid out x for the Q/K/V streams; next: the layer after it, whose Q/K/V activations the last launch
+// lays out (null: none).  Every matrix in a format that the streams take.
+prima_status run_layer_tok(const prima_dims &d, const prima_layer &L, int kv_cap, int n_past, int T,
+                           const float *x, float *y, void *ws, const WindowWs &w, hipStream_t st,
+                           float *tap_q, float *tap_o, float *tap_h, float *tap_a, int only, const AttnSeqs *seq,
+                           const prima_layer_formats *fm, bool prepared, const prima_layer *next, const prima_layer_formats *next_fm)
+{
+    static constexpr prima_layer_formats ALL_Q4_K = {0, 0, 0, 0, 0, 0, 0};
+    const prima_layer_formats &f = fm ? *fm : ALL_Q4_K, &nf = next_fm ? *next_fm : ALL_Q4_K;
+    const int64_t e = d.e, qd = static_cast<int64_t>(d.n_q_heads) * d.head_dim, kvd = static_cast<int64_t>(d.n_kv_heads) * d.head_dim, F = d.ffn;
+    float *q = at<float>(ws, w.q), *k = at<float>(ws, w.k), *v = at<float>(ws, w.v), *o = at<float>(ws, w.o), *h = at<float>(ws, w.h);
+    float *const ss = at<float>(ws, w.tok_ss), *const part = at<float>(ws, w.tok_part);
+    prima_status s;
+#define PRIMA_TRY(call) do { s = (call); if (s != PRIMA_OK) return s; } while (0)
+#define PRIMA_WANT(k) (only < 0 || only == (k))
+    // the matrices of a group with their activations (already laid out): one launch per format
+    auto streams = [&](const TokMat *m, const int *fmt, int count, int64_t cols, TokPart *out) -> prima_status {
+        size_t used = 0;
+        for (int i = 0; i < count; ++i) {
+            bool first = true;
+            for (int j = 0; j < i; ++j) first = first && fmt[j] != fmt[i];
+            if (!first) continue;
+            TokMat same[3];
+            TokPart parts[3];
+            int at_i[3], c = 0;
+            for (int j = i; j < count; ++j)
+                if (fmt[j] == fmt[i]) { same[c] = m[j]; at_i[c++] = j; }
+            const uint8_t *rec = at<uint8_t>(ws, w.tok_rec[fmt[i] == PRIMA_FMT_Q4_K ? 0 : 1]);
+            const prima_status ps = launch_tok_stream(fmt[i], same, c, cols, rec, T, part + used, w.tok_part_floats - used, parts, st);
+            if (ps != PRIMA_OK) return ps;
+            for (int j = 0; j < c; ++j) out[at_i[j]] = parts[j];
+            used += static_cast<size_t>(parts[0].n_parts) * T * static_cast<size_t>(parts[0].rows);
+        }
+        return PRIMA_OK;
+    };
+    auto prepare = [&](int mode, int64_t cols, const float *gain, std::initializer_list<int> fmts) {
+        TokPrepare a{};
+        a.mode = mode; a.T = T; a.nb = static_cast<int>(cols / QK); a.gain = gain; a.ss = ss;
+        for (int ff : fmts) a.rec[ff == PRIMA_FMT_Q4_K ? 0 : 1] = at<uint8_t>(ws, w.tok_rec[ff == PRIMA_FMT_Q4_K ? 0 : 1]);
+        return a;
+    };
+    const TokNorm norm{ss, static_cast<int>(e / QK), d.rms_eps};
+    auto W = [](const void *p) { return static_cast<const uint8_t *>(p); };
+
+    if (PRIMA_WANT(PRIMA_K_QKV)) {
+        if (!prepared) {
+            TokPrepare a = prepare(TOK_PLAIN, e, L.g_attn, {f.wq, f.wk, f.wv});
+            a.x = x;
+            PRIMA_TRY(launch_tok_prepare(a, st));
+        }
+        const TokMat m[3] = {{W(L.wq), qd}, {W(L.wk), kvd}, {W(L.wv), kvd}};
+        const int fmts[3] = {f.wq, f.wk, f.wv};
+        TokSum a{3, T, tok_slots(T), {}, {qd, kvd, kvd}, {q, k, v}, norm, nullptr};
+        PRIMA_TRY(streams(m, fmts, 3, e, a.p));
+        PRIMA_TRY(launch_tok_sum(a, st));
+    }
+    if (PRIMA_WANT(PRIMA_K_ATTN))
+        PRIMA_TRY(launch_attn(d, q, tap_q, k, v, at<float>(ws, w.rope), static_cast<__half *>(L.k_cache),
+                              static_cast<__half *>(L.v_cache), kv_cap, n_past, T, o, at<char>(ws, w.attn), st, seq));
+    if (tap_o && hipMemcpyAsync(tap_o, o, T * qd * sizeof(float), hipMemcpyDeviceToDevice, st) != hipSuccess) return PRIMA_E_DEVICE;
+    if (PRIMA_WANT(PRIMA_K_WO)) {
+        TokPrepare a = prepare(TOK_PLAIN, qd, nullptr, {f.wo});
+        a.x = o;
+        PRIMA_TRY(launch_tok_prepare(a, st));
+        const TokMat m{W(L.wo), e};
+        a = prepare(TOK_RESIDUAL, e, L.g_ffn, {f.wgate, f.wup});
+        PRIMA_TRY(streams(&m, &f.wo, 1, qd, a.p));
+        a.x = x;
+        a.out = h;
+        PRIMA_TRY(launch_tok_prepare(a, st));
+    }
+    if (tap_h && hipMemcpyAsync(tap_h, h, T * e * sizeof(float), hipMemcpyDeviceToDevice, st) != hipSuccess) return PRIMA_E_DEVICE;
+    if (PRIMA_WANT(PRIMA_K_GATE_UP)) {
+        const TokMat m[2] = {{W(L.wgate), F}, {W(L.wup), F}};
+        const int fmts[2] = {f.wgate, f.wup};
+        TokPrepare a = prepare(TOK_SWIGLU, F, nullptr, {f.wdown});
+        PRIMA_TRY(streams(m, fmts, 2, e, a.p));
+        a.norm = norm;
+        a.out = tap_a ? at<float>(ws, w.a) : nullptr;
+        PRIMA_TRY(launch_tok_prepare(a, st));
+    }
+    if (tap_a && hipMemcpyAsync(tap_a, at<char>(ws, w.a), T * F * sizeof(float), hipMemcpyDeviceToDevice, st) != hipSuccess) return PRIMA_E_DEVICE;
+    if (PRIMA_WANT(PRIMA_K_DOWN)) {
+        const TokMat m{W(L.wdown), e};
+        if (next) {
+            TokPrepare a = prepare(TOK_RESIDUAL, e, next->g_attn, {nf.wq, nf.wk, nf.wv});
+            PRIMA_TRY(streams(&m, &f.wdown, 1, F, a.p));
+            a.x = h;
+            a.out = y;
+            PRIMA_TRY(launch_tok_prepare(a, st));
+        } else {
+            TokSum a{1, T, tok_slots(T), {}, {e, 0, 0}, {y, nullptr, nullptr}, TokNorm{nullptr, 0, 0.f}, h};
+            PRIMA_TRY(streams(&m, &f.wdown, 1, F, a.p));
+            PRIMA_TRY(launch_tok_sum(a, st));
+        }
+    }
+#undef PRIMA_WANT
+#undef PRIMA_TRY
+    return PRIMA_OK;
+}
+
+// whether a layer with these formats goes through run_layer_tok()
+bool layer_is_tok(const prima_dims &d, int T, const prima_layer_formats *f)
+{
+    if (!tok_takes(d, T)) return false;
+    if (!f) return true;
+    for (int32_t v : {f->wq, f->wk, f->wv, f->wo, f->wgate, f->wup, f->wdown})
+        if (v == PRIMA_FMT_F32) return false;
+    return true;
+}
+
+// all layers of a step; caches(i, seq): a batch's caches of layer i
+template <class Caches>
+prima_status run_layers(const prima_dims &d, const prima_layer *layers, const prima_layer_formats *formats, int L, int kv_cap, int n_past, int T,
+                        const float *x_in, float *x_out, void *ws, const WindowWs &w, hipStream_t st, Caches caches)
+{
+    const float *cur = x_in;
+    bool prepared = false;
+    for (int i = 0; i < L; ++i) {
+        float *dst = (i == L - 1) ? x_out : at<float>(ws, (i & 1) ? w.xb1 : w.xb0);
+        const prima_layer_formats *f = formats ? &formats[i] : nullptr, *nf = formats && i + 1 < L ? &formats[i + 1] : nullptr;
+        const AttnSeqs *seq = caches(i);
+        prima_status s;
+        if (layer_is_tok(d, T, f)) {
+            const bool chain = i + 1 < L && layer_is_tok(d, T, nf);
+            s = run_layer_tok(d, layers[i], kv_cap, n_past, T, cur, dst, ws, w, st, nullptr, nullptr, nullptr, nullptr, -1, seq, f, prepared,
+                              chain ? &layers[i + 1] : nullptr, nf);
+            prepared = chain;
+        } else {
+            s = run_layer(d, layers[i], kv_cap, n_past, T, cur, dst, ws, w, st, nullptr, nullptr, nullptr, nullptr, -1, seq, f);
+            prepared = false;
+        }
+        if (s != PRIMA_OK) return s;
+        cur = dst;
+    }
     return PRIMA_OK;
 }
 
@@ -600,14 +762,7 @@ prima_status prima_layer_window_decode(const prima_dims *d, const prima_layer *l
     const WindowWs w = carve(*d, kv_cap, T);
     s = step_init(*d, workspace, w, T, n_past, nullptr, true, st);
     if (s != PRIMA_OK) return s;
-    const float *cur = x_in;
-    for (int i = 0; i < L; ++i) {
-        float *dst = (i == L - 1) ? x_out : at<float>(workspace, (i & 1) ? w.xb1 : w.xb0);
-        s = run_layer(*d, layers[i], kv_cap, n_past, T, cur, dst, workspace, w, st, nullptr, nullptr, nullptr, nullptr);
-        if (s != PRIMA_OK) return s;
-        cur = dst;
-    }
-    return PRIMA_OK;
+    return run_layers(*d, layers, nullptr, L, kv_cap, n_past, T, x_in, x_out, workspace, w, st, [](int) { return static_cast<const AttnSeqs *>(nullptr); });
 }
 
 prima_status prima_layer_window_decode_mixed(const prima_dims *d, const prima_layer *layers, const prima_layer_formats *formats,
@@ -629,14 +784,7 @@ prima_status prima_layer_window_decode_mixed(const prima_dims *d, const prima_la
     const WindowWs w = carve(*d, kv_cap, T);
     s = step_init(*d, workspace, w, T, n_past, nullptr, true, st);
     if (s != PRIMA_OK) return s;
-    const float *cur = x_in;
-    for (int i = 0; i < L; ++i) {
-        float *dst = (i == L - 1) ? x_out : at<float>(workspace, (i & 1) ? w.xb1 : w.xb0);
-        s = run_layer(*d, layers[i], kv_cap, n_past, T, cur, dst, workspace, w, st, nullptr, nullptr, nullptr, nullptr, -1, nullptr, &formats[i]);
-        if (s != PRIMA_OK) return s;
-        cur = dst;
-    }
-    return PRIMA_OK;
+    return run_layers(*d, layers, formats, L, kv_cap, n_past, T, x_in, x_out, workspace, w, st, [](int) { return static_cast<const AttnSeqs *>(nullptr); });
 }
 
 prima_status prima_layer_window_decode_batch(const prima_dims *d, const prima_layer *layers, int32_t L,
@@ -678,21 +826,15 @@ prima_status prima_layer_window_decode_batch_mixed(const prima_dims *d, const pr
     const WindowWs w = carve(*d, kv_cap, B);
     s = step_init(*d, workspace, w, B, 0, n_past, false, st);
     if (s != PRIMA_OK) return s;
-    const float *cur = x_in;
-    for (int i = 0; i < L; ++i) {
-        float *dst = (i == L - 1) ? x_out : at<float>(workspace, (i & 1) ? w.xb1 : w.xb0);
-        __half *kc[PRIMA_MAX_TOK], *vc[PRIMA_MAX_TOK];
+    __half *kc[PRIMA_MAX_TOK], *vc[PRIMA_MAX_TOK];
+    const AttnSeqs seq{n_past, kc, vc};
+    return run_layers(*d, layers, formats, L, kv_cap, 0, B, x_in, x_out, workspace, w, st, [&](int i) {
         for (int b = 0; b < B; ++b) {
             kc[b] = static_cast<__half *>(k_caches[static_cast<size_t>(i) * B + b]);
             vc[b] = static_cast<__half *>(v_caches[static_cast<size_t>(i) * B + b]);
         }
-        const AttnSeqs seq{n_past, kc, vc};
-        s = run_layer(*d, layers[i], kv_cap, 0, B, cur, dst, workspace, w, st, nullptr, nullptr, nullptr, nullptr, -1, &seq,
-                      formats ? &formats[i] : nullptr);
-        if (s != PRIMA_OK) return s;
-        cur = dst;
-    }
-    return PRIMA_OK;
+        return &seq;
+    });
 }
 
 void prima_set_prefill_small_tokens(int32_t n) { g_prefill_small_tokens = n < 0 ? 0 : n; }
@@ -738,14 +880,9 @@ prima_status prima_layer_window_prefill_mixed(const prima_dims *d, const prima_l
             const int Tc = std::min<int>(PRIMA_MAX_TOK, T - t0);
             prima_status cs = step_init(*d, dws, w.dec, Tc, n_past + t0, nullptr, false, st);
             if (cs != PRIMA_OK) return cs;
-            const float *cur = x_in + static_cast<int64_t>(t0) * d->e;
-            for (int i = 0; i < L; ++i) {
-                float *dst = (i == L - 1) ? x_out + static_cast<int64_t>(t0) * d->e : at<float>(dws, (i & 1) ? w.dec.xb1 : w.dec.xb0);
-                cs = run_layer(*d, layers[i], kv_cap, n_past + t0, Tc, cur, dst, dws, w.dec, st, nullptr, nullptr, nullptr, nullptr, -1, nullptr,
-                               formats ? &formats[i] : nullptr);
-                if (cs != PRIMA_OK) return cs;
-                cur = dst;
-            }
+            cs = run_layers(*d, layers, formats, L, kv_cap, n_past + t0, Tc, x_in + static_cast<int64_t>(t0) * d->e, x_out + static_cast<int64_t>(t0) * d->e,
+                            dws, w.dec, st, [](int) { return static_cast<const AttnSeqs *>(nullptr); });
+            if (cs != PRIMA_OK) return cs;
         }
         return PRIMA_OK;
     }
@@ -798,12 +935,8 @@ prima_status prima_layer_window_decode_profiled(const prima_dims *d, const prima
     // one ordinary step first: every intermediate buffer then holds this step's values
     auto ordinary_step = [&]() {
         prima_status os = step_init(*d, workspace, w, T, n_past, nullptr, false, st);
-        const float *cur = x_in;
-        for (int i = 0; i < L && os == PRIMA_OK; ++i) {
-            float *dst = (i == L - 1) ? x_out : at<float>(workspace, (i & 1) ? w.xb1 : w.xb0);
-            os = run_layer(*d, layers[i], kv_cap, n_past, T, cur, dst, workspace, w, st, nullptr, nullptr, nullptr, nullptr);
-            cur = dst;
-        }
+        if (os == PRIMA_OK)
+            os = run_layers(*d, layers, nullptr, L, kv_cap, n_past, T, x_in, x_out, workspace, w, st, [](int) { return static_cast<const AttnSeqs *>(nullptr); });
         return os;
     };
     s = ordinary_step();
@@ -823,7 +956,10 @@ prima_status prima_layer_window_decode_profiled(const prima_dims *d, const prima
     float *scratch_out = at<float>(workspace, w.xb0); // the isolated down projections write here, not to x_out
     for (int ki = 0; ki < n_kinds && s == PRIMA_OK; ++ki) {
         for (int i = 0; i < L && s == PRIMA_OK; ++i)
-            s = run_layer(*d, layers[i], kv_cap, n_past, T, x_in, scratch_out, workspace, w, st, nullptr, nullptr, nullptr, nullptr, kinds[ki]);
+            s = layer_is_tok(*d, T, nullptr)
+                    ? run_layer_tok(*d, layers[i], kv_cap, n_past, T, x_in, scratch_out, workspace, w, st, nullptr, nullptr, nullptr, nullptr, kinds[ki], nullptr,
+                                    nullptr, false, nullptr, nullptr)
+                    : run_layer(*d, layers[i], kv_cap, n_past, T, x_in, scratch_out, workspace, w, st, nullptr, nullptr, nullptr, nullptr, kinds[ki]);
         if (s == PRIMA_OK && !mark()) s = PRIMA_E_DEVICE;
     }
     // The replayed attention launches appended rows n_past .. n_past+T-1 of every layer's caches from whatever the
@@ -855,6 +991,8 @@ prima_status prima_layer_decode_taps(const prima_dims *d, const prima_layer *lay
     const WindowWs w = carve(*d, kv_cap, T);
     s = step_init(*d, workspace, w, T, n_past, nullptr, false, st);
     if (s != PRIMA_OK) return s;
+    if (layer_is_tok(*d, T, nullptr))
+        return run_layer_tok(*d, *layer, kv_cap, n_past, T, x_in, x_out, workspace, w, st, tap_q, tap_o, tap_h, tap_a, -1, nullptr, nullptr, false, nullptr, nullptr);
     return run_layer(*d, *layer, kv_cap, n_past, T, x_in, x_out, workspace, w, st, tap_q, tap_o, tap_h, tap_a);
 }
 
