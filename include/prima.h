@@ -97,7 +97,7 @@ size_t prima_gemv_workspace_bytes(int64_t n_rows, int64_t n_cols, int32_t T);
  * runs on holds its own copy until the process ends.  A shape whose scratch (prima_gemv_workspace_bytes) exceeds
  * that size returns PRIMA_E_WORKSPACE and launches nothing.  The call allocates and frees nothing (the array's
  * device address is looked up once per device, on the first call made with that device current).  Every call on
- * a GPU shares that GPU's array: the counters are cleared by a small fill kernel at the start of each call, and
+ * a GPU shares that GPU's array: the counters are cleared by a small fill kernel in calls that use them, and
  * calls that overlap on one GPU (two streams, two threads) race; calls on one stream are safe.
  */
 #define PRIMA_NOALLOC_SCRATCH_BYTES (4u << 20)

@@ -92,7 +92,8 @@ prima_status launch_dequant(const uint8_t *W, int64_t n_rows, int64_t n_cols, fl
 // ws: scratch; its first arrivals_region bytes (>= gemv_arrivals_bytes(rows)) are counters that must be
 // zero before the first launch (launch_zero_arrivals) and are left zero by every launch; the partial
 // sums follow (gemv_ws_bytes() covers both for a region of gemv_arrivals_bytes(rows))
-prima_status launch_gemv_mfma(const GemvArgs &a, void *ws, size_t ws_bytes, size_t arrivals_region, hipStream_t st);
+// zero_arrivals: the counters may hold anything; they are cleared by a launch of its own where a pass looks at them.
+prima_status launch_gemv_mfma(const GemvArgs &a, void *ws, size_t ws_bytes, size_t arrivals_region, hipStream_t st, bool zero_arrivals = false);
 size_t gemv_ws_bytes(int64_t n_rows_total, int64_t n_cols, int T);
 size_t gemv_arrivals_bytes(int64_t n_rows_total);
 prima_status launch_zero_arrivals(void *ws, size_t bytes, hipStream_t st);

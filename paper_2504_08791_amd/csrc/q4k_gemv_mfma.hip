@@ -169,7 +169,11 @@ prima_status gemv_plan_status(const GemvArgs &ga, void *ws, size_t ws_bytes, siz
     return PRIMA_OK;
 }
 
-prima_status launch_gemv_mfma(const GemvArgs &ga, void *ws, size_t ws_bytes, size_t arrivals_region, hipStream_t st)
+// Whether a pass of this launch counts arrivals: its slabs of K are added in place.  (With one slab, or with the slabs added by a
+// second kernel, the counters are not looked at.)
+static bool pass_counts(const PGemvArgs &a) { return a.n_slabs > 1 && !a.defer; }
+
+prima_status launch_gemv_mfma(const GemvArgs &ga, void *ws, size_t ws_bytes, size_t arrivals_region, hipStream_t st, bool zero_arrivals)
 {
     // up to MAX_T_PASS tokens per pass over the weights
     for (int t0 = 0; t0 < ga.T; t0 += MAX_T_PASS) {
@@ -178,6 +182,12 @@ prima_status launch_gemv_mfma(const GemvArgs &ga, void *ws, size_t ws_bytes, siz
         PGemvArgs a;
         const prima_status bs = build_pass(ga, t0, T, ws, ws_bytes, arrivals_region, a, p);
         if (bs != PRIMA_OK) return bs;
+        // a caller whose scratch is not known to hold zeros: cleared in front of the first pass that counts (every pass leaves them zero)
+        if (zero_arrivals && pass_counts(a)) {
+            const prima_status zs = launch_zero_arrivals(ws, arrivals_bytes(p.n_tiles), st);
+            if (zs != PRIMA_OK) return zs;
+            zero_arrivals = false;
+        }
         hipError_t e;
         switch (T) {
         case 1: e = launch_tt<1>(a, p, st); break;

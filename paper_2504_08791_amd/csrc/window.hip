@@ -559,9 +559,9 @@ prima_status prima_q4k_gemv(const void *W, int64_t n_rows, int64_t n_cols, const
     GemvArgs ga = gemv_args(1, n_cols, x, ldx, T);
     ga.seg[0] = seg(W, y, n_rows, ldy);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    prima_status s = launch_zero_arrivals(workspace, gemv_arrivals_bytes(n_rows), st);
-    if (s != PRIMA_OK) return s;
-    return launch_gemv_mfma(ga, workspace, workspace_bytes, gemv_arrivals_bytes(n_rows), st);
+    // The arrival counters are cleared only where a pass counts arrivals: a launch less for K that fits one slab, which
+    // in a small mat-vec (1024 x 4096, one token) was half of the call
+    return launch_gemv_mfma(ga, workspace, workspace_bytes, gemv_arrivals_bytes(n_rows), st, true);
 }
 
 } // extern "C"
@@ -609,10 +609,8 @@ prima_status prima_q4k_gemv_noalloc(const void *W, int64_t n_rows, int64_t n_col
     GemvArgs ga = gemv_args(1, n_cols, x, ldx, T);
     ga.seg[0] = seg(W, y, n_rows, ldy);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    // the array keeps what the last call left: the counters are cleared by a fill kernel (not a memset node)
-    s = launch_zero_arrivals(ws, gemv_arrivals_bytes(n_rows), st);
-    if (s != PRIMA_OK) return s;
-    return launch_gemv_mfma(ga, ws, PRIMA_NOALLOC_SCRATCH_BYTES, gemv_arrivals_bytes(n_rows), st);
+    // the array keeps what the last call left: where a pass looks at the counters they are cleared by a fill kernel (not a memset node)
+    return launch_gemv_mfma(ga, ws, PRIMA_NOALLOC_SCRATCH_BYTES, gemv_arrivals_bytes(n_rows), st, true);
 }
 
 size_t prima_gemm_workspace_bytes(int32_t T, int64_t n_cols) { return (T < 1 || n_cols <= 0 || n_cols % QK) ? 0 : gemm_ws_bytes(T, n_cols); }
@@ -1012,11 +1010,9 @@ prima_status prima_lm_head(const prima_dims *d, const float *g_final, const void
     if (!aligned(g_final, 16) || !aligned(w_lm, 16) || !aligned(x, 16) || !aligned(logits, 4) || !aligned(workspace, 256)) return PRIMA_E_ALIGN;
     if (workspace_bytes < prima_lm_head_workspace_bytes(d, vocab, T)) return PRIMA_E_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    prima_status s = launch_zero_arrivals(workspace, gemv_arrivals_bytes(vocab), st);
-    if (s != PRIMA_OK) return s;
     GemvArgs ga = gemv_args(1, d->e, x, d->e, T, X_RMSNORM, g_final, d->rms_eps);
     ga.seg[0] = seg(w_lm, logits, vocab, vocab);
-    return launch_gemv_mfma(ga, workspace, workspace_bytes, gemv_arrivals_bytes(vocab), st);
+    return launch_gemv_mfma(ga, workspace, workspace_bytes, gemv_arrivals_bytes(vocab), st, true);
 }
 
 } // extern "C"
