@@ -400,7 +400,7 @@ prima_status launch_fmt(FmtArgs a, hipStream_t st)
     const float *x = a.x, *resid = a.resid;
     float *y = a.y;
     const int T = a.T;
-    constexpr int PASS = FMT == PRIMA_FMT_F32 ? FG_MAX_T : 4; // (5 and more tokens: FP32 only, the others go to tok_gemv.hip)
+    constexpr int PASS = FMT == PRIMA_FMT_F32 ? FG_MAX_T : 6; // (7 and more tokens: FP32 only, the others go to tok_gemv.hip)
     for (int t0 = 0; t0 < T; t0 += PASS) {
         const int Tp = T - t0 < PASS ? T - t0 : PASS;
         a.x = x + t0 * a.ldx;
@@ -412,13 +412,10 @@ prima_status launch_fmt(FmtArgs a, hipStream_t st)
         else if (Tp == 2) s = launch_tt<FMT, 2>(a, st);
         else if (Tp == 3) s = launch_tt<FMT, 3>(a, st);
         else if (Tp == 4) s = launch_tt<FMT, 4>(a, st);
+        else if (Tp == 5) s = launch_tt<FMT, 5>(a, st);
+        else if (Tp == 6) s = launch_tt<FMT, 6>(a, st);
         else if constexpr (FMT == PRIMA_FMT_F32) {
-            switch (Tp) {
-            case 5: s = launch_tt<FMT, 5>(a, st); break;
-            case 6: s = launch_tt<FMT, 6>(a, st); break;
-            case 7: s = launch_tt<FMT, 7>(a, st); break;
-            default: s = launch_tt<FMT, 8>(a, st); break;
-            }
+            s = Tp == 7 ? launch_tt<FMT, 7>(a, st) : launch_tt<FMT, 8>(a, st);
         } else s = PRIMA_E_SHAPE; // (not reached)
         if (s != PRIMA_OK) return s;
     }

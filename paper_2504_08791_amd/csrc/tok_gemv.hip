@@ -290,18 +290,19 @@ prima_status launch_fmt(const TokArgs &a, hipStream_t st)
 
 } // namespace
 
-// Where the line lies, us, this kernel / the fp32 mat-vec (start of the measurement: 128256 x 8192 with the norm in front):
-//   Q6_K 128256 x 8192   2 tokens 204 / 201, 3: 197 / 223, 4: 195 / 266, 8: 203 / 578, 16: 297 / 1113
-//   Q8_0 128256 x 8192   2 tokens 183 / 181, 3: 183 / 201, 4: 182 / 246, 8: 191 / 506, 16: 264 / 972
-//   Q6_K 8192 x 28672    2 tokens  61 / 60,  3: 71 / 66,   4: 71 / 80,   8: 106 / 150, 16: 179 / 312
-//   Q8_0 8192 x 28672    2 tokens  58 / 50,  3: 72 / 58,   4: 71 / 70,   8: 118 / 126, 16: 153 / 264
-//   Q6_K 5120 x 13824    2 tokens  33 / 30,  3: 41 / 33,   4: 41 / 38,   8: 52 / 71,   16: 106 / 141
+// Where the line lies, us, this kernel / the fp32 mat-vec (the first two with the norm in front):
+//   Q6_K 128256 x 8192   2 tokens 186 / 201, 3: 198 / 223, 4: 194 / 266, 8: 203 / 578, 16: 297 / 1113
+//   Q8_0 128256 x 8192   2 tokens 179 / 181, 3: 182 / 201, 4: 182 / 246, 8: 191 / 506, 16: 264 / 972
+//   Q6_K 32000 x 4096    4 tokens  32 / 43,  5: 36 / 49,   8: 36 / 67    Q8_0  4: 34 / 38,  5: 36 / 43,  8: 37 / 55
+//   Q6_K 5120 x 13824    5 tokens  51 / 47,  6: 50 / 53,   8: 51 / 70    Q8_0  5: 48 / 41,  6: 48 / 49,  8: 48 / 61
+//   Q6_K 5120 x 5120     5 tokens  22 / 17,  6: 22 / 19,   8: 23 / 28    Q8_0  5: 21 / 16,  6: 21 / 18,  8: 21 / 25
+//   Q6_K 8192 x 28672    5 tokens 104 / 96,  6: 104 / 118, 8: 104 / 145  Q8_0  5: 115 / 85, 6: 116 / 103, 8: 117 / 130
 // With few rows every workgroup prepares all of the activations for a tile or two; the mat-vec keeps what it is faster at.
 bool tok_gemv_takes(int fmt, int64_t n_rows, int64_t n_cols, int T)
 {
     if (fmt != PRIMA_FMT_Q5_K && fmt != PRIMA_FMT_Q6_K && fmt != PRIMA_FMT_Q8_0 && fmt != PRIMA_FMT_F16) return false;
     if (T < 2 || T > PRIMA_MAX_TOK || n_cols / QK >= (1 << 18) || n_rows >= (int64_t{1} << 34)) return false; // (32-bit offsets in a tile's 16 rows, 32-bit tile numbers)
-    return T >= 5 || n_rows >= 65536 || (T == 4 && n_rows >= 8192);
+    return T >= 7 || n_rows >= 65536 || (T >= 4 && n_rows >= 16384);
 }
 
 prima_status launch_tok_gemv(int fmt, const uint8_t *W, int64_t n_rows, int64_t n_cols, const float *x, int64_t ldx, int T,

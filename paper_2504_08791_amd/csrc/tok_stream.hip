@@ -16,7 +16,8 @@
 // down 44 -> 25 (adding and preparing included); the batch step of three layers 585 -> 371.  What bounds the stream at 16
 // tokens: 27648 x 5120 (80 MB, 12 us at the rate of a linear read) takes 30 us, 21 without its products, 31 without its
 // loads: the LDS reads of the operands (17 KB a super-block and wave) and the unpacking under two waves a SIMD.
-// Up to eight tokens that kernel stays the better one (start / this, us: four layers of a 32B shape at 4 tokens 457 / 523, two of a 70B
+// From four tokens on the other formats' matrices of a window come here too (prepared, streamed and added each group for itself).
+// Up to eight tokens the Q4_K kernel stays the better one (start / this, us: four layers of a 32B shape at 4 tokens 457 / 523, two of a 70B
 // shape at 8 364 / 379): the launches between the streams cost 4 to 5 us each and the streams gain less than that.
 #include <algorithm>
 #include <atomic>
@@ -372,7 +373,12 @@ prima_status launch_fmt(StreamArgs &a, size_t part_floats, int &n_parts, hipStre
     a.n_slabs = p.n_slabs; a.slab = p.slab; a.ks_shift = p.ks_shift; a.rounds = p.rounds;
     n_parts = p.n_slabs << p.ks_shift;
     if (static_cast<size_t>(n_parts) * a.T * a.n_tiles * 16 > part_floats) return PRIMA_E_WORKSPACE;
-    return nt == 16 ? launch_nt<FMT, 16>(a, p, st) : PRIMA_E_SHAPE; // (windows of 9 to 16 tokens, see tok_takes() in window.hip)
+    if (nt == 16) return launch_nt<FMT, 16>(a, p, st);
+    if constexpr (FMT != PRIMA_FMT_Q4_K) { // (Q4_K: windows of 9 to 16 tokens only, see window.hip)
+        if (nt == 4) return launch_nt<FMT, 4>(a, p, st);
+        if (nt == 8) return launch_nt<FMT, 8>(a, p, st);
+    }
+    return PRIMA_E_SHAPE;
 }
 
 } // namespace
@@ -416,8 +422,12 @@ prima_status launch_tok_stream(int fmt, const TokMat *mats, int n_mats, int64_t 
 prima_status launch_tok_prepare(const TokPrepare &a, hipStream_t st)
 {
     const int nt = tk_slots(a.T), grid = a.nb * nt / 4;
-    if (nt != 16) return PRIMA_E_SHAPE;
-    hipLaunchKernelGGL((tok_prepare_kernel<16>), dim3(grid), dim3(64 * ADD_WAVES), 0, st, a);
+    switch (nt) {
+    case 4: hipLaunchKernelGGL((tok_prepare_kernel<4>), dim3(grid), dim3(64 * ADD_WAVES), 0, st, a); break;
+    case 8: hipLaunchKernelGGL((tok_prepare_kernel<8>), dim3(grid), dim3(64 * ADD_WAVES), 0, st, a); break;
+    case 16: hipLaunchKernelGGL((tok_prepare_kernel<16>), dim3(grid), dim3(64 * ADD_WAVES), 0, st, a); break;
+    default: return PRIMA_E_SHAPE;
+    }
     return last_launch_status();
 }
 

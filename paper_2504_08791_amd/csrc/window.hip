@@ -28,10 +28,15 @@ bool dims_ok(const prima_dims *d)
 // Windows of 9 to 16 tokens go through tok_stream.hip, in one pass over the weights (16 sequences through three 14B-shaped layers
 // 585 -> 371 us; at 8 tokens and fewer run_layer()'s one pass is faster, 364 us against 379 for two 70B-shaped layers).  K long
 // enough to need hundreds of slabs and layers with an FP32 matrix go through run_layer() too.
-bool tok_takes(const prima_dims &d, int T)
+constexpr int TOK_WINDOW = 9; // tokens from which whole windows go there
+// ... and from which the matrices in other formats of a smaller window do.  Two layers, V and down in Q6_K in one of them, us, there /
+// through a mat-vec for each: 14B shape 4 tokens 213 / 221, 5: 230 / 248, 8: 236 / 290; 70B shape 4: 342 / 376, 8: 385 / 492.  At
+// three tokens the mat-vec is as fast (14B shape 211; its launch reads the activations itself).
+constexpr int TOK_OTHERS = 4;
+bool tok_takes(const prima_dims &d, int T, int from = TOK_WINDOW)
 {
     const int64_t qd = static_cast<int64_t>(d.n_q_heads) * d.head_dim, widest = std::max<int64_t>({d.e, qd, d.ffn});
-    return T > 8 && widest / QK <= 1024 && tok_max_parts(static_cast<int>(widest / QK), tok_slots(T)) <= 256 &&
+    return T >= from && widest / QK <= 1024 && tok_max_parts(static_cast<int>(widest / QK), tok_slots(T)) <= 256 &&
            (2 * static_cast<int64_t>(d.ffn) + qd + 2 * static_cast<int64_t>(d.n_kv_heads) * d.head_dim) < (int64_t{1} << 30);
 }
 
@@ -65,7 +70,7 @@ WindowWs carve(const prima_dims &d, int kv_cap, int T)
     w.gemv_bytes += w.arrivals_bytes; // the counter region is sized for the tallest matrix
     w.gemv = take(w.gemv_bytes);
     w.sync = take(WAIT_FLAG_BYTES);
-    if (tok_takes(d, T)) {
+    if (tok_takes(d, T, TOK_OTHERS)) {
         const int64_t widest = std::max<int64_t>({d.e, static_cast<int64_t>(qd), d.ffn});
         for (size_t &r : w.tok_rec) r = take(tok_rec_bytes(widest, T));
         w.tok_ss = take(tok_ss_bytes(d.e, T));
@@ -128,6 +133,30 @@ void layer_gemv_args(const prima_dims &d, const prima_layer &L, int T, const flo
 // 64: 0.43 / 1.46, 128: 0.60 / 2.93, 256: 1.04 / 5.87).  A process-wide setting, read when a prompt call is enqueued.
 int g_prefill_small_tokens = 16;
 
+// The matrices of a group with their activations already laid out in the scratch: one stream per format; out[i]: where the
+// shares of matrix i lie.
+prima_status tok_streams(const TokMat *m, const int *fmt, int count, int64_t cols, int T, void *ws, const WindowWs &w, TokPart *out, hipStream_t st)
+{
+    float *const part = at<float>(ws, w.tok_part);
+    size_t used = 0;
+    for (int i = 0; i < count; ++i) {
+        bool first = true;
+        for (int j = 0; j < i; ++j) first = first && fmt[j] != fmt[i];
+        if (!first) continue;
+        TokMat same[3];
+        TokPart parts[3];
+        int at_i[3], c = 0;
+        for (int j = i; j < count; ++j)
+            if (fmt[j] == fmt[i]) { same[c] = m[j]; at_i[c++] = j; }
+        const uint8_t *rec = at<uint8_t>(ws, w.tok_rec[fmt[i] == PRIMA_FMT_Q4_K ? 0 : 1]);
+        const prima_status s = launch_tok_stream(fmt[i], same, c, cols, rec, T, part + used, w.tok_part_floats - used, parts, st);
+        if (s != PRIMA_OK) return s;
+        for (int j = 0; j < c; ++j) out[at_i[j]] = parts[j];
+        used += static_cast<size_t>(parts[0].n_parts) * T * static_cast<size_t>(parts[0].rows);
+    }
+    return PRIMA_OK;
+}
+
 // one decoder layer; x -> y (fp32 [T][e]); taps may be null.  Five launches: Q/K/V projections
 // (RMSNorm fused), attention (RoPE + KV append fused, key ranges merged by the last arriver), output projection
 // (+ residual), gate/up projections (RMSNorm fused in front, SwiGLU behind), down projection (+ residual).
@@ -145,6 +174,37 @@ prima_status run_layer(const prima_dims &d, const prima_layer &L, int kv_cap, in
                      const float *resid, float *out) {
         return launch_fmt_gemv(fmt, static_cast<const uint8_t *>(W), rows, cols, xin, cols, T, gain, d.rms_eps, resid, rows, out, rows, st);
     };
+    // The matrices of a group in other formats than Q4_K, n of them.  From TOK_OTHERS tokens on all but FP32 through the weight
+    // streams of tok_stream.hip (activations laid out, streamed, shares added), else a format mat-vec each.
+    struct Other { int fmt; const void *W; int64_t rows; float *out; };
+    auto others = [&](const Other *m, int n, int64_t cols, const float *xin, const float *gain, const float *resid) -> prima_status {
+        TokMat mats[3];
+        int n_tok = 0, fmts[3];
+        TokSum sum{};
+        const bool tok = tok_takes(d, T, TOK_OTHERS);
+        for (int i = 0; i < n; ++i) {
+            if (!tok || m[i].fmt == PRIMA_FMT_F32) {
+                const prima_status ps = other(m[i].fmt, m[i].W, m[i].rows, cols, xin, gain, resid, m[i].out);
+                if (ps != PRIMA_OK) return ps;
+                continue;
+            }
+            mats[n_tok] = TokMat{static_cast<const uint8_t *>(m[i].W), m[i].rows};
+            sum.rows[n_tok] = m[i].rows;
+            sum.y[n_tok] = m[i].out;
+            fmts[n_tok++] = m[i].fmt;
+        }
+        if (n_tok == 0) return PRIMA_OK;
+        TokPrepare a{};
+        a.mode = TOK_PLAIN; a.T = T; a.nb = static_cast<int>(cols / QK); a.x = xin; a.gain = gain; a.ss = at<float>(ws, w.tok_ss);
+        a.rec[1] = at<uint8_t>(ws, w.tok_rec[1]);
+        prima_status ps = launch_tok_prepare(a, st);
+        if (ps != PRIMA_OK) return ps;
+        ps = tok_streams(mats, fmts, n_tok, cols, T, ws, w, sum.p, st);
+        if (ps != PRIMA_OK) return ps;
+        sum.n = n_tok; sum.T = T; sum.nt = tok_slots(T); sum.resid = resid;
+        if (gain) sum.norm = TokNorm{a.ss, a.nb, d.rms_eps};
+        return launch_tok_sum(sum, st);
+    };
     const int64_t e = d.e, qd = static_cast<int64_t>(d.n_q_heads) * d.head_dim, kvd = static_cast<int64_t>(d.n_kv_heads) * d.head_dim, F = d.ffn;
     float *q = at<float>(ws, w.q), *k = at<float>(ws, w.k), *v = at<float>(ws, w.v);
     float *o = at<float>(ws, w.o), *h = at<float>(ws, w.h), *act = at<float>(ws, w.a);
@@ -157,9 +217,12 @@ prima_status run_layer(const prima_dims &d, const prima_layer &L, int kv_cap, in
         if (f_k == PRIMA_FMT_Q4_K) ga.seg[ga.nseg++] = seg(L.wk, k, kvd, kvd);
         if (f_v == PRIMA_FMT_Q4_K) ga.seg[ga.nseg++] = seg(L.wv, v, kvd, kvd);
         if (ga.nseg) PRIMA_TRY(launch_gemv_mfma(ga, at<char>(ws, w.gemv), w.gemv_bytes, w.arrivals_bytes, st));
-        if (f_q != PRIMA_FMT_Q4_K) PRIMA_TRY(other(f_q, L.wq, qd, e, x, L.g_attn, nullptr, q));
-        if (f_k != PRIMA_FMT_Q4_K) PRIMA_TRY(other(f_k, L.wk, kvd, e, x, L.g_attn, nullptr, k));
-        if (f_v != PRIMA_FMT_Q4_K) PRIMA_TRY(other(f_v, L.wv, kvd, e, x, L.g_attn, nullptr, v));
+        Other m[3];
+        int n = 0;
+        if (f_q != PRIMA_FMT_Q4_K) m[n++] = Other{f_q, L.wq, qd, q};
+        if (f_k != PRIMA_FMT_Q4_K) m[n++] = Other{f_k, L.wk, kvd, k};
+        if (f_v != PRIMA_FMT_Q4_K) m[n++] = Other{f_v, L.wv, kvd, v};
+        PRIMA_TRY(others(m, n, e, x, L.g_attn, nullptr));
     }
     if (PRIMA_WANT(PRIMA_K_ATTN))
         PRIMA_TRY(launch_attn(d, q, tap_q, k, v, at<float>(ws, w.rope), static_cast<__half *>(L.k_cache),
@@ -171,7 +234,8 @@ prima_status run_layer(const prima_dims &d, const prima_layer &L, int kv_cap, in
             ga.seg[0] = seg(L.wo, h, e, e, x, e);
             PRIMA_TRY(launch_gemv_mfma(ga, at<char>(ws, w.gemv), w.gemv_bytes, w.arrivals_bytes, st));
         } else {
-            PRIMA_TRY(other(f_o, L.wo, e, qd, o, nullptr, x, h));
+            const Other m{f_o, L.wo, e, h};
+            PRIMA_TRY(others(&m, 1, qd, o, nullptr, x));
         }
     }
     if (tap_h && hipMemcpyAsync(tap_h, h, T * e * sizeof(float), hipMemcpyDeviceToDevice, st) != hipSuccess) return PRIMA_E_DEVICE;
@@ -186,15 +250,18 @@ prima_status run_layer(const prima_dims &d, const prima_layer &L, int kv_cap, in
             const void *Wm[2] = {L.wgate, L.wup};
             float *out[2] = {act, up};
             const int fmt2[2] = {f_g, f_u};
+            Other m[2];
+            int n = 0;
             for (int i = 0; i < 2; ++i) {
                 if (fmt2[i] == PRIMA_FMT_Q4_K) {
                     GemvArgs ga = gemv_args(1, e, h, e, T, X_RMSNORM, L.g_ffn, d.rms_eps);
                     ga.seg[0] = seg(Wm[i], out[i], F, F);
                     PRIMA_TRY(launch_gemv_mfma(ga, at<char>(ws, w.gemv), w.gemv_bytes, w.arrivals_bytes, st));
                 } else {
-                    PRIMA_TRY(other(fmt2[i], Wm[i], F, e, h, L.g_ffn, nullptr, out[i]));
+                    m[n++] = Other{fmt2[i], Wm[i], F, out[i]};
                 }
             }
+            PRIMA_TRY(others(m, n, e, h, L.g_ffn, nullptr));
             PRIMA_TRY(launch_swiglu(act, up, static_cast<int64_t>(T) * F, st));
         }
     }
@@ -205,7 +272,8 @@ prima_status run_layer(const prima_dims &d, const prima_layer &L, int kv_cap, in
             ga.seg[0] = seg(L.wdown, y, e, e, h, e);
             PRIMA_TRY(launch_gemv_mfma(ga, at<char>(ws, w.gemv), w.gemv_bytes, w.arrivals_bytes, st));
         } else {
-            PRIMA_TRY(other(f_d, L.wdown, e, F, act, nullptr, h, y));
+            const Other m{f_d, L.wdown, e, y};
+            PRIMA_TRY(others(&m, 1, F, act, nullptr, h));
         }
     }
 #undef PRIMA_WANT
@@ -226,30 +294,11 @@ prima_status run_layer_tok(const prima_dims &d, const prima_layer &L, int kv_cap
     const prima_layer_formats &f = fm ? *fm : ALL_Q4_K, &nf = next_fm ? *next_fm : ALL_Q4_K;
     const int64_t e = d.e, qd = static_cast<int64_t>(d.n_q_heads) * d.head_dim, kvd = static_cast<int64_t>(d.n_kv_heads) * d.head_dim, F = d.ffn;
     float *q = at<float>(ws, w.q), *k = at<float>(ws, w.k), *v = at<float>(ws, w.v), *o = at<float>(ws, w.o), *h = at<float>(ws, w.h);
-    float *const ss = at<float>(ws, w.tok_ss), *const part = at<float>(ws, w.tok_part);
+    float *const ss = at<float>(ws, w.tok_ss);
     prima_status s;
 #define PRIMA_TRY(call) do { s = (call); if (s != PRIMA_OK) return s; } while (0)
 #define PRIMA_WANT(k) (only < 0 || only == (k))
-    // the matrices of a group with their activations (already laid out): one launch per format
-    auto streams = [&](const TokMat *m, const int *fmt, int count, int64_t cols, TokPart *out) -> prima_status {
-        size_t used = 0;
-        for (int i = 0; i < count; ++i) {
-            bool first = true;
-            for (int j = 0; j < i; ++j) first = first && fmt[j] != fmt[i];
-            if (!first) continue;
-            TokMat same[3];
-            TokPart parts[3];
-            int at_i[3], c = 0;
-            for (int j = i; j < count; ++j)
-                if (fmt[j] == fmt[i]) { same[c] = m[j]; at_i[c++] = j; }
-            const uint8_t *rec = at<uint8_t>(ws, w.tok_rec[fmt[i] == PRIMA_FMT_Q4_K ? 0 : 1]);
-            const prima_status ps = launch_tok_stream(fmt[i], same, c, cols, rec, T, part + used, w.tok_part_floats - used, parts, st);
-            if (ps != PRIMA_OK) return ps;
-            for (int j = 0; j < c; ++j) out[at_i[j]] = parts[j];
-            used += static_cast<size_t>(parts[0].n_parts) * T * static_cast<size_t>(parts[0].rows);
-        }
-        return PRIMA_OK;
-    };
+    auto streams = [&](const TokMat *m, const int *fmt, int count, int64_t cols, TokPart *out) { return tok_streams(m, fmt, count, cols, T, ws, w, out, st); };
     auto prepare = [&](int mode, int64_t cols, const float *gain, std::initializer_list<int> fmts) {
         TokPrepare a{};
         a.mode = mode; a.T = T; a.nb = static_cast<int>(cols / QK); a.gain = gain; a.ss = ss;
