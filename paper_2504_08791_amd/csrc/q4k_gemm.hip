@@ -358,21 +358,32 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
         if (q == GM_AHEAD - 2) issue_quants(0, 1); // as position (b - 1, 7) would have
     }
 
-    // B tile `rt` of sub-block s from this wave's quants and its headers of super-block `bb`:
-    // sc_s * q as binary16 (exact).  A dword holds the eight weights of lane (n, g); masked in pairs (0,4) (1,5) (2,6)
-    // (3,7) into the mantissas of 1024 + q, then one fused multiply-add per pair: (1024 + q) sc - 1024 sc
-    auto build_b = [&](half8 &B, int rt, int bb, int s) __attribute__((always_inline)) {
+    // Words 1 and 2 of the headers (stream bits 0 .. 63: the eight sub-scales) of the super-block whose B tiles are being built,
+    // this lane's row of each tile: read once per super-block.  (Read with the rest of the header for every tile and position
+    // they were 4 of the 13 KiB that a wave took out of LDS per position.  With the shorter unpacking below: 28672 x 8192 at 1024
+    // tokens 1175 -> 1151 us, 14336 x 4096 at 333 tokens 155 -> 149.)
+    uint2 hsc[GM_RT];
+    auto load_scales = [&](int rt, int bb) __attribute__((always_inline)) {
+        hsc[rt] = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint32_t *>(smem + HDR_RING + ((bb & 1) * GM_WAVES + wave) * 1024 + (16 * rt + n) * 16) + 1);
+    };
+    // an exponent in a vector register: an and-or takes one scalar operand, which the mask is
+    uint32_t e1024 = 0x64006400u;
+    asm("" : "+v"(e1024));
+    // B tile `rt` of sub-block s from this wave's quants and the sub-scales in hsc: sc_s * q as binary16 (exact).  A dword
+    // holds the eight weights of lane (n, g); masked in pairs (0,4) (1,5) (2,6) (3,7) into the mantissas of 1024 + q, the odd
+    // pairs (bits 4..7 of a half) of 64 + q without a shift, then one fused multiply-add per pair: (1024 + q) sc - 1024 sc
+    auto build_b = [&](half8 &B, int rt, int s) __attribute__((always_inline)) {
         // request rt of the half brought rows 16 rt .. 16 rt + 15: [row][sub-block of the half][16 bytes]
         const uint32_t w = *reinterpret_cast<const uint32_t *>(smem + WQ_BASE + wave * GM_WQ + (s >> 2) * 4096 + rt * 1024 + n * 64 + (s & 3) * 16 + 4 * g);
-        const uint4 hdr = *reinterpret_cast<const uint4 *>(smem + HDR_RING + ((bb & 1) * GM_WAVES + wave) * 1024 + (16 * rt + n) * 16);
-        const _Float16 sc = static_cast<_Float16>(static_cast<float>(hdr_field(hdr, s)));
+        const _Float16 sc = static_cast<_Float16>(static_cast<unsigned short>(hdr_field(make_uint4(0u, hsc[rt].x, hsc[rt].y, 0u), s)));
         const half2v sc2 = {sc, sc};
-        const _Float16 off = static_cast<_Float16>(-1024.f) * sc; // exact: at most 64512 in magnitude
-        const half2v off2 = {off, off};
+        const _Float16 offa = static_cast<_Float16>(-1024.f) * sc, offb = static_cast<_Float16>(-64.f) * sc; // exact: at most 64512 in magnitude
+        const half2v off2[2] = {{offa, offa}, {offb, offb}};
 #pragma unroll
         for (int pr = 0; pr < 4; ++pr) {
-            const uint32_t bits = ((w >> (4 * pr)) & 0x000f000fu) | 0x64006400u;
-            const half2v r = __builtin_elementwise_fma(__builtin_bit_cast(half2v, bits), sc2, off2);
+            const uint32_t v = pr < 2 ? w : w >> 8;
+            const uint32_t bits = (pr & 1) == 0 ? ((v & 0x000f000fu) | e1024) : ((v & 0x00f000f0u) | (e1024 ^ 0x30003000u));
+            const half2v r = __builtin_elementwise_fma(__builtin_bit_cast(half2v, bits), sc2, off2[pr & 1]);
             B[2 * pr] = r[0];
             B[2 * pr + 1] = r[1];
         }
@@ -383,7 +394,7 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
         d_ = hdr_d(hdr);
         dm_ = hdr_dmin(hdr);
 #pragma unroll
-        for (int s8 = 0; s8 < 8; ++s8) B[s8] = static_cast<_Float16>(static_cast<float>(hdr_field(hdr, 8 + s8)));
+        for (int s8 = 0; s8 < 8; ++s8) B[s8] = static_cast<_Float16>(static_cast<unsigned short>(hdr_field(hdr, 8 + s8)));
     };
 
     // The wave is alone on its SIMD and issues in order: an MFMA occupies the matrix pipe for 16 cycles, during which
@@ -395,7 +406,7 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
     float dd[GM_RT], dm[GM_RT];
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"(GM_AHEAD * DM + 4) : "memory"); // headers and first half of super-block 0 have landed
 #pragma unroll
-    for (int rt = 0; rt < GM_RT; ++rt) build_b(Bc[rt], rt, 0, 0);
+    for (int rt = 0; rt < GM_RT; ++rt) { load_scales(rt, 0); build_b(Bc[rt], rt, 0); }
 
     for (int b = 0; b < nbl; ++b) {
         // one position; s as a constant of the type system (a loop over s with "#pragma unroll" is refused by the
@@ -457,7 +468,7 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
                         acch[tt][rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(cl, Bc[rt], acch[tt][rt], 0, 0, 0);
                     }
                     if (tt < GM_RT) {
-                        if (s < 7) build_b(Bn[tt], tt, b, s + 1);
+                        if (s < 7) build_b(Bn[tt], tt, s + 1);
                         else build_m(Bn[tt], dd[tt], dm[tt], tt, b);
 #pragma unroll
                         for (int k = 0; k < 2 * GM_RT; ++k) { // one MFMA, then up to four VALU instructions of the build
@@ -485,7 +496,7 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
                             yacc[tt][rt][i] += fmaf(dd[rt], acch[tt][rt][i], -(dm[rt] * am[i]));
                     }
                     if (tt < GM_RT) {
-                        if (b + 1 < nbl) build_b(Bn[tt], tt, b + 1, 0);
+                        if (b + 1 < nbl) { load_scales(tt, b + 1); build_b(Bn[tt], tt, 0); }
                         else Bn[tt] = Bc[tt];
                     }
                     __builtin_amdgcn_sched_barrier(0);
