@@ -162,8 +162,8 @@ prima_status prima_layer_window_decode(const prima_dims *d, const prima_layer *l
 /*
  * One step of a batch of B independent sequences through the window: sequence b contributes one token
  * (x_in[b], fp32 [B][e]) that continues its own cached context of n_past[b] rows (continuous batching of
- * requests on a layer window, App. A.12).  The mat-vecs stream the weights once for up to 8 tokens, as for T
- * tokens of one sequence; attention, RoPE (position n_past[b]) and the KV append run per sequence.
+ * requests on a layer window, App. A.12).  The mat-vecs stream the weights once for all tokens (FP32 matrices and very
+ * long rows: once for up to 8), as for T tokens of one sequence; attention, RoPE (position n_past[b]) and the KV append run per sequence.
  *   n_past    HOST array of B lengths, 0 <= n_past[b] < kv_cap; they may differ.
  *   k_caches  HOST array of L*B DEVICE pointers: entry [l*B + b] is the fp16 K cache [n_kv_heads][kv_cap][head_dim]
  *   v_caches  of layer l for sequence b (same layout as prima_layer.k_cache / v_cache, which this call ignores;
@@ -313,7 +313,8 @@ prima_status prima_repack_gguf(int32_t fmt, const void *src, int64_t n_rows, int
  * naming the prima_format of each of layer i's seven matrices (the pointers of prima_layer then point at
  * tensors in those formats).  Same results as if every matrix were dequantised to fp32 and multiplied
  * (within the tolerance of prima_layer_window_decode).  Q4_K matrices run as in prima_layer_window_decode,
- * the others through the mat-vec of prima_fmt_gemv with the same fused RMSNorm and residual.
+ * the others through the mat-vec of prima_fmt_gemv, or from 4 tokens on through weight streams of their own, with the
+ * same RMSNorm and residual.
  * Errors as prima_layer_window_decode; a format code outside prima_format: PRIMA_E_SHAPE.
  */
 typedef struct {
