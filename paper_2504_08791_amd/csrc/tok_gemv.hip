@@ -1,5 +1,6 @@
-// Mat-vec of 2 to 16 tokens for weights in the other formats (Q5_K, Q6_K, Q8_0, FP16), without scratch: the kernel behind
-// prima_fmt_gemv and prima_lm_head_fmt for several tokens (one token: fmt_gemv.hip).  Arithmetic and layouts: tok_common.h.
+// Mat-vec of 2 to 16 tokens for weights in the other formats (Q5_K, Q6_K, Q8_0, FP16), and of 9 to 16 (11 to 16) for tall Q4_K matrices,
+// without scratch: the kernel behind prima_fmt_gemv and prima_lm_head_fmt for several tokens (one token: fmt_gemv.hip), and
+// behind prima_q4k_gemv and prima_lm_head where tok_gemv_takes() says so.  Arithmetic and layouts: tok_common.h.
 //
 // One workgroup of 8 waves per compute unit.  It owns a share of the 16-row tiles and walks all of K in chunks: the
 // activations of a chunk (all tokens) are normalised, split and laid out in LDS by the workgroup, then the waves stream
@@ -297,9 +298,14 @@ prima_status launch_fmt(const TokArgs &a, hipStream_t st)
 //   Q6_K 5120 x 13824    5 tokens  51 / 47,  6: 50 / 53,   8: 51 / 70    Q8_0  5: 48 / 41,  6: 48 / 49,  8: 48 / 61
 //   Q6_K 5120 x 5120     5 tokens  22 / 17,  6: 22 / 19,   8: 23 / 28    Q8_0  5: 21 / 16,  6: 21 / 18,  8: 21 / 25
 //   Q6_K 8192 x 28672    5 tokens 104 / 96,  6: 104 / 118, 8: 104 / 145  Q8_0  5: 115 / 85, 6: 116 / 103, 8: 117 / 130
+// Q4_K, against two passes of the integer mat-vec (q4k_gemv_mfma.hip), which has scratch to divide K among workgroups:
+//   128256 x 8192        9 tokens 190 / 256, 16: 192 / 326    60000 x 2048   9: 32 / 46, 16: 33 / 59
+//   28672 x 8192        11 tokens  66 / 77,  16: 66 / 86      8192 x 28672   9: 130 / 73, 16: 131 / 91
+//   40000 x 28672        9 tokens 325 / 300, 11: 335 / 334, 16: 340 / 391   33000 x 5120   9: 60 / 56, 11: 61 / 66, 16: 60 / 71
 // With few rows every workgroup prepares all of the activations for a tile or two; the mat-vec keeps what it is faster at.
 bool tok_gemv_takes(int fmt, int64_t n_rows, int64_t n_cols, int T)
 {
+    if (fmt == PRIMA_FMT_Q4_K) return T <= PRIMA_MAX_TOK && ((T >= 11 && n_rows >= 28672) || (T >= 9 && n_rows >= 65536)) && n_cols / QK < (1 << 18) && n_rows < (int64_t{1} << 34);
     if (fmt != PRIMA_FMT_Q5_K && fmt != PRIMA_FMT_Q6_K && fmt != PRIMA_FMT_Q8_0 && fmt != PRIMA_FMT_F16) return false;
     if (T < 2 || T > PRIMA_MAX_TOK || n_cols / QK >= (1 << 18) || n_rows >= (int64_t{1} << 34)) return false; // (32-bit offsets in a tile's 16 rows, 32-bit tile numbers)
     return T >= 7 || n_rows >= 65536 || (T >= 4 && n_rows >= 16384);
@@ -312,6 +318,7 @@ prima_status launch_tok_gemv(int fmt, const uint8_t *W, int64_t n_rows, int64_t 
     a.W = W; a.n_rows = n_rows; a.nb = static_cast<int>(n_cols / QK); a.x = x; a.ldx = ldx; a.gain = gain; a.eps = eps;
     a.resid = resid; a.ldr = ldr; a.y = y; a.ldy = ldy; a.T = T; a.n_tiles = static_cast<int>((n_rows + 15) / 16);
     switch (fmt) {
+    case PRIMA_FMT_Q4_K: return T > 8 ? launch_nt<PRIMA_FMT_Q4_K, 16>(a, st) : PRIMA_E_SHAPE;
     case PRIMA_FMT_Q5_K: return launch_fmt<PRIMA_FMT_Q5_K>(a, st);
     case PRIMA_FMT_Q6_K: return launch_fmt<PRIMA_FMT_Q6_K>(a, st);
     case PRIMA_FMT_Q8_0: return launch_fmt<PRIMA_FMT_Q8_0>(a, st);

@@ -605,9 +605,11 @@ prima_status prima_q4k_gemv(const void *W, int64_t n_rows, int64_t n_cols, const
     if (!aligned(W, 16) || !aligned(x, 16) || !aligned(y, 4) || ldx % 4 || !aligned(workspace, 256)) return PRIMA_E_ALIGN;
     if (workspace_bytes < std::max<size_t>(256, gemv_ws_bytes(n_rows, n_cols, T))) return PRIMA_E_WORKSPACE;
     if (n_rows == 0) return PRIMA_OK;
+    hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    if (tok_gemv_takes(PRIMA_FMT_Q4_K, n_rows, n_cols, T))
+        return launch_tok_gemv(PRIMA_FMT_Q4_K, static_cast<const uint8_t *>(W), n_rows, n_cols, x, ldx, T, nullptr, 0.f, nullptr, 0, y, ldy, st);
     GemvArgs ga = gemv_args(1, n_cols, x, ldx, T);
     ga.seg[0] = seg(W, y, n_rows, ldy);
-    hipStream_t st = static_cast<hipStream_t>(hip_stream);
     // The arrival counters are cleared only where a pass counts arrivals: a launch less for K that fits one slab, which
     // in a small mat-vec (1024 x 4096, one token) was half of the call
     return launch_gemv_mfma(ga, workspace, workspace_bytes, gemv_arrivals_bytes(n_rows), st, true);
@@ -652,6 +654,9 @@ prima_status prima_q4k_gemv_noalloc(const void *W, int64_t n_rows, int64_t n_col
     const size_t need = std::max<size_t>(256, gemv_ws_bytes(n_rows, n_cols, T));
     if (need > PRIMA_NOALLOC_SCRATCH_BYTES) return PRIMA_E_WORKSPACE; // beyond the fixed array: use prima_q4k_gemv
     if (n_rows == 0) return PRIMA_OK;
+    if (tok_gemv_takes(PRIMA_FMT_Q4_K, n_rows, n_cols, T))
+        return launch_tok_gemv(PRIMA_FMT_Q4_K, static_cast<const uint8_t *>(W), n_rows, n_cols, x, ldx, T, nullptr, 0.f, nullptr, 0, y, ldy,
+                               static_cast<hipStream_t>(hip_stream));
     void *ws = nullptr;
     prima_status s = noalloc_scratch(&ws);
     if (s != PRIMA_OK) return s;
@@ -1059,6 +1064,8 @@ prima_status prima_lm_head(const prima_dims *d, const float *g_final, const void
     if (!aligned(g_final, 16) || !aligned(w_lm, 16) || !aligned(x, 16) || !aligned(logits, 4) || !aligned(workspace, 256)) return PRIMA_E_ALIGN;
     if (workspace_bytes < prima_lm_head_workspace_bytes(d, vocab, T)) return PRIMA_E_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    if (tok_gemv_takes(PRIMA_FMT_Q4_K, vocab, d->e, T))
+        return launch_tok_gemv(PRIMA_FMT_Q4_K, static_cast<const uint8_t *>(w_lm), vocab, d->e, x, d->e, T, g_final, d->rms_eps, nullptr, 0, logits, vocab, st);
     GemvArgs ga = gemv_args(1, d->e, x, d->e, T, X_RMSNORM, g_final, d->rms_eps);
     ga.seg[0] = seg(w_lm, logits, vocab, vocab);
     return launch_gemv_mfma(ga, workspace, workspace_bytes, gemv_arrivals_bytes(vocab), st, true);

@@ -264,6 +264,22 @@ def test_matrix_core_matvec_edges(gpu_lib, fmt, rows, cols, tokens):
         assert rel_err(got[:, pick], ref) <= GEMV_TOL, (fmt, rows, T)
 
 
+@pytest.mark.parametrize("rows,nb,T", [(28672, 1, 11), (28687, 3, 16), (65537, 2, 9)])
+def test_tall_q4k_matvec_of_many_tokens(gpu_lib, rows, nb, T):
+    """Many tokens of a tall Q4_K matrix (one pass on the matrix cores): ragged last tile, one super-block, an odd number of
+    them; with and without scratch the same bits."""
+    rng = np.random.default_rng(rows + T)
+    W = _dev(synth.fmt_tensor(0, 1, "wq", "q4_k", rows, nb * 256)).view(rows, nb, 144)
+    x = rng.standard_normal((T, nb * 256)).astype(np.float32) * np.logspace(-3, 3, T, dtype=np.float32)[:, None]
+    w = gpu_lib.q4k_dequant(W).cpu().numpy().astype(np.float64)
+    ref = x.astype(np.float64) @ w.T
+    got = gpu_lib.q4k_gemv(W, _dev(x))
+    assert rel_err(got.cpu().numpy(), ref) <= GEMV_TOL
+    other = torch.empty_like(got)
+    gpu_lib.q4k_gemv_noalloc(W, _dev(x), other)
+    assert torch.equal(got, other)
+
+
 @pytest.mark.parametrize("mix", sorted(MIXES))
 @pytest.mark.parametrize("name,T", [("t1", 8), ("t0", 9), ("t1", 16), ("t2", 13)])
 def test_window_of_many_tokens(gpu_lib, mix, name, T):
