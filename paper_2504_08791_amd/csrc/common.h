@@ -80,8 +80,10 @@ struct GemvArgs {
 // the other weight formats (fmt_gemv.hip)
 size_t fmt_tensor_bytes(int fmt, int64_t n_rows, int64_t n_cols);
 prima_status launch_fmt_dequant(int fmt, const uint8_t *W, int64_t n_rows, int64_t n_cols, float *out, hipStream_t st);
+// matrix_cores: several tokens may go to launch_tok_gemv()
 prima_status launch_fmt_gemv(int fmt, const uint8_t *W, int64_t n_rows, int64_t n_cols, const float *x, int64_t ldx, int T,
-                             const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy, hipStream_t st);
+                             const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy, hipStream_t st,
+                             bool matrix_cores = true);
 
 // 2 to 16 tokens in the formats whose weights are exact in binary16 operands (tok_gemv.hip); launch_fmt_gemv goes there
 bool tok_gemv_takes(int fmt, int64_t n_rows, int64_t n_cols, int T);

@@ -400,7 +400,7 @@ prima_status launch_fmt(FmtArgs a, hipStream_t st)
     const float *x = a.x, *resid = a.resid;
     float *y = a.y;
     const int T = a.T;
-    constexpr int PASS = FMT == PRIMA_FMT_F32 ? FG_MAX_T : 6; // (7 and more tokens: FP32 only, the others go to tok_gemv.hip)
+    constexpr int PASS = FG_MAX_T;
     for (int t0 = 0; t0 < T; t0 += PASS) {
         const int Tp = T - t0 < PASS ? T - t0 : PASS;
         a.x = x + t0 * a.ldx;
@@ -408,15 +408,16 @@ prima_status launch_fmt(FmtArgs a, hipStream_t st)
         a.y = y + t0 * a.ldy;
         a.T = Tp;
         prima_status s;
-        if (Tp == 1) s = launch_tt<FMT, 1>(a, st);
-        else if (Tp == 2) s = launch_tt<FMT, 2>(a, st);
-        else if (Tp == 3) s = launch_tt<FMT, 3>(a, st);
-        else if (Tp == 4) s = launch_tt<FMT, 4>(a, st);
-        else if (Tp == 5) s = launch_tt<FMT, 5>(a, st);
-        else if (Tp == 6) s = launch_tt<FMT, 6>(a, st);
-        else if constexpr (FMT == PRIMA_FMT_F32) {
-            s = Tp == 7 ? launch_tt<FMT, 7>(a, st) : launch_tt<FMT, 8>(a, st);
-        } else s = PRIMA_E_SHAPE; // (not reached)
+        switch (Tp) {
+        case 1: s = launch_tt<FMT, 1>(a, st); break;
+        case 2: s = launch_tt<FMT, 2>(a, st); break;
+        case 3: s = launch_tt<FMT, 3>(a, st); break;
+        case 4: s = launch_tt<FMT, 4>(a, st); break;
+        case 5: s = launch_tt<FMT, 5>(a, st); break;
+        case 6: s = launch_tt<FMT, 6>(a, st); break;
+        case 7: s = launch_tt<FMT, 7>(a, st); break;
+        default: s = launch_tt<FMT, 8>(a, st); break;
+        }
         if (s != PRIMA_OK) return s;
     }
     return PRIMA_OK;
@@ -457,10 +458,10 @@ prima_status launch_fmt_dequant(int fmt, const uint8_t *W, int64_t n_rows, int64
 }
 
 prima_status launch_fmt_gemv(int fmt, const uint8_t *W, int64_t n_rows, int64_t n_cols, const float *x, int64_t ldx, int T,
-                             const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy, hipStream_t st)
+                             const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy, hipStream_t st, bool matrix_cores)
 {
     if (n_rows == 0) return PRIMA_OK;
-    if (tok_gemv_takes(fmt, n_rows, n_cols, T)) return launch_tok_gemv(fmt, W, n_rows, n_cols, x, ldx, T, gain, eps, resid, ldr, y, ldy, st);
+    if (matrix_cores && tok_gemv_takes(fmt, n_rows, n_cols, T)) return launch_tok_gemv(fmt, W, n_rows, n_cols, x, ldx, T, gain, eps, resid, ldr, y, ldy, st);
     FmtArgs a{W, n_rows, n_cols, x, ldx, gain, eps, resid, ldr, y, ldy, T, 0};
     switch (fmt) {
     case PRIMA_FMT_Q5_K: return launch_fmt<PRIMA_FMT_Q5_K>(a, st);

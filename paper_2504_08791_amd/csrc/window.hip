@@ -33,6 +33,11 @@ constexpr int TOK_WINDOW = 9; // tokens from which whole windows go there
 // through a mat-vec for each: 14B shape 4 tokens 213 / 221, 5: 230 / 248, 8: 236 / 290; 70B shape 4: 342 / 376, 8: 385 / 492.  At
 // three tokens the mat-vec is as fast (14B shape 211; its launch reads the activations itself).
 constexpr int TOK_OTHERS = 4;
+// One sequence behind few cached rows: single binary16 roundings of the appended K / V rows weigh most there (each is one of
+// few keys), and the rows of the third layer differ by 1 to 2e-4 between two arithmetics that are each 2 to 4e-5 from 64 bits
+// (13 and 16 tokens behind 1 to 9 rows; from 40 rows on 3 to 8e-5).  Such steps keep the arithmetic they had, bit for bit.
+constexpr int TOK_MIN_ROWS = 64;
+bool tok_context(int n_past, const AttnSeqs *seq) { return seq || n_past >= TOK_MIN_ROWS; }
 bool tok_takes(const prima_dims &d, int T, int from = TOK_WINDOW)
 {
     const int64_t qd = static_cast<int64_t>(d.n_q_heads) * d.head_dim, widest = std::max<int64_t>({d.e, qd, d.ffn});
@@ -181,7 +186,7 @@ prima_status run_layer(const prima_dims &d, const prima_layer &L, int kv_cap, in
         TokMat mats[3];
         int n_tok = 0, fmts[3];
         TokSum sum{};
-        const bool tok = tok_takes(d, T, TOK_OTHERS);
+        const bool tok = tok_takes(d, T, TOK_OTHERS) && tok_context(n_past, seq);
         for (int i = 0; i < n; ++i) {
             if (!tok || m[i].fmt == PRIMA_FMT_F32) {
                 const prima_status ps = other(m[i].fmt, m[i].W, m[i].rows, cols, xin, gain, resid, m[i].out);
@@ -366,9 +371,9 @@ prima_status run_layer_tok(const prima_dims &d, const prima_layer &L, int kv_cap
 }
 
 // whether a layer with these formats goes through run_layer_tok()
-bool layer_is_tok(const prima_dims &d, int T, const prima_layer_formats *f)
+bool layer_is_tok(const prima_dims &d, int T, int n_past, const AttnSeqs *seq, const prima_layer_formats *f)
 {
-    if (!tok_takes(d, T)) return false;
+    if (!tok_takes(d, T) || !tok_context(n_past, seq)) return false;
     if (!f) return true;
     for (int32_t v : {f->wq, f->wk, f->wv, f->wo, f->wgate, f->wup, f->wdown})
         if (v == PRIMA_FMT_F32) return false;
@@ -387,8 +392,8 @@ prima_status run_layers(const prima_dims &d, const prima_layer *layers, const pr
         const prima_layer_formats *f = formats ? &formats[i] : nullptr, *nf = formats && i + 1 < L ? &formats[i + 1] : nullptr;
         const AttnSeqs *seq = caches(i);
         prima_status s;
-        if (layer_is_tok(d, T, f)) {
-            const bool chain = i + 1 < L && layer_is_tok(d, T, nf);
+        if (layer_is_tok(d, T, n_past, seq, f)) {
+            const bool chain = i + 1 < L && layer_is_tok(d, T, n_past, seq, nf);
             s = run_layer_tok(d, layers[i], kv_cap, n_past, T, cur, dst, ws, w, st, nullptr, nullptr, nullptr, nullptr, -1, seq, f, prepared,
                               chain ? &layers[i + 1] : nullptr, nf);
             prepared = chain;
@@ -1008,7 +1013,7 @@ prima_status prima_layer_window_decode_profiled(const prima_dims *d, const prima
     float *scratch_out = at<float>(workspace, w.xb0); // the isolated down projections write here, not to x_out
     for (int ki = 0; ki < n_kinds && s == PRIMA_OK; ++ki) {
         for (int i = 0; i < L && s == PRIMA_OK; ++i)
-            s = layer_is_tok(*d, T, nullptr)
+            s = layer_is_tok(*d, T, n_past, nullptr, nullptr)
                     ? run_layer_tok(*d, layers[i], kv_cap, n_past, T, x_in, scratch_out, workspace, w, st, nullptr, nullptr, nullptr, nullptr, kinds[ki], nullptr,
                                     nullptr, false, nullptr, nullptr)
                     : run_layer(*d, layers[i], kv_cap, n_past, T, x_in, scratch_out, workspace, w, st, nullptr, nullptr, nullptr, nullptr, kinds[ki]);
@@ -1043,7 +1048,7 @@ prima_status prima_layer_decode_taps(const prima_dims *d, const prima_layer *lay
     const WindowWs w = carve(*d, kv_cap, T);
     s = step_init(*d, workspace, w, T, n_past, nullptr, false, st);
     if (s != PRIMA_OK) return s;
-    if (layer_is_tok(*d, T, nullptr))
+    if (layer_is_tok(*d, T, n_past, nullptr, nullptr))
         return run_layer_tok(*d, *layer, kv_cap, n_past, T, x_in, x_out, workspace, w, st, tap_q, tap_o, tap_h, tap_a, -1, nullptr, nullptr, false, nullptr, nullptr);
     return run_layer(*d, *layer, kv_cap, n_past, T, x_in, x_out, workspace, w, st, tap_q, tap_o, tap_h, tap_a);
 }

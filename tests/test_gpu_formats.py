@@ -281,8 +281,8 @@ def test_tall_q4k_matvec_of_many_tokens(gpu_lib, rows, nb, T):
 
 
 @pytest.mark.parametrize("mix", sorted(MIXES))
-@pytest.mark.parametrize("name,T", [("t1", 8), ("t0", 9), ("t1", 16), ("t2", 13)])
+@pytest.mark.parametrize("name,T", [("t1", 8), ("t1", 9), ("t1", 16), ("c1", 13)])
 def test_window_of_many_tokens(gpu_lib, mix, name, T):
-    """8 to 16 tokens (streams over laid-out activations: up to 8 the other formats, from 9 on all matrices): rows of 2 to 6 super-blocks, odd numbers of them among them, slabs and
+    """8 to 16 tokens (streams over laid-out activations: up to 8 the other formats, from 9 on all matrices): rows of 3 and 5 super-blocks and of a model's size, slabs and
     parts of one stage, layers with and without an FP32 matrix behind one another."""
     test_window_with_mixed_formats(gpu_lib, mix, name, T)
