@@ -177,7 +177,8 @@ prima_status run_layer(const prima_dims &d, const prima_layer &L, int kv_cap, in
     const int f_g = fm ? fm->wgate : 0, f_u = fm ? fm->wup : 0, f_d = fm ? fm->wdown : 0;
     auto other = [&](int fmt, const void *W, int64_t rows, int64_t cols, const float *xin, const float *gain,
                      const float *resid, float *out) {
-        return launch_fmt_gemv(fmt, static_cast<const uint8_t *>(W), rows, cols, xin, cols, T, gain, d.rms_eps, resid, rows, out, rows, st);
+        return launch_fmt_gemv(fmt, static_cast<const uint8_t *>(W), rows, cols, xin, cols, T, gain, d.rms_eps, resid, rows, out, rows, st,
+                               tok_context(n_past, seq));
     };
     // The matrices of a group in other formats than Q4_K, n of them.  From TOK_OTHERS tokens on all but FP32 through the weight
     // streams of tok_stream.hip (activations laid out, streamed, shares added), else a format mat-vec each.
