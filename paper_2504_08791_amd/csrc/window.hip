@@ -38,12 +38,16 @@ constexpr int TOK_OTHERS = 4;
 // (13 and 16 tokens behind 1 to 9 rows; from 40 rows on 3 to 8e-5).  Such steps keep the arithmetic they had, bit for bit.
 constexpr int TOK_MIN_ROWS = 64;
 bool tok_context(int n_past, const AttnSeqs *seq) { return seq || n_past >= TOK_MIN_ROWS; }
-bool tok_takes(const prima_dims &d, int T, int from = TOK_WINDOW)
+// Whether these dimensions have a region for the streams in their scratch: a rule on the widths alone, so that scratch sized for
+// more tokens holds what fewer need (with the token slots in it, K beyond 131072 had a region for 4 to 8 tokens and none for 9 to 16).
+bool tok_dims(const prima_dims &d)
 {
     const int64_t qd = static_cast<int64_t>(d.n_q_heads) * d.head_dim, widest = std::max<int64_t>({d.e, qd, d.ffn});
-    return T >= from && widest / QK <= 1024 && tok_max_parts(static_cast<int>(widest / QK), tok_slots(T)) <= 256 &&
+    return widest / QK <= 1024 && tok_max_parts(static_cast<int>(widest / QK), tok_slots(PRIMA_MAX_TOK)) <= 256 &&
            (2 * static_cast<int64_t>(d.ffn) + qd + 2 * static_cast<int64_t>(d.n_kv_heads) * d.head_dim) < (int64_t{1} << 30);
 }
+// ... and whether a step of T tokens on this scratch uses it
+bool tok_takes(const WindowWs &w, int T, int from = TOK_WINDOW) { return T >= from && w.tok_part_floats != 0; }
 
 WindowWs carve(const prima_dims &d, int kv_cap, int T)
 {
@@ -75,7 +79,7 @@ WindowWs carve(const prima_dims &d, int kv_cap, int T)
     w.gemv_bytes += w.arrivals_bytes; // the counter region is sized for the tallest matrix
     w.gemv = take(w.gemv_bytes);
     w.sync = take(WAIT_FLAG_BYTES);
-    if (tok_takes(d, T, TOK_OTHERS)) {
+    if (T >= TOK_OTHERS && tok_dims(d)) {
         const int64_t widest = std::max<int64_t>({d.e, static_cast<int64_t>(qd), d.ffn});
         for (size_t &r : w.tok_rec) r = take(tok_rec_bytes(widest, T));
         w.tok_ss = take(tok_ss_bytes(d.e, T));
@@ -187,7 +191,7 @@ prima_status run_layer(const prima_dims &d, const prima_layer &L, int kv_cap, in
         TokMat mats[3];
         int n_tok = 0, fmts[3];
         TokSum sum{};
-        const bool tok = tok_takes(d, T, TOK_OTHERS) && tok_context(n_past, seq);
+        const bool tok = tok_takes(w, T, TOK_OTHERS) && tok_context(n_past, seq);
         for (int i = 0; i < n; ++i) {
             if (!tok || m[i].fmt == PRIMA_FMT_F32) {
                 const prima_status ps = other(m[i].fmt, m[i].W, m[i].rows, cols, xin, gain, resid, m[i].out);
@@ -372,9 +376,9 @@ prima_status run_layer_tok(const prima_dims &d, const prima_layer &L, int kv_cap
 }
 
 // whether a layer with these formats goes through run_layer_tok()
-bool layer_is_tok(const prima_dims &d, int T, int n_past, const AttnSeqs *seq, const prima_layer_formats *f)
+bool layer_is_tok(const WindowWs &w, int T, int n_past, const AttnSeqs *seq, const prima_layer_formats *f)
 {
-    if (!tok_takes(d, T) || !tok_context(n_past, seq)) return false;
+    if (!tok_takes(w, T) || !tok_context(n_past, seq)) return false;
     if (!f) return true;
     for (int32_t v : {f->wq, f->wk, f->wv, f->wo, f->wgate, f->wup, f->wdown})
         if (v == PRIMA_FMT_F32) return false;
@@ -393,8 +397,8 @@ prima_status run_layers(const prima_dims &d, const prima_layer *layers, const pr
         const prima_layer_formats *f = formats ? &formats[i] : nullptr, *nf = formats && i + 1 < L ? &formats[i + 1] : nullptr;
         const AttnSeqs *seq = caches(i);
         prima_status s;
-        if (layer_is_tok(d, T, n_past, seq, f)) {
-            const bool chain = i + 1 < L && layer_is_tok(d, T, n_past, seq, nf);
+        if (layer_is_tok(w, T, n_past, seq, f)) {
+            const bool chain = i + 1 < L && layer_is_tok(w, T, n_past, seq, nf);
             s = run_layer_tok(d, layers[i], kv_cap, n_past, T, cur, dst, ws, w, st, nullptr, nullptr, nullptr, nullptr, -1, seq, f, prepared,
                               chain ? &layers[i + 1] : nullptr, nf);
             prepared = chain;
@@ -1014,7 +1018,7 @@ prima_status prima_layer_window_decode_profiled(const prima_dims *d, const prima
     float *scratch_out = at<float>(workspace, w.xb0); // the isolated down projections write here, not to x_out
     for (int ki = 0; ki < n_kinds && s == PRIMA_OK; ++ki) {
         for (int i = 0; i < L && s == PRIMA_OK; ++i)
-            s = layer_is_tok(*d, T, n_past, nullptr, nullptr)
+            s = layer_is_tok(w, T, n_past, nullptr, nullptr)
                     ? run_layer_tok(*d, layers[i], kv_cap, n_past, T, x_in, scratch_out, workspace, w, st, nullptr, nullptr, nullptr, nullptr, kinds[ki], nullptr,
                                     nullptr, false, nullptr, nullptr)
                     : run_layer(*d, layers[i], kv_cap, n_past, T, x_in, scratch_out, workspace, w, st, nullptr, nullptr, nullptr, nullptr, kinds[ki]);
@@ -1049,7 +1053,7 @@ prima_status prima_layer_decode_taps(const prima_dims *d, const prima_layer *lay
     const WindowWs w = carve(*d, kv_cap, T);
     s = step_init(*d, workspace, w, T, n_past, nullptr, false, st);
     if (s != PRIMA_OK) return s;
-    if (layer_is_tok(*d, T, n_past, nullptr, nullptr))
+    if (layer_is_tok(w, T, n_past, nullptr, nullptr))
         return run_layer_tok(*d, *layer, kv_cap, n_past, T, x_in, x_out, workspace, w, st, tap_q, tap_o, tap_h, tap_a, -1, nullptr, nullptr, false, nullptr, nullptr);
     return run_layer(*d, *layer, kv_cap, n_past, T, x_in, x_out, workspace, w, st, tap_q, tap_o, tap_h, tap_a);
 }

@@ -261,6 +261,18 @@ def test_format_calls_argument_errors():
     assert w(formats=bad) == 2
 
 
+def test_scratch_for_more_tokens_holds_what_fewer_need():
+    """prima_workspace_bytes promises scratch for up to T tokens, so it must not fall with T; widths on both sides of 131072
+    columns among them (the region of the weight streams once ended at 8 tokens there: a window made for 16 tokens refused 5)."""
+    L = _ffi.lib()
+    for D, Hkv, G in [(64, 1, 4), (128, 1, 2), (128, 2, 5), (128, 8, 8)]:
+        for e in (256, 1536, 5120, 8192):
+            for ffn in (256, 1280, 4864, 14336, 28672, 130816, 131072, 131328, 140032, 262144, 262400):
+                d = _ffi.Dims(e, Hkv * G, Hkv, D, ffn, 1e4, 1e-5, 0)
+                need = [L.prima_workspace_bytes(C.byref(d), 1100, T) for T in range(1, 17)]
+                assert need == sorted(need), (D, Hkv, G, e, ffn, need)
+
+
 def test_missing_library_is_an_error(monkeypatch, tmp_path):
     monkeypatch.setattr(_ffi, "_lib", None)
     monkeypatch.setattr(_ffi, "LIB_PATH", str(tmp_path / "absent.so"))

@@ -286,3 +286,28 @@ def test_window_of_many_tokens(gpu_lib, mix, name, T):
     """8 to 16 tokens (streams over laid-out activations: up to 8 the other formats, from 9 on all matrices): rows of 3 and 5 super-blocks and of a model's size, slabs and
     parts of one stage, layers with and without an FP32 matrix behind one another."""
     test_window_with_mixed_formats(gpu_lib, mix, name, T)
+
+
+def test_scratch_of_a_wide_model_serves_every_token_count(gpu_lib):
+    """Rows of more than 131072 columns, no scratch region for the weight streams: a window made for 16 tokens takes steps of
+    any number, and short prompts whose last piece has 4 to 8 tokens leave their scratch alone."""
+    from workloads.configs import ModelDims, WindowConfig
+    d = ModelDims(256, 2, 1, 128, 131328, 1e4)
+    fm = [{"wv": "q6_k", "wgate": "q5_k", "wup": "q6_k", "wdown": "q6_k"}]     # (Q4_K rows of this width take four tokens at most)
+    rng = np.random.default_rng(5)
+    for n_past, counts in ((64, (5, 8, 9, 16)), (3, (7,))):
+        host = synth.layer_tensors(WindowConfig("wide", 77, d, 1, 16, n_past), 0, kv_cap=n_past + 20, formats=fm[0])
+        x = rng.standard_normal((20, d.e)).astype(np.float32)
+        ref = oracle.layer(d, {k: np.array(v) for k, v in host.items()}, x.astype(np.float64), n_past, formats=fm[0])
+        dev = {k: _dev(v) for k, v in host.items()}
+        win = gpu_lib.Window(d, [dev], n_past + 20, T_max=16, formats=fm)
+        win.workspace.fill_(0xFF)
+        for T in counts:
+            y = win.decode(_dev(x[:T]), n_past).cpu().numpy()
+            check_hidden(f"wide, {n_past} cached rows, T={T}", rel_err(y, ref[:T]), d, [host], x[:T].astype(np.float64), n_past, formats=fm, eps=EPS_FP32)
+        gpu_lib.set_prefill_small_tokens(32)
+        try:
+            y = win.prefill(_dev(x), n_past).cpu().numpy()
+        finally:
+            gpu_lib.set_prefill_small_tokens(gpu_lib.PREFILL_SMALL_TOKENS)
+        check_hidden(f"wide, {n_past} cached rows, prompt", rel_err(y, ref), d, [host], x.astype(np.float64), n_past, formats=fm, eps=EPS_FP32)
