@@ -400,9 +400,8 @@ prima_status launch_fmt(FmtArgs a, hipStream_t st)
     const float *x = a.x, *resid = a.resid;
     float *y = a.y;
     const int T = a.T;
-    constexpr int PASS = FG_MAX_T;
-    for (int t0 = 0; t0 < T; t0 += PASS) {
-        const int Tp = T - t0 < PASS ? T - t0 : PASS;
+    for (int t0 = 0; t0 < T; t0 += FG_MAX_T) {
+        const int Tp = T - t0 < FG_MAX_T ? T - t0 : FG_MAX_T;
         a.x = x + t0 * a.ldx;
         a.resid = resid ? resid + t0 * a.ldr : nullptr;
         a.y = y + t0 * a.ldy;
@@ -461,7 +460,15 @@ prima_status launch_fmt_gemv(int fmt, const uint8_t *W, int64_t n_rows, int64_t 
                              const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy, hipStream_t st, bool matrix_cores)
 {
     if (n_rows == 0) return PRIMA_OK;
-    if (matrix_cores && tok_gemv_takes(fmt, n_rows, n_cols, T)) return launch_tok_gemv(fmt, W, n_rows, n_cols, x, ldx, T, gain, eps, resid, ldr, y, ldy, st);
+    if (matrix_cores && tok_gemv_takes(fmt, n_rows, n_cols, T)) {
+        const int first = tok_gemv_first(fmt, n_rows, n_cols, T);
+        const prima_status s = launch_tok_gemv(fmt, W, n_rows, n_cols, x, ldx, first, gain, eps, resid, ldr, y, ldy, st);
+        if (s != PRIMA_OK || first == T) return s;
+        x += first * ldx;
+        if (resid) resid += first * ldr;
+        y += first * ldy;
+        T -= first;
+    }
     FmtArgs a{W, n_rows, n_cols, x, ldx, gain, eps, resid, ldr, y, ldy, T, 0};
     switch (fmt) {
     case PRIMA_FMT_Q5_K: return launch_fmt<PRIMA_FMT_Q5_K>(a, st);

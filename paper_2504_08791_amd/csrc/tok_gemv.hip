@@ -264,8 +264,14 @@ prima_status launch_nt(TokArgs a, hipStream_t st)
         chunk = ((a.nb + n_chunks - 1) / n_chunks + SBS - 1) / SBS * SBS;
         const int last = a.nb - (a.nb - 1) / chunk * chunk; // super-blocks of the last chunk
         if (sh > 0 && (1 << sh) > (last + SBS - 1) / SBS) continue; // every part of every chunk has a stage
-        // a chunk costs its operands (about two stages' time) and, round by round, the longest part
-        const double t = static_cast<double>(n_chunks) * (2.0 * ((rounds + blk - 1) / blk) + rounds * static_cast<double>((chunk / SBS + (1 << sh) - 1) >> sh));
+        // A chunk costs its operands (about two stages' time) and, round by round, the longest part.  A wave requests its stages of
+        // a chunk in pairs; where the stream bounds the launch the odd one counts (us, not counted / counted, 8 tokens: FP16
+        // 8192 x 1024 11.6 / 8.8, 4096 x 8192 34 / 30, Q8_0 8192 x 4096 26 / 19; in Q6_K and Q5_K, which unpack longer
+        // than they load, 4096 x 2048 would go from 9.4 to 10.2).
+        const int part = (chunk / SBS + (1 << sh) - 1) >> sh, blocks = (rounds + blk - 1) / blk, last_blk = rounds - (blocks - 1) * blk;
+        const bool padding = FMT == PRIMA_FMT_F16 || (FMT == PRIMA_FMT_Q8_0 && NT <= 8 && a.n_tiles > grid);
+        auto requested = [&](int stages) { return padding ? (stages + 1) / 2 * 2 : stages; };
+        const double t = static_cast<double>(n_chunks) * (2.0 * blocks + (blocks - 1) * requested(blk * part) + requested(last_blk * part));
         if (sh == 0 || t < best * 0.999) {
             best = t;
             a.ks_shift = sh;
@@ -291,24 +297,45 @@ prima_status launch_fmt(const TokArgs &a, hipStream_t st)
 
 } // namespace
 
-// Where the line lies, us, this kernel / the fp32 mat-vec (the first two with the norm in front):
-//   Q6_K 128256 x 8192   2 tokens 186 / 201, 3: 198 / 223, 4: 194 / 266, 8: 203 / 578, 16: 297 / 1113
-//   Q8_0 128256 x 8192   2 tokens 179 / 181, 3: 182 / 201, 4: 182 / 246, 8: 191 / 506, 16: 264 / 972
-//   Q6_K 32000 x 4096    4 tokens  32 / 43,  5: 36 / 49,   8: 36 / 67    Q8_0  4: 34 / 38,  5: 36 / 43,  8: 37 / 55
-//   Q6_K 5120 x 13824    5 tokens  51 / 47,  6: 50 / 53,   8: 51 / 70    Q8_0  5: 48 / 41,  6: 48 / 49,  8: 48 / 61
-//   Q6_K 5120 x 5120     5 tokens  22 / 17,  6: 22 / 19,   8: 23 / 28    Q8_0  5: 21 / 16,  6: 21 / 18,  8: 21 / 25
-//   Q6_K 8192 x 28672    5 tokens 104 / 96,  6: 104 / 118, 8: 104 / 145  Q8_0  5: 115 / 85, 6: 116 / 103, 8: 117 / 130
+// Where the lines lie, us, this kernel / the fp32 mat-vec (replayed from a graph, weights cold; 256 shapes of 16 to 128256 rows and
+// 512 to 28672 columns in each format):
+//   7, 8 tokens     Q6_K 1024 x 8192   8 tokens  24 / 37   Q8_0 8192 x 4096  8: 19 / 20   FP16 8192 x 1024  7: 9.7 / 9.8, 4096 x 8192  8: 26 / 39
+//                   one tile of rows: Q6_K 16 x 4096  7: 14 / 11 (every activation laid out for 16 rows)
+//   9, 10 tokens    as 16 slots: Q6_K 1024 x 8192  9: 48 / 45, 16 x 8192  47 / 31; FP16 1024 x 8192  39 / 49
+//   4 to 6 tokens   Q8_0 16384 x 1024  4: 13 / 11, 16384 x 4096  5: 29 / 26, 16384 x 8192  4: 35 / 39; Q5_K 16384 x 1024  4: 10.6 / 11.1
+//   2 tokens        Q6_K 128256 x 8192  163 / 173, 100000 x 4096  113 / 84 (a fourth round of tiles for a twentieth of them)
+// Below the lines several tokens stay with the mat-vec; 9 and 10 tokens of few rows go as 8 here and the rest there.
 // Q4_K, against two passes of the integer mat-vec (q4k_gemv_mfma.hip), which has scratch to divide K among workgroups:
 //   128256 x 8192        9 tokens 190 / 256, 16: 192 / 326    60000 x 2048   9: 32 / 46, 16: 33 / 59
 //   28672 x 8192        11 tokens  66 / 77,  16: 66 / 86      8192 x 28672   9: 130 / 73, 16: 131 / 91
-//   40000 x 28672        9 tokens 325 / 300, 11: 335 / 334, 16: 340 / 391   33000 x 5120   9: 60 / 56, 11: 61 / 66, 16: 60 / 71
-// With few rows every workgroup prepares all of the activations for a tile or two; the mat-vec keeps what it is faster at.
+//   33000 x 8192        11 tokens  86 / 81 (a second round of tiles for 15 rows in a thousand), 33000 x 5120  11: 61 / 66
+namespace {
+// share of the waves' places in the rounds of a launch that have a tile (one round: the tiles are divided among the waves)
+double places_filled(int64_t n_rows)
+{
+    const int64_t tiles = (n_rows + 15) / 16, per_round = static_cast<int64_t>(TK_CUS) * 8, rounds = (tiles + per_round - 1) / per_round;
+    return rounds <= 1 ? 1. : static_cast<double>(tiles) / static_cast<double>(rounds * per_round);
+}
+bool in_limits(int64_t n_rows, int64_t n_cols) { return n_cols / QK < (1 << 18) && n_rows < (int64_t{1} << 34); } // (32-bit offsets in a tile's 16 rows, 32-bit tile numbers)
+} // namespace
+
 bool tok_gemv_takes(int fmt, int64_t n_rows, int64_t n_cols, int T)
 {
-    if (fmt == PRIMA_FMT_Q4_K) return T <= PRIMA_MAX_TOK && ((T >= 11 && n_rows >= 28672) || (T >= 9 && n_rows >= 65536)) && n_cols / QK < (1 << 18) && n_rows < (int64_t{1} << 34);
-    if (fmt != PRIMA_FMT_Q5_K && fmt != PRIMA_FMT_Q6_K && fmt != PRIMA_FMT_Q8_0 && fmt != PRIMA_FMT_F16) return false;
-    if (T < 2 || T > PRIMA_MAX_TOK || n_cols / QK >= (1 << 18) || n_rows >= (int64_t{1} << 34)) return false; // (32-bit offsets in a tile's 16 rows, 32-bit tile numbers)
-    return T >= 7 || n_rows >= 65536 || (T >= 4 && n_rows >= 16384);
+    if (T > PRIMA_MAX_TOK || !in_limits(n_rows, n_cols)) return false;
+    if (fmt == PRIMA_FMT_Q4_K) return (T >= 9 && n_rows >= 65536) || (T >= 11 && n_rows >= 28672 && (n_cols <= 6144 || places_filled(n_rows) >= 0.6));
+    const bool q8 = fmt == PRIMA_FMT_Q8_0, k_quant = fmt == PRIMA_FMT_Q5_K || fmt == PRIMA_FMT_Q6_K;
+    if (!q8 && !k_quant && fmt != PRIMA_FMT_F16) return false;
+    if (n_rows <= 16) return T >= 13 || (T >= 9 && n_cols <= 1024);
+    if (T >= 7) return !(q8 && T == 7 && n_cols > 16384 && n_rows <= 8192);
+    if (T >= 4) return n_rows >= (q8 && T == 4 ? 32768 : 24576) || (n_rows >= 16384 && (k_quant || n_cols >= (q8 ? 8192 : 2048)));
+    return T >= 2 && n_rows >= 65536 && (T == 3 || (!q8 && (!k_quant || places_filled(n_rows) >= 0.9)));
+}
+
+// tokens of T that go to launch_tok_gemv() in a call of few rows; the others after them to the fp32 mat-vec
+int tok_gemv_first(int fmt, int64_t n_rows, int64_t n_cols, int T)
+{
+    const bool few = n_cols >= 4096 && n_rows <= (fmt == PRIMA_FMT_Q8_0 ? 2048 : 4096);
+    return (T == 9 || T == 10) && few && fmt != PRIMA_FMT_Q4_K && fmt != PRIMA_FMT_F16 && tok_gemv_takes(fmt, n_rows, n_cols, 8) ? 8 : T;
 }
 
 prima_status launch_tok_gemv(int fmt, const uint8_t *W, int64_t n_rows, int64_t n_cols, const float *x, int64_t ldx, int T,
