@@ -33,6 +33,10 @@ constexpr int TOK_WINDOW = 9; // tokens from which whole windows go there
 // through a mat-vec for each: 14B shape 4 tokens 213 / 221, 5: 230 / 248, 8: 236 / 290; 70B shape 4: 342 / 376, 8: 385 / 492.  At
 // three tokens the mat-vec is as fast (14B shape 211; its launch reads the activations itself).
 constexpr int TOK_OTHERS = 4;
+// A group of these matrices takes a launch in front of its streams (one per format) and one behind, the mat-vecs one per matrix.  Up to
+// 7 tokens a launch more pays from about this many weights on.  Two layers, us, mat-vecs / streams, 4 tokens: hidden size 512, V
+// and down in Q6_K 86 / 99, V in Q5_K too 103 / 119; 2048, V in FP16 128 / 129; 4096, V in FP16 192 / 187, all in Q8_0 295 / 251.
+constexpr int64_t TOK_LAUNCH_WEIGHTS = int64_t{1} << 21;
 // One sequence behind few cached rows: single binary16 roundings of the appended K / V rows weigh most there (each is one of
 // few keys), and the rows of the third layer differ by 1 to 2e-4 between two arithmetics that are each 2 to 4e-5 from 64 bits
 // (13 and 16 tokens behind 1 to 9 rows; from 40 rows on 3 to 8e-5).  Such steps keep the arithmetic they had, bit for bit.
@@ -191,7 +195,20 @@ prima_status run_layer(const prima_dims &d, const prima_layer &L, int kv_cap, in
         TokMat mats[3];
         int n_tok = 0, fmts[3];
         TokSum sum{};
-        const bool tok = tok_takes(w, T, TOK_OTHERS) && tok_context(n_past, seq);
+        bool tok = tok_takes(w, T, TOK_OTHERS) && tok_context(n_past, seq);
+        if (T < 8) { // the streams' launches more than the mat-vecs', against what they save on the weights
+            int64_t weights = 0;
+            int n_fmt = 0, n_mats = 0;
+            for (int i = 0; i < n; ++i) {
+                if (m[i].fmt == PRIMA_FMT_F32) continue;
+                bool seen = false;
+                for (int j = 0; j < i; ++j) seen = seen || m[j].fmt == m[i].fmt;
+                n_fmt += !seen;
+                ++n_mats;
+                weights += m[i].rows * cols;
+            }
+            tok = tok && weights >= TOK_LAUNCH_WEIGHTS * (2 + n_fmt - n_mats);
+        }
         for (int i = 0; i < n; ++i) {
             if (!tok || m[i].fmt == PRIMA_FMT_F32) {
                 const prima_status ps = other(m[i].fmt, m[i].W, m[i].rows, cols, xin, gain, resid, m[i].out);
