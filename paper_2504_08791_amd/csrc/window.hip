@@ -517,13 +517,15 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
     auto W = [](const void *p) { return static_cast<const uint8_t *>(p); };
     prima_status s;
 #define PRIMA_TRY(call) do { s = (call); if (s != PRIMA_OK) return s; } while (0)
-    // one projection: out = W a (+ resid), a = xin or RMSNorm(xin; gain); split_ready as for the matrix product
+    // one projection: out = W a (+ resid), a = xin or RMSNorm(xin; gain); split_ready as for the matrix product.  A small matrix alone in
+    // its group and few tokens: two mat-vecs are fewer launches than the split, the product and its shares' sum (two layers of hidden
+    // size 512, down in Q8_0, us, product / mat-vecs: 17 tokens 255 / 212, 33 tokens 288 / 278).
     auto product = [&](int fmt, const void *Wm, int64_t rows, int64_t cols, const float *xin, const float *gain, const float *resid,
-                       float *out, bool split_ready) -> prima_status {
+                       float *out, bool split_ready, bool alone = false) -> prima_status {
         if (fmt == PRIMA_FMT_Q4_K)
             return launch_q4k_gemm(W(Wm), rows, cols, xin, cols, T, gain, d.rms_eps, resid, rows, out, rows, stat, st, split_ready, part,
                                    w.part_bytes);
-        if (fmt_gemm_takes(fmt))
+        if (fmt_gemm_takes(fmt) && !(alone && T <= 2 * PRIMA_MAX_TOK && rows * cols < (int64_t{1} << 20)))
             return launch_fmt_gemm(fmt, W(Wm), rows, cols, xin, cols, T, gain, d.rms_eps, resid, rows, out, rows, stat, st, split_ready, part,
                                    w.part_bytes);
         for (int t0 = 0; t0 < T; t0 += PRIMA_MAX_TOK) {
@@ -556,7 +558,7 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
     if (rest)
         PRIMA_TRY(launch_attn(d, q + n_pieces * PRIMA_MAX_TOK * qd, nullptr, nullptr, nullptr, nullptr, Kc, Vc, kv_cap,
                               n_past + n_pieces * PRIMA_MAX_TOK, rest, o + n_pieces * PRIMA_MAX_TOK * qd, at<char>(ws, w.attn), st));
-    PRIMA_TRY(product(f_o, L.wo, e, qd, o, nullptr, x, h, false));
+    PRIMA_TRY(product(f_o, L.wo, e, qd, o, nullptr, x, h, false, true));
     if (f_g == PRIMA_FMT_Q4_K && f_u == PRIMA_FMT_Q4_K) {
         const GemmMat gate_up[2] = {{W(L.wgate), act, F, F}, {W(L.wup), nullptr, F, F}};
         PRIMA_TRY(launch_q4k_gemm_multi(gate_up, 2, true, e, h, e, T, g_ffn, d.rms_eps, nullptr, 0, stat, st, false, part, w.part_bytes));
@@ -566,7 +568,7 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
         PRIMA_TRY(product(f_u, L.wup, F, e, h, g_ffn, nullptr, up, f_g == PRIMA_FMT_Q4_K || fmt_gemm_takes(f_g)));
         PRIMA_TRY(launch_swiglu(act, up, static_cast<int64_t>(T) * F, st));
     }
-    PRIMA_TRY(product(f_d, L.wdown, e, F, act, nullptr, h, y, false));
+    PRIMA_TRY(product(f_d, L.wdown, e, F, act, nullptr, h, y, false, true));
 #undef PRIMA_TRY
     return PRIMA_OK;
 }

@@ -110,7 +110,7 @@ MIXES = {
 
 
 @pytest.mark.parametrize("mix", sorted(MIXES))
-@pytest.mark.parametrize("name,T,n_past", [("t1", 37, 130), ("t2", 16, 63), ("t0", 70, 37), ("t1", 37, 9), ("t2", 100, 0)])
+@pytest.mark.parametrize("name,T,n_past", [("t1", 37, 130), ("t2", 16, 63), ("t0", 70, 37), ("t1", 37, 9), ("t2", 100, 0), ("t0", 32, 5)])
 def test_prefill_with_mixed_formats(gpu_lib, route, mix, name, T, n_past):
     """Layers whose matrices are in several formats (Q4_K ones through the matrix product, the others 16 tokens a launch
     through the format mat-vec): hidden state and appended rows against the oracle.  (With 37 tokens behind 9 rows the
