@@ -45,9 +45,11 @@ constexpr int tk_slots(int T) { return T <= 2 ? 2 : (T <= 4 ? 4 : (T <= 8 ? 8 : 
 // ---- activations -> operands ----------------------------------------------------------------------------------------
 // Sixteen lanes hold one token's super-block, lane i columns 16 i .. 16 i + 15 in v (RMSNorm gain applied); into the record.  ORD: the order of
 // a slice's 8 columns in the operand: 0: 0 4 1 5 2 6 3 7 (Q4_K's nibbles), 1: 0 2 1 3 4 6 5 7 (bytes).
+// INF: for formats whose products are not corrected afterwards (Q8_0, FP16), infinities pass as such; Q5_K and Q6_K give NaN for them,
+// as their one-token mat-vec does.
 // A 16-byte piece (8 columns of one row) c = 4 S + j, S the sub-block, j the slice, lies at a[c][row ^ f(c)], f(c) = (c >> 1) & 15:
 // the sixteen lanes write pieces whose rows would otherwise share their banks.
-template <int NT, int ORD>
+template <int NT, int ORD, bool INF>
 __device__ __forceinline__ void tk_split(const float (&v)[16], int i, int t, uint8_t *rec)
 {
     uint8_t *const a = rec, *const sums = rec + tk_sums_at(NT);
@@ -59,7 +61,10 @@ __device__ __forceinline__ void tk_split(const float (&v)[16], int i, int t, uin
     int ex = 0;
     if (amax > 0.f) frexpf(amax, &ex); // amax < 2^ex
     int p = 10 - ex;
-    p = p > 120 ? 120 : (p < -120 ? -120 : p);
+    p = p > 126 ? 126 : (p < -120 ? -120 : p); // (2^p and 2^-p are normal numbers)
+    // INF, an infinite activation: its hi part is infinite and its lo part finite (below), so that a product with a weight that is not zero
+    // stays infinite; the others, which no longer matter, must not become infinite beside it.
+    if constexpr (INF) p = amax > 3.40282347e38f ? -113 : p;
     const float S = ldexpf(1.0f, p);
     _Float16 hh[16], ll[16];
     // The sum of what the products will see: hi parts (whose sum is exact or nearly so) and lo parts on their own
@@ -69,7 +74,9 @@ __device__ __forceinline__ void tk_split(const float (&v)[16], int i, int t, uin
         float sv = v[k] * S;
         asm volatile("" : "+v"(sv)); // one rounded number for hi and lo (see gemm_split_kernel)
         hh[k] = static_cast<_Float16>(sv);
-        ll[k] = static_cast<_Float16>(sv - static_cast<float>(hh[k]));
+        float r = sv - static_cast<float>(hh[k]);
+        if constexpr (INF) r = fmaxf(r, -1024.f); // (in a NaN's place: inf - inf; any other is smaller)
+        ll[k] = static_cast<_Float16>(r);
         sum += static_cast<float>(hh[k]);
         suml += static_cast<float>(ll[k]);
     }

@@ -338,3 +338,32 @@ def test_scratch_of_a_wide_model_serves_every_token_count(gpu_lib):
         finally:
             gpu_lib.set_prefill_small_tokens(gpu_lib.PREFILL_SMALL_TOKENS)
         check_hidden(f"wide, {n_past} cached rows, prompt", rel_err(y, ref), d, [host], x.astype(np.float64), n_past, formats=fm, eps=EPS_FP32)
+
+
+@pytest.mark.parametrize("fmt", ["q5_k", "q6_k", "q8_0", "f16"])
+@pytest.mark.parametrize("T", [8, 16])
+def test_activations_that_are_not_finite_and_tiny_ones(gpu_lib, fmt, T):
+    """Infinities and NaN in some tokens of a several-token mat-vec: Q8_0 and FP16 (a weight times an activation, nothing taken
+    off again) give what one token at a time gives, infinity for infinity and NaN for NaN; no other token notices.  Activations
+    of 1e-35 keep their precision."""
+    rng = np.random.default_rng(23)
+    rows, cols = 300, 1024
+    W = _dev(_centred(rng, fmt, rows, cols))
+    x = _dev(rng.standard_normal((T, cols)).astype(np.float32))
+    x[1] *= 1e-35
+    clean = gpu_lib.fmt_gemv(fmt, W, rows, cols, x)
+    w = gpu_lib.fmt_dequant(fmt, W, rows, cols).double()
+    ref = x.double() @ w.T
+    err = (clean.double() - ref).norm(dim=1) / ref.norm(dim=1)
+    assert float(err.max()) < 1e-6, err
+    bad = x.clone()
+    bad[2, 5], bad[3, 700], bad[4, 3], bad[4, 900], bad[5, 17] = float("inf"), float("-inf"), float("inf"), float("-inf"), float("nan")
+    bad[3, 10:40] = 3e4                     # beside an infinity of the same super-block and of another
+    bad[3, 690:699] = -3e4
+    got = gpu_lib.fmt_gemv(fmt, W, rows, cols, bad)
+    others = [t for t in range(T) if t not in (2, 3, 4, 5)]
+    assert torch.equal(got[others], clean[others])
+    assert not torch.isfinite(got[2:6]).any()
+    if fmt in ("q8_0", "f16"):
+        apart = torch.cat([gpu_lib.fmt_gemv(fmt, W, rows, cols, bad[t:t + 1].contiguous()) for t in range(2, 6)])
+        assert torch.equal(torch.nan_to_num(got[2:6], 7.0, 8.0, -8.0), torch.nan_to_num(apart, 7.0, 8.0, -8.0))
