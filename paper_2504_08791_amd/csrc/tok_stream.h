@@ -40,10 +40,10 @@ struct TokSum {
     const float *resid; // [T][rows[0]], with n == 1 (null: none)
 };
 
-int tok_max_parts(int nb, int nt); // shares of K of any launch, at most
+int tok_max_parts(int nb, int nt, int64_t n_rows); // shares of K of a launch of n_rows rows in all, at most (fewer rows: not fewer)
 int tok_slots(int T);
 size_t tok_rec_bytes(int64_t n_cols, int T);
-size_t tok_part_floats(int64_t n_rows, int64_t n_cols, int T); // for matrices of n_rows rows in all, launched together or one by one
+size_t tok_part_floats(int64_t n_rows, int64_t n_cols, int T); // for one matrix; matrices launched together take no more than the sum of theirs
 size_t tok_ss_bytes(int64_t n_cols, int T);
 // sums of up to three matrices of one format (all but FP32) and equal columns with the activations rec; out[i]: where they lie
 prima_status launch_tok_stream(int fmt, const TokMat *mats, int n_mats, int64_t n_cols, const uint8_t *rec, int T, float *part, size_t part_floats,

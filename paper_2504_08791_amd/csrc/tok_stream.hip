@@ -327,7 +327,7 @@ StreamPlan plan_stream(int n_tiles, int nb, int nt)
 {
     constexpr int SBS = TkFmt<FMT>::SBS, WAVES = TkFmt<FMT>::WAVES;
     const int cap = static_cast<int>((TK_LDS - stage_lds<FMT>()) / tk_rec(nt)) / SBS * SBS;
-    const int min_slabs = (nb + cap - 1) / cap, max_parts = tok_max_parts(nb, nt);
+    const int min_slabs = (nb + cap - 1) / cap, max_parts = tok_max_parts(nb, nt, static_cast<int64_t>(n_tiles) * 16);
     StreamPlan best{};
     double best_t = 0.;
     for (int ns = min_slabs; ns <= std::min(max_parts, 2 * min_slabs + 6) && ns <= TK_CUS; ++ns) {
@@ -383,11 +383,16 @@ prima_status launch_fmt(StreamArgs &a, size_t part_floats, int &n_parts, hipStre
 
 } // namespace
 
-int tok_max_parts(int nb, int nt) { return std::max(16, 2 * most_slabs(nb, nt)); }
+// Tall launches fill the device without many shares (57344 x 8192 takes 8 at 16 tokens, 4 at 8), and theirs are the largest of the scratch.
+int tok_max_parts(int nb, int nt, int64_t n_rows)
+{
+    const int least = most_slabs(nb, nt);
+    return n_rows > 12288 ? std::max(8, least) : std::max(16, 2 * least);
+}
 size_t tok_rec_bytes(int64_t n_cols, int T) { return static_cast<size_t>(n_cols / QK) * tk_rec(tk_slots(T)); }
 size_t tok_part_floats(int64_t n_rows, int64_t n_cols, int T)
 {
-    return static_cast<size_t>(tok_max_parts(static_cast<int>(n_cols / QK), tk_slots(T))) * T * static_cast<size_t>(n_rows);
+    return static_cast<size_t>(tok_max_parts(static_cast<int>(n_cols / QK), tk_slots(T), n_rows)) * T * static_cast<size_t>(n_rows);
 }
 size_t tok_ss_bytes(int64_t n_cols, int T) { return static_cast<size_t>(n_cols / QK) * tk_slots(T) * sizeof(float); }
 int tok_slots(int T) { return tk_slots(T); }

@@ -14,7 +14,7 @@ namespace {
 
 struct WindowWs {
     size_t q, k, v, o, h, a, u, xb0, xb1, rope, attn, gemv, gemv_bytes, arrivals_bytes, sync, total;
-    // 9 and more tokens: activations laid out for Q4_K and for the other formats, their sums of squares, the shares of K
+    // 4 and more tokens: activations laid out for Q4_K and for the other formats, their sums of squares, the shares of K
     size_t tok_rec[2], tok_ss, tok_part, tok_part_floats;
 };
 
@@ -47,7 +47,7 @@ bool tok_context(int n_past, const AttnSeqs *seq) { return seq || n_past >= TOK_
 bool tok_dims(const prima_dims &d)
 {
     const int64_t qd = static_cast<int64_t>(d.n_q_heads) * d.head_dim, widest = std::max<int64_t>({d.e, qd, d.ffn});
-    return widest / QK <= 1024 && tok_max_parts(static_cast<int>(widest / QK), tok_slots(PRIMA_MAX_TOK)) <= 256 &&
+    return widest / QK <= 1024 && tok_max_parts(static_cast<int>(widest / QK), tok_slots(PRIMA_MAX_TOK), 1) <= 256 &&
            (2 * static_cast<int64_t>(d.ffn) + qd + 2 * static_cast<int64_t>(d.n_kv_heads) * d.head_dim) < (int64_t{1} << 30);
 }
 // ... and whether a step of T tokens on this scratch uses it
@@ -81,15 +81,22 @@ WindowWs carve(const prima_dims &d, int kv_cap, int T)
     w.arrivals_bytes = gemv_arrivals_bytes(rows_max);
     for (const auto &sh : shapes) w.gemv_bytes = std::max(w.gemv_bytes, gemv_ws_bytes(sh[0], sh[1], T)); // counters + partial sums
     w.gemv_bytes += w.arrivals_bytes; // the counter region is sized for the tallest matrix
-    w.gemv = take(w.gemv_bytes);
+    // The shares of the streams lie where the mat-vec keeps its partial sums, behind its counters (which a step needs cleared): a launch of
+    // one kind has used up its own before one of the other kind starts.
+    size_t region = w.gemv_bytes;
+    const bool tok = T >= TOK_OTHERS && tok_dims(d);
+    if (tok) {
+        auto floats = [&](size_t rows, int64_t cols) { return tok_part_floats(static_cast<int64_t>(rows), cols, T); };
+        w.tok_part_floats = std::max({floats(qd, d.e) + 2 * floats(kvd, d.e), floats(d.e, static_cast<int64_t>(qd)), 2 * floats(d.ffn, d.e), floats(d.e, d.ffn)});
+        region = std::max(region, round_up(w.arrivals_bytes, 256) + w.tok_part_floats * sizeof(float));
+    }
+    w.gemv = take(region);
+    w.tok_part = w.gemv + round_up(w.arrivals_bytes, 256);
     w.sync = take(WAIT_FLAG_BYTES);
-    if (T >= TOK_OTHERS && tok_dims(d)) {
+    if (tok) {
         const int64_t widest = std::max<int64_t>({d.e, static_cast<int64_t>(qd), d.ffn});
         for (size_t &r : w.tok_rec) r = take(tok_rec_bytes(widest, T));
         w.tok_ss = take(tok_ss_bytes(d.e, T));
-        w.tok_part_floats = std::max({tok_part_floats(static_cast<int64_t>(qd + 2 * kvd), d.e, T), tok_part_floats(d.e, static_cast<int64_t>(qd), T),
-                                      tok_part_floats(2 * static_cast<int64_t>(d.ffn), d.e, T), tok_part_floats(d.e, d.ffn, T)});
-        w.tok_part = take(w.tok_part_floats * sizeof(float));
     }
     w.total = off;
     return w;
