@@ -88,6 +88,7 @@ prima_status launch_fmt_gemv(int fmt, const uint8_t *W, int64_t n_rows, int64_t 
 // 2 to 16 tokens in the formats whose weights are exact in binary16 operands (tok_gemv.hip); launch_fmt_gemv goes there
 bool tok_gemv_takes(int fmt, int64_t n_rows, int64_t n_cols, int T);
 int tok_gemv_first(int fmt, int64_t n_rows, int64_t n_cols, int T);
+prima_status tok_gemv_plan_status(int fmt, int64_t n_rows, int64_t n_cols, int T); // host only: whether launch_tok_gemv() finds a plan
 prima_status launch_tok_gemv(int fmt, const uint8_t *W, int64_t n_rows, int64_t n_cols, const float *x, int64_t ldx, int T,
                              const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy, hipStream_t st);
 

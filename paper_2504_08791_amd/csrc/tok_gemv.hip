@@ -239,19 +239,15 @@ __global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64) __attribute__((amdgpu_
     }
 }
 
+int grid_of(const TokArgs &a) { return std::min(a.n_tiles, TK_CUS); }
+
+// chunks of K, parts of a unit and rounds (into a); the LDS they take
 template <int FMT, int NT>
-prima_status launch_nt(TokArgs a, hipStream_t st)
+prima_status plan_nt(TokArgs &a, size_t &lds)
 {
-    static std::atomic<bool> attr_set{false}; // set twice by two threads at worst: the attribute call is idempotent
-    if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(tok_gemv_kernel<FMT, NT>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                static_cast<int>(TK_LDS)) != hipSuccess)
-            return PRIMA_E_DEVICE;
-        attr_set = true;
-    }
     constexpr int SBS = TkFmt<FMT>::SBS, WAVES = TkFmt<FMT>::WAVES;
     constexpr size_t per_sb = tk_rec(NT) + 4 * NT, fixed = WAVES * tk_stage_bytes<FMT> + NT * 4;
-    const int grid = std::min(a.n_tiles, TK_CUS);
+    const int grid = grid_of(a);
     // Parts of a unit: with few tiles the waves share them (what the longest wave has to do counts); the sums of a workgroup's
     // units take at most 32 KiB, more rounds than that are worked off in blocks, each with a walk over K of its own.
     constexpr int ROUND_BYTES = WAVES * NT * 64, MAX_BLK = 32 * 1024 / ROUND_BYTES;
@@ -280,19 +276,47 @@ prima_status launch_nt(TokArgs a, hipStream_t st)
             a.chunk = chunk;
         }
     }
-    const size_t lds = fixed + static_cast<size_t>(a.chunk) * per_sb + static_cast<size_t>(a.blk_rounds) * ROUND_BYTES;
-    if (lds > TK_LDS || a.chunk < SBS) return PRIMA_E_SHAPE; // (does not happen: the smallest chunk fits beside the largest sums)
-    hipLaunchKernelGGL((tok_gemv_kernel<FMT, NT>), dim3(grid), dim3(WAVES * 64), lds, st, a);
+    lds = fixed + static_cast<size_t>(a.chunk) * per_sb + static_cast<size_t>(a.blk_rounds) * ROUND_BYTES;
+    return lds > TK_LDS || a.chunk < SBS ? PRIMA_E_SHAPE : PRIMA_OK; // (the smallest chunk fits beside the largest sums)
+}
+
+// launches, or plans only
+template <int FMT, int NT>
+prima_status launch_nt(TokArgs a, bool plan_only, hipStream_t st)
+{
+    size_t lds = 0;
+    const prima_status s = plan_nt<FMT, NT>(a, lds);
+    if (s != PRIMA_OK || plan_only) return s;
+    static std::atomic<bool> attr_set{false}; // set twice by two threads at worst: the attribute call is idempotent
+    if (!attr_set) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(tok_gemv_kernel<FMT, NT>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                static_cast<int>(TK_LDS)) != hipSuccess)
+            return PRIMA_E_DEVICE;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL((tok_gemv_kernel<FMT, NT>), dim3(grid_of(a)), dim3(TkFmt<FMT>::WAVES * 64), lds, st, a);
     return last_launch_status();
 }
 
 template <int FMT>
-prima_status launch_fmt(const TokArgs &a, hipStream_t st)
+prima_status launch_fmt(const TokArgs &a, bool plan_only, hipStream_t st)
 {
-    if (a.T <= 2) return launch_nt<FMT, 2>(a, st);
-    if (a.T <= 4) return launch_nt<FMT, 4>(a, st);
-    if (a.T <= 8) return launch_nt<FMT, 8>(a, st);
-    return launch_nt<FMT, 16>(a, st);
+    if (a.T <= 2) return launch_nt<FMT, 2>(a, plan_only, st);
+    if (a.T <= 4) return launch_nt<FMT, 4>(a, plan_only, st);
+    if (a.T <= 8) return launch_nt<FMT, 8>(a, plan_only, st);
+    return launch_nt<FMT, 16>(a, plan_only, st);
+}
+
+prima_status launch_any(int fmt, const TokArgs &a, bool plan_only, hipStream_t st)
+{
+    switch (fmt) {
+    case PRIMA_FMT_Q4_K: return a.T > 8 ? launch_nt<PRIMA_FMT_Q4_K, 16>(a, plan_only, st) : PRIMA_E_SHAPE;
+    case PRIMA_FMT_Q5_K: return launch_fmt<PRIMA_FMT_Q5_K>(a, plan_only, st);
+    case PRIMA_FMT_Q6_K: return launch_fmt<PRIMA_FMT_Q6_K>(a, plan_only, st);
+    case PRIMA_FMT_Q8_0: return launch_fmt<PRIMA_FMT_Q8_0>(a, plan_only, st);
+    case PRIMA_FMT_F16: return launch_fmt<PRIMA_FMT_F16>(a, plan_only, st);
+    default: return PRIMA_E_SHAPE;
+    }
 }
 
 } // namespace
@@ -344,14 +368,14 @@ prima_status launch_tok_gemv(int fmt, const uint8_t *W, int64_t n_rows, int64_t 
     TokArgs a{};
     a.W = W; a.n_rows = n_rows; a.nb = static_cast<int>(n_cols / QK); a.x = x; a.ldx = ldx; a.gain = gain; a.eps = eps;
     a.resid = resid; a.ldr = ldr; a.y = y; a.ldy = ldy; a.T = T; a.n_tiles = static_cast<int>((n_rows + 15) / 16);
-    switch (fmt) {
-    case PRIMA_FMT_Q4_K: return T > 8 ? launch_nt<PRIMA_FMT_Q4_K, 16>(a, st) : PRIMA_E_SHAPE;
-    case PRIMA_FMT_Q5_K: return launch_fmt<PRIMA_FMT_Q5_K>(a, st);
-    case PRIMA_FMT_Q6_K: return launch_fmt<PRIMA_FMT_Q6_K>(a, st);
-    case PRIMA_FMT_Q8_0: return launch_fmt<PRIMA_FMT_Q8_0>(a, st);
-    case PRIMA_FMT_F16: return launch_fmt<PRIMA_FMT_F16>(a, st);
-    default: return PRIMA_E_SHAPE;
-    }
+    return launch_any(fmt, a, false, st);
+}
+
+prima_status tok_gemv_plan_status(int fmt, int64_t n_rows, int64_t n_cols, int T)
+{
+    TokArgs a{};
+    a.nb = static_cast<int>(n_cols / QK); a.T = T; a.n_tiles = static_cast<int>((n_rows + 15) / 16);
+    return launch_any(fmt, a, true, nullptr);
 }
 
 } // namespace prima

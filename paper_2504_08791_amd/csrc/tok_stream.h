@@ -48,6 +48,8 @@ size_t tok_ss_bytes(int64_t n_cols, int T);
 // sums of up to three matrices of one format (all but FP32) and equal columns with the activations rec; out[i]: where they lie
 prima_status launch_tok_stream(int fmt, const TokMat *mats, int n_mats, int64_t n_cols, const uint8_t *rec, int T, float *part, size_t part_floats,
                                TokPart *out, hipStream_t st);
+// host only: whether matrices of n_rows rows in all find a plan whose shares fit
+prima_status tok_stream_plan_status(int fmt, int64_t n_rows, int64_t n_cols, int T, size_t part_floats);
 prima_status launch_tok_prepare(const TokPrepare &a, hipStream_t st);
 prima_status launch_tok_sum(const TokSum &a, hipStream_t st);
 

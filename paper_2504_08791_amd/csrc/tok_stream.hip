@@ -364,21 +364,35 @@ prima_status launch_nt(StreamArgs &a, const StreamPlan &p, hipStream_t st)
     return last_launch_status();
 }
 
+// launches, or plans only
 template <int FMT>
-prima_status launch_fmt(StreamArgs &a, size_t part_floats, int &n_parts, hipStream_t st)
+prima_status launch_fmt(StreamArgs &a, size_t part_floats, int &n_parts, bool plan_only, hipStream_t st)
 {
     const int nt = tk_slots(a.T);
     const StreamPlan p = plan_stream<FMT>(a.n_tiles, a.nb, nt);
-    if (p.n_slabs == 0) return PRIMA_E_SHAPE;
+    if (p.n_slabs == 0 || nt < (FMT == PRIMA_FMT_Q4_K ? 16 : 4)) return PRIMA_E_SHAPE;
     a.n_slabs = p.n_slabs; a.slab = p.slab; a.ks_shift = p.ks_shift; a.rounds = p.rounds;
     n_parts = p.n_slabs << p.ks_shift;
     if (static_cast<size_t>(n_parts) * a.T * a.n_tiles * 16 > part_floats) return PRIMA_E_WORKSPACE;
+    if (plan_only) return p.lds > TK_LDS ? PRIMA_E_SHAPE : PRIMA_OK;
     if (nt == 16) return launch_nt<FMT, 16>(a, p, st);
     if constexpr (FMT != PRIMA_FMT_Q4_K) { // (Q4_K: windows of 9 to 16 tokens only, see window.hip)
         if (nt == 4) return launch_nt<FMT, 4>(a, p, st);
         if (nt == 8) return launch_nt<FMT, 8>(a, p, st);
     }
     return PRIMA_E_SHAPE;
+}
+
+prima_status launch_any(int fmt, StreamArgs &a, size_t part_floats, int &n_parts, bool plan_only, hipStream_t st)
+{
+    switch (fmt) {
+    case PRIMA_FMT_Q4_K: return launch_fmt<PRIMA_FMT_Q4_K>(a, part_floats, n_parts, plan_only, st);
+    case PRIMA_FMT_Q5_K: return launch_fmt<PRIMA_FMT_Q5_K>(a, part_floats, n_parts, plan_only, st);
+    case PRIMA_FMT_Q6_K: return launch_fmt<PRIMA_FMT_Q6_K>(a, part_floats, n_parts, plan_only, st);
+    case PRIMA_FMT_Q8_0: return launch_fmt<PRIMA_FMT_Q8_0>(a, part_floats, n_parts, plan_only, st);
+    case PRIMA_FMT_F16: return launch_fmt<PRIMA_FMT_F16>(a, part_floats, n_parts, plan_only, st);
+    default: return PRIMA_E_SHAPE;
+    }
 }
 
 } // namespace
@@ -397,6 +411,14 @@ size_t tok_part_floats(int64_t n_rows, int64_t n_cols, int T)
 size_t tok_ss_bytes(int64_t n_cols, int T) { return static_cast<size_t>(n_cols / QK) * tk_slots(T) * sizeof(float); }
 int tok_slots(int T) { return tk_slots(T); }
 
+prima_status tok_stream_plan_status(int fmt, int64_t n_rows, int64_t n_cols, int T, size_t part_floats)
+{
+    StreamArgs a{};
+    a.nb = static_cast<int>(n_cols / QK); a.T = T; a.n_tiles = static_cast<int>(n_rows / 16);
+    int n_parts = 0;
+    return launch_any(fmt, a, part_floats, n_parts, true, nullptr);
+}
+
 prima_status launch_tok_stream(int fmt, const TokMat *mats, int n_mats, int64_t n_cols, const uint8_t *rec, int T, float *part, size_t part_floats,
                                TokPart *out, hipStream_t st)
 {
@@ -411,15 +433,7 @@ prima_status launch_tok_stream(int fmt, const TokMat *mats, int n_mats, int64_t 
     if (tiles >= (int64_t{1} << 27) || n_cols / QK >= (1 << 18)) return PRIMA_E_SHAPE;
     a.rec = rec; a.part = part; a.nb = static_cast<int>(n_cols / QK); a.T = T; a.n_tiles = static_cast<int>(tiles);
     int n_parts = 0;
-    prima_status s;
-    switch (fmt) {
-    case PRIMA_FMT_Q4_K: s = launch_fmt<PRIMA_FMT_Q4_K>(a, part_floats, n_parts, st); break;
-    case PRIMA_FMT_Q5_K: s = launch_fmt<PRIMA_FMT_Q5_K>(a, part_floats, n_parts, st); break;
-    case PRIMA_FMT_Q6_K: s = launch_fmt<PRIMA_FMT_Q6_K>(a, part_floats, n_parts, st); break;
-    case PRIMA_FMT_Q8_0: s = launch_fmt<PRIMA_FMT_Q8_0>(a, part_floats, n_parts, st); break;
-    case PRIMA_FMT_F16: s = launch_fmt<PRIMA_FMT_F16>(a, part_floats, n_parts, st); break;
-    default: return PRIMA_E_SHAPE;
-    }
+    const prima_status s = launch_any(fmt, a, part_floats, n_parts, false, st);
     for (int i = 0; i < n_mats; ++i) out[i] = TokPart{part, n_parts, tiles * 16, static_cast<int64_t>(a.seg[i].tile0) * 16};
     return s;
 }

@@ -798,6 +798,7 @@ prima_status prima_gemv_plan_status(int64_t n_rows, int64_t n_cols, int32_t T)
     if (n_rows < 0 || n_cols <= 0 || n_cols % QK) return PRIMA_E_SHAPE;
     if (T < 1 || T > PRIMA_MAX_TOK) return PRIMA_E_RANGE;
     if (n_rows == 0) return PRIMA_OK;
+    if (tok_gemv_takes(PRIMA_FMT_Q4_K, n_rows, n_cols, T)) return tok_gemv_plan_status(PRIMA_FMT_Q4_K, n_rows, n_cols, T);
     static float dummy[4]; // addresses only: nothing is read or written
     GemvArgs ga = gemv_args(1, n_cols, dummy, n_cols, T);
     ga.seg[0] = seg(dummy, dummy, n_rows, n_rows);
@@ -825,6 +826,22 @@ prima_status prima_window_plan_status(const prima_dims *d, int32_t kv_cap, int32
         for (int i = 0; i < l.nseg; ++i) ga.seg[i] = seg(ws, dummy, l.rows[i], l.rows[i]);
         const prima_status s = gemv_plan_status(ga, ws, w.gemv_bytes, w.arrivals_bytes);
         if (s != PRIMA_OK) return s;
+    }
+    // the same groups, and their matrices alone, in every format through the weight streams and the format mat-vec
+    for (const Launch &l : launches) {
+        int64_t rows = 0;
+        size_t floats = 0;
+        for (int i = 0; i < l.nseg; ++i) {
+            rows += l.rows[i];
+            if (w.tok_part_floats != 0) floats += tok_part_floats(l.rows[i], l.cols, T);
+        }
+        for (int fmt = PRIMA_FMT_Q4_K; fmt <= PRIMA_FMT_F16; ++fmt) {
+            prima_status s = PRIMA_OK;
+            if (tok_takes(w, T, fmt == PRIMA_FMT_Q4_K ? TOK_WINDOW : TOK_OTHERS)) s = tok_stream_plan_status(fmt, rows, l.cols, T, std::min(floats, w.tok_part_floats));
+            const int first = tok_gemv_first(fmt, rows, l.cols, T);
+            if (s == PRIMA_OK && l.nseg == 1 && fmt != PRIMA_FMT_Q4_K && tok_gemv_takes(fmt, rows, l.cols, T)) s = tok_gemv_plan_status(fmt, rows, l.cols, first);
+            if (s != PRIMA_OK) return s;
+        }
     }
     return PRIMA_OK;
 }

@@ -261,6 +261,18 @@ def test_format_calls_argument_errors():
     assert w(formats=bad) == 2
 
 
+def test_every_stream_shape_can_be_planned():
+    """Weight streams of 4 to 16 tokens: every number of super-blocks per row up to 160 and some beyond, as columns of the down
+    projection and of the others, few and many rows: slabs, parts and shares fit the scratch, in every format."""
+    L = _ffi.lib()
+    for nb in list(range(1, 161)) + [200, 255, 256]:      # (longer rows in Q4_K take four tokens at most)
+        for T in (4, 5, 8, 9, 16):
+            for d in (_ffi.Dims(256, 2, 1, 128, 256 * nb, 1e4, 1e-5, 0), _ffi.Dims(256 * nb, 2, 1, 128, 512, 1e4, 1e-5, 0),
+                      _ffi.Dims(2048, 64, 8, 128, 256 * nb, 1e4, 1e-5, 0)):
+                assert L.prima_window_plan_status(C.byref(d), 1100, T) == 0, (nb, T, d.e, d.ffn)
+    assert L.prima_gemv_plan_status(128256, 8192, 16) == 0 and L.prima_gemv_plan_status(65536, 256, 9) == 0
+
+
 def test_scratch_for_more_tokens_holds_what_fewer_need():
     """prima_workspace_bytes promises scratch for up to T tokens, so it must not fall with T; widths on both sides of 131072
     columns among them (the region of the weight streams once ended at 8 tokens there: a window made for 16 tokens refused 5)."""
