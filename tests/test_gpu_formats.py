@@ -213,14 +213,15 @@ def test_mixed_window_full_shape(gpu_lib):
                  formats=formats, eps=EPS_FP32)
 
 
-@pytest.mark.parametrize("name", ["t0", "t1", "t2"])
-def test_batch_of_sequences_with_mixed_formats(gpu_lib, name):
+@pytest.mark.parametrize("name,more,mix", [("t0", 0, "all_kinds"), ("t1", 0, "all_kinds"), ("t2", 0, "all_kinds"), ("t1", 4, "all_kinds"),
+                                           ("t0", 6, "q4_k_m"), ("t2", 11, "q4_k_m")])
+def test_batch_of_sequences_with_mixed_formats(gpu_lib, name, more, mix):
     """One token for each of several sequences of different lengths (one empty, one full) through two layers whose
     matrices are in several formats: hidden states against the oracle (each sequence alone), appended rows."""
-    formats = MIXES["all_kinds"][:2]
+    formats = MIXES[mix][:2]
     cfg = TINY[name].with_(n_layers=2)
     d = cfg.dims
-    lens = [0, 5, cfg.n_past, 17, 5]
+    lens = [0, 5, cfg.n_past, 17, 5] + [3 * i + 1 for i in range(more)]
     B = len(lens)
     cap = cfg.n_past + 1
     host = [synth.layer_tensors(cfg.with_(n_past=0), l, kv_cap=1, formats=formats[l]) for l in range(2)]
@@ -245,9 +246,10 @@ def test_batch_of_sequences_with_mixed_formats(gpu_lib, name):
 
 
 @pytest.mark.parametrize("fmt", ["q5_k", "q6_k", "q8_0", "f16"])
-@pytest.mark.parametrize("rows,cols,tokens", [(65551, 256, (2, 3)),   # a tile of 15 rows at the end, rows of one super-block
-                                              (8199, 1280, (4,)),     # an odd number of super-blocks, 7 rows over
-                                              (17, 9 * 256, (5, 8)),  # two tiles: parts of a unit
+@pytest.mark.parametrize("rows,cols,tokens", [(98289, 256, (2, 3)),   # a tile of one row at the end, rows of one super-block (2 tokens: not Q8_0)
+                                              (32775, 1280, (4, 6)),  # an odd number of super-blocks, 7 rows over
+                                              (17, 9 * 256, (7, 8)),  # two tiles: parts of a unit
+                                              (1001, 4352, (9, 10)),  # 8 tokens there and the others through the fp32 mat-vec
                                               (131105, 256, (9, 16))])  # more rounds than sums fit LDS
 def test_matrix_core_matvec_edges(gpu_lib, fmt, rows, cols, tokens):
     """The several-token kernel at the edges of its tiles, parts, chunks and rounds, rows sampled from both ends and between."""
@@ -261,6 +263,8 @@ def test_matrix_core_matvec_edges(gpu_lib, fmt, rows, cols, tokens):
         got = gpu_lib.fmt_gemv(fmt, Wd, rows, cols, _dev(x)).cpu().numpy()
         again = gpu_lib.fmt_gemv(fmt, Wd, rows, cols, _dev(x)).cpu().numpy()
         assert np.array_equal(got, again)
+        one = gpu_lib.fmt_gemv(fmt, Wd, rows, cols, _dev(x[:1])).cpu().numpy()
+        assert (fmt == "q8_0" and T == 2) or not np.array_equal(got[:1], one)      # (the fp32 mat-vec's sums: not the same bits)
         ref = x.astype(np.float64) @ w.T
         assert rel_err(got[:, pick], ref) <= GEMV_TOL, (fmt, rows, T)
 

@@ -23,10 +23,10 @@ def _windows(gpu_lib, cfg, cap, n):
     return [gpu_lib.Window(cfg.dims, [{k: _dev(v) for k, v in t.items()} for t in copy.deepcopy(host)], cap, T_max=16) for _ in range(n)]
 
 
-@pytest.mark.parametrize("T", [1, 4, 16])
-def test_decode_step_replayed_from_a_graph(gpu_lib, T):
-    cfg = TINY["t1"].with_(T=T, n_past=37)
-    cap = 80
+@pytest.mark.parametrize("T,n_past", [(1, 37), (4, 37), (16, 37), (16, 70)])     # (the last: through the weight streams)
+def test_decode_step_replayed_from_a_graph(gpu_lib, T, n_past):
+    cfg = TINY["t1"].with_(T=T, n_past=n_past)
+    cap = 90
     eager, captured, other = _windows(gpu_lib, cfg, cap, 3)
     x = _dev(synth.window_input(cfg))
     want = eager.decode(x, cfg.n_past).clone()

@@ -206,9 +206,12 @@ def _window(gpu_lib, cfg, cap, layers_host):
     return win, dev_layers
 
 
-@pytest.mark.parametrize("name", ["t0", "t1", "t2"])
-def test_layer_taps_vs_oracle(gpu_lib, name):
-    cfg = TINY[name]
+MANY = dict(T=11, n_past=70)      # a step that goes through the weight streams
+
+
+@pytest.mark.parametrize("name,other", [("t0", {}), ("t1", {}), ("t2", {}), ("t0", MANY), ("t1", MANY), ("t2", MANY)])
+def test_layer_taps_vs_oracle(gpu_lib, name, other):
+    cfg = TINY[name].with_(**other)
     cap = cfg.n_past + cfg.T
     host = [synth.layer_tensors(cfg, 0, kv_cap=cap)]
     win, dev_layers = _window(gpu_lib, cfg, cap, host)
@@ -246,14 +249,14 @@ def test_window_vs_oracle(gpu_lib, name):
     assert torch.equal(y2, y)
 
 
-@pytest.mark.parametrize("name", ["t0", "t1", "t2"])
-def test_batch_of_sequences_vs_oracle(gpu_lib, name):
+@pytest.mark.parametrize("name,more", [("t0", 0), ("t1", 0), ("t2", 0), ("t0", 2), ("t1", 9), ("t2", 5)])
+def test_batch_of_sequences_vs_oracle(gpu_lib, name, more):
     """One token for each of B sequences with their own caches and lengths (an empty one, a full one, equal
-    ones): hidden states against the oracle's independent one-token steps, the appended rows, nothing else
+    ones; up to 8 through the mat-vecs, from 9 on through the weight streams): hidden states against the oracle's independent one-token steps, the appended rows, nothing else
     written, and the same bits on a second run."""
     cfg = TINY[name]
     cap = cfg.n_past + 6
-    n_past = [0, cfg.n_past, cap - 1, 17, 17, 1, cfg.n_past + 3]
+    n_past = [0, cfg.n_past, cap - 1, 17, 17, 1, cfg.n_past + 3] + [5 + 3 * i for i in range(more)]
     B = len(n_past)
     host = [synth.layer_tensors(cfg, l, kv_cap=cap) for l in range(cfg.n_layers)]
     win, _ = _window(gpu_lib, cfg, cap, host)
@@ -365,12 +368,12 @@ def test_rerun_is_bit_identical(gpu_lib):
     assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("name", ["t0", "t1", "t2"])
-def test_profiled_step_leaves_what_a_plain_step_leaves(gpu_lib, name):
+@pytest.mark.parametrize("name,other", [("t0", {}), ("t1", {}), ("t2", {}), ("t1", MANY), ("t2", MANY)])
+def test_profiled_step_leaves_what_a_plain_step_leaves(gpu_lib, name, other):
     """The measurement hook replays each kind of launch on its own; afterwards x_out and every layer's caches
     (the step's new rows included) must be bit-equal to those after prima_layer_window_decode, so that a caller
     who advances n_past after it attends over the right rows."""
-    cfg = TINY[name]
+    cfg = TINY[name].with_(**other)
     cap = cfg.n_past + cfg.T + 2
     host = [synth.layer_tensors(cfg, l, kv_cap=cap) for l in range(cfg.n_layers)]
     wa, la = _window(gpu_lib, cfg, cap, host)

@@ -151,31 +151,65 @@ def _centred(rng, fmt, rows, cols):
     return W
 
 
+def _layer64(gpu_lib, d, fmt, t, x, n_past):
+    """A layer in 64 bits from dequantised weights, with the cache rows as the library left them (their rounding to binary16,
+    which no product is to blame for, is then the same on both sides)."""
+    w = {k: gpu_lib.fmt_dequant(fmt, t[k], *s).double() for k, s in _shapes(d).items()}
+    norm = lambda v, g: v * g.double() / torch.sqrt((v * v).mean(1, keepdim=True) + float(np.float32(d.rms_eps)))
+    T, D, G = x.shape[0], d.head_dim, d.n_q_heads // d.n_kv_heads
+    x = x.double()
+    q = (norm(x, t["g_attn"]) @ w["wq"].T).view(T, d.n_q_heads, D)
+    ang = torch.arange(n_past, n_past + T, device="cuda").double()[:, None] * float(d.rope_theta) ** (-2.0 * torch.arange(D // 2, device="cuda").double() / D)
+    c, s, p, r = torch.cos(ang)[:, None], torch.sin(ang)[:, None], q[..., :D // 2], q[..., D // 2:]
+    q = torch.cat([p * c - r * s, p * s + r * c], 2)
+    n = n_past + T
+    seen = torch.arange(n, device="cuda")[None] <= torch.arange(n_past, n, device="cuda")[:, None]
+    o = torch.empty_like(q)
+    for h in range(d.n_q_heads):
+        k, v = (t[c][h // G, :n].double() for c in ("k_cache", "v_cache"))
+        o[:, h] = torch.softmax((q[:, h] @ k.T / D ** 0.5).masked_fill(~seen, -float("inf")), 1) @ v
+    h = x + o.view(T, -1) @ w["wo"].T
+    a = norm(h, t["g_ffn"])
+    g = a @ w["wgate"].T
+    return h + (g / (1 + torch.exp(-g)) * (a @ w["wup"].T)) @ w["wdown"].T
+
+
+def _shapes(d):
+    return {"wq": (d.qd, d.e), "wk": (d.kvd, d.e), "wv": (d.kvd, d.e), "wo": (d.e, d.qd), "wgate": (d.ffn, d.e), "wup": (d.ffn, d.e),
+            "wdown": (d.e, d.ffn)}
+
+
+@pytest.mark.parametrize("dist", ["normal", "spread"])
 @pytest.mark.parametrize("T", [17, 64, 65, 129, 490])
 @pytest.mark.parametrize("fmt", ["q5_k", "q6_k", "q8_0", "f16"])
-def test_products_of_the_other_formats_agree_with_the_mat_vec(gpu_lib, fmt, T):
+def test_products_of_the_other_formats_are_no_less_exact_than_the_mat_vec(gpu_lib, fmt, T, dist):
     """One layer with all seven matrices in one format, as one prompt call (matrix product: 64- and 128-token workgroups, ragged
-    last ones, rows ragged against 128, K divided and whole) and as decode calls of 16 tokens (fp32 mat-vec, which the oracle
-    tests cover).  The products are within 2.3e-7 of 64 bits either way; a token that appends a K / V value which rounds to the
-    other fp16 neighbour may move by up to the hidden-state bar, the others must not."""
+    last ones, rows ragged against 128, K divided and whole) and as decode calls of 3 tokens (the fp32 mat-vec), each against
+    64 bits: the prompt's error no larger, both below 1e-6 of what the layer adds.  spread: magnitudes over six decades within a
+    token, whose activations share one power of two; what is added is then small beside the token and its rounding
+    (2^-24 of the token's largest values) is most of the error."""
     from workloads.configs import ModelDims
     d = ModelDims(2560, 20, 5, 128, 8448, 1e5)
     rng = np.random.default_rng(T)
-    shapes = {"wq": (d.qd, d.e), "wk": (d.kvd, d.e), "wv": (d.kvd, d.e), "wo": (d.e, d.qd), "wgate": (d.ffn, d.e), "wup": (d.ffn, d.e),
-              "wdown": (d.e, d.ffn)}
-    t = {k: _dev(_centred(rng, fmt, *shapes[k])) for k in shapes}
+    t = {k: _dev(_centred(rng, fmt, *s)) for k, s in _shapes(d).items()}
     n_past, cap = 64, 64 + T
     t["g_attn"], t["g_ffn"] = (_dev((1 + 0.1 * rng.standard_normal(d.e)).astype(np.float32)) for _ in range(2))
     kv = [_dev(rng.standard_normal((d.n_kv_heads, cap, d.head_dim)).astype(np.float16)) for _ in range(2)]
-    x = _dev(rng.standard_normal((T, d.e)).astype(np.float32))
-    fm = [{k: fmt for k in shapes}]
-    wins = [gpu_lib.Window(d, [dict(t, k_cache=kv[0].clone(), v_cache=kv[1].clone())], cap, formats=fm) for _ in range(2)]
-    print("case", fmt, T, flush=True)
+    x = rng.standard_normal((T, d.e)) * (1 if dist == "normal" else 10 ** rng.uniform(-3, 3, (T, d.e)))
+    x = _dev(x.astype(np.float32))
+    fm = [{k: fmt for k in _shapes(d)}]
+    layers = [dict(t, k_cache=kv[0].clone(), v_cache=kv[1].clone()) for _ in range(2)]
+    wins = [gpu_lib.Window(d, [l], cap, formats=fm) for l in layers]
+    print("case", fmt, T, dist, flush=True)
     got = wins[0].prefill(x, n_past)
     assert torch.equal(got, wins[0].prefill(x, n_past))
-    ref = torch.cat([wins[1].decode(x[i:i + 16].contiguous(), n_past + i) for i in range(0, T, 16)]).cpu().numpy().astype(np.float64)
-    per_token = [rel_err(got[i].cpu().numpy(), ref[i]) for i in range(T)]
-    assert max(per_token) < HID_TOL and float(np.median(per_token)) < 2e-5, (max(per_token), float(np.median(per_token)))
+    apart = torch.cat([wins[1].decode(x[i:i + 3].contiguous(), n_past + i).clone() for i in range(0, T, 3)])
+    err = []
+    for y, l in ((got, layers[0]), (apart, layers[1])):
+        ref = _layer64(gpu_lib, d, fmt, l, x, n_past)
+        err.append(float((y.double() - ref).norm() / (ref - x.double()).norm()))
+    print(f"{err[0]:.3e} {err[1]:.3e}", flush=True)
+    assert err[0] <= 1.02 * err[1] and (dist == "spread" or err[1] < 1e-6), err
 
 
 def test_prefill_then_decode_continues(gpu_lib, route):
