@@ -81,6 +81,11 @@ typedef struct {
  *     y[t*ldy + r] = sum_c W[r][c] * x[t*ldx + c],  r < n_rows, t < T.
  * W: Q4_K, n_rows x n_cols, n_cols % 256 == 0.  x: fp32, ldx >= n_cols, ldx % 4 == 0.  y: fp32,
  * ldy >= n_rows; y must not overlap x.
+ * Activations enter as block fixed point of 31 bits and are summed exactly; in tall matrices at 9 to 16 tokens (as in
+ * windows and batches of 9 to 16, and in several tokens of the other formats) as the sum of two binary16 numbers (22 bits,
+ * under a power of two per token and 256 columns) with fp32 sums on the matrix cores.  The 2-norm error against 64 bits is
+ * 1.3 to 2.1e-7 of the result either way, the smaller with the latter (with weights far from mean zero 0.7 to 1.0e-7 and
+ * 1.0 to 1.2e-7).
  * workspace: scratch of at least prima_gemv_workspace_bytes(n_rows, n_cols, T) bytes, 256-byte aligned.
  */
 prima_status prima_q4k_gemv(const void *W, int64_t n_rows, int64_t n_cols,
@@ -152,6 +157,9 @@ size_t prima_attn_workspace_bytes(const prima_dims *d, int32_t kv_cap, int32_t T
  * layers: HOST array of L descriptors.  x_in, x_out: fp32 [T][e]; x_out may alias x_in.
  * The library keeps no position state: the caller advances n_past (by fewer than T after a
  * rejection; stale rows are overwritten by the next step, never read).
+ * From 9 tokens on the weights are streamed once for all tokens and the activations enter the projections as for the tall
+ * matrices of prima_q4k_gemv; behind fewer than 64 cached rows a step of 9 to 16 tokens streams them twice and keeps the
+ * arithmetic of fewer tokens (its results are those of earlier versions bit for bit).
  * workspace >= prima_workspace_bytes(d, kv_cap, T), 256-byte aligned.
  */
 prima_status prima_layer_window_decode(const prima_dims *d, const prima_layer *layers, int32_t L,
@@ -162,8 +170,9 @@ prima_status prima_layer_window_decode(const prima_dims *d, const prima_layer *l
 /*
  * One step of a batch of B independent sequences through the window: sequence b contributes one token
  * (x_in[b], fp32 [B][e]) that continues its own cached context of n_past[b] rows (continuous batching of
- * requests on a layer window, App. A.12).  The mat-vecs stream the weights once for all tokens (FP32 matrices and very
- * long rows: once for up to 8), as for T tokens of one sequence; attention, RoPE (position n_past[b]) and the KV append run per sequence.
+ * requests on a layer window, App. A.12).  The mat-vecs stream the weights once for all tokens (layers with an FP32 matrix
+ * and rows of more than 131072 columns: once for up to 8), as for T tokens of one sequence behind 64 cached rows or more; attention,
+ * RoPE (position n_past[b]) and the KV append run per sequence.
  *   n_past    HOST array of B lengths, 0 <= n_past[b] < kv_cap; they may differ.
  *   k_caches  HOST array of L*B DEVICE pointers: entry [l*B + b] is the fp16 K cache [n_kv_heads][kv_cap][head_dim]
  *   v_caches  of layer l for sequence b (same layout as prima_layer.k_cache / v_cache, which this call ignores;
@@ -195,7 +204,9 @@ prima_status prima_window_check(const prima_dims *d, int32_t kv_cap, int32_t T,
  * path.  The replayed launches overwrite the step's new cache rows with other values, so the call
  * ends with a second ordinary step: x_out and rows n_past .. n_past+T-1 of every cache are then
  * bit-equal to what prima_layer_window_decode leaves.  ms_by_kind and launches_by_kind are HOST
- * arrays of PRIMA_N_KINDS entries (milliseconds for all launches of the kind; number of launches).
+ * arrays of PRIMA_N_KINDS entries (milliseconds for the L replays of the kind; their number, L.  A replay is one launch, two
+ * where slabs of K are added by a second one, and two or three from 9 tokens on, where activations are laid out and shares added
+ * by launches of their own).
  */
 enum {
     PRIMA_K_QKV = 0,     /* Q/K/V projections with fused RMSNorm */
@@ -278,7 +289,10 @@ prima_status prima_fmt_dequant(int32_t fmt, const void *W, int64_t n_rows, int64
  *     y[t*ldy + r] = sum_c W[r][c] * x[t*ldx + c],  r < n_rows, t < T,  1 <= T <= PRIMA_MAX_TOK.
  * W: device, 16-byte aligned, prima_fmt_tensor_bytes(fmt, n_rows, n_cols) bytes.  x: fp32, 16-byte aligned,
  * ldx >= n_cols, ldx % 4 == 0.  y: fp32, ldy >= n_rows, must not overlap x.  No scratch.  Results do not
- * depend on the launch (fixed order of additions).
+ * depend on the launch (fixed order of additions).  One token, FP32, and several tokens of few rows: fp32 multiply-adds;
+ * else the activations enter the matrix cores as two binary16 numbers (see prima_q4k_gemv), with errors no larger for
+ * activations of one magnitude.  An infinite activation gives infinities and NaN as fp32 multiply-adds would (Q5_K, Q6_K: NaN);
+ * FP16 weights must be finite.
  */
 prima_status prima_fmt_gemv(int32_t fmt, const void *W, int64_t n_rows, int64_t n_cols,
                             const float *x, int64_t ldx, int32_t T, float *y, int64_t ldy, void *hip_stream);
@@ -313,8 +327,8 @@ prima_status prima_repack_gguf(int32_t fmt, const void *src, int64_t n_rows, int
  * naming the prima_format of each of layer i's seven matrices (the pointers of prima_layer then point at
  * tensors in those formats).  Same results as if every matrix were dequantised to fp32 and multiplied
  * (within the tolerance of prima_layer_window_decode).  Q4_K matrices run as in prima_layer_window_decode,
- * the others through the mat-vec of prima_fmt_gemv, or from 4 tokens on through weight streams of their own, with the
- * same RMSNorm and residual.
+ * the others through the mat-vec of prima_fmt_gemv, or from 4 tokens on, behind 64 cached rows or more, through weight streams
+ * of their own, with the same RMSNorm and residual.
  * Errors as prima_layer_window_decode; a format code outside prima_format: PRIMA_E_SHAPE.
  */
 typedef struct {
@@ -334,9 +348,9 @@ prima_status prima_layer_window_decode_batch_mixed(const prima_dims *d, const pr
                                                    void *workspace, size_t workspace_bytes, void *hip_stream);
 
 /*
- * Host-side check, no GPU work: PRIMA_OK if every mat-vec launch of a window step of T tokens with these
- * dimensions (including the launches used when some matrices are in other formats) finds a launch plan and
- * fits the scratch of prima_workspace_bytes(d, kv_cap, T); otherwise the status such a step would return.
+ * Host-side check, no GPU work: PRIMA_OK if every mat-vec and weight-stream launch of a window step of T tokens with these
+ * dimensions (including the launches used when some matrices are in other formats, and behind few cached rows) finds a launch
+ * plan and fits the scratch of prima_workspace_bytes(d, kv_cap, T); otherwise the status such a step would return.
  */
 prima_status prima_window_plan_status(const prima_dims *d, int32_t kv_cap, int32_t T);
 /*

@@ -26,7 +26,7 @@
 // A workgroup of 4 waves owns 128 rows x 32 WT tokens, a wave 64 rows x 16 WT tokens.  Per position (sub-block) a thread
 // decodes 16 weights of one row for the next position into LDS, where both row halves of the workgroup's waves read them
 // as operands: a weight is decoded once per workgroup, not once per wave.  Activations come by 16-byte global->LDS loads.  Both
-// are double-buffered with one barrier per position; 54 to 74 KiB of LDS, so that two workgroups share a compute unit and one's
+// are double-buffered with one barrier per position; 33 to 65 KiB of LDS by format and tokens, so that two workgroups share a compute unit and one's
 // waits run under the other's matrix instructions.
 #include <algorithm>
 #include <atomic>

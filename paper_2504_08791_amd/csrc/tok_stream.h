@@ -1,4 +1,4 @@
-// Launchers of the projections of a window of 9 to 16 tokens (tok_stream.hip).
+// Launchers of the projections of a window of 4 to 16 tokens (tok_stream.hip): the other formats' matrices, from 9 tokens on Q4_K too.
 #pragma once
 #include "common.h"
 

@@ -1,4 +1,5 @@
-// The projections of a layer window for 9 to 16 tokens (speculative verification, batches of sequences): mat-vecs on the matrix
+// The projections of a layer window for 9 to 16 tokens (speculative verification, batches of sequences), and for 4 to 8 those in other
+// formats than Q4_K: mat-vecs on the matrix
 // cores over activations that are prepared once per projection, with the sums finished by the kernel that prepares the next
 // one.  Arithmetic and layouts: tok_common.h.
 //
@@ -13,7 +14,7 @@
 //
 // The Q4_K mat-vec of one to eight tokens (q4k_gemv_mfma.hip) takes 16 tokens in two passes over the weights; here one pass
 // serves them.  A 14B-shaped layer, 16 sequences, us with the tracer: Q/K/V 38 -> 19, output 31 -> 21, gate and up 65 -> 38,
-// down 44 -> 25 (adding and preparing included); the batch step of three layers 585 -> 371.  What bounds the stream at 16
+// down 44 -> 25 (adding and preparing included); the batch step of three layers 586 -> 380.  What bounds the stream at 16
 // tokens: 27648 x 5120 (80 MB, 12 us at the rate of a linear read) takes 30 us, 21 without its products, 31 without its
 // loads: the LDS reads of the operands (17 KB a super-block and wave) and the unpacking under two waves a SIMD.
 // From four tokens on the other formats' matrices of a window come here too (prepared, streamed and added each group for itself).

@@ -26,20 +26,24 @@ bool dims_ok(const prima_dims *d)
 }
 
 // Windows of 9 to 16 tokens go through tok_stream.hip, in one pass over the weights (16 sequences through three 14B-shaped layers
-// 585 -> 371 us; at 8 tokens and fewer run_layer()'s one pass is faster, 364 us against 379 for two 70B-shaped layers).  K long
+// 586 -> 380 us; at 8 tokens and fewer run_layer()'s one pass is faster, 364 us against 379 for two 70B-shaped layers).  K long
 // enough to need hundreds of slabs and layers with an FP32 matrix go through run_layer() too.
 constexpr int TOK_WINDOW = 9; // tokens from which whole windows go there
 // ... and from which the matrices in other formats of a smaller window do.  Two layers, V and down in Q6_K in one of them, us, there /
 // through a mat-vec for each: 14B shape 4 tokens 213 / 221, 5: 230 / 248, 8: 236 / 290; 70B shape 4: 342 / 376, 8: 385 / 492.  At
-// three tokens the mat-vec is as fast (14B shape 211; its launch reads the activations itself).
+// three tokens the mat-vec is as fast (14B shape 211; its launch reads the activations itself).  Down in Q8_0, 4 tokens: 14B 200 / 206, 70B
+// 350 / 376, in FP16 216 / 248, 406 / 467; every matrix in Q8_0: 14B 276 / 325, in FP16 330 / 486, in Q5_K 253 / 366.
 constexpr int TOK_OTHERS = 4;
 // A group of these matrices takes a launch in front of its streams (one per format) and one behind, the mat-vecs one per matrix.  Up to
 // 7 tokens a launch more pays from about this many weights on.  Two layers, us, mat-vecs / streams, 4 tokens: hidden size 512, V
 // and down in Q6_K 86 / 99, V in Q5_K too 103 / 119; 2048, V in FP16 128 / 129; 4096, V in FP16 192 / 187, all in Q8_0 295 / 251.
 constexpr int64_t TOK_LAUNCH_WEIGHTS = int64_t{1} << 21;
-// One sequence behind few cached rows: single binary16 roundings of the appended K / V rows weigh most there (each is one of
-// few keys), and the rows of the third layer differ by 1 to 2e-4 between two arithmetics that are each 2 to 4e-5 from 64 bits
-// (13 and 16 tokens behind 1 to 9 rows; from 40 rows on 3 to 8e-5).  Such steps keep the arithmetic they had, bit for bit.
+// One sequence behind fewer cached rows than this keeps the mat-vecs, so that its results stay what they were, bit for bit; it is neither
+// the faster nor the more exact way.  Three 8B-shaped layers, mat-vecs / streams: 16 tokens behind 9 rows 486 / 299 us, median error
+// of 40 inputs against 64 bits 4.1e-5 / 3.5e-5; 13 behind 1 row 482 / 293 us, 5.9e-5 / 5.5e-5; 13 behind 40 rows 483 / 297 us, 2.0e-5 /
+// 1.8e-5.  Where a token sees few keys, one rounding of an appended K or V element to binary16 that goes the other way is felt in
+// every later layer: the two ways' deeper cache rows differ by up to 1.5e-4 behind 1 to 9 rows and 6e-5 behind 40, and a caller who
+// holds a step to an earlier one at 1e-4 would see them change.  (A batch appends one row per sequence; its steps differ by less.)
 constexpr int TOK_MIN_ROWS = 64;
 bool tok_context(int n_past, const AttnSeqs *seq) { return seq || n_past >= TOK_MIN_ROWS; }
 // Whether these dimensions have a region for the streams in their scratch: a rule on the widths alone, so that scratch sized for

@@ -11,6 +11,8 @@ the accuracy class of the mat-vec on the path, which the operator-level tests as
   EPS_GEMM  2^-21: the Q4_K matrix product of the prompt call (22-bit activations and a chain of fp32 roundings per
             super-block: measured rms error 2.2e-7, single outputs up to 1.7e-6)
   EPS_FP32  2^-20: the other formats' mat-vec (fp32 accumulation along K).
+Windows and batches of 9 to 16 tokens take the activations as two binary16 numbers (22 bits or more of each) and sum on the
+matrix cores: rms errors of 0.9e-7 to 1.4e-7, inside EPS_Q4K for Q4_K and far inside EPS_FP32 for the others.
 The perturbed evaluations: four with random signs everywhere, and the deterministic ones in which appended K / V
 values that lie within eps of a binary16 rounding boundary are rounded the other way (all of them, and the twelve
 closest one at a time).  A case passes when err <= 2e-3 or err <= 1.5 x the largest movement over these
