@@ -260,14 +260,15 @@ prima_status plan_nt(TokArgs &a, size_t &lds)
         chunk = ((a.nb + n_chunks - 1) / n_chunks + SBS - 1) / SBS * SBS;
         const int last = a.nb - (a.nb - 1) / chunk * chunk; // super-blocks of the last chunk
         if (sh > 0 && (1 << sh) > (last + SBS - 1) / SBS) continue; // every part of every chunk has a stage
-        // A chunk costs its operands (about two stages' time) and, round by round, the longest part.  A wave requests its stages of
+        // A chunk costs its operands (about two stages' time) and, round by round, the longest part and half a stage for the unit (its
+        // addresses and sums; without that tall matrices went in eighths: Q6_K 100000 x 4096, 2 tokens, 109 us, now 80).  A wave requests its stages of
         // a chunk in pairs; where the stream bounds the launch the odd one counts (us, not counted / counted, 8 tokens: FP16
         // 8192 x 1024 11.6 / 8.8, 4096 x 8192 34 / 30, Q8_0 8192 x 4096 26 / 19; in Q6_K and Q5_K, which unpack longer
         // than they load, 4096 x 2048 would go from 9.4 to 10.2).
         const int part = (chunk / SBS + (1 << sh) - 1) >> sh, blocks = (rounds + blk - 1) / blk, last_blk = rounds - (blocks - 1) * blk;
         const bool padding = FMT == PRIMA_FMT_F16 || (FMT == PRIMA_FMT_Q8_0 && NT <= 8 && a.n_tiles > grid);
         auto requested = [&](int stages) { return padding ? (stages + 1) / 2 * 2 : stages; };
-        const double t = static_cast<double>(n_chunks) * (2.0 * blocks + (blocks - 1) * requested(blk * part) + requested(last_blk * part));
+        const double t = static_cast<double>(n_chunks) * (2.0 * blocks + 0.5 * rounds + (blocks - 1) * requested(blk * part) + requested(last_blk * part));
         if (sh == 0 || t < best * 0.999) {
             best = t;
             a.ks_shift = sh;
@@ -327,7 +328,7 @@ prima_status launch_any(int fmt, const TokArgs &a, bool plan_only, hipStream_t s
 //                   one tile of rows: Q6_K 16 x 4096  7: 14 / 11 (every activation laid out for 16 rows)
 //   9, 10 tokens    as 16 slots: Q6_K 1024 x 8192  9: 48 / 45, 16 x 8192  47 / 31; FP16 1024 x 8192  39 / 49
 //   4 to 6 tokens   Q8_0 16384 x 1024  4: 13 / 11, 16384 x 4096  5: 29 / 26, 16384 x 8192  4: 35 / 39; Q5_K 16384 x 1024  4: 10.6 / 11.1
-//   2 tokens        Q6_K 128256 x 8192  163 / 173, 100000 x 4096  113 / 84 (a fourth round of tiles for a twentieth of them)
+//   2 tokens        Q6_K 128256 x 8192  162 / 167, 100000 x 4096  80 / 80, 65536 x 4096  48 / 54; Q8_0 128256 x 8192  184 / 175, 65536 x 4096  56 / 50
 // Below the lines several tokens stay with the mat-vec; 9 and 10 tokens of few rows go as 8 here and the rest there.
 // Q4_K, against two passes of the integer mat-vec (q4k_gemv_mfma.hip), which has scratch to divide K among workgroups:
 //   128256 x 8192        9 tokens 190 / 256, 16: 192 / 326    60000 x 2048   9: 32 / 46, 16: 33 / 59
@@ -352,7 +353,7 @@ bool tok_gemv_takes(int fmt, int64_t n_rows, int64_t n_cols, int T)
     if (n_rows <= 16) return T >= 13 || (T >= 9 && n_cols <= 1024);
     if (T >= 7) return !(q8 && T == 7 && n_cols > 16384 && n_rows <= 8192);
     if (T >= 4) return n_rows >= (q8 && T == 4 ? 32768 : 24576) || (n_rows >= 16384 && (k_quant || n_cols >= (q8 ? 8192 : 2048)));
-    return T >= 2 && n_rows >= 65536 && (T == 3 || (!q8 && (!k_quant || places_filled(n_rows) >= 0.9)));
+    return T >= 2 && n_rows >= 65536 && (T == 3 || !q8);
 }
 
 // tokens of T that go to launch_tok_gemv() in a call of few rows; the others after them to the fp32 mat-vec
