@@ -52,10 +52,11 @@ constexpr int tk_slots(int T) { return T <= 2 ? 2 : (T <= 4 ? 4 : (T <= 8 ? 8 : 
 // Sixteen lanes hold one token's super-block, lane i columns 16 i .. 16 i + 15 in v (RMSNorm gain applied); into the record.  ORD: the order of
 // a slice's 8 columns in the operand: 0: 0 4 1 5 2 6 3 7 (Q4_K's nibbles), 1: 0 2 1 3 4 6 5 7 (bytes).
 // INF: for formats whose products are not corrected afterwards (Q8_0, FP16), infinities pass as such; Q5_K and Q6_K give NaN for them,
-// as their one-token mat-vec does.
+// as their one-token mat-vec does.  SUMS: the sub-block sums too (what Q4_K and Q5_K take the centre and the minima from; without them
+// Q6_K 16 x 14336, 8 tokens, 36.8 -> 32.8 us: every workgroup lays out all of the activations).
 // A 16-byte piece (8 columns of one row) c = 4 S + j, S the sub-block, j the slice, lies at a[c][row ^ f(c)], f(c) = (c >> 1) & 15:
 // the sixteen lanes write pieces whose rows would otherwise share their banks.
-template <int NT, int ORD, bool INF>
+template <int NT, int ORD, bool INF, bool SUMS>
 __device__ __forceinline__ void tk_split(const float (&v)[16], int i, int t, uint8_t *rec)
 {
     uint8_t *const a = rec, *const sums = rec + tk_sums_at(NT);
@@ -83,8 +84,10 @@ __device__ __forceinline__ void tk_split(const float (&v)[16], int i, int t, uin
         float r = sv - static_cast<float>(hh[k]);
         if constexpr (INF) r = fmaxf(r, -1024.f); // (in a NaN's place: inf - inf; any other is smaller)
         ll[k] = static_cast<_Float16>(r);
-        sum += static_cast<float>(hh[k]);
-        suml += static_cast<float>(ll[k]);
+        if constexpr (SUMS) {
+            sum += static_cast<float>(hh[k]);
+            suml += static_cast<float>(ll[k]);
+        }
     }
 #pragma unroll
     for (int gi = 0; gi < 2; ++gi) {
@@ -106,9 +109,11 @@ __device__ __forceinline__ void tk_split(const float (&v)[16], int i, int t, uin
         }
     }
     // the sub-block's sum (this lane and its neighbour), as hi + lo; [part (16 tokens)][S & 3][row][S >> 2]
-    sum += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sum), 0xB1, 0xf, 0xf, true));
-    suml += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, suml), 0xB1, 0xf, 0xf, true));
-    if ((i & 1) == 0) {
+    if constexpr (SUMS) {
+        sum += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sum), 0xB1, 0xf, 0xf, true));
+        suml += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, suml), 0xB1, 0xf, 0xf, true));
+    }
+    if (SUMS && (i & 1) == 0) {
         const int S8 = i >> 1;
         const _Float16 sh = static_cast<_Float16>(sum + suml), sl = static_cast<_Float16>((sum - static_cast<float>(sh)) + suml);
         _Float16 *q = reinterpret_cast<_Float16 *>(sums);

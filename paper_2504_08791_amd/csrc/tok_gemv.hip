@@ -167,7 +167,7 @@ __global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64) __attribute__((amdgpu_
                         ss = row_sum16(ss);
                         if (n == 0) l_ss[b * NT + t] = ss;
                     }
-                    tk_split<NT, TkFmt<FMT>::ORD, FMT == PRIMA_FMT_Q8_0 || FMT == PRIMA_FMT_F16>(v, n, t, l_a + b * tk_rec(NT));
+                    tk_split<NT, TkFmt<FMT>::ORD, FMT == PRIMA_FMT_Q8_0 || FMT == PRIMA_FMT_F16, FMT == PRIMA_FMT_Q4_K || FMT == PRIMA_FMT_Q5_K>(v, n, t, l_a + b * tk_rec(NT));
                 }
             }
             __syncthreads();

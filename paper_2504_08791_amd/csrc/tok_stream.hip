@@ -271,8 +271,8 @@ __global__ void __launch_bounds__(64 * ADD_WAVES) tok_prepare_kernel(TokPrepare 
             v[4 * k] *= q.x; v[4 * k + 1] *= q.y; v[4 * k + 2] *= q.z; v[4 * k + 3] *= q.w;
         }
     }
-    if (a.rec[0]) tk_split<NT, 0, false>(v, n, t, a.rec[0] + static_cast<int64_t>(b) * tk_rec(NT));
-    if (a.rec[1]) tk_split<NT, 1, true>(v, n, t, a.rec[1] + static_cast<int64_t>(b) * tk_rec(NT));
+    if (a.rec[0]) tk_split<NT, 0, false, true>(v, n, t, a.rec[0] + static_cast<int64_t>(b) * tk_rec(NT));
+    if (a.rec[1]) tk_split<NT, 1, true, true>(v, n, t, a.rec[1] + static_cast<int64_t>(b) * tk_rec(NT));
 }
 
 // y[t][row] = 1/rms * sum of the shares (+ residual) of up to three vectors of their own lengths, 256 rows per 16 lanes
