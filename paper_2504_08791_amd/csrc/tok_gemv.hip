@@ -325,10 +325,12 @@ prima_status launch_any(int fmt, const TokArgs &a, bool plan_only, hipStream_t s
 // Where the lines lie, us, this kernel / the fp32 mat-vec (replayed from a graph, weights cold; 256 shapes of 16 to 128256 rows and
 // 512 to 28672 columns in each format):
 //   7, 8 tokens     Q6_K 1024 x 8192   8 tokens  24 / 37   Q8_0 8192 x 4096  8: 19 / 20   FP16 8192 x 1024  7: 9.7 / 9.8, 4096 x 8192  8: 26 / 39
-//                   one tile of rows: Q6_K 16 x 4096  7: 14 / 11 (every activation laid out for 16 rows)
+//                   one tile of rows: Q6_K 16 x 4096  7: 14 / 11 (every activation laid out for 16 rows), 16 x 14336  7: 33 / 45; 16 x 28672  8: FP16 69 / 91, Q8_0 103 / 84,
+//                   12: Q5_K 127 / 146, Q6_K 138 / 143
 //   9, 10 tokens    as 16 slots: Q6_K 1024 x 8192  9: 48 / 45, 16 x 8192  47 / 31; FP16 1024 x 8192  39 / 49
-//   4 to 6 tokens   Q8_0 16384 x 1024  4: 13 / 11, 16384 x 4096  5: 29 / 26, 16384 x 8192  4: 35 / 39; Q5_K 16384 x 1024  4: 10.6 / 11.1
-//   2 tokens        Q6_K 128256 x 8192  162 / 167, 100000 x 4096  80 / 80, 65536 x 4096  48 / 54; Q8_0 128256 x 8192  184 / 175, 65536 x 4096  56 / 50
+//   4 to 6 tokens   16384 rows fill a round of the mat-vec: Q8_0 16384 x 2048  5: 16.8 / 15.7, 6: 16.7 / 17.9, 16384 x 4096  5: 27.6 / 25.0,
+//                   17408 x 4096  5: 27 / 33, 16384 x 12288  4: 47 / 57; FP16 16384 x 1024  5: 14.1 / 12.2, 17408 x 1024  5: 12.4 / 15.6
+//   2 tokens        Q6_K 128256 x 8192  162 / 167, 100000 x 4096  80 / 80, 65536 x 4096  48 / 54; Q8_0 128256 x 8192  184 / 175, 65536 x 4096  56 / 50, 65536 x 512  15.9 / 17.9
 // Below the lines several tokens stay with the mat-vec; 9 and 10 tokens of few rows go as 8 here and the rest there.
 // Q4_K, against two passes of the integer mat-vec (q4k_gemv_mfma.hip), which has scratch to divide K among workgroups:
 //   128256 x 8192        9 tokens 190 / 256, 16: 192 / 326    60000 x 2048   9: 32 / 46, 16: 33 / 59
@@ -350,10 +352,10 @@ bool tok_gemv_takes(int fmt, int64_t n_rows, int64_t n_cols, int T)
     if (fmt == PRIMA_FMT_Q4_K) return (T >= 9 && n_rows >= 65536) || (T >= 11 && n_rows >= 28672 && (n_cols <= 6144 || places_filled(n_rows) >= 0.6));
     const bool q8 = fmt == PRIMA_FMT_Q8_0, k_quant = fmt == PRIMA_FMT_Q5_K || fmt == PRIMA_FMT_Q6_K;
     if (!q8 && !k_quant && fmt != PRIMA_FMT_F16) return false;
-    if (n_rows <= 16) return T >= 13 || (T >= 9 && n_cols <= 1024);
+    if (n_rows <= 16) return T >= (n_cols > 16384 ? 12 : 13) || (T >= 9 && n_cols <= 1024) || ((T == 7 || T == 8) && n_cols >= 5120 && !(q8 && n_cols > 16384));
     if (T >= 7) return !(q8 && T == 7 && n_cols > 16384 && n_rows <= 8192);
-    if (T >= 4) return n_rows >= (q8 && T == 4 ? 32768 : 24576) || (n_rows >= 16384 && (k_quant || n_cols >= (q8 ? 8192 : 2048)));
-    return T >= 2 && n_rows >= 65536 && (T == 3 || !q8);
+    if (T >= 4) return n_rows > (T == 4 ? 16512 : 16384) || (n_rows == 16384 && T == 6) || (n_rows >= 16384 && (k_quant || n_cols <= 512 || n_cols >= (q8 ? 8192 : 2048)));
+    return T >= 2 && n_rows >= 65536 && (T == 3 || !q8 || n_cols <= 512);
 }
 
 // tokens of T that go to launch_tok_gemv() in a call of few rows; the others after them to the fp32 mat-vec
