@@ -277,7 +277,7 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
     const uint8_t *wsrc = row_ptr(lane);
     const uint8_t *wq[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) wq[k] = row_ptr(16 * k + (lane >> 2)) + 16 + (lane & 3) * 16;
+    for (int k = 0; k < 4; ++k) wq[k] = row_ptr(16 * k + (lane >> 2)) + 16 + ((lane & 3) ^ (lane >> 4)) * 16;
     const int tile0 = tb * TT;
     const uint32_t lds0 = lds_address(smem);
     // this workgroup's share of K: super-blocks [b_lo, b_lo + nbl) (all of them unless K is divided; never empty: the
@@ -372,9 +372,12 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
     // B tile `rt` of sub-block s from this wave's quants and the sub-scales in hsc: sc_s * q as binary16 (exact).  A dword
     // holds the eight weights of lane (n, g); masked in pairs (0,4) (1,5) (2,6) (3,7) into the mantissas of 1024 + q, the odd
     // pairs (bits 4..7 of a half) of 64 + q without a shift, then one fused multiply-add per pair: (1024 + q) sc - 1024 sc
-    auto build_b = [&](half8 &B, int rt, int s) __attribute__((always_inline)) {
+    const int lane_q = n * 64 + ((n >> 2) << 4) + 4 * g;
+    auto quants_of = [&](int rt, int s) __attribute__((always_inline)) {
         // request rt of the half brought rows 16 rt .. 16 rt + 15: [row][sub-block of the half][16 bytes]
-        const uint32_t w = *reinterpret_cast<const uint32_t *>(smem + WQ_BASE + wave * GM_WQ + (s >> 2) * 4096 + rt * 1024 + n * 64 + (s & 3) * 16 + 4 * g);
+        return *reinterpret_cast<const uint32_t *>(smem + WQ_BASE + wave * GM_WQ + (s >> 2) * 4096 + rt * 1024 + (lane_q ^ ((s & 3) << 4)));
+    };
+    auto build_b = [&](half8 &B, uint32_t w, int rt, int s) __attribute__((always_inline)) {
         const _Float16 sc = static_cast<_Float16>(static_cast<unsigned short>(hdr_field(make_uint4(0u, hsc[rt].x, hsc[rt].y, 0u), s)));
         const half2v sc2 = {sc, sc};
         const _Float16 offa = static_cast<_Float16>(-1024.f) * sc, offb = static_cast<_Float16>(-64.f) * sc; // exact: at most 64512 in magnitude
@@ -406,7 +409,7 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
     float dd[GM_RT], dm[GM_RT];
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"(GM_AHEAD * DM + 4) : "memory"); // headers and first half of super-block 0 have landed
 #pragma unroll
-    for (int rt = 0; rt < GM_RT; ++rt) { load_scales(rt, 0); build_b(Bc[rt], rt, 0); }
+    for (int rt = 0; rt < GM_RT; ++rt) { load_scales(rt, 0); build_b(Bc[rt], quants_of(rt, 0), rt, 0); }
 
     for (int b = 0; b < nbl; ++b) {
         // one position; s as a constant of the type system (a loop over s with "#pragma unroll" is refused by the
@@ -451,6 +454,8 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
                 // LDS reads run two tiles ahead of their MFMAs (one tile, 8 MFMAs, is shorter than the LDS latency
                 // while four waves and the incoming requests share the LDS)
                 half8 ah[3], al[3];
+                uint32_t wn[2];
+                if (s < 7) wn[0] = quants_of(0, s + 1);
                 ah[0] = *reinterpret_cast<const half8 *>(base);
                 al[0] = *reinterpret_cast<const half8 *>(base + 1024);
                 ah[1] = *reinterpret_cast<const half8 *>(base + 2048);
@@ -467,14 +472,19 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
                         acch[tt][rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ch, Bc[rt], s == 0 ? zero : acch[tt][rt], 0, 0, 0);
                         acch[tt][rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(cl, Bc[rt], acch[tt][rt], 0, 0, 0);
                     }
+                    if (s < 7 && tt + 1 < TT) wn[(tt + 1) & 1] = quants_of(tt + 1, s + 1);
                     if (tt < GM_RT) {
-                        if (s < 7) build_b(Bn[tt], tt, s + 1);
+                        if (s < 7) build_b(Bn[tt], wn[tt & 1], tt, s + 1);
                         else build_m(Bn[tt], dd[tt], dm[tt], tt, b);
+                        __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
 #pragma unroll
                         for (int k = 0; k < 2 * GM_RT; ++k) { // one MFMA, then up to four VALU instructions of the build
                             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                            __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+                            __builtin_amdgcn_sched_group_barrier(0x002, s < 7 ? 2 : 4, 0);
                         }
+                        // built here, not where it is used: the compiler moved the unpacking into the next position, in front of its
+                        // first matrix instruction
+                        asm volatile("" : "+v"(Bn[tt]));
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -496,7 +506,7 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
                             yacc[tt][rt][i] += fmaf(dd[rt], acch[tt][rt][i], -(dm[rt] * am[i]));
                     }
                     if (tt < GM_RT) {
-                        if (b + 1 < nbl) { load_scales(tt, b + 1); build_b(Bn[tt], tt, 0); }
+                        if (b + 1 < nbl) { load_scales(tt, b + 1); build_b(Bn[tt], quants_of(tt, 0), tt, 0); }
                         else Bn[tt] = Bc[tt];
                     }
                     __builtin_amdgcn_sched_barrier(0);
