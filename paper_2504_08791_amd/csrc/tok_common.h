@@ -403,9 +403,18 @@ __device__ __forceinline__ void tk_mul(const uint8_t *stage, int b, const uint8_
     }
     if constexpr (Q6) d = tk_h2f(*reinterpret_cast<const unsigned short *>(row + 13 * SBS * 16 + b * 2));
     tk_v4f acc[2] = {zero, zero}, rem = zero, lo = zero; // a chain per half of the super-block; Q6_K's R; 16 tokens: the lo parts
+    tk_half8 B[2][4], R[2][Q6 ? 4 : 1]; // Q6_K: R with the sub-scale's low 4 bits, B with the others (and a 16th of their value)
+    tk_half8 A[2][4], Al[2][NT > 8 ? 4 : 1]; // the activations of a half
+    auto operands = [&](auto half) __attribute__((always_inline)) {
+        constexpr int h = decltype(half)::value;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        tk_half8 B[4], R[Q6 ? 4 : 1]; // Q6_K: R with the sub-scale's low 4 bits, B with the others (and a 16th of their value)
+        for (int j = 0; j < 4; ++j) {
+            A[h][j] = a_at(16 * h + j, 4 * g, 8 * h | (j >> 1), 2 * g, 0);
+            if constexpr (NT > 8) Al[h][j] = a_at(16 * h + j, 4 * g, 8 * h | (j >> 1), 2 * g, 1);
+        }
+    };
+    auto unpack = [&](auto half) __attribute__((always_inline)) {
+        constexpr int h = decltype(half)::value;
         if constexpr (Q4 || Q5) {
             const _Float16 s = ODD ? -tk_small(sc[h]) : tk_small(sc[h]), m = ODD ? -tk_small(mn[h]) : tk_small(mn[h]);
             Bc[h] = static_cast<_Float16>(Q4 ? 8.f : 16.f) * s;
@@ -423,7 +432,7 @@ __device__ __forceinline__ void tk_mul(const uint8_t *stage, int b, const uint8_
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
                         p[i] = __builtin_elementwise_fma(__builtin_bit_cast(tk_half2, (u[i] & 0x00f000f0u) | e64), s2, off);
-                    B[j] = tk_join(p);
+                    B[h][j] = tk_join(p);
                 }
             } else {
                 const tk_v4u q = *reinterpret_cast<const tk_v4u *>(row + (8 * b + 4 * h + g) * 16);
@@ -441,7 +450,7 @@ __device__ __forceinline__ void tk_mul(const uint8_t *stage, int b, const uint8_
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
                         p[i] = __builtin_elementwise_fma(__builtin_bit_cast(tk_half2, (u[i] & 0x01f001f0u) | e64), s2, off);
-                    B[j] = tk_join(p);
+                    B[h][j] = tk_join(p);
                 }
             }
         } else if constexpr (Q6) {
@@ -470,8 +479,8 @@ __device__ __forceinline__ void tk_mul(const uint8_t *stage, int b, const uint8_
                         p[i] = __builtin_elementwise_fma(v[i], tk_both(s1[jj]), tk_both(o1[jj]));
                         e[i] = __builtin_elementwise_fma(v[i], tk_both(s2[jj]), tk_both(o2[jj]));
                     }
-                    B[2 * jj + j2] = tk_join(p);
-                    R[2 * jj + j2] = tk_join(e);
+                    B[h][2 * jj + j2] = tk_join(p);
+                    R[h][2 * jj + j2] = tk_join(e);
                 }
             }
         } else {
@@ -482,29 +491,41 @@ __device__ __forceinline__ void tk_mul(const uint8_t *stage, int b, const uint8_
                 tk_v4u o; // numbers 0..7 as pairs (0, 2) (1, 3) (4, 6) (5, 7)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_perm(q[(i & 2) + 1], q[i & 2], (i & 1) ? 0x07060302u : 0x05040100u) ^ neg;
-                B[j] = __builtin_bit_cast(tk_half8, o);
+                B[h][j] = __builtin_bit_cast(tk_half8, o);
             }
         }
+    };
+    auto products = [&](auto half) __attribute__((always_inline)) {
+        constexpr int h = decltype(half)::value;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const tk_half8 A = a_at(16 * h + j, 4 * g, 8 * h | (j >> 1), 2 * g, 0);
             if constexpr (H) {
                 tk_v4f c = zero;
-                if constexpr (NT > 8) c = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_at(16 * h + j, 4 * g, 8 * h | (j >> 1), 2 * g, 1), B[j], c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, B[j], c, 0, 0, 0);
+                if constexpr (NT > 8) c = __builtin_amdgcn_mfma_f32_16x16x32_f16(Al[h][j], B[h][j], c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[h][j], B[h][j], c, 0, 0, 0);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) acc[h][i] = j & 1 ? acc[h][i] - c[i] : (j == 0 ? c[i] : acc[h][i] + c[i]);
                 continue;
             }
-            if constexpr (Q6) rem = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, R[j], rem, 0, 0, 0);
-            acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, B[j], acc[h], 0, 0, 0);
+            if constexpr (Q6) rem = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[h][j], R[h][j], rem, 0, 0, 0);
+            acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[h][j], B[h][j], acc[h], 0, 0, 0);
             if constexpr (NT > 8) {
-                const tk_half8 Al = a_at(16 * h + j, 4 * g, 8 * h | (j >> 1), 2 * g, 1);
-                lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(Al, B[j], lo, 0, 0, 0);
-                if constexpr (Q6) rem = __builtin_amdgcn_mfma_f32_16x16x32_f16(Al, R[j], rem, 0, 0, 0);
+                lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(Al[h][j], B[h][j], lo, 0, 0, 0);
+                if constexpr (Q6) rem = __builtin_amdgcn_mfma_f32_16x16x32_f16(Al[h][j], R[h][j], rem, 0, 0, 0);
             }
         }
-    }
+    };
+    typedef std::integral_constant<int, 0> First;
+    typedef std::integral_constant<int, 1> Second;
+    operands(First{});
+    __builtin_amdgcn_sched_barrier(0);
+    unpack(First{});
+    __builtin_amdgcn_sched_barrier(0);
+    operands(Second{});
+    products(First{});
+    unpack(Second{});
+    __builtin_amdgcn_sched_barrier(0);
+    products(Second{});
     tk_v4f ac = zero, am = zero;
     if constexpr (Q4 || Q5) {
         tk_v4u xs = {0u, 0u, 0u, 0u};

@@ -38,10 +38,11 @@ struct TokArgs {
     int n_tiles;  // 16-row tiles
     int chunk;    // super-blocks per chunk of K (a multiple of the stage's)
     int ks_shift; // a unit is one of 2^ks_shift parts of a (tile, chunk)
-    // Rounds: in each every wave has one unit at most.  Round k covers tiles [n_tiles k / rounds, n_tiles (k + 1) / rounds), dealt
-    // to the workgroups one by one (a run of neighbouring tiles for each was measured 3 to 10 % slower: the requests of the
-    // device then crowd on fewer memory channels).
-    int rounds, blk_rounds; // in all; whose sums are in LDS at a time
+    // Rounds: in each every wave has one unit at most.  Round k covers tiles k per_round .. (k + 1) per_round - 1 (the last: what is left, maybe
+    // none), dealt to the workgroups one by one (a run of neighbouring tiles for each was measured 3 to 10 % slower: the requests of the
+    // device then crowd on fewer memory channels).  (Rounds of n_tiles k / rounds tiles took some 600 scalar instructions of division per
+    // unit and wave, a fifth of its time at 8 tokens.)
+    int rounds, per_round, blk_rounds; // blk_rounds: whose sums are in LDS at a time
 };
 
 // LDS: the waves' stage buffers | activations [chunk] | sums of squares [chunk][NT] | 1/rms [NT] |
@@ -62,20 +63,12 @@ __global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64) __attribute__((amdgpu_
 
     const int ks_shift = a.ks_shift, ks = 1 << ks_shift, nb = a.nb, chunk = a.chunk;
     const int my_l = wave >> ks_shift, part = wave & (ks - 1); // this wave's tile of a round's and its part
-    // tiles of round k: this workgroup's are first + i * gridDim.x, i < count
-    auto share = [&](int k, int &first, int &count) __attribute__((always_inline)) {
-        const int t0 = static_cast<int>(static_cast<int64_t>(a.n_tiles) * k / a.rounds), nt = static_cast<int>(static_cast<int64_t>(a.n_tiles) * (k + 1) / a.rounds) - t0;
-        first = t0 + static_cast<int>(blockIdx.x);
-        count = (nt + static_cast<int>(gridDim.x) - 1 - static_cast<int>(blockIdx.x)) / static_cast<int>(gridDim.x);
-    };
+    const int my_tile = static_cast<int>(blockIdx.x) + my_l * static_cast<int>(gridDim.x); // counted from the round's first
     // the first round from k on in which this wave has a tile (k_end: none), and the tile
     auto next_round = [&](int k, int k_end, int &tile) __attribute__((always_inline)) {
-        for (; k < k_end; ++k) {
-            int first, count;
-            share(k, first, count);
-            if (my_l < count) { tile = first + my_l * static_cast<int>(gridDim.x); break; }
-        }
-        return k;
+        tile = k * a.per_round + my_tile;
+        if (my_tile >= a.per_round || tile >= a.n_tiles) return k_end;
+        return min(k, k_end);
     };
     // stages [s0, s1) of the chunk of `len` super-blocks are this wave's part (never empty: the host keeps ks <= a chunk's stages)
     auto part_of = [&](int len, int &s0, int &s1) __attribute__((always_inline)) {
@@ -220,8 +213,10 @@ __global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64) __attribute__((amdgpu_
         __syncthreads();
         // ---- a unit's parts in order, 1/rms, the residual ----
         for (int k = k0; k < k_end; ++k) {
-            int first, count;
-            share(k, first, count);
+            // this workgroup's tiles of the round: first + i * gridDim.x, i < count
+            const int first = k * a.per_round + static_cast<int>(blockIdx.x);
+            const int left = min(a.per_round, a.n_tiles - k * a.per_round) - static_cast<int>(blockIdx.x);
+            const int count = left > 0 ? static_cast<int>((static_cast<unsigned>(left) + gridDim.x - 1) / gridDim.x) : 0;
             const int n_out = count * 16 * a.T;
             for (int idx = threadIdx.x; idx < n_out; idx += THREADS) {
                 const int l = idx / (16 * a.T), rem = idx - l * (16 * a.T), t = rem >> 4, j = rem & 15;
@@ -273,6 +268,7 @@ prima_status plan_nt(TokArgs &a, size_t &lds)
             best = t;
             a.ks_shift = sh;
             a.rounds = rounds;
+            a.per_round = (a.n_tiles + rounds - 1) / rounds;
             a.blk_rounds = blk;
             a.chunk = chunk;
         }

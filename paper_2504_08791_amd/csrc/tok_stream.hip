@@ -42,7 +42,7 @@ struct StreamArgs {
     int nb, T, n_tiles;
     int n_slabs, slab; // slabs of K, super-blocks of one (a multiple of the stage's; the last may be shorter)
     int ks_shift;      // a unit is one of 2^ks_shift parts of a (tile, slab)
-    int rounds;        // as in tok_gemv.hip, among the workgroups of a slab
+    int rounds, per_round; // as in tok_gemv.hip, among the workgroups of a slab
 };
 
 template <int FMT, int NT>
@@ -62,14 +62,12 @@ __global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64) __attribute__((amdgpu_
     const int sb0 = slab * a.slab, nsb = min(a.slab, nb - sb0);
     const int my_l = wave >> ks_shift, part = wave & (ks - 1);
     const int stages = (nsb + SBS - 1) / SBS, s0 = (stages * part) >> ks_shift, s1 = (stages * (part + 1)) >> ks_shift; // this wave's stages (not none: host)
+    const int my_tile = rank + my_l * ranks; // counted from the round's first
     // the first round from k on in which this wave has a tile (rounds: none), and the tile
     auto next_round = [&](int k, int &tile) __attribute__((always_inline)) {
-        for (; k < a.rounds; ++k) {
-            const int t0 = static_cast<int>(static_cast<int64_t>(a.n_tiles) * k / a.rounds), t1 = static_cast<int>(static_cast<int64_t>(a.n_tiles) * (k + 1) / a.rounds);
-            tile = t0 + rank + my_l * ranks;
-            if (tile < t1) break;
-        }
-        return k;
+        tile = k * a.per_round + my_tile;
+        if (my_tile >= a.per_round || tile >= a.n_tiles) return a.rounds;
+        return min(k, a.rounds);
     };
     int n_active = 0;
     {
@@ -373,6 +371,7 @@ prima_status launch_fmt(StreamArgs &a, size_t part_floats, int &n_parts, bool pl
     const StreamPlan p = plan_stream<FMT>(a.n_tiles, a.nb, nt);
     if (p.n_slabs == 0 || nt < (FMT == PRIMA_FMT_Q4_K ? 16 : 4)) return PRIMA_E_SHAPE;
     a.n_slabs = p.n_slabs; a.slab = p.slab; a.ks_shift = p.ks_shift; a.rounds = p.rounds;
+    a.per_round = (a.n_tiles + p.rounds - 1) / p.rounds;
     n_parts = p.n_slabs << p.ks_shift;
     if (static_cast<size_t>(n_parts) * a.T * a.n_tiles * 16 > part_floats) return PRIMA_E_WORKSPACE;
     if (plan_only) return p.lds > TK_LDS ? PRIMA_E_SHAPE : PRIMA_OK;
