@@ -327,121 +327,99 @@ __device__ __forceinline__ float tk_h2f(unsigned v) { return __half2float(__usho
 // bits of m from a, the others from b
 __device__ __forceinline__ unsigned tk_sel(unsigned m, unsigned a, unsigned b) { return (a & m) | (b & ~m); }
 
-// y[i] += the super-block's share: tokens 2 g' + i (NT <= 8, g' = g modulo the token pairs) or 4 g + i of row n.
-// stage: the wave's buffer; b: super-block of the stage; ODD: multiplied as its negative (the K-quants); a: the activations' record
-template <int FMT, int NT, bool ODD>
-__device__ __forceinline__ void tk_mul(const uint8_t *stage, int b, const uint8_t *a, int lane, float *y)
-{
-    const uint8_t *const sums = a + tk_sums_at(NT);
-    const float *const inv = reinterpret_cast<const float *>(a + tk_inv_at(NT));
-    constexpr int RS = TkFmt<FMT>::RS, SBS = TkFmt<FMT>::SBS;
-    constexpr int MR = NT <= 8 ? 2 * NT : 16, PS = NT <= 8 ? MR : 32; // rows of a part, rows between pieces
-    constexpr int NY = NT <= 8 ? 2 : 4;
-    constexpr bool Q4 = FMT == PRIMA_FMT_Q4_K, Q5 = FMT == PRIMA_FMT_Q5_K, Q6 = FMT == PRIMA_FMT_Q6_K, Q8 = FMT == PRIMA_FMT_Q8_0, H = FMT == PRIMA_FMT_F16;
-    const int n = lane & 15, g = lane >> 4;
-    const uint8_t *row = stage + n * RS * 16;
-    const tk_v4f zero = {0.f, 0.f, 0.f, 0.f};
-    const unsigned e1024 = tk_vconst(0x64006400u), e64 = tk_vconst(0x54005400u); // exponents of 1024 and 64 in both halves
-    auto a_at = [&](int c_static, int c_lane, int f_static, int f_lane, int part) __attribute__((always_inline)) {
-        const int m = ((n ^ f_lane) ^ f_static) & (MR - 1);
-        return *reinterpret_cast<const tk_half8 *>(a + (c_lane * PS + m) * 16 + (c_static * PS + part * 16) * 16);
-    };
-    float iv[NY];
-    if constexpr (NT <= 8) {
-        const float2 t = *reinterpret_cast<const float2 *>(inv + 2 * (g & (NT / 2 - 1)));
-        iv[0] = t.x; iv[1] = t.y;
-    } else {
-        const float4 t = *reinterpret_cast<const float4 *>(inv + 4 * g);
-        iv[0] = t.x; iv[1] = t.y; iv[2] = t.z; iv[3] = t.w;
-    }
+// One super-block of 16 rows: its share of y[i], tokens 2 g' + i (NT <= 8, g' = g modulo the token pairs) or 4 g + i of row n.  ODD: multiplied
+// as its negative (the K-quants).  In steps, so that two super-blocks can be worked on at a time (tk_mul2)
+template <int FMT, int NT, bool ODD> struct TkSb {
+    static constexpr int RS = TkFmt<FMT>::RS, SBS = TkFmt<FMT>::SBS;
+    static constexpr int MR = NT <= 8 ? 2 * NT : 16, PS = NT <= 8 ? MR : 32; // rows of a part, rows between pieces
+    static constexpr int NY = NT <= 8 ? 2 : 4;
+    static constexpr bool Q4 = FMT == PRIMA_FMT_Q4_K, Q5 = FMT == PRIMA_FMT_Q5_K, Q6 = FMT == PRIMA_FMT_Q6_K, H = FMT == PRIMA_FMT_F16;
 
-    if constexpr (Q8) {
-        const tk_v4u dv = *reinterpret_cast<const tk_v4u *>(row + (16 * SBS + b) * 16);
-        float t[NY];
-#pragma unroll
-        for (int i = 0; i < NY; ++i) t[i] = 0.f;
-        const tk_half2 off = tk_both(static_cast<_Float16>(-1152.f));
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const uint2 w = *reinterpret_cast<const uint2 *>(row + b * 256 + s * 32 + g * 8);
-            tk_half2 p[4];
-            tk_pairs(w.x ^ 0x80808080u, 0x00ff00ffu, e1024, p);
-            tk_pairs(w.y ^ 0x80808080u, 0x00ff00ffu, e1024, p + 2);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) p[i] = s & 1 ? -off - p[i] : p[i] + off;
-            const tk_half8 B = tk_join(p);
-            const float d = tk_h2f(s & 1 ? dv[s >> 1] >> 16 : dv[s >> 1]);
-            if constexpr (NT <= 8) {
-                const tk_v4f c = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_at(4 * s, g, 2 * s, g >> 1, 0), B, zero, 0, 0, 0);
-#pragma unroll
-                for (int i = 0; i < 2; ++i) t[i] = fmaf(s & 1 ? -d : d, c[2 * i] + c[2 * i + 1], t[i]);
-            } else {
-                tk_v4f c = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_at(4 * s, g, 2 * s, g >> 1, 1), B, zero, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_at(4 * s, g, 2 * s, g >> 1, 0), B, c, 0, 0, 0);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) t[i] = fmaf(s & 1 ? -d : d, c[i], t[i]);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < NY; ++i) y[i] = fmaf(t[i], iv[i], y[i]);
-        return;
-    }
-
-    // ---- four steps (sub-blocks 4h .. 4h+3) at a time: their operands, then their products ----
+    const uint8_t *row, *a; // this lane's row in the wave's stage buffer; the activations' record
+    int b, n, g;            // super-block of the stage; lane coordinates
+    unsigned e1024, e64;    // exponents of 1024 and 64 in both halves
     float d = 1.f, dmin = 0.f;
-    tk_half8 Bc = {}, Bm = {}; // sums: centre times sub-scale, sub-min (slots 0 and 1: sub-blocks g and 4 + g)
     unsigned sc[2] = {}, mn[2] = {};
-    if constexpr (Q4 || Q5) {
-        const uint4 hdr = *reinterpret_cast<const uint4 *>(row + (Q4 ? b * 9 : 10 * SBS + b) * 16);
-        const int fsh = 6 * g;
-        sc[0] = __builtin_amdgcn_ubfe(hdr.y, fsh, 6);
-        sc[1] = __builtin_amdgcn_ubfe(__builtin_amdgcn_alignbit(hdr.z, hdr.y, 24), fsh, 6);
-        mn[0] = __builtin_amdgcn_ubfe(__builtin_amdgcn_alignbit(hdr.w, hdr.z, 16), fsh, 6);
-        mn[1] = __builtin_amdgcn_ubfe(hdr.w, 8 + fsh, 6);
-        d = hdr_d(hdr);
-        dmin = hdr_dmin(hdr);
-    }
-    if constexpr (Q6) d = tk_h2f(*reinterpret_cast<const unsigned short *>(row + 13 * SBS * 16 + b * 2));
-    tk_v4f acc[2] = {zero, zero}, rem = zero, lo = zero; // a chain per half of the super-block; Q6_K's R; 16 tokens: the lo parts
+    tk_v4u quants[H ? 1 : 2]; // as stored, of a half of the super-block each
+    uint2 high[2];            // Q5_K, Q6_K: their high bits
+    tk_half8 Bc = {}, Bm = {}; // sums: centre times sub-scale, sub-min (slots 0 and 1: sub-blocks g and 4 + g)
+    tk_v4f acc[2] = {}, rem = {}, lo = {}, ac = {}, am = {}; // a chain per half of the super-block; Q6_K's R; 16 tokens: the lo parts; centres, minima
     tk_half8 B[2][4], R[2][Q6 ? 4 : 1]; // Q6_K: R with the sub-scale's low 4 bits, B with the others (and a 16th of their value)
     tk_half8 A[2][4], Al[2][NT > 8 ? 4 : 1]; // the activations of a half
-    auto operands = [&](auto half) __attribute__((always_inline)) {
-        constexpr int h = decltype(half)::value;
+
+    __device__ __forceinline__ TkSb(const uint8_t *stage, int b_, const uint8_t *a_, int lane) : row(stage + (lane & 15) * RS * 16), a(a_), b(b_), n(lane & 15), g(lane >> 4)
+    {
+        e1024 = tk_vconst(0x64006400u);
+        e64 = tk_vconst(0x54005400u);
+    }
+    __device__ __forceinline__ tk_half8 a_at(int c_static, int c_lane, int f_static, int f_lane, int part) const
+    {
+        const int m = ((n ^ f_lane) ^ f_static) & (MR - 1);
+        return *reinterpret_cast<const tk_half8 *>(a + (c_lane * PS + m) * 16 + (c_static * PS + part * 16) * 16);
+    }
+    // the fields of the super-block (FP16: read where they are unpacked)
+    __device__ __forceinline__ void fetch()
+    {
+        if constexpr (Q4 || Q5) {
+            const uint4 hdr = *reinterpret_cast<const uint4 *>(row + (Q4 ? b * 9 : 10 * SBS + b) * 16);
+            const int fsh = 6 * g;
+            sc[0] = __builtin_amdgcn_ubfe(hdr.y, fsh, 6);
+            sc[1] = __builtin_amdgcn_ubfe(__builtin_amdgcn_alignbit(hdr.z, hdr.y, 24), fsh, 6);
+            mn[0] = __builtin_amdgcn_ubfe(__builtin_amdgcn_alignbit(hdr.w, hdr.z, 16), fsh, 6);
+            mn[1] = __builtin_amdgcn_ubfe(hdr.w, 8 + fsh, 6);
+            d = hdr_d(hdr);
+            dmin = hdr_dmin(hdr);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if constexpr (Q4) quants[h] = *reinterpret_cast<const tk_v4u *>(row + (b * 9 + 1 + 4 * h + g) * 16);
+            if constexpr (Q5 || Q6) quants[h] = *reinterpret_cast<const tk_v4u *>(row + (8 * b + 4 * h + g) * 16);
+            if constexpr (Q5) high[h].x = *reinterpret_cast<const unsigned *>(row + (8 * SBS + 2 * b) * 16 + (4 * h + g) * 4);
+            if constexpr (Q6) {
+                high[h] = *reinterpret_cast<const uint2 *>(row + (8 * SBS + 4 * b) * 16 + (4 * h + g) * 8);
+                sc[h] = *reinterpret_cast<const unsigned short *>(row + (12 * SBS + b) * 16 + (4 * h + g) * 2);
+            }
+        }
+        if constexpr (Q6) d = tk_h2f(*reinterpret_cast<const unsigned short *>(row + 13 * SBS * 16 + b * 2));
+    }
+    // half h (sub-blocks 4h .. 4h+3): its activations, its weights, their products
+    template <int h> __device__ __forceinline__ void operands()
+    {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             A[h][j] = a_at(16 * h + j, 4 * g, 8 * h | (j >> 1), 2 * g, 0);
             if constexpr (NT > 8) Al[h][j] = a_at(16 * h + j, 4 * g, 8 * h | (j >> 1), 2 * g, 1);
         }
-    };
-    auto unpack = [&](auto half) __attribute__((always_inline)) {
-        constexpr int h = decltype(half)::value;
+    }
+    template <int h> __device__ __forceinline__ void unpack()
+    {
         if constexpr (Q4 || Q5) {
             const _Float16 s = ODD ? -tk_small(sc[h]) : tk_small(sc[h]), m = ODD ? -tk_small(mn[h]) : tk_small(mn[h]);
             Bc[h] = static_cast<_Float16>(Q4 ? 8.f : 16.f) * s;
             Bm[h] = m;
             const tk_half2 s2 = tk_both(s);
             if constexpr (Q4) {
-                const tk_half2 off = s2 * tk_both(static_cast<_Float16>(-72.f)); // exact
-                const tk_v4u q = *reinterpret_cast<const tk_v4u *>(row + (b * 9 + 1 + 4 * h + g) * 16);
+                // A nibble in bits 0..3 of a half is the binary16 number q 2^-24, in bits 4..7 q 2^-20: times the sub-scale's 2^10 and 2^6, less
+                // 8 of them, every pair becomes (q - 8) s 2^-14 (exact, and a normal number) with one instruction and one mask
+                const tk_half2 s10 = s2 * tk_both(static_cast<_Float16>(1024.f)), s6 = s2 * tk_both(static_cast<_Float16>(64.f));
+                const tk_half2 off = s2 * tk_both(static_cast<_Float16>(-0.00048828125f)); // -8 s 2^-14
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    // a nibble in bits 4..7 of a half, under the exponent of 64: 64 + q
-                    const unsigned w = q[j];
-                    const unsigned u[4] = {w << 4, w, w >> 4, w >> 8};
+                    const unsigned w = quants[h][j], w8 = w >> 8;
                     tk_half2 p[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        p[i] = __builtin_elementwise_fma(__builtin_bit_cast(tk_half2, (u[i] & 0x00f000f0u) | e64), s2, off);
+                    p[0] = __builtin_elementwise_fma(__builtin_bit_cast(tk_half2, w & 0x000f000fu), s10, off);
+                    p[1] = __builtin_elementwise_fma(__builtin_bit_cast(tk_half2, w & 0x00f000f0u), s6, off);
+                    p[2] = __builtin_elementwise_fma(__builtin_bit_cast(tk_half2, w8 & 0x000f000fu), s10, off);
+                    p[3] = __builtin_elementwise_fma(__builtin_bit_cast(tk_half2, w8 & 0x00f000f0u), s6, off);
                     B[h][j] = tk_join(p);
                 }
             } else {
-                const tk_v4u q = *reinterpret_cast<const tk_v4u *>(row + (8 * b + 4 * h + g) * 16);
-                const unsigned hb = *reinterpret_cast<const unsigned *>(row + (8 * SBS + 2 * b) * 16 + (4 * h + g) * 4);
+                const unsigned hb = high[h].x;
                 const tk_half2 off = s2 * tk_both(static_cast<_Float16>(-80.f)); // exact
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     // bit 4 of the four weights 8 j + 4 x .. : bit 2 j + x of every byte
-                    const unsigned w = q[j];
+                    const unsigned w = quants[h][j];
                     const unsigned h0 = 2 * j <= 4 ? hb << (4 - 2 * j) : hb >> (2 * j - 4), h1 = 2 * j + 1 <= 4 ? hb << (3 - 2 * j) : hb >> (2 * j - 3);
                     const unsigned u0 = tk_sel(0x0f0f0f0fu, w, h0), u1 = tk_sel(0x0f0f0f0fu, w >> 4, h1);
                     // a byte's 5 bits in bits 4..8 of a half, under the exponent of 64: 64 + q
@@ -454,9 +432,8 @@ __device__ __forceinline__ void tk_mul(const uint8_t *stage, int b, const uint8_
                 }
             }
         } else if constexpr (Q6) {
-            const tk_v4u q = *reinterpret_cast<const tk_v4u *>(row + (8 * b + 4 * h + g) * 16);
-            const uint2 hw = *reinterpret_cast<const uint2 *>(row + (8 * SBS + 4 * b) * 16 + (4 * h + g) * 8);
-            const unsigned scw = *reinterpret_cast<const unsigned short *>(row + (12 * SBS + b) * 16 + (4 * h + g) * 2);
+            const uint2 hw = high[h];
+            const unsigned scw = sc[h];
             // sub-scale = 16 s1 + s2, 0 <= s2 < 16: both parts' products with q - 32, and with 1056, are exact in 11 bits.  The two
             // sub-scales of the sub-block as bytes s + 128 in the halves of a word, their parts under the exponent of 1024
             const unsigned sb = __builtin_amdgcn_perm(0u, scw, 0x0c010c00u) ^ 0x00800080u;
@@ -469,7 +446,7 @@ __device__ __forceinline__ void tk_mul(const uint8_t *stage, int b, const uint8_
                 const unsigned x = jj == 0 ? hw.x : hw.y;
 #pragma unroll
                 for (int j2 = 0; j2 < 2; ++j2) {
-                    const unsigned w = q[2 * jj + j2];
+                    const unsigned w = quants[h][2 * jj + j2];
                     const unsigned u0 = tk_sel(0x0f0f0f0fu, w, j2 ? x : x << 4), u1 = tk_sel(0x0f0f0f0fu, w >> 4, j2 ? x >> 2 : x << 2);
                     tk_half2 v[4], p[4], e[4];
                     tk_pairs(u0, 0x003f003fu, e1024, v);
@@ -494,9 +471,10 @@ __device__ __forceinline__ void tk_mul(const uint8_t *stage, int b, const uint8_
                 B[h][j] = __builtin_bit_cast(tk_half8, o);
             }
         }
-    };
-    auto products = [&](auto half) __attribute__((always_inline)) {
-        constexpr int h = decltype(half)::value;
+    }
+    template <int h> __device__ __forceinline__ void products()
+    {
+        const tk_v4f zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if constexpr (H) {
@@ -514,50 +492,178 @@ __device__ __forceinline__ void tk_mul(const uint8_t *stage, int b, const uint8_
                 if constexpr (Q6) rem = __builtin_amdgcn_mfma_f32_16x16x32_f16(Al[h][j], R[h][j], rem, 0, 0, 0);
             }
         }
-    };
-    typedef std::integral_constant<int, 0> First;
-    typedef std::integral_constant<int, 1> Second;
-    operands(First{});
-    __builtin_amdgcn_sched_barrier(0);
-    unpack(First{});
-    __builtin_amdgcn_sched_barrier(0);
-    operands(Second{});
-    products(First{});
-    unpack(Second{});
-    __builtin_amdgcn_sched_barrier(0);
-    products(Second{});
-    tk_v4f ac = zero, am = zero;
-    if constexpr (Q4 || Q5) {
-        tk_v4u xs = {0u, 0u, 0u, 0u};
-        if constexpr (NT > 8) {
-            xs[0] = *reinterpret_cast<const unsigned *>(sums + ((4 + g) * MR + n) * 4);
+    }
+    // the sub-block sums times centres and minima
+    __device__ __forceinline__ void centre()
+    {
+        if constexpr (Q4 || Q5) {
+            const uint8_t *const sums = a + tk_sums_at(NT);
+            tk_v4u xs = {0u, 0u, 0u, 0u};
+            if constexpr (NT > 8) {
+                xs[0] = *reinterpret_cast<const unsigned *>(sums + ((4 + g) * MR + n) * 4);
+                ac = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(tk_half8, xs), Bc, ac, 0, 0, 0);
+                am = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(tk_half8, xs), Bm, am, 0, 0, 0);
+            }
+            xs[0] = *reinterpret_cast<const unsigned *>(sums + (g * MR + (n & (MR - 1))) * 4);
             ac = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(tk_half8, xs), Bc, ac, 0, 0, 0);
             am = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(tk_half8, xs), Bm, am, 0, 0, 0);
         }
-        xs[0] = *reinterpret_cast<const unsigned *>(sums + (g * MR + (n & (MR - 1))) * 4);
-        ac = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(tk_half8, xs), Bc, ac, 0, 0, 0);
-        am = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(tk_half8, xs), Bm, am, 0, 0, 0);
     }
     // d s + (d ac - dmin am): the two in brackets are larger than their difference, the second's rounding is taken back
-    auto finish = [&](float v, float vc, float vm) __attribute__((always_inline)) {
+    __device__ __forceinline__ float scaled(float v, float vc, float vm) const
+    {
         const float p = __fmul_rn(dmin, vm), e = __fmaf_rn(dmin, vm, -p);
-        return fmaf(d, v, __fmaf_rn(d, vc, -p) - e);
-    };
-#pragma unroll
-    for (int i = 0; i < NY; ++i) {
-        float s;
+        return fmaf(Q4 ? d * 16384.f : d, v, __fmaf_rn(d, vc, -p) - e); // (Q4_K's products are 2^-14 of the sums: exact)
+    }
+    __device__ __forceinline__ void finish(float *y) const
+    {
+        const float *const inv = reinterpret_cast<const float *>(a + tk_inv_at(NT));
+        float iv[NY];
         if constexpr (NT <= 8) {
-            const float s0 = acc[0][2 * i] + acc[1][2 * i], s1 = acc[0][2 * i + 1] + acc[1][2 * i + 1];
-            s = s0 + s1;
-            if constexpr (Q6) s = fmaf(16.f, s, rem[2 * i] + rem[2 * i + 1]);
-            if constexpr (Q4 || Q5) s = finish(s, ac[2 * i] + ac[2 * i + 1], am[2 * i] + am[2 * i + 1]);
+            const float2 t = *reinterpret_cast<const float2 *>(inv + 2 * (g & (NT / 2 - 1)));
+            iv[0] = t.x; iv[1] = t.y;
         } else {
-            s = (acc[0][i] + acc[1][i]) + lo[i];
-            if constexpr (Q6) s = fmaf(16.f, s, rem[i]);
-            if constexpr (Q4 || Q5) s = finish(s, ac[i], am[i]);
+            const float4 t = *reinterpret_cast<const float4 *>(inv + 4 * g);
+            iv[0] = t.x; iv[1] = t.y; iv[2] = t.z; iv[3] = t.w;
         }
-        if constexpr (Q6) s *= d;
-        y[i] = fmaf(s, ODD && !H ? -iv[i] : iv[i], y[i]);
+#pragma unroll
+        for (int i = 0; i < NY; ++i) {
+            float s;
+            if constexpr (NT <= 8) {
+                const float s0 = acc[0][2 * i] + acc[1][2 * i], s1 = acc[0][2 * i + 1] + acc[1][2 * i + 1];
+                s = s0 + s1;
+                if constexpr (Q6) s = fmaf(16.f, s, rem[2 * i] + rem[2 * i + 1]);
+                if constexpr (Q4 || Q5) s = scaled(s, ac[2 * i] + ac[2 * i + 1], am[2 * i] + am[2 * i + 1]);
+            } else {
+                s = (acc[0][i] + acc[1][i]) + lo[i];
+                if constexpr (Q6) s = fmaf(16.f, s, rem[i]);
+                if constexpr (Q4 || Q5) s = scaled(s, ac[i], am[i]);
+            }
+            if constexpr (Q6) s *= d;
+            y[i] = fmaf(s, ODD && !H ? -iv[i] : iv[i], y[i]);
+        }
+    }
+};
+
+// Q8_0, whose scales multiply finished sums
+template <int NT>
+__device__ __forceinline__ void tk_mul_q8(const uint8_t *stage, int b, const uint8_t *a, int lane, float *y)
+{
+    constexpr int RS = TkFmt<PRIMA_FMT_Q8_0>::RS, SBS = TkFmt<PRIMA_FMT_Q8_0>::SBS;
+    constexpr int MR = NT <= 8 ? 2 * NT : 16, PS = NT <= 8 ? MR : 32, NY = NT <= 8 ? 2 : 4;
+    const int n = lane & 15, g = lane >> 4;
+    const uint8_t *row = stage + n * RS * 16;
+    const tk_v4f zero = {0.f, 0.f, 0.f, 0.f};
+    const unsigned e1024 = tk_vconst(0x64006400u);
+    auto a_at = [&](int c_static, int c_lane, int f_static, int f_lane, int part) __attribute__((always_inline)) {
+        const int m = ((n ^ f_lane) ^ f_static) & (MR - 1);
+        return *reinterpret_cast<const tk_half8 *>(a + (c_lane * PS + m) * 16 + (c_static * PS + part * 16) * 16);
+    };
+    const float *const inv = reinterpret_cast<const float *>(a + tk_inv_at(NT));
+    float iv[NY];
+    if constexpr (NT <= 8) {
+        const float2 t = *reinterpret_cast<const float2 *>(inv + 2 * (g & (NT / 2 - 1)));
+        iv[0] = t.x; iv[1] = t.y;
+    } else {
+        const float4 t = *reinterpret_cast<const float4 *>(inv + 4 * g);
+        iv[0] = t.x; iv[1] = t.y; iv[2] = t.z; iv[3] = t.w;
+    }
+    const tk_v4u dv = *reinterpret_cast<const tk_v4u *>(row + (16 * SBS + b) * 16);
+    float t[NY];
+#pragma unroll
+    for (int i = 0; i < NY; ++i) t[i] = 0.f;
+    const tk_half2 off = tk_both(static_cast<_Float16>(-1152.f));
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        const uint2 w = *reinterpret_cast<const uint2 *>(row + b * 256 + s * 32 + g * 8);
+        tk_half2 p[4];
+        tk_pairs(w.x ^ 0x80808080u, 0x00ff00ffu, e1024, p);
+        tk_pairs(w.y ^ 0x80808080u, 0x00ff00ffu, e1024, p + 2);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] = s & 1 ? -off - p[i] : p[i] + off;
+        const tk_half8 B = tk_join(p);
+        const float d = tk_h2f(s & 1 ? dv[s >> 1] >> 16 : dv[s >> 1]);
+        if constexpr (NT <= 8) {
+            const tk_v4f c = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_at(4 * s, g, 2 * s, g >> 1, 0), B, zero, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) t[i] = fmaf(s & 1 ? -d : d, c[2 * i] + c[2 * i + 1], t[i]);
+        } else {
+            tk_v4f c = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_at(4 * s, g, 2 * s, g >> 1, 1), B, zero, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_at(4 * s, g, 2 * s, g >> 1, 0), B, c, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) t[i] = fmaf(s & 1 ? -d : d, c[i], t[i]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NY; ++i) y[i] = fmaf(t[i], iv[i], y[i]);
+}
+
+// y[i] += the share of super-block b of the stage
+template <int FMT, int NT, bool ODD>
+__device__ __forceinline__ void tk_mul(const uint8_t *stage, int b, const uint8_t *a, int lane, float *y)
+{
+    if constexpr (FMT == PRIMA_FMT_Q8_0) {
+        tk_mul_q8<NT>(stage, b, a, lane, y);
+    } else {
+        TkSb<FMT, NT, ODD> s(stage, b, a, lane);
+        s.fetch();
+        s.template operands<0>();
+        s.template unpack<0>();
+        s.template operands<1>();
+        s.template products<0>();
+        s.template unpack<1>();
+        s.template products<1>();
+        s.centre();
+        s.finish(y);
+    }
+}
+
+// a matrix instruction, then some of the vector instructions that stand beside it, N times
+template <int N, int V>
+__device__ __forceinline__ void tk_interleave()
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// ... and of both super-blocks of a stage (a0, a1: their records), the second as its negative
+template <int FMT, int NT>
+__device__ __forceinline__ void tk_mul2(const uint8_t *stage, const uint8_t *a0, const uint8_t *a1, int lane, float *y)
+{
+    if constexpr (FMT == PRIMA_FMT_Q8_0) {
+        tk_mul_q8<NT>(stage, 0, a0, lane, y);
+        tk_mul_q8<NT>(stage, 1, a1, lane, y);
+    } else {
+        constexpr int M = (NT > 8 ? 8 : 4) * (FMT == PRIMA_FMT_Q6_K ? 2 : 1); // matrix instructions of a half
+        constexpr int V = (FMT == PRIMA_FMT_Q6_K ? 100 : (FMT == PRIMA_FMT_Q5_K ? 72 : 52)) / M;
+        TkSb<FMT, NT, false> s(stage, 0, a0, lane);
+        TkSb<FMT, NT, true> t(stage, 1, a1, lane);
+        s.fetch();
+        s.template operands<0>();
+        t.fetch();
+        s.template unpack<0>();
+        __builtin_amdgcn_sched_barrier(0);
+        s.template operands<1>();
+        s.template products<0>();
+        s.template unpack<1>();
+        tk_interleave<M, V>();
+        t.template operands<0>();
+        s.template products<1>();
+        t.template unpack<0>();
+        tk_interleave<M, V>();
+        s.centre();
+        t.template operands<1>();
+        t.template products<0>();
+        t.template unpack<1>();
+        tk_interleave<M, V>();
+        t.template products<1>();
+        s.finish(y);
+        t.centre();
+        t.finish(y);
     }
 }
 

@@ -133,8 +133,7 @@ __global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64) __attribute__((amdgpu_
             if constexpr (SBS == 1) {
                 mul(0, s, second);
             } else if (2 * s + 1 < nsb) {
-                mul(0, 2 * s, std::false_type{});
-                mul(1, 2 * s + 1, std::true_type{});
+                tk_mul2<FMT, NT>(l_stage, l_a + 2 * s * tk_rec(NT), l_a + (2 * s + 1) * tk_rec(NT), lane, y);
             } else {
                 mul(nb == 1 ? 0 : 1, 2 * s, std::false_type{});
             }
