@@ -24,6 +24,7 @@ struct AttnArgs {
     unsigned *err;        // raised when the merging workgroup's bounded wait gives up
     float *o;             // [T][Hq][D]
     int Hq, Hkv, kv_cap, n_past, T, nsplit, keys_per_split;
+    int merge_apart; // the key ranges' records are merged by a launch of its own
     // Batch of sequences (continuous batching, App. A.12: one token each): token b is the next token of a
     // sequence of its own, with its own caches and length.  Query group z of the grid then belongs to sequence
     // z / ceil(G / QG), and a workgroup works like a one-token call for that sequence.

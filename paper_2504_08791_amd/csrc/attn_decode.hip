@@ -369,7 +369,7 @@ __global__ void __launch_bounds__(ATT_THREADS, 4) attn_decode_kernel(AttnArgs a)
         }
         __hip_atomic_store(rec + REC_HDR + e, accv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (a.nsplit == 1 || split != 0) return;
+    if (a.nsplit == 1 || split != 0 || a.merge_apart) return;
 
     // ---- the workgroup of the first key range merges the ranges of its (KV head, query group) ----
     // o[t][h][:] = sum_i part_i.o * exp(m_i - M) / sum_i part_i.l * exp(m_i - M); a key range that held no
@@ -540,6 +540,53 @@ __global__ void __launch_bounds__(ATT_THREADS, 4) attn_decode_kernel(AttnArgs a)
     }
 }
 
+// The merge as a launch of its own: a wave per query, the same sums in the same order.  For a call on its own: without the wait inside
+// the launch its scratch need not be marked "not written" first, so this launch stands in the fill's place.
+template <int D>
+__global__ void __launch_bounds__(256) attn_merge_kernel(const float *__restrict__ part, float *__restrict__ o, int heads, int nsplit)
+{
+    constexpr int LPR = D / 4, RPI = 64 / LPR, MERGE_LD = 16;
+    const int lane = threadIdx.x & 63;
+    const int64_t head = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    if (head >= heads) return;
+    const int sub = lane / LPR, c4 = (lane % LPR) * 4;
+    const float *const rec0 = part + head * nsplit * (REC_HDR + D);
+    const float2 ml = *reinterpret_cast<const float2 *>(rec0 + min(lane, nsplit - 1) * (REC_HDR + D));
+    float wgt = 0.f;
+    v4f accq = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < nsplit; s0 += MERGE_LD * RPI) {
+        v4f v[MERGE_LD];
+#pragma unroll
+        for (int i = 0; i < MERGE_LD; ++i) // past the last range: the last again, not added
+            v[i] = *reinterpret_cast<const v4f *>(rec0 + min(s0 + i * RPI + sub, nsplit - 1) * (REC_HDR + D) + REC_HDR + c4);
+        if (s0 == 0) {
+            const float ms = lane < nsplit ? ml.x : -INFINITY;
+            const float ls = lane < nsplit ? ml.y : 0.f;
+            const float mm = wave_max(ms);
+            const float w = (ms == -INFINITY) ? 0.f : __expf(ms - mm);
+            const float ll = wave_sum(ls * w);
+            wgt = w / ll; // lanes past the last range carry weight 0
+        }
+#pragma unroll
+        for (int i = 0; i < MERGE_LD; ++i) {
+            const int r = s0 + i * RPI + sub;
+            const float ws = __shfl(wgt, min(r, 63), 64);
+            if (r < nsplit) {
+                accq[0] = fmaf(v[i][0], ws, accq[0]);
+                accq[1] = fmaf(v[i][1], ws, accq[1]);
+                accq[2] = fmaf(v[i][2], ws, accq[2]);
+                accq[3] = fmaf(v[i][3], ws, accq[3]);
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (RPI == 4) accq[k] = add_across_16(accq[k]);
+        accq[k] = add_across_32(accq[k]);
+    }
+    if (lane < LPR) *reinterpret_cast<float4 *>(o + head * D + c4) = make_float4(accq[0], accq[1], accq[2], accq[3]);
+}
+
 // key ranges for several tokens of one sequence: about one workgroup per compute unit
 static int tile_query_groups(const prima_dims &d, int T, bool batch)
 {
@@ -582,7 +629,7 @@ size_t attn_records_bytes(const prima_dims &d, int n_total, int T, bool batch)
 
 prima_status launch_attn(const prima_dims &d, const float *q, float *q_rot_out, const float *k_new, const float *v_new,
                             const float *rope_tab, __half *K, __half *V, int kv_cap, int n_past, int T, float *o,
-                            void *ws, hipStream_t st, const AttnSeqs *seq)
+                            void *ws, hipStream_t st, const AttnSeqs *seq, bool merge_apart)
 {
     AttnArgs a = build_attn_args(d, q, q_rot_out, k_new, v_new, rope_tab, K, V, kv_cap, n_past, T, o, ws, seq);
     int n_total = n_past + T;
@@ -592,7 +639,14 @@ prima_status launch_attn(const prima_dims &d, const float *q, float *q_rot_out, 
     }
     attn_ranges(d, n_total, T, seq != nullptr, a.keys_per_split, a.nsplit);
     const dim3 grid(a.nsplit, d.n_kv_heads, tile_query_groups(d, T, seq != nullptr));
-    return launch_attn_kernel(d, grid, a, st);
+    a.merge_apart = merge_apart ? 1 : 0;
+    const prima_status s = launch_attn_kernel(d, grid, a, st);
+    if (s != PRIMA_OK || !merge_apart || a.nsplit == 1) return s;
+    const int heads = T * d.n_q_heads;
+    const dim3 merge_grid((heads + 3) / 4);
+    if (d.head_dim == 128) hipLaunchKernelGGL(attn_merge_kernel<128>, merge_grid, dim3(256), 0, st, a.part, o, heads, a.nsplit);
+    else hipLaunchKernelGGL(attn_merge_kernel<64>, merge_grid, dim3(256), 0, st, a.part, o, heads, a.nsplit);
+    return last_launch_status();
 }
 
 // Attention for the tokens of a prompt whose rotated K and V rows are in the caches already and whose queries are

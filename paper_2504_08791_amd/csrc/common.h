@@ -158,7 +158,7 @@ size_t attn_records_bytes(const prima_dims &d, int n_total, int T, bool batch);
 struct AttnSeqs;
 prima_status launch_attn(const prima_dims &d, const float *q, float *q_rot_out, const float *k_new, const float *v_new,
                          const float *rope_tab, __half *K, __half *V, int kv_cap, int n_past, int T, float *o,
-                         void *ws, hipStream_t st, const AttnSeqs *seq = nullptr);
+                         void *ws, hipStream_t st, const AttnSeqs *seq = nullptr, bool merge_apart = false);
 
 // a prompt: rotated K / V rows already in the caches, q rotated; n_pieces pieces of PRIMA_MAX_TOK tokens in one launch
 prima_status launch_attn_prompt(const prima_dims &d, const float *q, __half *K, __half *V, int kv_cap, int n_past, int n_pieces,

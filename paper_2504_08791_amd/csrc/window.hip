@@ -753,13 +753,9 @@ prima_status prima_attn_decode(const prima_dims *d, const float *q, const void *
     if (T < 1 || T > PRIMA_MAX_TOK || n_past < 0 || kv_cap < 1 || static_cast<int64_t>(n_past) + T > kv_cap) return PRIMA_E_RANGE;
     if (!aligned(q, 16) || !aligned(o, 16) || !aligned(k_cache, 16) || !aligned(v_cache, 16) || !aligned(workspace, 256)) return PRIMA_E_ALIGN;
     if (workspace_bytes < attn_ws_bytes(*d, kv_cap, T)) return PRIMA_E_WORKSPACE;
-    // the give-up flag cleared, the records this launch uses marked "not written"
-    const prima_status s = launch_fill_words(workspace, attn_counter_bytes(*d, T), 0u, static_cast<char *>(workspace) + attn_counter_bytes(*d, T),
-                                             attn_records_bytes(*d, n_past + T, T, false), ATTN_REC_EMPTY, static_cast<hipStream_t>(hip_stream));
-    if (s != PRIMA_OK) return s;
     return launch_attn(*d, q, nullptr, nullptr, nullptr, nullptr,
                        static_cast<__half *>(const_cast<void *>(k_cache)), static_cast<__half *>(const_cast<void *>(v_cache)),
-                       kv_cap, n_past, T, o, workspace, static_cast<hipStream_t>(hip_stream));
+                       kv_cap, n_past, T, o, workspace, static_cast<hipStream_t>(hip_stream), nullptr, true);
 }
 
 size_t prima_fmt_tensor_bytes(int32_t fmt, int64_t n_rows, int64_t n_cols) { return fmt_tensor_bytes(fmt, n_rows, n_cols); }
