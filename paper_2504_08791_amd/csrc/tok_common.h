@@ -128,6 +128,86 @@ __device__ __forceinline__ void tk_split(const float (&v)[16], int i, int t, uin
     if (i == 0) reinterpret_cast<float *>(rec + tk_inv_at(NT))[t] = ldexpf(1.0f, -p);
 }
 
+// The same record by a whole wave, lane i columns 4 i .. 4 i + 3 in v, with the sub-block sums.  Two neighbouring lanes hold a piece's eight columns; they
+// exchange halves, so that the even lane stores the hi part's piece and the odd lane the lo part's.
+template <int CTRL>
+__device__ __forceinline__ unsigned tk_dpp(unsigned v) { return static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xf, 0xf, true)); }
+template <int CTRL>
+__device__ __forceinline__ float tk_dppf(float v) { return __builtin_bit_cast(float, tk_dpp<CTRL>(__builtin_bit_cast(unsigned, v))); }
+__device__ __forceinline__ float tk_sum8(float v) // over the eight lanes of a sub-block
+{
+    v += tk_dppf<0xB1>(v);         // its neighbour's
+    v += tk_dppf<0x4E>(v);         // the other pair's of the four
+    return v + tk_dppf<0x141>(v);  // the other four's
+}
+template <int NT, int ORD, bool INF>
+__device__ __forceinline__ void tk_split_wave(const float (&v)[4], int i, int t, uint8_t *rec)
+{
+    uint8_t *const a = rec, *const sums = rec + tk_sums_at(NT);
+    constexpr int MR = NT <= 8 ? 2 * NT : 16;
+    const float amax = wave_max(fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))));
+    int ex = 0;
+    if (amax > 0.f) frexpf(amax, &ex); // amax < 2^ex
+    int p = 10 - ex;
+    p = p > 126 ? 126 : (p < -120 ? -120 : p);
+    if constexpr (INF) p = amax > 3.40282347e38f ? -113 : p; // (see tk_split)
+    const float S = ldexpf(1.0f, p);
+    tk_half2 hh[2], ll[2];
+    float sum = 0.f, suml = 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        float sv = v[k] * S;
+        asm volatile("" : "+v"(sv));
+        const _Float16 h = static_cast<_Float16>(sv);
+        float r = sv - static_cast<float>(h);
+        if constexpr (INF) r = fmaxf(r, -1024.f);
+        const _Float16 l = static_cast<_Float16>(r);
+        hh[k >> 1][k & 1] = h;
+        ll[k >> 1][k & 1] = l;
+        sum += static_cast<float>(h);
+        suml += static_cast<float>(l);
+    }
+    const bool odd = i & 1;
+    unsigned w0[2], w1[2]; // columns 0..3 and 4..7 of the piece this lane stores
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const unsigned h = __builtin_bit_cast(unsigned, hh[k]), l = __builtin_bit_cast(unsigned, ll[k]);
+        const unsigned own = odd ? l : h, got = tk_dpp<0xB1>(odd ? h : l);
+        w0[k] = odd ? got : own;
+        w1[k] = odd ? own : got;
+    }
+    tk_v4u o;
+    if constexpr (ORD == 0) { // 0 4 1 5 2 6 3 7
+        o[0] = __builtin_amdgcn_perm(w1[0], w0[0], 0x05040100u);
+        o[1] = __builtin_amdgcn_perm(w1[0], w0[0], 0x07060302u);
+        o[2] = __builtin_amdgcn_perm(w1[1], w0[1], 0x05040100u);
+        o[3] = __builtin_amdgcn_perm(w1[1], w0[1], 0x07060302u);
+    } else { // 0 2 1 3 4 6 5 7
+        o[0] = __builtin_amdgcn_perm(w0[1], w0[0], 0x05040100u);
+        o[1] = __builtin_amdgcn_perm(w0[1], w0[0], 0x07060302u);
+        o[2] = __builtin_amdgcn_perm(w1[1], w1[0], 0x05040100u);
+        o[3] = __builtin_amdgcn_perm(w1[1], w1[0], 0x07060302u);
+    }
+    const int c = i >> 1, f = (c >> 1) & 15, part = i & 1;
+    if constexpr (NT <= 8) *reinterpret_cast<tk_v4u *>(a + (c * MR + (((2 * t + part) ^ f) & (MR - 1))) * 16) = o;
+    else *reinterpret_cast<tk_v4u *>(a + (c * 32 + part * 16 + ((t ^ f) & 15)) * 16) = o;
+    sum = tk_sum8(sum);
+    suml = tk_sum8(suml);
+    if ((i & 7) == 0) {
+        const int S8 = i >> 3;
+        const _Float16 sh = static_cast<_Float16>(sum + suml), sl = static_cast<_Float16>((sum - static_cast<float>(sh)) + suml);
+        _Float16 *q = reinterpret_cast<_Float16 *>(sums);
+        if constexpr (NT <= 8) {
+            q[((S8 & 3) * MR + 2 * t) * 2 + (S8 >> 2)] = sh;
+            q[((S8 & 3) * MR + 2 * t + 1) * 2 + (S8 >> 2)] = sl;
+        } else {
+            q[((S8 & 3) * 16 + t) * 2 + (S8 >> 2)] = sh;
+            q[((4 + (S8 & 3)) * 16 + t) * 2 + (S8 >> 2)] = sl;
+        }
+    }
+    if (i == 0) reinterpret_cast<float *>(rec + tk_inv_at(NT))[t] = ldexpf(1.0f, -p);
+}
+
 // ---- the weight stream of a wave --------------------------------------------------------------------------------------
 // A stage is 16 rows x SBS super-blocks: requested in runs along the rows into registers, written to the wave's LDS buffer (a
 // row's fields side by side, rows an odd number of 16-byte pieces apart) and read from there in operand order.

@@ -160,148 +160,119 @@ __global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64) __attribute__((amdgpu_
     }
 }
 
-// Sum over the shares of 16 consecutive rows (this lane's) of a token.  The shares come from other XCDs, a trip through memory
-// each: the four waves of a workgroup take every fourth share, up to four of them at a time, and wave 0 adds the waves' sums
-// in order (one wave adding two shares at a time took 5 to 8 us a launch).
+// What the launches between the streams have to do is little; they are chains of trips through memory (the shares come from other
+// XCDs).  So a wave takes 256 numbers of one token, four a lane, and everything that it will read is requested in front of the first use:
+// one trip.  (Four waves that took every fourth share and met in LDS, wave 0 going on to read the residual, the gains and the
+// sums of squares one after the other: 4.6 to 5.3 us a launch, 6.8 in front of the down projection; now 3 to 4.8.  16 sequences through
+// three 14B-shaped layers 365 -> 335 us.)
 constexpr int ADD_WAVES = 4;
-__device__ __forceinline__ void add_shares(const TokPart &p, int T, int t, int64_t row, int wave, float (&v)[16])
+typedef float tk_f4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ tk_f4 load_f4(const float *p) { return *reinterpret_cast<const tk_f4 *>(p); }
+
+// v, u: the sums over the shares of p, q (TWO), in order, of this lane's four rows of token t.  N: shares requested at a time
+template <int N, bool TWO>
+__device__ __forceinline__ void add_shares_n(const TokPart &p, const TokPart &q, int T, int t, int64_t row, tk_f4 &v, tk_f4 &u)
 {
+    const float *const sp = p.part + t * p.rows + p.row0 + row, *const sq = TWO ? q.part + t * q.rows + q.row0 + row : nullptr;
+    const int64_t dp = static_cast<int64_t>(T) * p.rows, dq = static_cast<int64_t>(T) * q.rows;
+    const int parts = TWO ? max(p.n_parts, q.n_parts) : p.n_parts;
+    for (int i = 0; i < parts; i += N) {
+        tk_f4 a[N], b[TWO ? N : 1];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = 0.f;
-    const float *s = p.part + t * p.rows + p.row0 + row;
-    const int64_t stride = static_cast<int64_t>(T) * p.rows;
-    for (int i = wave; i < p.n_parts; i += 4 * ADD_WAVES) {
-        float4 a[4][4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float *sj = s + min(i + j * ADD_WAVES, p.n_parts - 1) * stride; // (past the last: the last again, not added)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) a[j][k] = *reinterpret_cast<const float4 *>(sj + 4 * k);
+        for (int j = 0; j < N; ++j) { // (past the last share: the last again, not added)
+            a[j] = load_f4(sp + min(i + j, p.n_parts - 1) * dp);
+            if constexpr (TWO) b[j] = load_f4(sq + min(i + j, q.n_parts - 1) * dq);
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (i + j * ADD_WAVES < p.n_parts) {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) { v[4 * k] += a[j][k].x; v[4 * k + 1] += a[j][k].y; v[4 * k + 2] += a[j][k].z; v[4 * k + 3] += a[j][k].w; }
+        for (int j = 0; j < N; ++j) {
+            if (i + j < p.n_parts) v += a[j];
+            if constexpr (TWO) {
+                if (i + j < q.n_parts) u += b[j];
             }
         }
     }
 }
-// wave 0's v becomes the sum over the waves' (all threads; `buf`: 12 KiB of LDS)
-__device__ __forceinline__ void add_waves(float (&v)[16], int wave, int lane, float4 (*buf)[4][64])
+template <bool TWO>
+__device__ __forceinline__ void add_shares(const TokPart &p, const TokPart &q, int T, int t, int64_t row, tk_f4 &v, tk_f4 &u)
 {
-    if (wave != 0) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) buf[wave - 1][k][lane] = make_float4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
-    }
-    __syncthreads();
-    if (wave == 0) {
-#pragma unroll
-        for (int w = 0; w < ADD_WAVES - 1; ++w)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const float4 q = buf[w][k][lane];
-                v[4 * k] += q.x; v[4 * k + 1] += q.y; v[4 * k + 2] += q.z; v[4 * k + 3] += q.w;
-            }
-    }
+    const int parts = TWO ? max(p.n_parts, q.n_parts) : p.n_parts;
+    if (parts <= 4) add_shares_n<4, TWO>(p, q, T, t, row, v, u);
+    else if (parts <= 8) add_shares_n<8, TWO>(p, q, T, t, row, v, u);
+    else add_shares_n<16, TWO>(p, q, T, t, row, v, u);
 }
 
-// 1/rms of token t from the sums of squares of its super-blocks; sixteen lanes together (i: lane in the group)
-__device__ __forceinline__ float inv_rms(const TokNorm &nm, int nt, int t, int i)
+// this lane's part of the sums of squares of token t; then 1/rms from those of the wave
+__device__ __forceinline__ float squares_of(const TokNorm &nm, int nt, int t, int lane)
 {
-    float s = 0.f;
-    for (int b = i; b < nm.nb; b += 16) s += nm.ss[b * nt + t];
-    return 1.0f / sqrtf(row_sum16(s) / (static_cast<float>(nm.nb) * 256.f) + nm.eps);
+    float s = lane < nm.nb ? nm.ss[lane * nt + t] : 0.f;
+    if (nm.nb > 64)
+        for (int b = lane + 64; b < nm.nb; b += 64) s += nm.ss[b * nt + t];
+    return s;
+}
+__device__ __forceinline__ float inv_rms(const TokNorm &nm, float squares)
+{
+    return 1.0f / sqrtf(wave_sum(squares) / (static_cast<float>(nm.nb) * 256.f) + nm.eps);
 }
 
-// Four (token, super-block) pairs a workgroup, one per 16 lanes.  Token slots past T: zeros.
+// A (token, super-block) pair a wave.  Token slots past T: zeros.
 template <int NT>
 __global__ void __launch_bounds__(64 * ADD_WAVES) tok_prepare_kernel(TokPrepare a)
 {
-    __shared__ float4 buf[2][ADD_WAVES - 1][4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15;
-    const int pi = blockIdx.x * 4 + (lane >> 4), t = pi & (NT - 1), b = pi / NT; // (pairs: a multiple of four)
-    const int64_t col = static_cast<int64_t>(b) * 256 + n * 16, K = static_cast<int64_t>(a.nb) * 256;
-    const int ts = min(t, a.T - 1); // (a slot past the last token reads the last)
-    float v[16], u[16];
-    if (a.mode != TOK_PLAIN) {
-        add_shares(a.p[0], a.T, ts, col, wave, v);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int pi = blockIdx.x * ADD_WAVES + wave, t = pi & (NT - 1), b = pi / NT; // (pairs: a multiple of four)
+    const int64_t col = static_cast<int64_t>(b) * 256 + lane * 4, K = static_cast<int64_t>(a.nb) * 256;
+    tk_f4 v = {0.f, 0.f, 0.f, 0.f};
+    if (t < a.T) {
+        const tk_f4 one = {1.f, 1.f, 1.f, 1.f};
+        const tk_f4 gain = a.gain ? load_f4(a.gain + col) : one;
         if (a.mode == TOK_SWIGLU) {
-            add_shares(a.p[1], a.T, ts, col, wave, u);
-            add_waves(u, wave, lane, buf[1]);
+            const float squares = squares_of(a.norm, NT, t, lane);
+            tk_f4 u = v;
+            add_shares<true>(a.p[0], a.p[1], a.T, t, col, v, u);
+            const float ir = inv_rms(a.norm, squares);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float gt = v[k] * ir;
+                v[k] = gt / (1.0f + expf(-gt)) * (u[k] * ir);
+            }
+        } else { // the vector itself, or the residual of the sums
+            const tk_f4 x = load_f4(a.x + t * K + col);
+            if (a.mode != TOK_PLAIN) add_shares<false>(a.p[0], a.p[0], a.T, t, col, v, v);
+            v += x;
         }
-        add_waves(v, wave, lane, buf[0]);
-    }
-    if (wave != 0) return;
-    if (a.mode == TOK_SWIGLU) {
-        const float ir = inv_rms(a.norm, NT, ts, n);
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const float gt = v[k] * ir;
-            v[k] = gt / (1.0f + expf(-gt)) * (u[k] * ir);
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) { // the vector itself, or the residual of the sums
-            const float4 q = *reinterpret_cast<const float4 *>(a.x + ts * K + col + 4 * k);
-            const float r[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[4 * k + e] = a.mode == TOK_PLAIN ? r[e] : v[4 * k + e] + r[e];
-        }
-    }
-    if (t >= a.T) {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) v[k] = 0.f;
-    } else if (a.out) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) *reinterpret_cast<float4 *>(a.out + t * K + col + 4 * k) = make_float4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
-    }
-    if (a.gain) {
-        float ss = 0.f;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) ss += v[k] * v[k];
-        ss = row_sum16(ss);
-        if (n == 0) a.ss[b * NT + t] = ss;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float4 q = *reinterpret_cast<const float4 *>(a.gain + col + 4 * k);
-            v[4 * k] *= q.x; v[4 * k + 1] *= q.y; v[4 * k + 2] *= q.z; v[4 * k + 3] *= q.w;
+        if (a.out) *reinterpret_cast<tk_f4 *>(a.out + t * K + col) = v;
+        if (a.gain) {
+            const float ss = wave_sum(v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3]);
+            if (lane == 0) a.ss[b * NT + t] = ss;
+            v *= gain;
         }
     }
-    if (a.rec[0]) tk_split<NT, 0, false, true>(v, n, t, a.rec[0] + static_cast<int64_t>(b) * tk_rec(NT));
-    if (a.rec[1]) tk_split<NT, 1, true, true>(v, n, t, a.rec[1] + static_cast<int64_t>(b) * tk_rec(NT));
+    const float o[4] = {v[0], v[1], v[2], v[3]};
+    if (a.rec[0]) tk_split_wave<NT, 0, false>(o, lane, t, a.rec[0] + static_cast<int64_t>(b) * tk_rec(NT));
+    if (a.rec[1]) tk_split_wave<NT, 1, true>(o, lane, t, a.rec[1] + static_cast<int64_t>(b) * tk_rec(NT));
 }
 
-// y[t][row] = 1/rms * sum of the shares (+ residual) of up to three vectors of their own lengths, 256 rows per 16 lanes
+// y[t][row] = 1/rms * sum of the shares (+ residual) of up to three vectors of their own lengths, 256 rows a wave
 __global__ void __launch_bounds__(64 * ADD_WAVES) tok_sum_kernel(TokSum a)
 {
-    __shared__ float4 buf[ADD_WAVES - 1][4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int t = blockIdx.y;
-    int64_t row = (static_cast<int64_t>(blockIdx.x) * 4 + (lane >> 4)) * 256 + n * 16;
+    int64_t first = (static_cast<int64_t>(blockIdx.x) * ADD_WAVES + wave) * 256;
     int i = 0;
-    while (i < a.n && row >= (a.rows[i] + 255) / 256 * 256) { row -= (a.rows[i] + 255) / 256 * 256; ++i; }
-    const bool mine = i < a.n && row < a.rows[i < 3 ? i : 2]; // (rows are a multiple of 16)
-    const int j = mine ? i : 0;
-    const TokPart p = j == 0 ? a.p[0] : (j == 1 ? a.p[1] : a.p[2]);
-    const int64_t rows = j == 0 ? a.rows[0] : (j == 1 ? a.rows[1] : a.rows[2]);
-    float *const y = j == 0 ? a.y[0] : (j == 1 ? a.y[1] : a.y[2]);
-    if (!mine) row = 0; // (a valid address, not stored)
-    float v[16];
-    add_shares(p, a.T, t, row, wave, v);
-    add_waves(v, wave, lane, buf);
-    if (wave != 0) return;
-    const float ir = a.norm.ss ? inv_rms(a.norm, a.nt, t, n) : 1.f;
-    if (!mine) return;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        float4 o = make_float4(v[4 * k] * ir, v[4 * k + 1] * ir, v[4 * k + 2] * ir, v[4 * k + 3] * ir);
-        if (a.resid) {
-            const float4 q = *reinterpret_cast<const float4 *>(a.resid + t * rows + row + 4 * k);
-            o.x += q.x; o.y += q.y; o.z += q.z; o.w += q.w;
-        }
-        *reinterpret_cast<float4 *>(y + t * rows + row + 4 * k) = o;
-    }
+    while (i < a.n && first >= (a.rows[i] + 255) / 256 * 256) { first -= (a.rows[i] + 255) / 256 * 256; ++i; }
+    if (i >= a.n) return;
+    const TokPart &p = i == 0 ? a.p[0] : (i == 1 ? a.p[1] : a.p[2]);
+    const int64_t rows = i == 0 ? a.rows[0] : (i == 1 ? a.rows[1] : a.rows[2]);
+    float *const y = i == 0 ? a.y[0] : (i == 1 ? a.y[1] : a.y[2]);
+    const bool mine = first + lane * 4 < rows; // (rows are a multiple of 16)
+    const int64_t row = mine ? first + lane * 4 : 0; // (else a valid address, not stored)
+    tk_f4 v = {0.f, 0.f, 0.f, 0.f}, r = v;
+    float squares = 0.f;
+    if (a.norm.ss) squares = squares_of(a.norm, a.nt, t, lane);
+    if (a.resid) r = load_f4(a.resid + t * rows + row);
+    add_shares<false>(p, p, a.T, t, row, v, v);
+    const float ir = a.norm.ss ? inv_rms(a.norm, squares) : 1.f;
+    if (mine) *reinterpret_cast<tk_f4 *>(y + t * rows + row) = v * ir + r;
 }
 
 struct StreamPlan {

@@ -373,3 +373,21 @@ def test_activations_that_are_not_finite_and_tiny_ones(gpu_lib, fmt, T):
     if fmt in ("q8_0", "f16"):
         apart = torch.cat([gpu_lib.fmt_gemv(fmt, W, rows, cols, bad[t:t + 1].contiguous()) for t in range(2, 6)])
         assert torch.equal(torch.nan_to_num(got[2:6], 7.0, 8.0, -8.0), torch.nan_to_num(apart, 7.0, 8.0, -8.0))
+
+
+@pytest.mark.parametrize("T", [5, 9, 16])
+def test_streams_between_launches(gpu_lib, T):
+    """The launches that add the streams' shares: rows of more than 64 super-blocks (their sums of squares take a wave twice), 16 and more
+    shares of a short matrix, vectors of 64 rows (a wave's 256 end inside), shares of two formats for gate and up."""
+    from workloads.configs import ModelDims, WindowConfig
+    d = ModelDims(16640, 4, 1, 64, 768, 1e4)
+    fm = [{"wq": "q8_0", "wk": "q5_k", "wv": "q5_k", "wo": "q6_k", "wgate": "q5_k", "wup": "q6_k", "wdown": "q6_k"}, {}]
+    n_past = 70
+    host = [synth.layer_tensors(WindowConfig("rows", 78, d, 2, T, n_past), l, kv_cap=n_past + T, formats=fm[l]) for l in range(2)]
+    x = np.random.default_rng(T).standard_normal((T, d.e)).astype(np.float32)
+    dev = [{k: _dev(v) for k, v in t.items()} for t in host]
+    ref = oracle.window(d, host, x.astype(np.float64), n_past, formats=fm)
+    win = gpu_lib.Window(d, dev, n_past + T, T_max=T, formats=fm)
+    win.workspace.fill_(0xFF)
+    y = win.decode(_dev(x), n_past).cpu().numpy()
+    check_hidden(f"launches between streams, T={T}", rel_err(y, ref), d, host, x.astype(np.float64), n_past, formats=fm, eps=EPS_FP32)
