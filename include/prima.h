@@ -82,7 +82,7 @@ typedef struct {
  * W: Q4_K, n_rows x n_cols, n_cols % 256 == 0.  x: fp32, ldx >= n_cols, ldx % 4 == 0.  y: fp32,
  * ldy >= n_rows; y must not overlap x.
  * Activations enter as block fixed point of 31 bits and are summed exactly; in tall matrices at 9 to 16 tokens (as in
- * windows and batches of 9 to 16, and in several tokens of the other formats) as the sum of two binary16 numbers (22 bits,
+ * windows and batches of several, and in several tokens of the other formats) as the sum of two binary16 numbers (22 bits,
  * under a power of two per token and 256 columns) with fp32 sums on the matrix cores.  The 2-norm error against 64 bits is
  * 1.3 to 2.1e-7 of the result either way, the smaller with the latter (with weights far from mean zero 0.7 to 1.0e-7 and
  * 1.0 to 1.2e-7).
@@ -157,9 +157,9 @@ size_t prima_attn_workspace_bytes(const prima_dims *d, int32_t kv_cap, int32_t T
  * layers: HOST array of L descriptors.  x_in, x_out: fp32 [T][e]; x_out may alias x_in.
  * The library keeps no position state: the caller advances n_past (by fewer than T after a
  * rejection; stale rows are overwritten by the next step, never read).
- * From 9 tokens on the weights are streamed once for all tokens and the activations enter the projections as for the tall
- * matrices of prima_q4k_gemv; behind fewer than 64 cached rows a step of 9 to 16 tokens streams them twice and keeps the
- * arithmetic of fewer tokens (its results are those of earlier versions bit for bit).
+ * From several tokens on (3 to 9, by the hidden size and the formats) the activations enter the projections as for the tall
+ * matrices of prima_q4k_gemv; behind fewer than 64 cached rows a step of any number keeps the arithmetic of one token (and
+ * one of 9 to 16 streams the weights twice).
  * workspace >= prima_workspace_bytes(d, kv_cap, T), 256-byte aligned.
  */
 prima_status prima_layer_window_decode(const prima_dims *d, const prima_layer *layers, int32_t L,

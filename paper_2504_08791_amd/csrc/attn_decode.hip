@@ -17,9 +17,13 @@
 //  * RoPE + KV append fused: a workgroup whose key range holds new rows builds them once from the projection
 //    output (rotate k, round k and v to fp16, nearest even), keeps them in LDS (they replace what the tile
 //    loads brought from the cache) and stores them to the cache on the side: no store-to-load round trip.
-//  * Waves meet in LDS, key ranges in global memory: every workgroup writes its record (max, sum, D columns) per query
-//    with device-scope stores, and the workgroup of the first key range merges them.  It does not wait for an
-//    arrival count (a store acknowledgement, an atomic and two dependent loads: four trips through global memory):
+//  * Waves meet in LDS, key ranges in global memory: every workgroup writes its record (max, sum, D columns) per query,
+//    and the next launch merges them: attn_merge_kernel, or in a window of several tokens the launch that lays out the
+//    output projection's activations.  (The merge inside the launch, below, costs its records' trip to memory and back while the device
+//    waits, and a fill of the records in front: 4 tokens behind 4096 rows, 40 / 8 heads, 18.3 us a launch with it, 12 without.  70B
+//    shape, one token, three layers: 335 -> 331 us; 32B, four tokens through the streams, four layers: 467 -> 449.)
+//  * The last T mod 16 tokens of a prompt still have them merged inside: the workgroup of the first key range merges
+//    them.  It does not wait for an arrival count (a store acknowledgement, an atomic and two dependent loads: four trips through global memory):
 //    the records say themselves whether they are complete.  Before a launch every word of a record holds a NaN
 //    pattern that no arithmetic produces; the merging workgroup requests (max, sum) and the columns of all ranges
 //    in one go and repeats the request until no word shows the pattern (the ranges finish together, so the first or
@@ -40,7 +44,7 @@ size_t attn_counter_bytes(const prima_dims &d, int T)
 }
 
 // a key range's record for one query: max, sum, two unused words (the columns start 16-byte aligned), D columns
-constexpr int REC_HDR = 4;
+constexpr int REC_HDR = ATTN_REC_HDR;
 
 size_t attn_ws_bytes(const prima_dims &d, int, int T)
 {
@@ -540,8 +544,8 @@ __global__ void __launch_bounds__(ATT_THREADS, 4) attn_decode_kernel(AttnArgs a)
     }
 }
 
-// The merge as a launch of its own: a wave per query, the same sums in the same order.  For a call on its own: without the wait inside
-// the launch its scratch need not be marked "not written" first, so this launch stands in the fill's place.
+// The merge as a launch of its own: a wave per query, the same sums in the same order.  Without the wait inside the launch the scratch need
+// not be marked "not written" first.
 template <int D>
 __global__ void __launch_bounds__(256) attn_merge_kernel(const float *__restrict__ part, float *__restrict__ o, int heads, int nsplit)
 {
@@ -597,10 +601,12 @@ static int tile_query_groups(const prima_dims &d, int T, bool batch)
 static int tile_num_splits(const prima_dims &d, int n_total, int T, bool batch)
 {
     const int wgs = d.n_kv_heads * tile_query_groups(d, T, batch);
-    // at least two 16-key tiles per wave: every key range costs a record, an arrival and a share of the merge
-    // (4096 rows, one token: 16 ranges 14.8 us, 32 ranges 16.0 us, 8 ranges 16.8 us)
-    const int by_len = n_total / (32 * ATT_WAVES); // (rounded down: 4097 rows are 16 ranges of 257, not 16 of 256 and one of 1)
-    const int by_grid = (256 + wgs - 1) / wgs; // measured: 128, 192 and 384 workgroups are slower
+    // At least one 16-key tile per wave.  (Two while the merge sat inside the launch and a range cost an arrival: 4096 rows, one token, 16
+    // ranges 14.8 us, 32 16.0.  Now an 8B layer behind 512 rows 55.6 us with two, 54.2 with one; longer contexts are cut by the grid.)
+    const int by_len = n_total / (16 * ATT_WAVES); // (rounded down: no range of a few rows)
+    // About one workgroup per compute unit (128 and 192 are slower; 512 with the merge apart: 30001 rows, one token 24.4 -> 27.0 us, 70B shape, 8
+    // tokens behind 8192, two layers 321.5 -> 329.8, 16 sequences, three 14B layers 338 -> 348)
+    const int by_grid = (256 + wgs - 1) / wgs;
     int ns = by_len < by_grid ? by_len : by_grid;
     if (ns < 1) ns = 1;
     if (ns > MAX_SPLITS) ns = MAX_SPLITS;
@@ -629,24 +635,24 @@ size_t attn_records_bytes(const prima_dims &d, int n_total, int T, bool batch)
 
 prima_status launch_attn(const prima_dims &d, const float *q, float *q_rot_out, const float *k_new, const float *v_new,
                             const float *rope_tab, __half *K, __half *V, int kv_cap, int n_past, int T, float *o,
-                            void *ws, hipStream_t st, const AttnSeqs *seq, bool merge_apart)
+                            void *ws, hipStream_t st, const AttnSeqs *seq, AttnMerge merge)
 {
     AttnArgs a = build_attn_args(d, q, q_rot_out, k_new, v_new, rope_tab, K, V, kv_cap, n_past, T, o, ws, seq);
-    int n_total = n_past + T;
-    if (seq) { // the longest sequence sets the key ranges
-        n_total = 0;
-        for (int b = 0; b < T; ++b) n_total = seq->n_past[b] + 1 > n_total ? seq->n_past[b] + 1 : n_total;
-    }
-    attn_ranges(d, n_total, T, seq != nullptr, a.keys_per_split, a.nsplit);
     const dim3 grid(a.nsplit, d.n_kv_heads, tile_query_groups(d, T, seq != nullptr));
-    a.merge_apart = merge_apart ? 1 : 0;
+    a.merge_apart = merge != ATTN_MERGE_INSIDE;
     const prima_status s = launch_attn_kernel(d, grid, a, st);
-    if (s != PRIMA_OK || !merge_apart || a.nsplit == 1) return s;
+    if (s != PRIMA_OK || merge != ATTN_MERGE_APART || a.nsplit == 1) return s;
     const int heads = T * d.n_q_heads;
     const dim3 merge_grid((heads + 3) / 4);
     if (d.head_dim == 128) hipLaunchKernelGGL(attn_merge_kernel<128>, merge_grid, dim3(256), 0, st, a.part, o, heads, a.nsplit);
     else hipLaunchKernelGGL(attn_merge_kernel<64>, merge_grid, dim3(256), 0, st, a.part, o, heads, a.nsplit);
     return last_launch_status();
+}
+
+AttnRecords attn_records(const prima_dims &d, int n_past, int T, void *ws, const AttnSeqs *seq)
+{
+    const AttnArgs a = build_attn_args(d, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, n_past, T, nullptr, ws, seq);
+    return AttnRecords{a.part, a.nsplit};
 }
 
 // Attention for the tokens of a prompt whose rotated K and V rows are in the caches already and whose queries are

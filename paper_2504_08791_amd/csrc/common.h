@@ -155,10 +155,20 @@ size_t attn_records_bytes(const prima_dims &d, int n_total, int T, bool batch);
 // appends k_new / v_new to the caches; otherwise q is used as is and the caches are complete.
 // seq: null, or (a batch of T sequences, one token each) per token its sequence's caches and length; K, V and
 // n_past are then not used.
+// merge: by the workgroup of the first key range inside the launch (the records must be "not written" before); by a launch of its own; or
+// by the caller's next one (tok_prepare_kernel), which finds them with attn_records() (nsplit 1: none, o is complete).
 struct AttnSeqs;
+enum AttnMerge { ATTN_MERGE_INSIDE = 0, ATTN_MERGE_APART = 1, ATTN_MERGE_LATER = 2 };
+constexpr int ATTN_REC_HDR = 4; // a record: (max, sum, -, -), o[D]
+struct AttnRecords {
+    const float *part; // [T][Hq][nsplit][ATTN_REC_HDR + D]
+    int nsplit;
+};
 prima_status launch_attn(const prima_dims &d, const float *q, float *q_rot_out, const float *k_new, const float *v_new,
                          const float *rope_tab, __half *K, __half *V, int kv_cap, int n_past, int T, float *o,
-                         void *ws, hipStream_t st, const AttnSeqs *seq = nullptr, bool merge_apart = false);
+                         void *ws, hipStream_t st, const AttnSeqs *seq = nullptr, AttnMerge merge = ATTN_MERGE_INSIDE);
+// where that launch's records lie
+AttnRecords attn_records(const prima_dims &d, int n_past, int T, void *ws, const AttnSeqs *seq);
 
 // a prompt: rotated K / V rows already in the caches, q rotated; n_pieces pieces of PRIMA_MAX_TOK tokens in one launch
 prima_status launch_attn_prompt(const prima_dims &d, const float *q, __half *K, __half *V, int kv_cap, int n_past, int n_pieces,

@@ -1,4 +1,4 @@
-// Launchers of the projections of a window of 4 to 16 tokens (tok_stream.hip): the other formats' matrices, from 9 tokens on Q4_K too.
+// Launchers of the projections of a window of several tokens (tok_stream.hip).
 #pragma once
 #include "common.h"
 
@@ -20,12 +20,14 @@ struct TokMat {
     int64_t n_rows; // a multiple of 16
 };
 
-enum { TOK_PLAIN = 0, TOK_RESIDUAL = 1, TOK_SWIGLU = 2 };
+enum { TOK_PLAIN = 0, TOK_RESIDUAL = 1, TOK_SWIGLU = 2, TOK_ATTENTION = 3 };
 struct TokPrepare {
     int mode, T, nb;  // v: [T][256 nb]
     const float *x;   // TOK_PLAIN: v; TOK_RESIDUAL: added to the shares of p[0]
     TokPart p[2];     // TOK_SWIGLU: silu(gate / rms) * up / rms of p[0] (gate), p[1] (up)
     TokNorm norm;     // TOK_SWIGLU
+    AttnRecords att;  // TOK_ATTENTION: v from the key ranges' records of heads of D columns
+    int D;
     float *out;       // v stored (null: not); may be x
     const float *gain; // null: none; else ss gets the sums of squares of v, and v * gain is laid out
     float *ss;

@@ -1,5 +1,5 @@
-// The projections of a layer window for 9 to 16 tokens (speculative verification, batches of sequences), and for 4 to 8 those in other
-// formats than Q4_K: mat-vecs on the matrix
+// The projections of a layer window for several tokens (speculative verification, batches of sequences; from how many on: tok_from() in
+// window.hip), and of narrow windows of 4 to 8 tokens those in other formats than Q4_K: mat-vecs on the matrix
 // cores over activations that are prepared once per projection, with the sums finished by the kernel that prepares the next
 // one.  Arithmetic and layouts: tok_common.h.
 //
@@ -7,8 +7,8 @@
 //                       waves' stage buffers; a workgroup copies its slab's records (one pass over L2, no arithmetic) and
 //                       its waves stream (tile, part of the slab) units.  A unit's sums go to global memory, nothing meets
 //                       inside the launch: no barrier behind the first, no arrival counts, no waiting.
-//   tok_prepare_kernel  adds the shares of K in a fixed order, finishes them (residual, or 1/rms and SwiGLU), stores the vector
-//                       where it is needed and lays it out as the next projection's activations (gain applied; its sums of
+//   tok_prepare_kernel  adds the shares of K in a fixed order, finishes them (residual, or 1/rms and SwiGLU; attention's key ranges are
+//                       merged there too), stores the vector where it is needed and lays it out as the next projection's activations (gain applied; its sums of
 //                       squares beside it: 1/rms multiplies the finished sums of the next projection).
 //   tok_sum_kernel      adds the shares where plain vectors are wanted (Q, K, V; the window's output).
 //
@@ -17,9 +17,10 @@
 // down 44 -> 25 (adding and preparing included); the batch step of three layers 586 -> 380.  What bounds the stream at 16
 // tokens: 27648 x 5120 (80 MB, 12 us at the rate of a linear read) takes 30 us, 21 without its products, 31 without its
 // loads: the LDS reads of the operands (17 KB a super-block and wave) and the unpacking under two waves a SIMD.
-// From four tokens on the other formats' matrices of a window come here too (prepared, streamed and added each group for itself).
-// Up to eight tokens the Q4_K kernel stays the better one (start / this, us: four layers of a 32B shape at 4 tokens 457 / 523, two of a 70B
-// shape at 8 364 / 379): the launches between the streams cost 4 to 5 us each and the streams gain less than that.
+// At 3 to 8 tokens the stream alone, products left out, takes 52 of the 59 us of 57344 x 8192 at 8 tokens (5.0 TB/s; 34 of 37 of 55296 x 5120 at 4):
+// it stands at what ordinary loads of short runs reach, with about 5 us of fixed parts a launch.  Twelve waves (three a SIMD) for
+// Q4_K and Q5_K: 2 to 5 % slower; non-temporal loads of Q4_K: 6 % slower (a row's run of a stage is 288 bytes, and the
+// lines that straddle two stages are fetched twice); the waves' walks along K begun at different stages: no change.
 #include <algorithm>
 #include <atomic>
 
@@ -214,6 +215,40 @@ __device__ __forceinline__ float inv_rms(const TokNorm &nm, float squares)
     return 1.0f / sqrtf(wave_sum(squares) / (static_cast<float>(nm.nb) * 256.f) + nm.eps);
 }
 
+// Attention's key ranges merged, this lane's four columns of its head (heads: 64 or 128 columns, so several in a wave):
+// o = sum_i o_i exp(m_i - M) / sum_i l_i exp(m_i - M); a range without a visible key has (max, sum) = (-inf, 0).  N ranges at a time
+template <int N>
+__device__ __forceinline__ tk_f4 merge_records(const float *rec, int nsplit, int64_t stride, int c)
+{
+    float M = -INFINITY, L = 0.f;
+    tk_f4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < nsplit; s0 += N) {
+        tk_f4 o[N];
+        float2 ml[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) { // (past the last range: the last again, with weight 0)
+            const float *r = rec + min(s0 + i, nsplit - 1) * stride;
+            ml[i] = *reinterpret_cast<const float2 *>(r);
+            o[i] = load_f4(r + ATTN_REC_HDR + c);
+        }
+        float m = M;
+#pragma unroll
+        for (int i = 0; i < N; ++i) m = fmaxf(m, ml[i].x);
+        const float keep = M == -INFINITY ? 0.f : __expf(M - m);
+        acc *= keep;
+        L *= keep;
+        M = m;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const float w = s0 + i >= nsplit || ml[i].x == -INFINITY ? 0.f : __expf(ml[i].x - m);
+            L = fmaf(ml[i].y, w, L);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[k] = fmaf(o[i][k], w, acc[k]);
+        }
+    }
+    return acc * (1.0f / L);
+}
+
 // A (token, super-block) pair a wave.  Token slots past T: zeros.
 template <int NT>
 __global__ void __launch_bounds__(64 * ADD_WAVES) tok_prepare_kernel(TokPrepare a)
@@ -235,6 +270,13 @@ __global__ void __launch_bounds__(64 * ADD_WAVES) tok_prepare_kernel(TokPrepare 
                 const float gt = v[k] * ir;
                 v[k] = gt / (1.0f + expf(-gt)) * (u[k] * ir);
             }
+        } else if (a.mode == TOK_ATTENTION) {
+            const int head = static_cast<int>(col) / a.D, c = static_cast<int>(col) - head * a.D;
+            const int64_t stride = ATTN_REC_HDR + a.D;
+            const float *rec = a.att.part + (t * (K / a.D) + head) * a.att.nsplit * stride;
+            if (a.att.nsplit <= 4) v = merge_records<4>(rec, a.att.nsplit, stride, c);
+            else if (a.att.nsplit <= 8) v = merge_records<8>(rec, a.att.nsplit, stride, c);
+            else v = merge_records<16>(rec, a.att.nsplit, stride, c);
         } else { // the vector itself, or the residual of the sums
             const tk_f4 x = load_f4(a.x + t * K + col);
             if (a.mode != TOK_PLAIN) add_shares<false>(a.p[0], a.p[0], a.T, t, col, v, v);
@@ -337,20 +379,16 @@ prima_status launch_nt(StreamArgs &a, const StreamPlan &p, hipStream_t st)
 template <int FMT>
 prima_status launch_fmt(StreamArgs &a, size_t part_floats, int &n_parts, bool plan_only, hipStream_t st)
 {
-    const int nt = tk_slots(a.T);
+    const int nt = tok_slots(a.T);
     const StreamPlan p = plan_stream<FMT>(a.n_tiles, a.nb, nt);
-    if (p.n_slabs == 0 || nt < (FMT == PRIMA_FMT_Q4_K ? 16 : 4)) return PRIMA_E_SHAPE;
+    if (p.n_slabs == 0 || nt < 4) return PRIMA_E_SHAPE;
     a.n_slabs = p.n_slabs; a.slab = p.slab; a.ks_shift = p.ks_shift; a.rounds = p.rounds;
     a.per_round = (a.n_tiles + p.rounds - 1) / p.rounds;
     n_parts = p.n_slabs << p.ks_shift;
     if (static_cast<size_t>(n_parts) * a.T * a.n_tiles * 16 > part_floats) return PRIMA_E_WORKSPACE;
     if (plan_only) return p.lds > TK_LDS ? PRIMA_E_SHAPE : PRIMA_OK;
     if (nt == 16) return launch_nt<FMT, 16>(a, p, st);
-    if constexpr (FMT != PRIMA_FMT_Q4_K) { // (Q4_K: windows of 9 to 16 tokens only, see window.hip)
-        if (nt == 4) return launch_nt<FMT, 4>(a, p, st);
-        if (nt == 8) return launch_nt<FMT, 8>(a, p, st);
-    }
-    return PRIMA_E_SHAPE;
+    return nt == 8 ? launch_nt<FMT, 8>(a, p, st) : launch_nt<FMT, 4>(a, p, st);
 }
 
 prima_status launch_any(int fmt, StreamArgs &a, size_t part_floats, int &n_parts, bool plan_only, hipStream_t st)
@@ -373,13 +411,13 @@ int tok_max_parts(int nb, int nt, int64_t n_rows)
     const int least = most_slabs(nb, nt);
     return n_rows > 12288 ? std::max(8, least) : std::max(16, 2 * least);
 }
-size_t tok_rec_bytes(int64_t n_cols, int T) { return static_cast<size_t>(n_cols / QK) * tk_rec(tk_slots(T)); }
+size_t tok_rec_bytes(int64_t n_cols, int T) { return static_cast<size_t>(n_cols / QK) * tk_rec(tok_slots(T)); }
 size_t tok_part_floats(int64_t n_rows, int64_t n_cols, int T)
 {
-    return static_cast<size_t>(tok_max_parts(static_cast<int>(n_cols / QK), tk_slots(T), n_rows)) * T * static_cast<size_t>(n_rows);
+    return static_cast<size_t>(tok_max_parts(static_cast<int>(n_cols / QK), tok_slots(T), n_rows)) * T * static_cast<size_t>(n_rows);
 }
-size_t tok_ss_bytes(int64_t n_cols, int T) { return static_cast<size_t>(n_cols / QK) * tk_slots(T) * sizeof(float); }
-int tok_slots(int T) { return tk_slots(T); }
+size_t tok_ss_bytes(int64_t n_cols, int T) { return static_cast<size_t>(n_cols / QK) * tok_slots(T) * sizeof(float); }
+int tok_slots(int T) { return std::max(4, tk_slots(T)); }
 
 prima_status tok_stream_plan_status(int fmt, int64_t n_rows, int64_t n_cols, int T, size_t part_floats)
 {
@@ -410,7 +448,7 @@ prima_status launch_tok_stream(int fmt, const TokMat *mats, int n_mats, int64_t 
 
 prima_status launch_tok_prepare(const TokPrepare &a, hipStream_t st)
 {
-    const int nt = tk_slots(a.T), grid = a.nb * nt / 4;
+    const int nt = tok_slots(a.T), grid = a.nb * nt / 4;
     switch (nt) {
     case 4: hipLaunchKernelGGL((tok_prepare_kernel<4>), dim3(grid), dim3(64 * ADD_WAVES), 0, st, a); break;
     case 8: hipLaunchKernelGGL((tok_prepare_kernel<8>), dim3(grid), dim3(64 * ADD_WAVES), 0, st, a); break;

@@ -25,14 +25,23 @@ bool dims_ok(const prima_dims *d)
            (static_cast<int64_t>(d->n_q_heads) * d->head_dim) % QK == 0 && (d->rope_mode == 0 || d->rope_mode == 1);
 }
 
-// Windows of 9 to 16 tokens go through tok_stream.hip, in one pass over the weights (16 sequences through three 14B-shaped layers
-// 586 -> 380 us; at 8 tokens and fewer run_layer()'s one pass is faster, 364 us against 379 for two 70B-shaped layers).  K long
-// enough to need hundreds of slabs and layers with an FP32 matrix go through run_layer() too.
-constexpr int TOK_WINDOW = 9; // tokens from which whole windows go there
-// ... and from which the matrices in other formats of a smaller window do.  Two layers, V and down in Q6_K in one of them, us, there /
-// through a mat-vec for each: 14B shape 4 tokens 213 / 221, 5: 230 / 248, 8: 236 / 290; 70B shape 4: 342 / 376, 8: 385 / 492.  At
-// three tokens the mat-vec is as fast (14B shape 211; its launch reads the activations itself).  Down in Q8_0, 4 tokens: 14B 200 / 206, 70B
-// 350 / 376, in FP16 216 / 248, 406 / 467; every matrix in Q8_0: 14B 276 / 325, in FP16 330 / 486, in Q5_K 253 / 366.
+// Layers of several tokens go through tok_stream.hip, its launches between the streams included, from so many tokens on; it has four launches a layer
+// more than run_layer(), which narrow models feel.  Windows behind 2000 rows, us, run_layer() / there:
+// 8B shape, three layers, 3 tokens 236 / 240, 4: 241 / 244, 5: 274 / 241, 8: 281 / 244; V and down in Q6_K in one of two layers 3: 184 / 176, 4: 181 / 176;
+// 14B, two layers, 2: 170 / 172, 3: 181 / 175, 4: 181 / 177, 5: 202 / 182, 8: 212 / 185; down in Q8_0 in one of them 3: 189 / 186, 4: 192 / 186;
+// 32B, two layers, 3: 223 / 224, 4: 226 / 226, 5: 254 / 232, 8: 262 / 241; 70B, one layer, 3: 152 / 152, 4: 156 / 154, 5: 175 / 159, 8: 176 / 159;
+// 8 sequences through two 14B layers 214 / 188.  Narrow ones behind 1000 rows: hidden size 3072, six layers, 3: 371 / 376, 5: 427 / 393, with
+// V and down in Q6_K in every other layer 3: 419 / 402; 2048, eight layers, 3: 378 / 428, 5: 474 / 440, Q6_K as above 3: 441 / 467, 5: 541 / 475; 1024, eight,
+// 5: 326 / 332, 8: 342 / 337, Q6_K 3: 324 / 347, 5: 370 / 359; 512, eight, 5: 296 / 321, 8: 309 / 323, Q6_K 5: 333 / 344, 12: 338 / 337.
+// K long enough to need hundreds of slabs and layers with an FP32 matrix go through run_layer().
+constexpr int TOK_LEAST = 3; // (the scratch has a region for the streams from here on)
+int tok_from(const prima_dims &d, bool others) // others: a matrix in another format than Q4_K
+{
+    if (others ? d.e >= 3072 : d.e > 4096) return TOK_LEAST;
+    return d.e >= (others ? 1024 : 2048) ? 5 : 9;
+}
+// In run_layer(), tokens from which the matrices in other formats go through streams of their own.  Two layers, V
+// and down in Q6_K in one of them, us, there / through a mat-vec for each: 14B shape 4 tokens 213 / 221, 5: 230 / 248, 8: 236 / 290.
 constexpr int TOK_OTHERS = 4;
 // A group of these matrices takes a launch in front of its streams (one per format) and one behind, the mat-vecs one per matrix.  Up to
 // 7 tokens a launch more pays from about this many weights on.  Two layers, us, mat-vecs / streams, 4 tokens: hidden size 512, V
@@ -55,7 +64,7 @@ bool tok_dims(const prima_dims &d)
            (2 * static_cast<int64_t>(d.ffn) + qd + 2 * static_cast<int64_t>(d.n_kv_heads) * d.head_dim) < (int64_t{1} << 30);
 }
 // ... and whether a step of T tokens on this scratch uses it
-bool tok_takes(const WindowWs &w, int T, int from = TOK_WINDOW) { return T >= from && w.tok_part_floats != 0; }
+bool tok_takes(const WindowWs &w, int T, int from) { return T >= from && w.tok_part_floats != 0; }
 
 WindowWs carve(const prima_dims &d, int kv_cap, int T)
 {
@@ -88,7 +97,7 @@ WindowWs carve(const prima_dims &d, int kv_cap, int T)
     // The shares of the streams lie where the mat-vec keeps its partial sums, behind its counters (which a step needs cleared): a launch of
     // one kind has used up its own before one of the other kind starts.
     size_t region = w.gemv_bytes;
-    const bool tok = T >= TOK_OTHERS && tok_dims(d);
+    const bool tok = T >= TOK_LEAST && tok_dims(d);
     if (tok) {
         auto floats = [&](size_t rows, int64_t cols) { return tok_part_floats(static_cast<int64_t>(rows), cols, T); };
         w.tok_part_floats = std::max({floats(qd, d.e) + 2 * floats(kvd, d.e), floats(d.e, static_cast<int64_t>(qd)), 2 * floats(d.ffn, d.e), floats(d.e, d.ffn)});
@@ -181,8 +190,8 @@ prima_status tok_streams(const TokMat *m, const int *fmt, int count, int64_t col
     return PRIMA_OK;
 }
 
-// one decoder layer; x -> y (fp32 [T][e]); taps may be null.  Five launches: Q/K/V projections
-// (RMSNorm fused), attention (RoPE + KV append fused, key ranges merged by the last arriver), output projection
+// one decoder layer; x -> y (fp32 [T][e]); taps may be null.  Six launches: Q/K/V projections
+// (RMSNorm fused), attention (RoPE + KV append fused), the merge of its key ranges (none with one range), output projection
 // (+ residual), gate/up projections (RMSNorm fused in front, SwiGLU behind), down projection (+ residual).
 prima_status run_layer(const prima_dims &d, const prima_layer &L, int kv_cap, int n_past, int T,
                        const float *x, float *y, void *ws, const WindowWs &w, hipStream_t st,
@@ -264,7 +273,8 @@ prima_status run_layer(const prima_dims &d, const prima_layer &L, int kv_cap, in
     }
     if (PRIMA_WANT(PRIMA_K_ATTN))
         PRIMA_TRY(launch_attn(d, q, tap_q, k, v, at<float>(ws, w.rope), static_cast<__half *>(L.k_cache),
-                              static_cast<__half *>(L.v_cache), kv_cap, n_past, T, o, at<char>(ws, w.attn), st, seq));
+                              static_cast<__half *>(L.v_cache), kv_cap, n_past, T, o, at<char>(ws, w.attn), st, seq,
+                              ATTN_MERGE_APART));
     if (tap_o && hipMemcpyAsync(tap_o, o, T * qd * sizeof(float), hipMemcpyDeviceToDevice, st) != hipSuccess) return PRIMA_E_DEVICE;
     if (PRIMA_WANT(PRIMA_K_WO)) {
         if (f_o == PRIMA_FMT_Q4_K) {
@@ -319,7 +329,7 @@ prima_status run_layer(const prima_dims &d, const prima_layer &L, int kv_cap, in
     return PRIMA_OK;
 }
 
-// One decoder layer for 9 to 16 tokens (tok_stream.hip), x -> y.  Launches: the weight streams (one per format in a group), and
+// One decoder layer for several tokens (tok_stream.hip), x -> y.  Launches: the weight streams (one per format in a group), and
 // between them one that adds their shares, finishes the vector and lays it out for the next stream.  prepared: the layer
 // before this one has laid out x for the Q/K/V streams; next: the layer after it, whose Q/K/V activations the last launch
 // lays out (null: none).  Every matrix in a format that the streams take.
@@ -360,12 +370,16 @@ prima_status run_layer_tok(const prima_dims &d, const prima_layer &L, int kv_cap
     }
     if (PRIMA_WANT(PRIMA_K_ATTN))
         PRIMA_TRY(launch_attn(d, q, tap_q, k, v, at<float>(ws, w.rope), static_cast<__half *>(L.k_cache),
-                              static_cast<__half *>(L.v_cache), kv_cap, n_past, T, o, at<char>(ws, w.attn), st, seq));
-    if (tap_o && hipMemcpyAsync(tap_o, o, T * qd * sizeof(float), hipMemcpyDeviceToDevice, st) != hipSuccess) return PRIMA_E_DEVICE;
+                              static_cast<__half *>(L.v_cache), kv_cap, n_past, T, o, at<char>(ws, w.attn), st, seq, ATTN_MERGE_LATER));
     if (PRIMA_WANT(PRIMA_K_WO)) {
-        TokPrepare a = prepare(TOK_PLAIN, qd, nullptr, {f.wo});
+        const AttnRecords rec = attn_records(d, n_past, T, at<char>(ws, w.attn), seq);
+        TokPrepare a = prepare(rec.nsplit == 1 ? TOK_PLAIN : TOK_ATTENTION, qd, nullptr, {f.wo});
         a.x = o;
+        a.att = rec;
+        a.D = d.head_dim;
+        a.out = tap_o && rec.nsplit != 1 ? o : nullptr;
         PRIMA_TRY(launch_tok_prepare(a, st));
+        if (tap_o && hipMemcpyAsync(tap_o, o, T * qd * sizeof(float), hipMemcpyDeviceToDevice, st) != hipSuccess) return PRIMA_E_DEVICE;
         const TokMat m{W(L.wo), e};
         a = prepare(TOK_RESIDUAL, e, L.g_ffn, {f.wgate, f.wup});
         PRIMA_TRY(streams(&m, &f.wo, 1, qd, a.p));
@@ -404,13 +418,16 @@ prima_status run_layer_tok(const prima_dims &d, const prima_layer &L, int kv_cap
 }
 
 // whether a layer with these formats goes through run_layer_tok()
-bool layer_is_tok(const WindowWs &w, int T, int n_past, const AttnSeqs *seq, const prima_layer_formats *f)
+bool layer_is_tok(const prima_dims &d, const WindowWs &w, int T, int n_past, const AttnSeqs *seq, const prima_layer_formats *f)
 {
-    if (!tok_takes(w, T) || !tok_context(n_past, seq)) return false;
-    if (!f) return true;
-    for (int32_t v : {f->wq, f->wk, f->wv, f->wo, f->wgate, f->wup, f->wdown})
-        if (v == PRIMA_FMT_F32) return false;
-    return true;
+    bool others = false;
+    if (f) {
+        for (int32_t v : {f->wq, f->wk, f->wv, f->wo, f->wgate, f->wup, f->wdown}) {
+            if (v == PRIMA_FMT_F32) return false;
+            others = others || v != PRIMA_FMT_Q4_K;
+        }
+    }
+    return tok_takes(w, T, tok_from(d, others)) && tok_context(n_past, seq);
 }
 
 // all layers of a step; caches(i, seq): a batch's caches of layer i
@@ -425,8 +442,8 @@ prima_status run_layers(const prima_dims &d, const prima_layer *layers, const pr
         const prima_layer_formats *f = formats ? &formats[i] : nullptr, *nf = formats && i + 1 < L ? &formats[i + 1] : nullptr;
         const AttnSeqs *seq = caches(i);
         prima_status s;
-        if (layer_is_tok(w, T, n_past, seq, f)) {
-            const bool chain = i + 1 < L && layer_is_tok(w, T, n_past, seq, nf);
+        if (layer_is_tok(d, w, T, n_past, seq, f)) {
+            const bool chain = i + 1 < L && layer_is_tok(d, w, T, n_past, seq, nf);
             s = run_layer_tok(d, layers[i], kv_cap, n_past, T, cur, dst, ws, w, st, nullptr, nullptr, nullptr, nullptr, -1, seq, f, prepared,
                               chain ? &layers[i + 1] : nullptr, nf);
             prepared = chain;
@@ -441,19 +458,12 @@ prima_status run_layers(const prima_dims &d, const prima_layer *layers, const pr
 }
 
 // before the first layer of a step: RoPE table, the counters of the mat-vec and attention scratch zeroed (and, where
-// asked, the error flag that prima_window_check reads), the attention's records set to "not written": one launch
+// asked, the error flag that prima_window_check reads): one launch
 prima_status step_init(const prima_dims &d, void *ws, const WindowWs &w, int T, int n_past, const int *positions, bool with_sync, hipStream_t st)
 {
-    // rows the longest sequence of the step holds after it: sets the attention's key ranges, hence the records it uses
-    int n_total = n_past + T;
-    if (positions) {
-        n_total = 1;
-        for (int t = 0; t < T; ++t) n_total = positions[t] + 1 > n_total ? positions[t] + 1 : n_total;
-    }
-    char *const attn = at<char>(ws, w.attn);
-    void *const fp[4] = {at<char>(ws, w.gemv), attn, with_sync ? at<char>(ws, w.sync) : nullptr, attn + attn_counter_bytes(d, T)};
-    const size_t fb[4] = {w.arrivals_bytes, attn_counter_bytes(d, T), WAIT_FLAG_BYTES, attn_records_bytes(d, n_total, T, positions != nullptr)};
-    const unsigned fw[4] = {0u, 0u, 0u, ATTN_REC_EMPTY};
+    void *const fp[4] = {at<char>(ws, w.gemv), at<char>(ws, w.attn), with_sync ? at<char>(ws, w.sync) : nullptr, nullptr};
+    const size_t fb[4] = {w.arrivals_bytes, attn_counter_bytes(d, T), WAIT_FLAG_BYTES, 0};
+    const unsigned fw[4] = {0u, 0u, 0u, 0u};
     return launch_step_init(at<float>(ws, w.rope), T, d.head_dim, n_past, d.rope_theta, positions, fp, fb, fw, st);
 }
 
@@ -755,7 +765,7 @@ prima_status prima_attn_decode(const prima_dims *d, const float *q, const void *
     if (workspace_bytes < attn_ws_bytes(*d, kv_cap, T)) return PRIMA_E_WORKSPACE;
     return launch_attn(*d, q, nullptr, nullptr, nullptr, nullptr,
                        static_cast<__half *>(const_cast<void *>(k_cache)), static_cast<__half *>(const_cast<void *>(v_cache)),
-                       kv_cap, n_past, T, o, workspace, static_cast<hipStream_t>(hip_stream), nullptr, true);
+                       kv_cap, n_past, T, o, workspace, static_cast<hipStream_t>(hip_stream), nullptr, ATTN_MERGE_APART);
 }
 
 size_t prima_fmt_tensor_bytes(int32_t fmt, int64_t n_rows, int64_t n_cols) { return fmt_tensor_bytes(fmt, n_rows, n_cols); }
@@ -837,7 +847,7 @@ prima_status prima_window_plan_status(const prima_dims *d, int32_t kv_cap, int32
         }
         for (int fmt = PRIMA_FMT_Q4_K; fmt <= PRIMA_FMT_F16; ++fmt) {
             prima_status s = PRIMA_OK;
-            if (tok_takes(w, T, fmt == PRIMA_FMT_Q4_K ? TOK_WINDOW : TOK_OTHERS)) s = tok_stream_plan_status(fmt, rows, l.cols, T, std::min(floats, w.tok_part_floats));
+            if (tok_takes(w, T, TOK_LEAST)) s = tok_stream_plan_status(fmt, rows, l.cols, T, std::min(floats, w.tok_part_floats));
             const int first = tok_gemv_first(fmt, rows, l.cols, T);
             if (s == PRIMA_OK && l.nseg == 1 && fmt != PRIMA_FMT_Q4_K && tok_gemv_takes(fmt, rows, l.cols, T)) s = tok_gemv_plan_status(fmt, rows, l.cols, first);
             if (s != PRIMA_OK) return s;
@@ -1061,7 +1071,7 @@ prima_status prima_layer_window_decode_profiled(const prima_dims *d, const prima
     float *scratch_out = at<float>(workspace, w.xb0); // the isolated down projections write here, not to x_out
     for (int ki = 0; ki < n_kinds && s == PRIMA_OK; ++ki) {
         for (int i = 0; i < L && s == PRIMA_OK; ++i)
-            s = layer_is_tok(w, T, n_past, nullptr, nullptr)
+            s = layer_is_tok(*d, w, T, n_past, nullptr, nullptr)
                     ? run_layer_tok(*d, layers[i], kv_cap, n_past, T, x_in, scratch_out, workspace, w, st, nullptr, nullptr, nullptr, nullptr, kinds[ki], nullptr,
                                     nullptr, false, nullptr, nullptr)
                     : run_layer(*d, layers[i], kv_cap, n_past, T, x_in, scratch_out, workspace, w, st, nullptr, nullptr, nullptr, nullptr, kinds[ki]);
@@ -1096,7 +1106,7 @@ prima_status prima_layer_decode_taps(const prima_dims *d, const prima_layer *lay
     const WindowWs w = carve(*d, kv_cap, T);
     s = step_init(*d, workspace, w, T, n_past, nullptr, false, st);
     if (s != PRIMA_OK) return s;
-    if (layer_is_tok(w, T, n_past, nullptr, nullptr))
+    if (layer_is_tok(*d, w, T, n_past, nullptr, nullptr))
         return run_layer_tok(*d, *layer, kv_cap, n_past, T, x_in, x_out, workspace, w, st, tap_q, tap_o, tap_h, tap_a, -1, nullptr, nullptr, false, nullptr, nullptr);
     return run_layer(*d, *layer, kv_cap, n_past, T, x_in, x_out, workspace, w, st, tap_q, tap_o, tap_h, tap_a);
 }

@@ -375,14 +375,14 @@ def test_activations_that_are_not_finite_and_tiny_ones(gpu_lib, fmt, T):
         assert torch.equal(torch.nan_to_num(got[2:6], 7.0, 8.0, -8.0), torch.nan_to_num(apart, 7.0, 8.0, -8.0))
 
 
-@pytest.mark.parametrize("T", [5, 9, 16])
-def test_streams_between_launches(gpu_lib, T):
+@pytest.mark.parametrize("T,n_past", [(3, 2500), (5, 700), (9, 300), (16, 70)])
+def test_streams_between_launches(gpu_lib, T, n_past):
     """The launches that add the streams' shares: rows of more than 64 super-blocks (their sums of squares take a wave twice), 16 and more
-    shares of a short matrix, vectors of 64 rows (a wave's 256 end inside), shares of two formats for gate and up."""
+    shares of a short matrix, vectors of 64 rows (a wave's 256 end inside), shares of two formats for gate and up; attention merged there:
+    20, 6, 3 and one key range, four heads of 64 columns in a wave."""
     from workloads.configs import ModelDims, WindowConfig
     d = ModelDims(16640, 4, 1, 64, 768, 1e4)
     fm = [{"wq": "q8_0", "wk": "q5_k", "wv": "q5_k", "wo": "q6_k", "wgate": "q5_k", "wup": "q6_k", "wdown": "q6_k"}, {}]
-    n_past = 70
     host = [synth.layer_tensors(WindowConfig("rows", 78, d, 2, T, n_past), l, kv_cap=n_past + T, formats=fm[l]) for l in range(2)]
     x = np.random.default_rng(T).standard_normal((T, d.e)).astype(np.float32)
     dev = [{k: _dev(v) for k, v in t.items()} for t in host]
