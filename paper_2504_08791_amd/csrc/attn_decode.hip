@@ -22,7 +22,7 @@
 //    output projection's activations.  (The merge inside the launch, below, costs its records' trip to memory and back while the device
 //    waits, and a fill of the records in front: 4 tokens behind 4096 rows, 40 / 8 heads, 18.3 us a launch with it, 12 without.  70B
 //    shape, one token, three layers: 335 -> 331 us; 32B, four tokens through the streams, four layers: 467 -> 449.)
-//  * The last T mod 16 tokens of a prompt still have them merged inside: the workgroup of the first key range merges
+//  * A prompt of fewer than 16 tokens (on the matrix-product route) still has them merged inside: the workgroup of the first key range merges
 //    them.  It does not wait for an arrival count (a store acknowledgement, an atomic and two dependent loads: four trips through global memory):
 //    the records say themselves whether they are complete.  Before a launch every word of a record holds a NaN
 //    pattern that no arithmetic produces; the merging workgroup requests (max, sum) and the columns of all ranges
@@ -81,13 +81,13 @@ __global__ void __launch_bounds__(ATT_THREADS, 4) attn_decode_kernel(AttnArgs a)
     // caches and length are read by hand from the argument segment (indexing the by-value argument with a
     // run-time index would make the compiler copy all of it to scratch memory).
     // A prompt (batch == 2, caches complete, one key range): piece z / gps of the grid is a call of its own for the
-    // tokens 16 piece .. 16 piece + 15, which see the n_past + 16 piece rows before them and, causally, their own.
+    // tokens 16 piece .. 16 piece + 15 (the last: what is left), which see the n_past + 16 piece rows before them and, causally, their own.
     const bool batch = a.batch == 1, prompt = a.batch == 2, pieces = batch || prompt;
     const int gps = prompt ? (G * PRIMA_MAX_TOK + QGM - 1) / QGM : (G + QGM - 1) / QGM; // query groups of one token / one piece
     const int piece = pieces ? blockIdx.z / gps : 0;
     const int tok0 = prompt ? piece * PRIMA_MAX_TOK : piece;
     const int qgrp = pieces ? blockIdx.z - piece * gps : blockIdx.z, nqg = pieces ? gps : gridDim.z;
-    const int arg_T = batch ? 1 : (prompt ? PRIMA_MAX_TOK : a.T);
+    const int arg_T = batch ? 1 : (prompt ? min(PRIMA_MAX_TOK, a.T - tok0) : a.T);
     __half *arg_K = a.K, *arg_V = a.V;
     int arg_n_past = a.n_past + (prompt ? tok0 : 0);
     if (batch) {
@@ -100,6 +100,7 @@ __global__ void __launch_bounds__(ATT_THREADS, 4) attn_decode_kernel(AttnArgs a)
     const int NQ = G * arg_T; // queries on this KV head, index = t*G + hg
     const int q0 = qgrp * QGM;
     const int nq = min(QGM, NQ - q0);
+    if (nq <= 0) return; // (groups of a short last piece; the whole workgroup, before any barrier)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n_total = arg_n_past + arg_T;
     const int p_begin = split * a.keys_per_split;
@@ -656,21 +657,23 @@ AttnRecords attn_records(const prima_dims &d, int n_past, int T, void *ws, const
 }
 
 // Attention for the tokens of a prompt whose rotated K and V rows are in the caches already and whose queries are
-// rotated: n_pieces pieces of PRIMA_MAX_TOK tokens in one launch, each piece over the n_past + 16 piece rows before it
-// and, causally, its own; one key range per workgroup (there are Hkv * G workgroups per piece), no scratch.
-prima_status launch_attn_prompt(const prima_dims &d, const float *q, __half *K, __half *V, int kv_cap, int n_past, int n_pieces,
+// rotated: pieces of PRIMA_MAX_TOK tokens in one launch (the last may be shorter), each piece over the n_past + 16 piece rows before it
+// and, causally, its own; one key range per workgroup (there are Hkv * G workgroups per piece), no scratch.  (The last T mod 16 tokens in
+// a launch of their own, with key ranges: 15 us a layer and a fill for 13 of 333 tokens of an 8B shape, beside 43 for the others.)
+prima_status launch_attn_prompt(const prima_dims &d, const float *q, __half *K, __half *V, int kv_cap, int n_past, int T,
                                 float *o, hipStream_t st)
 {
-    if (n_pieces < 1) return PRIMA_OK;
+    if (T < 1) return PRIMA_OK;
+    const int n_pieces = (T + PRIMA_MAX_TOK - 1) / PRIMA_MAX_TOK;
     const int G = d.n_q_heads / d.n_kv_heads;
     const int64_t gz = static_cast<int64_t>(n_pieces) * ((G * PRIMA_MAX_TOK + QGM - 1) / QGM);
-    if (gz > 65535 || static_cast<int64_t>(n_past) + static_cast<int64_t>(n_pieces) * PRIMA_MAX_TOK > kv_cap) return PRIMA_E_SHAPE;
+    if (gz > 65535 || static_cast<int64_t>(n_past) + T > kv_cap) return PRIMA_E_SHAPE;
     AttnArgs a{};
     a.batch = 2;
     a.q = q; a.K = K; a.V = V; a.o = o;
-    a.Hq = d.n_q_heads; a.Hkv = d.n_kv_heads; a.kv_cap = kv_cap; a.n_past = n_past; a.T = PRIMA_MAX_TOK;
+    a.Hq = d.n_q_heads; a.Hkv = d.n_kv_heads; a.kv_cap = kv_cap; a.n_past = n_past; a.T = T;
     a.nsplit = 1;
-    a.keys_per_split = (n_past + n_pieces * PRIMA_MAX_TOK + 15) / 16 * 16;
+    a.keys_per_split = (n_past + T + 15) / 16 * 16;
     return launch_attn_kernel(d, dim3(1, d.n_kv_heads, static_cast<unsigned>(gz)), a, st);
 }
 

@@ -170,8 +170,8 @@ prima_status launch_attn(const prima_dims &d, const float *q, float *q_rot_out, 
 // where that launch's records lie
 AttnRecords attn_records(const prima_dims &d, int n_past, int T, void *ws, const AttnSeqs *seq);
 
-// a prompt: rotated K / V rows already in the caches, q rotated; n_pieces pieces of PRIMA_MAX_TOK tokens in one launch
-prima_status launch_attn_prompt(const prima_dims &d, const float *q, __half *K, __half *V, int kv_cap, int n_past, int n_pieces,
+// a prompt: rotated K / V rows already in the caches, q rotated; pieces of PRIMA_MAX_TOK tokens in one launch
+prima_status launch_attn_prompt(const prima_dims &d, const float *q, __half *K, __half *V, int kv_cap, int n_past, int T,
                                 float *o, hipStream_t st);
 // RoPE on q (in place) and k, and k, v appended to the caches as rows n_past .. n_past + T - 1, for any T; tab from
 // launch_rope_table

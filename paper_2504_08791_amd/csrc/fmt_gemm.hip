@@ -428,10 +428,9 @@ __global__ void __launch_bounds__(256) fmt_gemm_reduce_kernel(FmtGemmArgs a)
     const int64_t row = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     const int t = blockIdx.y;
     if (row >= a.n_rows) return;
-    float v = a.part[static_cast<int64_t>(t) * a.n_rows + row];
-    for (int ks = 1; ks < a.ksplit; ++ks) v += a.part[(static_cast<int64_t>(ks) * a.T + t) * a.n_rows + row];
-    if (a.resid) v += a.resid[t * a.ldr + row];
-    a.y[t * a.ldy + row] = v;
+    const float r = a.resid ? a.resid[t * a.ldr + row] : 0.f;
+    const float v = gemm_add_shares(a.part + static_cast<int64_t>(t) * a.n_rows + row, static_cast<int64_t>(a.T) * a.n_rows, a.ksplit);
+    a.y[t * a.ldy + row] = a.resid ? v + r : v;
 }
 
 template <int FMT, int WT>
@@ -456,11 +455,22 @@ prima_status launch_fm(FmtGemmArgs a, void *part, size_t part_bytes, hipStream_t
     a.n_tb = narrow ? (a.n_tiles + 3) / 4 : (a.n_tiles + 7) / 8;
     const int64_t wgs = static_cast<int64_t>(a.n_rb) * a.n_tb, slots = 2 * GM_CUS;
     const int64_t nb = a.n_cols / QK;
-    // shares of K: as the Q4_K product divides it (at least 4 super-blocks each), as far as the scratch holds the shares
+    // Shares of K (at least 4 super-blocks each, as far as the scratch holds them): rounds of workgroups times a share's super-blocks, about
+    // 7 us each at 64 tokens and 14 at 128, against the shares' way to memory and back (4 TB/s).  (As many as fit the device at once
+    // left a quarter of it idle where they do not come out even: 4096 x 14336 in Q6_K, 333 tokens, two shares 227 us and 6 for their sum, five 200 and 7.)
     a.ksplit = 1;
-    if (part && a.T <= 65535 && wgs * 2 <= slots) {
-        const int64_t room = static_cast<int64_t>(part_bytes / (static_cast<size_t>(a.T) * static_cast<size_t>(a.n_rows) * sizeof(float)));
-        a.ksplit = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({slots / wgs, nb / 4, 16, room})));
+    if (part && a.T <= 65535) {
+        const int64_t share_bytes = static_cast<int64_t>(a.T) * a.n_rows * static_cast<int64_t>(sizeof(float));
+        const int64_t most = std::min<int64_t>({nb / 4, 16, static_cast<int64_t>(part_bytes) / share_bytes});
+        double best = 0.;
+        for (int64_t ks = 1; ks <= std::max<int64_t>(1, most); ++ks) {
+            const double us = static_cast<double>((wgs * ks + slots - 1) / slots) * static_cast<double>((nb + ks - 1) / ks) * (narrow ? 7. : 14.) +
+                              (ks > 1 ? 4. + static_cast<double>(ks * share_bytes) * 2. / 4e6 : 0.);
+            if (ks == 1 || us < best) {
+                best = us;
+                a.ksplit = static_cast<int>(ks);
+            }
+        }
     }
     a.part = static_cast<float *>(part);
     const int64_t grid = (a.n_rb + GM_XCDS - 1) / GM_XCDS * static_cast<int64_t>(GM_XCDS) * a.n_tb;

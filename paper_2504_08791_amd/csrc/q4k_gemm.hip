@@ -90,12 +90,23 @@ __global__ void __launch_bounds__(256) gemm_token_scale_kernel(const float *__re
     __shared__ float red[2][4];
     const int t = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     float ss = 0.f, amax = 0.f;
-    for (int64_t k = static_cast<int64_t>(threadIdx.x) * 4; k < K; k += 1024) {
-        const float4 v = *reinterpret_cast<const float4 *>(x + t * ldx + k);
-        float4 g = make_float4(1.f, 1.f, 1.f, 1.f);
-        if (gain) g = *reinterpret_cast<const float4 *>(gain + k);
-        ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-        amax = fmaxf(fmaxf(amax, fmaxf(fabsf(v.x * g.x), fabsf(v.y * g.y))), fmaxf(fabsf(v.z * g.z), fabsf(v.w * g.w)));
+    // eight pieces of the row requested at a time: one by one they were a chain of K / 1024 trips through memory (1024 tokens of 8192 columns 11.6 -> 7 us, 333 of 4096 5.2 -> 4.7)
+    constexpr int AT = 8;
+    for (int64_t k0 = static_cast<int64_t>(threadIdx.x) * 4; k0 < K; k0 += AT * 1024) {
+        float4 v[AT], g[AT];
+#pragma unroll
+        for (int j = 0; j < AT; ++j) { // (past the end: the thread's first piece again, not counted)
+            const int64_t k = k0 + j * 1024 < K ? k0 + j * 1024 : k0;
+            v[j] = *reinterpret_cast<const float4 *>(x + t * ldx + k);
+            g[j] = make_float4(1.f, 1.f, 1.f, 1.f);
+            if (gain) g[j] = *reinterpret_cast<const float4 *>(gain + k);
+        }
+#pragma unroll
+        for (int j = 0; j < AT; ++j) {
+            if (k0 + j * 1024 >= K) break;
+            ss += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
+            amax = fmaxf(fmaxf(amax, fmaxf(fabsf(v[j].x * g[j].x), fabsf(v[j].y * g[j].y))), fmaxf(fabsf(v[j].z * g[j].z), fabsf(v[j].w * g[j].w)));
+        }
     }
     ss = wave_sum(ss);
     amax = wave_max(amax);
@@ -589,11 +600,9 @@ __global__ void __launch_bounds__(256) gemm_ksplit_reduce_kernel(GemmArgs a)
         // shares, its up sums 32 columns further
         if (col >= a.seg[0].n_rows) return;
         const int64_t gc = (col / (GM_ROWS / 2)) * GM_ROWS + ((col % (GM_ROWS / 2)) / 32) * 64 + col % 32;
-        float gt = a.part[static_cast<int64_t>(t) * a.ldp + gc], up = a.part[static_cast<int64_t>(t) * a.ldp + gc + 32];
-        for (int ks = 1; ks < a.ksplit; ++ks) {
-            gt += a.part[(static_cast<int64_t>(ks) * a.T + t) * a.ldp + gc];
-            up += a.part[(static_cast<int64_t>(ks) * a.T + t) * a.ldp + gc + 32];
-        }
+        const float *const p = a.part + static_cast<int64_t>(t) * a.ldp + gc;
+        const float gt = gemm_add_shares(p, static_cast<int64_t>(a.T) * a.ldp, a.ksplit);
+        const float up = gemm_add_shares(p + 32, static_cast<int64_t>(a.T) * a.ldp, a.ksplit);
         a.seg[0].y[t * a.seg[0].ldy + col] = gt / (1.0f + expf(-gt)) * up;
         return;
     }
@@ -603,10 +612,9 @@ __global__ void __launch_bounds__(256) gemm_ksplit_reduce_kernel(GemmArgs a)
     const GemmSegDev &my = a.seg[sg];
     const int64_t row = col - static_cast<int64_t>(my.rb0) * GM_ROWS;
     if (row >= my.n_rows) return;
-    float v = a.part[static_cast<int64_t>(t) * a.ldp + col];
-    for (int ks = 1; ks < a.ksplit; ++ks) v += a.part[(static_cast<int64_t>(ks) * a.T + t) * a.ldp + col];
-    if (a.resid) v += a.resid[t * a.ldr + row];
-    my.y[t * my.ldy + row] = v;
+    const float r = a.resid ? a.resid[t * a.ldr + row] : 0.f;
+    const float v = gemm_add_shares(a.part + static_cast<int64_t>(t) * a.ldp + col, static_cast<int64_t>(a.T) * a.ldp, a.ksplit);
+    my.y[t * my.ldy + row] = a.resid ? v + r : v;
 }
 
 // Into how many shares K is cut: none while the row and token blocks alone give every compute unit a workgroup; else as

@@ -570,15 +570,12 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
         ready = ready || splits(f_k);
         PRIMA_TRY(product(f_v, L.wv, kvd, e, x, g_attn, nullptr, v, ready));
     }
-    // RoPE and the cache rows of all T tokens first; then the full pieces of PRIMA_MAX_TOK tokens in one launch and the
-    // rest in a launch of the decode kind (caches complete, queries rotated)
+    // RoPE and the cache rows of all T tokens first; then the pieces of PRIMA_MAX_TOK tokens in one launch, or fewer tokens
+    // than that in a launch of the decode kind (caches complete, queries rotated)
     __half *Kc = static_cast<__half *>(L.k_cache), *Vc = static_cast<__half *>(L.v_cache);
     PRIMA_TRY(launch_rope_append(d, q, k, v, at<float>(ws, w.rope), Kc, Vc, kv_cap, n_past, T, st));
-    const int n_pieces = T / PRIMA_MAX_TOK, rest = T - n_pieces * PRIMA_MAX_TOK;
-    PRIMA_TRY(launch_attn_prompt(d, q, Kc, Vc, kv_cap, n_past, n_pieces, o, st));
-    if (rest)
-        PRIMA_TRY(launch_attn(d, q + n_pieces * PRIMA_MAX_TOK * qd, nullptr, nullptr, nullptr, nullptr, Kc, Vc, kv_cap,
-                              n_past + n_pieces * PRIMA_MAX_TOK, rest, o + n_pieces * PRIMA_MAX_TOK * qd, at<char>(ws, w.attn), st));
+    if (T >= PRIMA_MAX_TOK) PRIMA_TRY(launch_attn_prompt(d, q, Kc, Vc, kv_cap, n_past, T, o, st));
+    else PRIMA_TRY(launch_attn(d, q, nullptr, nullptr, nullptr, nullptr, Kc, Vc, kv_cap, n_past, T, o, at<char>(ws, w.attn), st));
     PRIMA_TRY(product(f_o, L.wo, e, qd, o, nullptr, x, h, false, true));
     if (f_g == PRIMA_FMT_Q4_K && f_u == PRIMA_FMT_Q4_K) {
         const GemmMat gate_up[2] = {{W(L.wgate), act, F, F}, {W(L.wup), nullptr, F, F}};
@@ -1003,11 +1000,10 @@ prima_status prima_layer_window_prefill_mixed(const prima_dims *d, const prima_l
     }
     prima_status s = launch_rope_table(at<float>(workspace, w.rope), T, d->head_dim, n_past, d->rope_theta, st);
     if (s != PRIMA_OK) return s;
-    {   // the attention launch for the last T mod 16 tokens (the only one with key ranges to merge): its records marked "not written"
-        const int rest = T % PRIMA_MAX_TOK;
+    if (T < PRIMA_MAX_TOK) { // the attention launch then merges its key ranges inside: its records marked "not written"
         char *const attn = at<char>(workspace, w.attn);
-        const size_t head_bytes = attn_counter_bytes(*d, rest ? rest : 1); // the records of that launch start behind it
-        s = launch_fill_words(attn, head_bytes, 0u, attn + head_bytes, rest ? attn_records_bytes(*d, n_past + T, rest, false) : 0, ATTN_REC_EMPTY, st);
+        const size_t head_bytes = attn_counter_bytes(*d, T); // the records start behind it
+        s = launch_fill_words(attn, head_bytes, 0u, attn + head_bytes, attn_records_bytes(*d, n_past + T, T, false), ATTN_REC_EMPTY, st);
         if (s != PRIMA_OK) return s;
     }
     const float *cur = x_in;
