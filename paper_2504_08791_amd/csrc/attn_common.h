@@ -20,7 +20,7 @@ struct AttnArgs {
     const float *v_new;   // fused append: v [T][Hkv][D]
     const float2 *rope_tab; // [T][D/2] (cos, sin) or null
     __half *K, *V;        // caches [Hkv][kv_cap][D]
-    float *part;          // the key ranges' records [T*Hq][nsplit][4 + D], every word "not written" between launches
+    float *part;          // the key ranges' records [T*Hq][nsplit][4 + D] (merged inside: every word "not written" between launches)
     unsigned *err;        // raised when the merging workgroup's bounded wait gives up
     float *o;             // [T][Hq][D]
     int Hq, Hkv, kv_cap, n_past, T, nsplit, keys_per_split;

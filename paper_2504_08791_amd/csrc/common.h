@@ -144,8 +144,8 @@ prima_status launch_fill_words(void *a, size_t a_bytes, unsigned a_word, void *b
 void attn_ranges(const prima_dims &d, int n_total, int T, bool batch, int &keys_per_split, int &nsplit);
 size_t attn_ws_bytes(const prima_dims &d, int kv_cap, int T);
 // The attention scratch: attn_counter_bytes() whose first word is the flag a bounded wait raises when it gives up
-// (zero before a launch), then the key ranges' records.  A record that has not been written holds ATTN_REC_EMPTY in
-// every word: before the first launch the records a launch will use (attn_records_bytes) must be filled with it
+// (zero before a launch), then the key ranges' records.  Where a launch merges them itself, a record that has not been written holds
+// ATTN_REC_EMPTY in every word: before the first such launch the records a launch will use (attn_records_bytes) must be filled with it
 // (launch_step_init / launch_fill_words); every launch leaves them so.
 size_t attn_counter_bytes(const prima_dims &d, int T);
 constexpr unsigned ATTN_REC_EMPTY = 0x7fa5c3e1u; // a NaN pattern that no arithmetic produces

@@ -42,7 +42,7 @@ __device__ __forceinline__ void gm_barrier()
 }
 
 // The shares of K of one number, `stride` numbers apart, added in order.  Eight are requested at a time (one by one, a trip through memory
-// each: 333 tokens of 4096 rows, four or five shares, 9.4 -> 8.2 us).
+// each: 333 tokens of 4096 rows, four or five shares, 8.5 to 9.6 us, now 8 to 8.5).
 __device__ __forceinline__ float gemm_add_shares(const float *p, int64_t stride, int n)
 {
     constexpr int AT = 8;
