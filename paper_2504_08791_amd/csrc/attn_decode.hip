@@ -29,6 +29,7 @@
 //    in one go and repeats the request until no word shows the pattern (the ranges finish together, so the first or
 //    second request succeeds), merges, and writes the pattern back for the next launch.  The polling is bounded
 //    (error flag in the scratch); the other workgroups wait for nothing, so the launch always drains.
+#include <algorithm>
 #include <atomic>
 
 #include "attn_common.h"
@@ -663,18 +664,23 @@ AttnRecords attn_records(const prima_dims &d, int n_past, int T, void *ws, const
 prima_status launch_attn_prompt(const prima_dims &d, const float *q, __half *K, __half *V, int kv_cap, int n_past, int T,
                                 float *o, hipStream_t st)
 {
-    if (T < 1) return PRIMA_OK;
-    const int n_pieces = (T + PRIMA_MAX_TOK - 1) / PRIMA_MAX_TOK;
-    const int G = d.n_q_heads / d.n_kv_heads;
-    const int64_t gz = static_cast<int64_t>(n_pieces) * ((G * PRIMA_MAX_TOK + QGM - 1) / QGM);
-    if (gz > 65535 || static_cast<int64_t>(n_past) + T > kv_cap) return PRIMA_E_SHAPE;
-    AttnArgs a{};
-    a.batch = 2;
-    a.q = q; a.K = K; a.V = V; a.o = o;
-    a.Hq = d.n_q_heads; a.Hkv = d.n_kv_heads; a.kv_cap = kv_cap; a.n_past = n_past; a.T = T;
-    a.nsplit = 1;
-    a.keys_per_split = (n_past + T + 15) / 16 * 16;
-    return launch_attn_kernel(d, dim3(1, d.n_kv_heads, static_cast<unsigned>(gz)), a, st);
+    const int G = d.n_q_heads / d.n_kv_heads, groups = (G * PRIMA_MAX_TOK + QGM - 1) / QGM; // query groups of a piece
+    const int most = 65535 / groups; // pieces that one grid holds
+    if (most < 1 || T / PRIMA_MAX_TOK > most || static_cast<int64_t>(n_past) + T > kv_cap) return PRIMA_E_SHAPE;
+    // (one launch; two if the short last piece is the one too many: it is then a prompt of its own behind the others)
+    for (int t0 = 0; t0 < T; t0 += most * PRIMA_MAX_TOK) {
+        const int n = std::min(T - t0, most * PRIMA_MAX_TOK);
+        const int64_t at = static_cast<int64_t>(t0) * d.n_q_heads * d.head_dim;
+        AttnArgs a{};
+        a.batch = 2;
+        a.q = q + at; a.K = K; a.V = V; a.o = o + at;
+        a.Hq = d.n_q_heads; a.Hkv = d.n_kv_heads; a.kv_cap = kv_cap; a.n_past = n_past + t0; a.T = n;
+        a.nsplit = 1;
+        a.keys_per_split = (n_past + t0 + n + 15) / 16 * 16;
+        const prima_status s = launch_attn_kernel(d, dim3(1, d.n_kv_heads, static_cast<unsigned>((n + PRIMA_MAX_TOK - 1) / PRIMA_MAX_TOK * groups)), a, st);
+        if (s != PRIMA_OK) return s;
+    }
+    return PRIMA_OK;
 }
 
 static prima_status launch_attn_kernel(const prima_dims &d, dim3 grid, const AttnArgs &a, hipStream_t st)

@@ -15,7 +15,7 @@ import oracle
 from metrics import rel_err
 from tolerance import EPS_FP32, EPS_GEMM, EPS_Q4K, check_hidden
 from workloads import synth
-from workloads.configs import CONFIGS, TINY
+from workloads.configs import CONFIGS, TINY, ModelDims, WindowConfig
 
 pytestmark = pytest.mark.gpu
 
@@ -293,6 +293,31 @@ def test_prefill_at_the_largest_token_count(gpu_lib):
         b = lb[0][key][:, 8176:].float().cpu().numpy().astype(np.float64).reshape(1, -1)
         assert rel_err(a, b) < 1e-3
         assert torch.equal(la[0][key][:, :8176], lb[0][key][:, :8176])
+
+
+@pytest.mark.parametrize("T", [8177, 8185])
+def test_prompt_whose_last_piece_does_not_fit_one_grid(gpu_lib, T):
+    """128 query heads on one KV head: 511 pieces of 16 tokens are 65408 query groups, one piece more is past the 65535 of a launch's
+    grid, so the last, short piece takes a launch of its own.  The full pieces' outputs are those of a call without it, bit for bit;
+    the rest agrees with a decode call behind them.  8192 tokens, 512 full pieces, are refused."""
+    from paper_2504_08791_amd import _ffi
+    d = ModelDims(256, 128, 1, 64, 256, 1e4)
+    cfg = WindowConfig("heads", 79, d, 1, 8192, 0)
+    cap = 8192
+    host = [synth.layer_tensors(cfg, 0, kv_cap=cap)]
+    x = _dev(synth.window_input(cfg))
+    wa, la = _window(gpu_lib, cfg, cap, host)
+    wb, lb = _window(gpu_lib, cfg, cap, host)
+    print("case 128 heads,", T, "tokens", flush=True)
+    ya = wa.prefill(x[:T].contiguous(), 0)
+    yb = wb.prefill(x[:8176].contiguous(), 0)
+    yc = wb.decode(x[8176:T].contiguous(), 8176)
+    assert torch.equal(ya[:8176], yb)
+    per_token = [rel_err(ya[8176 + t].cpu().numpy(), yc[t].cpu().numpy().astype(np.float64)) for t in range(T - 8176)]
+    assert max(per_token) < HID_TOL, per_token
+    assert torch.equal(la[0]["v_cache"][:, :8176], lb[0]["v_cache"][:, :8176])
+    with pytest.raises(_ffi.PrimaError):
+        wa.prefill(x, 0)
 
 
 def test_prefill_argument_errors(gpu_lib):
