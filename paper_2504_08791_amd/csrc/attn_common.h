@@ -123,7 +123,7 @@ struct AttnSeqs {
 
 inline AttnArgs build_attn_args(const prima_dims &d, const float *q, float *q_rot_out, const float *k_new, const float *v_new,
                                 const float *rope_tab, __half *K, __half *V, int kv_cap, int n_past, int T, float *o, void *ws,
-                                const AttnSeqs *seq = nullptr)
+                                AttnMerge merge, const AttnSeqs *seq)
 {
     int n_total = n_past + T;
     AttnArgs a{};
@@ -145,7 +145,7 @@ inline AttnArgs build_attn_args(const prima_dims &d, const float *q, float *q_ro
     a.o = o;
     a.Hq = d.n_q_heads; a.Hkv = d.n_kv_heads; a.kv_cap = kv_cap; a.n_past = n_past; a.T = T;
     // key ranges are multiples of 16 so that tiles never straddle two workgroups, and none is empty
-    attn_ranges(d, n_total, T, seq != nullptr, a.keys_per_split, a.nsplit);
+    attn_ranges(d, n_total, T, seq != nullptr, merge, a.keys_per_split, a.nsplit);
     return a;
 }
 

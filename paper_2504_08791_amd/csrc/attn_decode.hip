@@ -600,12 +600,15 @@ static int tile_query_groups(const prima_dims &d, int T, bool batch)
     return batch ? (G + QGM - 1) / QGM * T : (G * T + QGM - 1) / QGM;
 }
 
-static int tile_num_splits(const prima_dims &d, int n_total, int T, bool batch)
+static int tile_num_splits(const prima_dims &d, int n_total, int T, bool batch, AttnMerge merge)
 {
     const int wgs = d.n_kv_heads * tile_query_groups(d, T, batch);
-    // At least one 16-key tile per wave.  (Two while the merge sat inside the launch and a range cost an arrival: 4096 rows, one token, 16
-    // ranges 14.8 us, 32 16.0.  Now an 8B layer behind 512 rows 55.6 us with two, 54.2 with one; longer contexts are cut by the grid.)
-    const int by_len = n_total / (16 * ATT_WAVES); // (rounded down: no range of a few rows)
+    // At least one 16-key tile per wave (rounded down: no range of a few rows).  Merged inside the launch, where a range costs an arrival, two:
+    // 4096 rows, one token, 16 ranges 14.8 us, 32 16.0.  Merged by a launch of its own, one range below 512 rows: one token, us, several
+    // ranges / one, three 8B layers behind 256 rows 158.7 / 153.0, 384: 158.4 / 156.5, 500: 159.4 / 158.6, 512: 157.5 / 160.0, 800: 157.7 / 167.9;
+    // six layers of hidden size 1024 450: 184.3 / 178.3, 512: 182.8 / 180.9, 600: 180.2 / 181.0; two of 70B 256: 220.5 / 216.8, 500: 221.0 / 220.8,
+    // 512: 220.0 / 222.1.  Merged by a launch that is there anyway: 16 sequences, two 14B layers 256: 195.6 / 197.9, 500: 199.8 / 204.3.
+    const int by_len = merge == ATTN_MERGE_APART && n_total < 512 ? 1 : n_total / ((merge == ATTN_MERGE_INSIDE ? 32 : 16) * ATT_WAVES);
     // About one workgroup per compute unit (128 and 192 are slower; 512 with the merge apart: 30001 rows, one token 24.4 -> 27.0 us, 70B shape, 8
     // tokens behind 8192, two layers 321.5 -> 329.8, 16 sequences, three 14B layers 338 -> 348)
     const int by_grid = (256 + wgs - 1) / wgs;
@@ -621,17 +624,17 @@ static prima_status launch_attn_kernel(const prima_dims &d, dim3 grid, const Att
 // giving the keys left over a small range of their own, so that no wave has a tile more than the others, was
 // measured: no change at 4096 rows and one token, and 28 -> 40 us at 8 tokens behind 8192 rows, where the ninth range
 // of each query group no longer fits the compute units in one round.)
-void attn_ranges(const prima_dims &d, int n_total, int T, bool batch, int &keys_per_split, int &nsplit)
+void attn_ranges(const prima_dims &d, int n_total, int T, bool batch, AttnMerge merge, int &keys_per_split, int &nsplit)
 {
-    const int want = tile_num_splits(d, n_total, T, batch);
+    const int want = tile_num_splits(d, n_total, T, batch, merge);
     keys_per_split = ((n_total + want - 1) / want + 15) / 16 * 16;
     nsplit = (n_total + keys_per_split - 1) / keys_per_split;
 }
 
-size_t attn_records_bytes(const prima_dims &d, int n_total, int T, bool batch)
+size_t attn_records_bytes(const prima_dims &d, int n_total, int T)
 {
     int kps, ns;
-    attn_ranges(d, n_total, T, batch, kps, ns);
+    attn_ranges(d, n_total, T, false, ATTN_MERGE_INSIDE, kps, ns);
     return ns == 1 ? 0 : static_cast<size_t>(T) * d.n_q_heads * ns * (REC_HDR + d.head_dim) * sizeof(float);
 }
 
@@ -639,7 +642,7 @@ prima_status launch_attn(const prima_dims &d, const float *q, float *q_rot_out, 
                             const float *rope_tab, __half *K, __half *V, int kv_cap, int n_past, int T, float *o,
                             void *ws, hipStream_t st, const AttnSeqs *seq, AttnMerge merge)
 {
-    AttnArgs a = build_attn_args(d, q, q_rot_out, k_new, v_new, rope_tab, K, V, kv_cap, n_past, T, o, ws, seq);
+    AttnArgs a = build_attn_args(d, q, q_rot_out, k_new, v_new, rope_tab, K, V, kv_cap, n_past, T, o, ws, merge, seq);
     const dim3 grid(a.nsplit, d.n_kv_heads, tile_query_groups(d, T, seq != nullptr));
     a.merge_apart = merge != ATTN_MERGE_INSIDE;
     const prima_status s = launch_attn_kernel(d, grid, a, st);
@@ -653,7 +656,7 @@ prima_status launch_attn(const prima_dims &d, const float *q, float *q_rot_out, 
 
 AttnRecords attn_records(const prima_dims &d, int n_past, int T, void *ws, const AttnSeqs *seq)
 {
-    const AttnArgs a = build_attn_args(d, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, n_past, T, nullptr, ws, seq);
+    const AttnArgs a = build_attn_args(d, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, n_past, T, nullptr, ws, ATTN_MERGE_LATER, seq);
     return AttnRecords{a.part, a.nsplit};
 }
 

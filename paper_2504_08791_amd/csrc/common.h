@@ -141,7 +141,6 @@ prima_status launch_swiglu(float *a, const float *u, int64_t n, hipStream_t st);
 prima_status launch_step_init(float *tab, int T, int D, int n_past, float theta, const int *positions,
                               void *const fill_ptr[4], const size_t fill_bytes[4], const unsigned fill_word[4], hipStream_t st);
 prima_status launch_fill_words(void *a, size_t a_bytes, unsigned a_word, void *b, size_t b_bytes, unsigned b_word, hipStream_t st);
-void attn_ranges(const prima_dims &d, int n_total, int T, bool batch, int &keys_per_split, int &nsplit);
 size_t attn_ws_bytes(const prima_dims &d, int kv_cap, int T);
 // The attention scratch: attn_counter_bytes() whose first word is the flag a bounded wait raises when it gives up
 // (zero before a launch), then the key ranges' records.  Where a launch merges them itself, a record that has not been written holds
@@ -149,8 +148,8 @@ size_t attn_ws_bytes(const prima_dims &d, int kv_cap, int T);
 // (launch_step_init / launch_fill_words); every launch leaves them so.
 size_t attn_counter_bytes(const prima_dims &d, int T);
 constexpr unsigned ATTN_REC_EMPTY = 0x7fa5c3e1u; // a NaN pattern that no arithmetic produces
-// bytes of records (from the start of the record area) that a launch for T tokens over n_total rows uses
-size_t attn_records_bytes(const prima_dims &d, int n_total, int T, bool batch);
+// bytes of records (from the start of the record area) that such a launch for T tokens over n_total rows uses
+size_t attn_records_bytes(const prima_dims &d, int n_total, int T);
 // q: [T][Hq][D].  With rope_tab set, q and k_new are un-rotated and the kernel rotates them and
 // appends k_new / v_new to the caches; otherwise q is used as is and the caches are complete.
 // seq: null, or (a batch of T sequences, one token each) per token its sequence's caches and length; K, V and
@@ -159,6 +158,7 @@ size_t attn_records_bytes(const prima_dims &d, int n_total, int T, bool batch);
 // by the caller's next one (tok_prepare_kernel), which finds them with attn_records() (nsplit 1: none, o is complete).
 struct AttnSeqs;
 enum AttnMerge { ATTN_MERGE_INSIDE = 0, ATTN_MERGE_APART = 1, ATTN_MERGE_LATER = 2 };
+void attn_ranges(const prima_dims &d, int n_total, int T, bool batch, AttnMerge merge, int &keys_per_split, int &nsplit);
 constexpr int ATTN_REC_HDR = 4; // a record: (max, sum, -, -), o[D]
 struct AttnRecords {
     const float *part; // [T][Hq][nsplit][ATTN_REC_HDR + D]

@@ -1003,7 +1003,7 @@ prima_status prima_layer_window_prefill_mixed(const prima_dims *d, const prima_l
     if (T < PRIMA_MAX_TOK) { // the attention launch then merges its key ranges inside: its records marked "not written"
         char *const attn = at<char>(workspace, w.attn);
         const size_t head_bytes = attn_counter_bytes(*d, T); // the records start behind it
-        s = launch_fill_words(attn, head_bytes, 0u, attn + head_bytes, attn_records_bytes(*d, n_past + T, T, false), ATTN_REC_EMPTY, st);
+        s = launch_fill_words(attn, head_bytes, 0u, attn + head_bytes, attn_records_bytes(*d, n_past + T, T), ATTN_REC_EMPTY, st);
         if (s != PRIMA_OK) return s;
     }
     const float *cur = x_in;

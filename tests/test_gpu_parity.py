@@ -199,6 +199,22 @@ def test_attention_peaked_logits(gpu_lib):
     assert rel_err(got.reshape(T, -1), ref.reshape(T, -1)) < ATT_TOL
 
 
+@pytest.mark.parametrize("Hq,Hkv,D", [(32, 8, 128), (8, 2, 64)])
+@pytest.mark.parametrize("rows,T", [(256, 1), (300, 2), (511, 1), (511, 4), (512, 1), (600, 2)])
+def test_attention_of_fewer_than_512_rows_has_one_key_range(gpu_lib, Hq, Hkv, D, rows, T):
+    """Key ranges that a launch of their own has to merge pay from 512 rows on: below, the one range writes the result and the scratch
+    stays as it was."""
+    rng = np.random.default_rng(rows + T)
+    dims = ModelDims(Hq * D, Hq, Hkv, D, 256, 1e4)
+    K, V = (rng.standard_normal((Hkv, rows, D)).astype(np.float16) for _ in range(2))
+    q = rng.standard_normal((T, Hq, D)).astype(np.float32)
+    ws = torch.full((gpu_lib.attn_workspace_bytes(dims, rows, T),), 0xFF, dtype=torch.uint8, device="cuda")
+    got = gpu_lib.attn_decode(dims, _dev(q), _dev(K), _dev(V), rows - T, workspace=ws).cpu().numpy()
+    ref = oracle.attn_decode(dims, q.astype(np.float64), K, V, rows - T, T)
+    assert rel_err(got.reshape(T, -1), ref.reshape(T, -1)) < ATT_TOL
+    assert bool((ws == 0xFF).all()) == (rows < 512)
+
+
 def _window(gpu_lib, cfg, cap, layers_host):
     dev_layers = [{k: _dev(v) for k, v in t.items()} for t in layers_host]
     win = gpu_lib.Window(cfg.dims, dev_layers, cap, T_max=16)
