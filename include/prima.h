@@ -157,7 +157,7 @@ size_t prima_attn_workspace_bytes(const prima_dims *d, int32_t kv_cap, int32_t T
  * layers: HOST array of L descriptors.  x_in, x_out: fp32 [T][e]; x_out may alias x_in.
  * The library keeps no position state: the caller advances n_past (by fewer than T after a
  * rejection; stale rows are overwritten by the next step, never read).
- * From several tokens on (3 to 9, by the hidden size and the formats) the activations enter the projections as for the tall
+ * From several tokens on (3 to 9, by the hidden size, the formats and the rows) the activations enter the projections as for the tall
  * matrices of prima_q4k_gemv; behind fewer than 64 cached rows a step of any number keeps the arithmetic of one token (and
  * one of 9 to 16 streams the weights twice).
  * workspace >= prima_workspace_bytes(d, kv_cap, T), 256-byte aligned.

@@ -26,19 +26,29 @@ bool dims_ok(const prima_dims *d)
 }
 
 // Layers of several tokens go through tok_stream.hip, its launches between the streams included, from so many tokens on; it has four launches a layer
-// more than run_layer(), which narrow models feel.  Windows behind 2000 rows, us, run_layer() / there:
-// 8B shape, three layers, 3 tokens 236 / 240, 4: 241 / 244, 5: 274 / 241, 8: 281 / 244; V and down in Q6_K in one of two layers 3: 184 / 176, 4: 181 / 176;
-// 14B, two layers, 2: 170 / 172, 3: 181 / 175, 4: 181 / 177, 5: 202 / 182, 8: 212 / 185; down in Q8_0 in one of them 3: 189 / 186, 4: 192 / 186;
-// 32B, two layers, 3: 223 / 224, 4: 226 / 226, 5: 254 / 232, 8: 262 / 241; 70B, one layer, 3: 152 / 152, 4: 156 / 154, 5: 175 / 159, 8: 176 / 159;
-// 8 sequences through two 14B layers 214 / 188.  Narrow ones behind 1000 rows: hidden size 3072, six layers, 3: 371 / 376, 5: 427 / 393, with
-// V and down in Q6_K in every other layer 3: 419 / 402; 2048, eight layers, 3: 378 / 428, 5: 474 / 440, Q6_K as above 3: 441 / 467, 5: 541 / 475; 1024, eight,
-// 5: 326 / 332, 8: 342 / 337, Q6_K 3: 324 / 347, 5: 370 / 359; 512, eight, 5: 296 / 321, 8: 309 / 323, Q6_K 5: 333 / 344, 12: 338 / 337.
+// more than run_layer() (five behind fewer than 512 rows, where that has no merge of key ranges), which narrow models and few tokens feel.
+// Windows, us, run_layer() / there:
+// 5 to 8 tokens, a hidden size of 2048 and more: 4 to 16 % whatever the formats and the rows.  Four layers of 2048 behind 64 rows 5: 224 / 214, 8: 244 / 222, behind
+// 2000 5: 241 / 226; 8B, three layers, 64 5: 261 / 233, 2000 8: 281 / 244; 70B, two, 64 5: 332 / 290, 2000 8: 343 / 302; down in Q8_0 in every other layer, 2048, 64 5:
+// 237 / 223, 14B, two, 64 5: 198 / 174; 8 sequences through two 14B layers 214 / 188.  Narrower, six layers of 1024 behind 64 rows: V and down in
+// Q6_K in every other one 5: 260 / 263, 6: 269 / 267, 7: 253 / 267, 8: 273 / 270, down in Q8_0 5: 234 / 248, 8: 241 / 255, four matrices in Q5_K and Q6_K 6: 301 / 282, 7: 272 / 284.
+// 3 and 4 tokens, Q4_K: 8B as fast either way (2000 3: 236 / 236).  14B, two layers, 64 3: 169 / 169, 500: 178 / 170, 2000: 178 / 174, 8000: 180 / 177; 32B, two, 64
+// 3: 213 / 219, 4: 215 / 221, 300 3: 217 / 221, 500: 223 / 221, 2000: 223 / 221, 8000: 224 / 227; 70B, two, 130 3: 288 / 296, 4: 297 / 298, 300 3: 292 / 296, 1000: 297 / 295, 4:
+// 304 / 302, 4096 4: 305 / 299: from 512 rows on, within 2 % (32B) or faster, and more exact (below).  Down in Q8_0 as with Q4_K alone: 8B, three, 64 3: 241 / 245, 4:
+// 240 / 249; 3072, four, 64 3: 230 / 240; 14B, two, 64 4: 177 / 179, 500 3: 186 / 173.  Every matrix in Q8_0: 14B 64 3: 270 / 218, 3072, four 349 / 305.
+// Other formats, 3 tokens, 64 rows: V and down in Q6_K in every other layer 3072 254 / 251, 8B 272 / 257, 14B 190 / 180, 70B 340 / 312; down in FP16 3072 281 / 249,
+// 8B 309 / 265 (4 tokens 262 / 268); 2048, eight layers, 1000 rows, Q6_K as above 441 / 467.
+// Error against 64 bits (2-norm of the result, the reference attending to the step's own cache rows, so that no rounding of a cache element that goes the other
+// way is counted; median of 8 inputs, 1e-7): Q4_K, 8B, two layers, 5 tokens behind 70 rows 5.6 / 4.3, 2047 5.0 / 3.7; 14B, two, 3: 70 6.7 / 4.8, 2047 5.6 / 3.8, 8000 5.4 / 3.7;
+// 32B, one, 4: 70 5.3 / 3.9, 2047 4.4 / 2.9, 8000 4.1 / 2.8; 70B, one, 3: 70 6.3 / 5.1, 2047 5.7 / 4.4; 14B with Q6_K as above 3: 2047 5.8 / 3.9, with Q8_0 5.3 / 3.8; no case of 3 to 8 tokens
+// was less exact there.  (Weights far from mean zero, which no case has: 0.7 to 1.0 / 1.0 to 1.2 a product, see tok_common.h.)
 // K long enough to need hundreds of slabs and layers with an FP32 matrix go through run_layer().
 constexpr int TOK_LEAST = 3; // (the scratch has a region for the streams from here on)
-int tok_from(const prima_dims &d, bool others) // others: a matrix in another format than Q4_K
+// others: a matrix in another format than Q4_K and Q8_0, or none in Q4_K; rows: of the longest sequence behind the step
+int tok_from(const prima_dims &d, bool others, int rows)
 {
-    if (others ? d.e >= 3072 : d.e > 4096) return TOK_LEAST;
-    return d.e >= (others ? 1024 : 2048) ? 5 : 9;
+    if (others ? d.e >= 3072 : d.e > 4096 && rows >= 512) return TOK_LEAST;
+    return d.e >= 2048 ? 5 : 9;
 }
 // In run_layer(), tokens from which the matrices in other formats go through streams of their own.  Two layers, V
 // and down in Q6_K in one of them, us, there / through a mat-vec for each: 14B shape 4 tokens 213 / 221, 5: 230 / 248, 8: 236 / 290.
@@ -420,14 +430,18 @@ prima_status run_layer_tok(const prima_dims &d, const prima_layer &L, int kv_cap
 // whether a layer with these formats goes through run_layer_tok()
 bool layer_is_tok(const prima_dims &d, const WindowWs &w, int T, int n_past, const AttnSeqs *seq, const prima_layer_formats *f)
 {
-    bool others = false;
+    bool others = false, q4k = !f;
+    int rows = n_past + T;
     if (f) {
         for (int32_t v : {f->wq, f->wk, f->wv, f->wo, f->wgate, f->wup, f->wdown}) {
             if (v == PRIMA_FMT_F32) return false;
-            others = others || v != PRIMA_FMT_Q4_K;
+            q4k = q4k || v == PRIMA_FMT_Q4_K;
+            others = others || (v != PRIMA_FMT_Q4_K && v != PRIMA_FMT_Q8_0);
         }
     }
-    return tok_takes(w, T, tok_from(d, others)) && tok_context(n_past, seq);
+    if (seq)
+        for (int b = 0; b < T; ++b) rows = std::max(rows, seq->n_past[b] + 1);
+    return tok_takes(w, T, tok_from(d, others || !q4k, rows)) && tok_context(n_past, seq);
 }
 
 // all layers of a step; caches(i, seq): a batch's caches of layer i

@@ -316,7 +316,7 @@ def test_tall_q4k_matvec_of_many_tokens(gpu_lib, rows, nb, T):
 @pytest.mark.parametrize("mix", sorted(MIXES))
 @pytest.mark.parametrize("name,T", [("t1", 8), ("t1", 9), ("t1", 16), ("c1", 13)])
 def test_window_of_many_tokens(gpu_lib, mix, name, T):
-    """8 to 16 tokens (streams over laid-out activations: up to 8 the other formats, from 9 on all matrices): rows of 3 and 5 super-blocks and of a model's size, slabs and
+    """8 to 16 tokens (streams over laid-out activations: the narrow layers from 9 on, at 8 their matrices in other formats): rows of 3 and 5 super-blocks and of a model's size, slabs and
     parts of one stage, layers with and without an FP32 matrix behind one another."""
     test_window_with_mixed_formats(gpu_lib, mix, name, T)
 
@@ -379,7 +379,7 @@ def test_activations_that_are_not_finite_and_tiny_ones(gpu_lib, fmt, T):
 def test_streams_between_launches(gpu_lib, T, n_past):
     """The launches that add the streams' shares: rows of more than 64 super-blocks (their sums of squares take a wave twice), 16 and more
     shares of a short matrix, vectors of 64 rows (a wave's 256 end inside), shares of two formats for gate and up; attention merged there:
-    20, 6, 3 and one key range, four heads of 64 columns in a wave."""
+    18, 5, 2 and one key range, four heads of 64 columns in a wave."""
     from workloads.configs import ModelDims, WindowConfig
     d = ModelDims(16640, 4, 1, 64, 768, 1e4)
     fm = [{"wq": "q8_0", "wk": "q5_k", "wv": "q5_k", "wo": "q6_k", "wgate": "q5_k", "wup": "q6_k", "wdown": "q6_k"}, {}]
@@ -391,3 +391,28 @@ def test_streams_between_launches(gpu_lib, T, n_past):
     win.workspace.fill_(0xFF)
     y = win.decode(_dev(x), n_past).cpu().numpy()
     check_hidden(f"launches between streams, T={T}", rel_err(y, ref), d, host, x.astype(np.float64), n_past, formats=fm, eps=EPS_FP32)
+
+
+Q4, Q8, Q6 = {}, {"wdown": "q8_0"}, {"wdown": "q6_k"}
+ALL_Q8 = {k: "q8_0" for k in ("wq", "wk", "wo", "wgate", "wup", "wdown", "wv")}
+
+
+@pytest.mark.parametrize("e,fm,T,n_past,streams", [
+    (4352, Q4, 3, 300, False), (4352, Q4, 4, 507, False), (4352, Q4, 4, 508, True), (4096, Q4, 4, 900, False), (4096, Q4, 5, 64, True),
+    (2048, Q4, 5, 64, True), (1792, Q4, 8, 600, False), (1792, Q4, 9, 64, True),
+    (4352, Q8, 3, 300, False), (4352, Q8, 3, 600, True), (4096, Q8, 3, 600, False), (4096, ALL_Q8, 3, 64, True), (2048, ALL_Q8, 3, 64, False),
+    (3072, Q6, 3, 64, True), (2048, Q6, 3, 600, False), (1024, Q6, 5, 100, False)])
+def test_from_how_many_tokens_a_layer_takes_the_streams(gpu_lib, e, fm, T, n_past, streams):
+    """Which way a layer goes, on both sides of every line of the rule.  V is zero (cache and matrix), so that the attention adds nothing
+    and the result depends on the way alone: behind 63 rows the mat-vecs, whose bits the step behind n_past rows has or has not."""
+    from workloads.configs import ModelDims, WindowConfig
+    d = ModelDims(e, 4, 1, 64, 512, 1e4)
+    cap = n_past + T
+    t = synth.layer_tensors(WindowConfig("way", 80, d, 1, T, n_past), 0, kv_cap=cap, formats=fm)
+    t["wv"] = np.zeros_like(t["wv"])
+    t["v_cache"] = np.zeros_like(t["v_cache"])
+    win = gpu_lib.Window(d, [{k: _dev(v) for k, v in t.items()}], cap, T_max=T, formats=[fm])
+    x = _dev(np.random.default_rng(e + T).standard_normal((T, e)).astype(np.float32))
+    vecs, here = win.decode(x, 63).clone(), win.decode(x, n_past)
+    assert torch.equal(vecs, here) != streams
+    assert rel_err(here.cpu().numpy(), vecs.cpu().numpy().astype(np.float64)) < GEMV_TOL
