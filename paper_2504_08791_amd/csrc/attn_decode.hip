@@ -609,9 +609,11 @@ static int tile_num_splits(const prima_dims &d, int n_total, int T, bool batch, 
     // six layers of hidden size 1024 450: 184.3 / 178.3, 512: 182.8 / 180.9, 600: 180.2 / 181.0; two of 70B 256: 220.5 / 216.8, 500: 221.0 / 220.8,
     // 512: 220.0 / 222.1.  Merged by a launch that is there anyway: 16 sequences, two 14B layers 256: 195.6 / 197.9, 500: 199.8 / 204.3.
     const int by_len = merge == ATTN_MERGE_APART && n_total < 512 ? 1 : n_total / ((merge == ATTN_MERGE_INSIDE ? 32 : 16) * ATT_WAVES);
-    // About one workgroup per compute unit (128 and 192 are slower; 512 with the merge apart: 30001 rows, one token 24.4 -> 27.0 us, 70B shape, 8
-    // tokens behind 8192, two layers 321.5 -> 329.8, 16 sequences, three 14B layers 338 -> 348)
-    const int by_grid = (256 + wgs - 1) / wgs;
+    // At most one workgroup per compute unit: a few more (rounded up: 264 of 24 query groups and KV heads) and some units have two, for which all
+    // wait.  Attention, us, rounded up / down: 14B, 7 tokens behind 2000 rows 14.7 / 13.1, 8000: 25.3 / 18.2; 70B, 13 behind 4000 27.2 / 19.9; 3 sequences of 2000 rows
+    // through three 8B layers 241.6 / 232.4 (238.3 with ranges twice as long).  512: 30001 rows, one token 24.4 -> 27.0, 16 sequences, three 14B layers
+    // 338 -> 348; 128 and 192 are slower too.
+    const int by_grid = 256 / wgs;
     int ns = by_len < by_grid ? by_len : by_grid;
     if (ns < 1) ns = 1;
     if (ns > MAX_SPLITS) ns = MAX_SPLITS;

@@ -215,6 +215,25 @@ def test_attention_of_fewer_than_512_rows_has_one_key_range(gpu_lib, Hq, Hkv, D,
     assert bool((ws == 0xFF).all()) == (rows < 512)
 
 
+@pytest.mark.parametrize("Hq,Hkv,T", [(40, 8, 7), (64, 8, 13), (32, 8, 9), (8, 2, 9), (36, 6, 16), (64, 64, 5), (12, 3, 16)])
+def test_key_ranges_leave_a_workgroup_per_compute_unit(gpu_lib, Hq, Hkv, T):
+    """The key ranges' workgroups are 256 at most (their number from the records written: two words and D columns per query and range)
+    and, that far, as many as there can be; the result is the oracle's."""
+    D, n_past = 64, 8000
+    rng = np.random.default_rng(Hq + T)
+    dims = ModelDims(Hq * D, Hq, Hkv, D, 256, 1e4)
+    K, V = (rng.standard_normal((Hkv, n_past + T, D)).astype(np.float16) for _ in range(2))
+    q = rng.standard_normal((T, Hq, D)).astype(np.float32)
+    ws = torch.full((gpu_lib.attn_workspace_bytes(dims, n_past + T, T),), 0xFF, dtype=torch.uint8, device="cuda")
+    got = gpu_lib.attn_decode(dims, _dev(q), _dev(K), _dev(V), n_past, workspace=ws).cpu().numpy()
+    pick = [0, Hq // Hkv, Hq - 1]
+    ref = oracle.attn_decode(dims, q.astype(np.float64), K, V, n_past, T)
+    assert rel_err(got[:, pick].reshape(T, -1), ref.reshape(T, Hq, D)[:, pick].reshape(T, -1)) < ATT_TOL
+    ranges, rest = divmod(int((ws.view(torch.int32) != -1).sum()), T * Hq * (D + 2))
+    groups = Hkv * -(-(Hq // Hkv * T) // 16)
+    assert rest == 0 and ranges * groups <= 256 < (ranges + 1) * groups, (ranges, rest)
+
+
 def _window(gpu_lib, cfg, cap, layers_host):
     dev_layers = [{k: _dev(v) for k, v in t.items()} for t in layers_host]
     win = gpu_lib.Window(cfg.dims, dev_layers, cap, T_max=16)
