@@ -187,11 +187,8 @@ prima_status prima_layer_window_decode_batch(const prima_dims *d, const prima_la
                                              void *workspace, size_t workspace_bytes, void *hip_stream);
 
 /*
- * Some kernels of a window step wait, inside the launch, for records that other workgroups of the same launch write
- * (the workgroup that merges the key ranges of the attention, the one that adds the slabs of a long mat-vec).  These
- * waits are bounded; one that gives up (it never should) raises a flag in the workspace and the step's results are
- * invalid.  prima_window_check() waits for `hip_stream` (it SYNCHRONISES) and returns PRIMA_E_DEVICE if a wait of the
- * last window call on this workspace gave up, else PRIMA_OK.
+ * Waits for `hip_stream` (it SYNCHRONISES) and returns PRIMA_E_DEVICE if that reports an error of the last window call on this
+ * workspace, else PRIMA_OK.  (No kernel of a window step waits for other workgroups of its launch, so none can give up a wait.)
  */
 prima_status prima_window_check(const prima_dims *d, int32_t kv_cap, int32_t T,
                                 const void *workspace, size_t workspace_bytes, void *hip_stream);
@@ -205,13 +202,14 @@ prima_status prima_window_check(const prima_dims *d, int32_t kv_cap, int32_t T,
  * ends with a second ordinary step: x_out and rows n_past .. n_past+T-1 of every cache are then
  * bit-equal to what prima_layer_window_decode leaves.  ms_by_kind and launches_by_kind are HOST
  * arrays of PRIMA_N_KINDS entries (milliseconds for the L replays of the kind; their number, L.  A replay is one launch, two
- * where slabs of K are added by a second one, and two or three from 9 tokens on, where activations are laid out and shares added
- * by launches of their own).
+ * where slabs of K are added or the attention's key ranges merged by a second one, and two or three where several tokens go
+ * through the weight streams (prima_layer_window_decode), with activations laid out and shares added by launches of their own; the
+ * key ranges are then merged in the output projection's).
  */
 enum {
     PRIMA_K_QKV = 0,     /* Q/K/V projections with fused RMSNorm */
     PRIMA_K_ROPE_KV = 1, /* unused: RoPE + fp16 KV append run inside the attention kernel */
-    PRIMA_K_ATTN = 2,    /* attention: partial (with RoPE + KV append) and merge */
+    PRIMA_K_ATTN = 2,    /* attention: partial (with RoPE + KV append) and merge (see above) */
     PRIMA_K_WO = 3,      /* output projection + residual */
     PRIMA_K_GATE_UP = 4, /* gate/up projections with fused RMSNorm */
     PRIMA_K_DOWN = 5,    /* down projection with fused SwiGLU + residual */

@@ -320,7 +320,7 @@ class Window:
         return x_out
 
     def check(self, T=1):
-        """Waits for the stream; raises if a bounded wait inside a kernel of the last step gave up."""
+        """Waits for the stream; raises if that reports an error of the last step."""
         _ffi.check(_ffi.lib().prima_window_check(C.byref(self.dims), self.kv_cap, T, _ptr(self.workspace),
                                                  self.workspace.numel(), _stream()), "prima_window_check")
 

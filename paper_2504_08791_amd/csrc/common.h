@@ -136,16 +136,15 @@ prima_status launch_rope_table(float *tab, int T, int D, int n_past, float theta
 
 prima_status launch_stream_read(const void *src, size_t bytes, void *sink, hipStream_t st, bool nt);
 prima_status launch_swiglu(float *a, const float *u, int64_t n, hipStream_t st);
-// the RoPE table [T][D/2] of (cos, sin) and up to four regions filled with a word each (null: none) in one launch.
+// the RoPE table [T][D/2] of (cos, sin), and `zero` cleared, in one launch.
 // positions: null (token t sits at n_past + t) or T positions, one per token (a batch of sequences)
-prima_status launch_step_init(float *tab, int T, int D, int n_past, float theta, const int *positions,
-                              void *const fill_ptr[4], const size_t fill_bytes[4], const unsigned fill_word[4], hipStream_t st);
+prima_status launch_step_init(float *tab, int T, int D, int n_past, float theta, const int *positions, void *zero, size_t zero_bytes, hipStream_t st);
 prima_status launch_fill_words(void *a, size_t a_bytes, unsigned a_word, void *b, size_t b_bytes, unsigned b_word, hipStream_t st);
 size_t attn_ws_bytes(const prima_dims &d, int kv_cap, int T);
 // The attention scratch: attn_counter_bytes() whose first word is the flag a bounded wait raises when it gives up
 // (zero before a launch), then the key ranges' records.  Where a launch merges them itself, a record that has not been written holds
 // ATTN_REC_EMPTY in every word: before the first such launch the records a launch will use (attn_records_bytes) must be filled with it
-// (launch_step_init / launch_fill_words); every launch leaves them so.
+// (launch_fill_words); every launch leaves them so.
 size_t attn_counter_bytes(const prima_dims &d, int T);
 constexpr unsigned ATTN_REC_EMPTY = 0x7fa5c3e1u; // a NaN pattern that no arithmetic produces
 // bytes of records (from the start of the record area) that such a launch for T tokens over n_total rows uses
@@ -177,10 +176,6 @@ prima_status launch_attn_prompt(const prima_dims &d, const float *q, __half *K, 
 // launch_rope_table
 prima_status launch_rope_append(const prima_dims &d, float *q, const float *k, const float *v, const float *tab,
                                 __half *K, __half *V, int kv_cap, int n_past, int T, hipStream_t st);
-
-// Bounded waits inside kernels (a workgroup that waits for records of other workgroups of its launch) raise this
-// flag when they give up; it lives in the window scratch and prima_window_check reports it.
-constexpr size_t WAIT_FLAG_BYTES = 256; // the flag is the first word
 
 // 16 bytes per lane from global memory straight into LDS: lane l writes bytes [16 l, 16 l + 16) of the
 // 1 KiB at LDS byte address lds_addr (wave-uniform, goes through M0).  Written as inline assembly on

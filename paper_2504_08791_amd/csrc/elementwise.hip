@@ -1,5 +1,7 @@
 // RoPE angle table of a window step.  (RMSNorm and SwiGLU are fused into the mat-vec that consumes
 // them; the rotation itself and the fp16 KV append are fused into the attention kernel.)
+#include <algorithm>
+
 #include "common.h"
 
 namespace prima {
@@ -8,22 +10,14 @@ struct RopePositions {
     int pos[PRIMA_MAX_TOK];
 };
 
-// Everything a window step needs before its first layer, in one launch: counter regions zeroed, the attention's
-// records marked "not written" and the RoPE table, tab[t][i] = (cos, sin) of pos_t * theta^(-2i/D) with pos_t = n_past + t (or the token's own position in
+// Everything a window step needs before its first layer, in one launch: the mat-vec's counters zeroed and the RoPE table,
+// tab[t][i] = (cos, sin) of pos_t * theta^(-2i/D) with pos_t = n_past + t (or the token's own position in
 // a batch of sequences), evaluated in fp64: at positions of several thousand an fp32 angle would already be off
 // by ~1e-4 rad.
-struct FillRegions {
-    unsigned *p[4];
-    unsigned n[4]; // 32-bit words
-    unsigned v[4]; // the word each region is filled with
-};
-__global__ void step_init_kernel(float2 *tab, int T, int half, RopePositions p, double theta, FillRegions z)
+__global__ void step_init_kernel(float2 *tab, int T, int half, RopePositions p, double theta, unsigned *zero, unsigned n_zero)
 {
     const unsigned idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx < z.n[0]) z.p[0][idx] = z.v[0];
-    if (idx < z.n[1]) z.p[1][idx] = z.v[1];
-    if (idx < z.n[2]) z.p[2][idx] = z.v[2];
-    if (idx < z.n[3]) z.p[3][idx] = z.v[3];
+    if (idx < n_zero) zero[idx] = 0u;
     if (idx >= static_cast<unsigned>(T * half)) return;
     const int t = idx / half, i = idx - t * half;
     int pos = 0;
@@ -33,21 +27,14 @@ __global__ void step_init_kernel(float2 *tab, int T, int half, RopePositions p, 
     tab[idx] = make_float2(static_cast<float>(cos(ang)), static_cast<float>(sin(ang)));
 }
 
-prima_status launch_step_init(float *tab, int T, int D, int n_past, float theta, const int *positions,
-                              void *const fill_ptr[4], const size_t fill_bytes[4], const unsigned fill_word[4], hipStream_t st)
+prima_status launch_step_init(float *tab, int T, int D, int n_past, float theta, const int *positions, void *zero, size_t zero_bytes, hipStream_t st)
 {
     RopePositions p{};
     for (int t = 0; t < T && t < PRIMA_MAX_TOK; ++t) p.pos[t] = positions ? positions[t] : n_past + t;
-    FillRegions z{};
-    unsigned n = static_cast<unsigned>(T * (D / 2));
-    for (int k = 0; k < 4; ++k) {
-        z.p[k] = static_cast<unsigned *>(fill_ptr[k]);
-        z.n[k] = fill_ptr[k] ? static_cast<unsigned>(fill_bytes[k] / sizeof(unsigned)) : 0u;
-        z.v[k] = fill_word[k];
-        n = z.n[k] > n ? z.n[k] : n;
-    }
+    const unsigned n_zero = static_cast<unsigned>(zero_bytes / sizeof(unsigned));
+    const unsigned n = std::max(static_cast<unsigned>(T * (D / 2)), n_zero);
     hipLaunchKernelGGL(step_init_kernel, dim3((n + 255) / 256), dim3(256), 0, st,
-                       reinterpret_cast<float2 *>(tab), T, D / 2, p, static_cast<double>(theta), z);
+                       reinterpret_cast<float2 *>(tab), T, D / 2, p, static_cast<double>(theta), static_cast<unsigned *>(zero), n_zero);
     return last_launch_status();
 }
 

@@ -13,7 +13,7 @@ using namespace prima;
 namespace {
 
 struct WindowWs {
-    size_t q, k, v, o, h, a, u, xb0, xb1, rope, attn, gemv, gemv_bytes, arrivals_bytes, sync, total;
+    size_t q, k, v, o, h, a, u, xb0, xb1, rope, attn, gemv, gemv_bytes, arrivals_bytes, total;
     // 4 and more tokens: activations laid out for Q4_K and for the other formats, their sums of squares, the shares of K
     size_t tok_rec[2], tok_ss, tok_part, tok_part_floats;
 };
@@ -115,7 +115,6 @@ WindowWs carve(const prima_dims &d, int kv_cap, int T)
     }
     w.gemv = take(region);
     w.tok_part = w.gemv + round_up(w.arrivals_bytes, 256);
-    w.sync = take(WAIT_FLAG_BYTES);
     if (tok) {
         const int64_t widest = std::max<int64_t>({d.e, static_cast<int64_t>(qd), d.ffn});
         for (size_t &r : w.tok_rec) r = take(tok_rec_bytes(widest, T));
@@ -471,14 +470,10 @@ prima_status run_layers(const prima_dims &d, const prima_layer *layers, const pr
     return PRIMA_OK;
 }
 
-// before the first layer of a step: RoPE table, the counters of the mat-vec and attention scratch zeroed (and, where
-// asked, the error flag that prima_window_check reads): one launch
-prima_status step_init(const prima_dims &d, void *ws, const WindowWs &w, int T, int n_past, const int *positions, bool with_sync, hipStream_t st)
+// before the first layer of a step: RoPE table, the counters of the mat-vec zeroed; one launch
+prima_status step_init(const prima_dims &d, void *ws, const WindowWs &w, int T, int n_past, const int *positions, hipStream_t st)
 {
-    void *const fp[4] = {at<char>(ws, w.gemv), at<char>(ws, w.attn), with_sync ? at<char>(ws, w.sync) : nullptr, nullptr};
-    const size_t fb[4] = {w.arrivals_bytes, attn_counter_bytes(d, T), WAIT_FLAG_BYTES, 0};
-    const unsigned fw[4] = {0u, 0u, 0u, 0u};
-    return launch_step_init(at<float>(ws, w.rope), T, d.head_dim, n_past, d.rope_theta, positions, fp, fb, fw, st);
+    return launch_step_init(at<float>(ws, w.rope), T, d.head_dim, n_past, d.rope_theta, positions, at<char>(ws, w.gemv), w.arrivals_bytes, st);
 }
 
 prima_status check_window_args(const prima_dims *d, int32_t kv_cap, int32_t n_past, int32_t T,
@@ -886,7 +881,7 @@ prima_status prima_layer_window_decode(const prima_dims *d, const prima_layer *l
         if ((s = check_layer(layers[i])) != PRIMA_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const WindowWs w = carve(*d, kv_cap, T);
-    s = step_init(*d, workspace, w, T, n_past, nullptr, true, st);
+    s = step_init(*d, workspace, w, T, n_past, nullptr, st);
     if (s != PRIMA_OK) return s;
     return run_layers(*d, layers, nullptr, L, kv_cap, n_past, T, x_in, x_out, workspace, w, st, [](int) { return static_cast<const AttnSeqs *>(nullptr); });
 }
@@ -908,7 +903,7 @@ prima_status prima_layer_window_decode_mixed(const prima_dims *d, const prima_la
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const WindowWs w = carve(*d, kv_cap, T);
-    s = step_init(*d, workspace, w, T, n_past, nullptr, true, st);
+    s = step_init(*d, workspace, w, T, n_past, nullptr, st);
     if (s != PRIMA_OK) return s;
     return run_layers(*d, layers, formats, L, kv_cap, n_past, T, x_in, x_out, workspace, w, st, [](int) { return static_cast<const AttnSeqs *>(nullptr); });
 }
@@ -950,7 +945,7 @@ prima_status prima_layer_window_decode_batch_mixed(const prima_dims *d, const pr
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const WindowWs w = carve(*d, kv_cap, B);
-    s = step_init(*d, workspace, w, B, 0, n_past, false, st);
+    s = step_init(*d, workspace, w, B, 0, n_past, st);
     if (s != PRIMA_OK) return s;
     __half *kc[PRIMA_MAX_TOK], *vc[PRIMA_MAX_TOK];
     const AttnSeqs seq{n_past, kc, vc};
@@ -1004,7 +999,7 @@ prima_status prima_layer_window_prefill_mixed(const prima_dims *d, const prima_l
         void *dws = at<char>(workspace, w.dec_base);
         for (int t0 = 0; t0 < T; t0 += PRIMA_MAX_TOK) {
             const int Tc = std::min<int>(PRIMA_MAX_TOK, T - t0);
-            prima_status cs = step_init(*d, dws, w.dec, Tc, n_past + t0, nullptr, false, st);
+            prima_status cs = step_init(*d, dws, w.dec, Tc, n_past + t0, nullptr, st);
             if (cs != PRIMA_OK) return cs;
             cs = run_layers(*d, layers, formats, L, kv_cap, n_past + t0, Tc, x_in + static_cast<int64_t>(t0) * d->e, x_out + static_cast<int64_t>(t0) * d->e,
                             dws, w.dec, st, [](int) { return static_cast<const AttnSeqs *>(nullptr); });
@@ -1036,11 +1031,7 @@ prima_status prima_window_check(const prima_dims *d, int32_t kv_cap, int32_t T, 
     if (!dims_ok(d) || T < 1 || T > PRIMA_MAX_TOK || kv_cap < 1) return PRIMA_E_SHAPE;
     const WindowWs w = carve(*d, kv_cap, T);
     if (workspace_bytes < w.total) return PRIMA_E_WORKSPACE;
-    if (hipStreamSynchronize(static_cast<hipStream_t>(hip_stream)) != hipSuccess) return PRIMA_E_DEVICE;
-    int flag = 0, attn_flag = 0; // the flags of the mat-vec's and the attention's bounded waits
-    if (hipMemcpy(&flag, static_cast<const char *>(workspace) + w.sync, sizeof(flag), hipMemcpyDeviceToHost) != hipSuccess) return PRIMA_E_DEVICE;
-    if (hipMemcpy(&attn_flag, static_cast<const char *>(workspace) + w.attn, sizeof(attn_flag), hipMemcpyDeviceToHost) != hipSuccess) return PRIMA_E_DEVICE;
-    return (flag | attn_flag) == 0 ? PRIMA_OK : PRIMA_E_DEVICE;
+    return hipStreamSynchronize(static_cast<hipStream_t>(hip_stream)) == hipSuccess ? PRIMA_OK : PRIMA_E_DEVICE;
 }
 
 prima_status prima_layer_window_decode_profiled(const prima_dims *d, const prima_layer *layers, int32_t L,
@@ -1059,7 +1050,7 @@ prima_status prima_layer_window_decode_profiled(const prima_dims *d, const prima
     const WindowWs w = carve(*d, kv_cap, T);
     // one ordinary step first: every intermediate buffer then holds this step's values
     auto ordinary_step = [&]() {
-        prima_status os = step_init(*d, workspace, w, T, n_past, nullptr, false, st);
+        prima_status os = step_init(*d, workspace, w, T, n_past, nullptr, st);
         if (os == PRIMA_OK)
             os = run_layers(*d, layers, nullptr, L, kv_cap, n_past, T, x_in, x_out, workspace, w, st, [](int) { return static_cast<const AttnSeqs *>(nullptr); });
         return os;
@@ -1114,7 +1105,7 @@ prima_status prima_layer_decode_taps(const prima_dims *d, const prima_layer *lay
     if ((s = check_layer(*layer)) != PRIMA_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const WindowWs w = carve(*d, kv_cap, T);
-    s = step_init(*d, workspace, w, T, n_past, nullptr, false, st);
+    s = step_init(*d, workspace, w, T, n_past, nullptr, st);
     if (s != PRIMA_OK) return s;
     if (layer_is_tok(*d, w, T, n_past, nullptr, nullptr))
         return run_layer_tok(*d, *layer, kv_cap, n_past, T, x_in, x_out, workspace, w, st, tap_q, tap_o, tap_h, tap_a, -1, nullptr, nullptr, false, nullptr, nullptr);

@@ -82,6 +82,25 @@ def test_prefill_vs_oracle(gpu_lib, route, name, T, n_past):
                 assert rel_err(g[:, n_past:n_past + T].reshape(1, -1), r[:, n_past:n_past + T].reshape(1, -1)) < 1e-3
 
 
+@pytest.mark.parametrize("name,T,n_past", [("t0", 7, 700), ("t1", 15, 1500), ("t2", 1, 505), ("t2", 12, 4000), ("t2", 1, 9000)])
+def test_short_prompts_merge_several_key_ranges_inside_the_launch(gpu_lib, matrix_product_route, name, T, n_past):
+    """Fewer than 16 tokens on the matrix-product route: the workgroup of the first key range merges the others' records (2, 5, 1, 15 and 34
+    ranges, the last more than one request brings; queries for fewer and for more waves than a workgroup has) and marks them
+    for the next layer's launch.  Twice with the same bits: the second call finds the scratch as the first left it."""
+    cfg = TINY[name].with_(T=T, n_past=n_past)
+    cap = n_past + T
+    host = [synth.layer_tensors(cfg, l, kv_cap=cap) for l in range(cfg.n_layers)]
+    win, _ = _window(gpu_lib, cfg, cap, host)
+    x = synth.window_input(cfg)
+    print("case", name, T, n_past, flush=True)
+    first = win.prefill(_dev(x), n_past).clone()
+    again = win.prefill(_dev(x), n_past)
+    assert torch.equal(first, again)
+    ref = _oracle_prompt(cfg.dims, host, x, n_past)
+    check_hidden(f"short prompt {name} T={T} n_past={n_past}", rel_err(first.cpu().numpy(), ref), cfg.dims, host, x.astype(np.float64), n_past,
+                 eps=PREFILL_EPS)
+
+
 def test_prefill_fills_the_cache_to_its_last_row(gpu_lib, route):
     """n_past + T == kv_cap: the last piece ends on the cache's last row; a token count with full pieces only and one
     with a rest."""
