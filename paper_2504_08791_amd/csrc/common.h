@@ -165,7 +165,7 @@ struct AttnRecords {
 };
 prima_status launch_attn(const prima_dims &d, const float *q, float *q_rot_out, const float *k_new, const float *v_new,
                          const float *rope_tab, __half *K, __half *V, int kv_cap, int n_past, int T, float *o,
-                         void *ws, hipStream_t st, const AttnSeqs *seq = nullptr, AttnMerge merge = ATTN_MERGE_INSIDE);
+                         void *ws, hipStream_t st, const AttnSeqs *seq, AttnMerge merge);
 // where that launch's records lie
 AttnRecords attn_records(const prima_dims &d, int n_past, int T, void *ws, const AttnSeqs *seq);
 

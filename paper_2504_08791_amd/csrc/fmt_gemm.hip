@@ -458,6 +458,9 @@ prima_status launch_fm(FmtGemmArgs a, void *part, size_t part_bytes, hipStream_t
     // Shares of K (at least 4 super-blocks each, as far as the scratch holds them): rounds of workgroups times a share's super-blocks, about
     // 7 us each at 64 tokens and 14 at 128, against the shares' way to memory and back (4 TB/s).  (As many as fit the device at once
     // left a quarter of it idle where they do not come out even: 4096 x 14336 in Q6_K, 333 tokens, two shares 227 us and 6 for their sum, five 200 and 7.)
+    // The two figures serve every format: one layer of 8B, 14B and 70B shapes, 40 to 900 tokens, us, that rule / this one where they differ: down in Q5_K 8B 333
+    // tokens (two shares / five) 576 / 553, Q8_0 576 / 561, FP16 604 / 587; 14B 400 (one / three) Q5_K 934 / 837, Q6_K 958 / 855, Q8_0 920 / 834, FP16 949 / 848; 70B
+    // 180 (two / five) Q5_K 1034 / 971, FP16 1057 / 1018; every matrix, 14B, 180 tokens Q5_K 623 / 581, Q8_0 652 / 602, 512 tokens 1364 / 1197, 1357 / 1202.
     a.ksplit = 1;
     if (part && a.T <= 65535) {
         const int64_t share_bytes = static_cast<int64_t>(a.T) * a.n_rows * static_cast<int64_t>(sizeof(float));

@@ -381,7 +381,7 @@ prima_status launch_fmt(StreamArgs &a, size_t part_floats, int &n_parts, bool pl
 {
     const int nt = tok_slots(a.T);
     const StreamPlan p = plan_stream<FMT>(a.n_tiles, a.nb, nt);
-    if (p.n_slabs == 0 || nt < 4) return PRIMA_E_SHAPE;
+    if (p.n_slabs == 0) return PRIMA_E_SHAPE;
     a.n_slabs = p.n_slabs; a.slab = p.slab; a.ks_shift = p.ks_shift; a.rounds = p.rounds;
     a.per_round = (a.n_tiles + p.rounds - 1) / p.rounds;
     n_parts = p.n_slabs << p.ks_shift;

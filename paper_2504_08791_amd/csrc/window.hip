@@ -584,7 +584,8 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
     __half *Kc = static_cast<__half *>(L.k_cache), *Vc = static_cast<__half *>(L.v_cache);
     PRIMA_TRY(launch_rope_append(d, q, k, v, at<float>(ws, w.rope), Kc, Vc, kv_cap, n_past, T, st));
     if (T >= PRIMA_MAX_TOK) PRIMA_TRY(launch_attn_prompt(d, q, Kc, Vc, kv_cap, n_past, T, o, st));
-    else PRIMA_TRY(launch_attn(d, q, nullptr, nullptr, nullptr, nullptr, Kc, Vc, kv_cap, n_past, T, o, at<char>(ws, w.attn), st));
+    else PRIMA_TRY(launch_attn(d, q, nullptr, nullptr, nullptr, nullptr, Kc, Vc, kv_cap, n_past, T, o, at<char>(ws, w.attn), st, nullptr,
+                               ATTN_MERGE_INSIDE));
     PRIMA_TRY(product(f_o, L.wo, e, qd, o, nullptr, x, h, false, true));
     if (f_g == PRIMA_FMT_Q4_K && f_u == PRIMA_FMT_Q4_K) {
         const GemmMat gate_up[2] = {{W(L.wgate), act, F, F}, {W(L.wup), nullptr, F, F}};
