@@ -7,7 +7,7 @@ import torch
 import oracle
 from metrics import rel_err
 from tolerance import EPS_FP32, check_hidden
-from test_gpu_prefill import _centred
+from test_gpu_prefill import _centred, _shapes
 from workloads import synth
 from workloads.configs import CONFIGS, TINY
 
@@ -391,6 +391,30 @@ def test_streams_between_launches(gpu_lib, T, n_past):
     win.workspace.fill_(0xFF)
     y = win.decode(_dev(x), n_past).cpu().numpy()
     check_hidden(f"launches between streams, T={T}", rel_err(y, ref), d, host, x.astype(np.float64), n_past, formats=fm, eps=EPS_FP32)
+
+
+
+@pytest.mark.parametrize("e,ffn,T", [(512, 65536, 16), (512, 65536, 9), (256, 131072, 16), (2048, 28672, 16)])
+def test_many_shares_of_a_product_add_up_no_less_exactly_than_few(gpu_lib, e, ffn, T):
+    """A down projection cut into many shares of K, against 64 bits from the activations that the step itself made.  A product's own error
+    is 1.3 to 1.45e-7 (activations of 22 bits, fp32 sums along a share); n shares added pairwise put sqrt(log2 n) roundings of 2.4e-8 beside it
+    (0.5e-7 for 32: 1.4 to 1.55e-7), one after the other sqrt(n / 2) of them (1e-7: 1.65e-7 and more)."""
+    from workloads.configs import ModelDims
+    d = ModelDims(e, 4, 1, 64, ffn, 1e4)
+    n_past = 70
+    rng = np.random.default_rng(e + T)
+    dev = {k: _dev(_centred(rng, "q4_k", r, c).reshape(r, c // 256, 144)) for k, (r, c) in _shapes(d).items()}
+    for k in ("k_cache", "v_cache"):
+        dev[k] = _dev(rng.standard_normal((1, n_past + T, 64)).astype(np.float16))
+    for k in ("g_attn", "g_ffn"):
+        dev[k] = _dev((1 + 0.1 * rng.standard_normal(e)).astype(np.float32))
+    win = gpu_lib.Window(d, [dev], n_past + T, T_max=T)
+    x = _dev((1e-3 * rng.standard_normal((T, e))).astype(np.float32))   # (a small residual beside the product)
+    y, taps = win.decode_layer_taps(0, x, n_past)
+    product = taps["a"].double() @ gpu_lib.q4k_dequant(dev["wdown"]).double().T
+    err = float((y.double() - taps["h"].double() - product).norm() / product.norm())
+    print("shares", e, ffn, T, err, flush=True)
+    assert err < 1.6e-7, err
 
 
 Q4, Q8, Q6 = {}, {"wdown": "q8_0"}, {"wdown": "q6_k"}
