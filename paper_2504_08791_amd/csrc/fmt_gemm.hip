@@ -49,7 +49,8 @@ struct FmtGemmArgs {
     int64_t ldr;
     float *y;
     int64_t ldy;
-    int T, n_tiles, n_rb, n_tb;
+    int T, n_tiles, n_rb, n_tb, band;
+    int share_q, share_r, tile_q, tile_r; // as in q4k_gemm.hip
     int ksplit; // as in q4k_gemm.hip: shares of K, each share's sums in part[share][token][n_rows]
     float *part;
 };
@@ -88,7 +89,9 @@ struct FmLds {
     static_assert(TOTAL <= 81920, "two workgroups per compute unit");
 };
 
-template <int FMT, int WT>
+// FULL: every workgroup does 2 WT token tiles (past the last: the last again, not stored); else the tiles are shared out evenly over the
+// workgroups, which skip those they do not have.  (The branches cost 3 to 5 %; both in one kernel spill.)
+template <int FMT, int WT, bool FULL>
 __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
 {
     extern __shared__ __align__(16) uint8_t smem[];
@@ -97,16 +100,14 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, g = lane >> 4;
-    // consecutive workgroup numbers go to consecutive XCDs: an XCD owns the row blocks xcd, xcd + 8, ... and takes all token
-    // blocks of a row block one after the other, so that the weights come into one L2 only
-    const int xcd = blockIdx.x % GM_XCDS, seq = blockIdx.x / GM_XCDS;
-    const int rb = seq / a.n_tb * GM_XCDS + xcd, tb = seq % a.n_tb;
-    if (rb >= a.n_rb) return; // the whole workgroup, before any barrier
+    int rb, tb, share;
+    if (!gemm_unit(blockIdx.x, a.n_rb, a.n_tb, a.ksplit, a.band, rb, tb, share)) return; // the whole workgroup, before any barrier
+    const int tile0 = FULL ? tb * 2 * WT : tb * a.tile_q + min(tb, a.tile_r);
+    const int tiles = FULL ? 2 * WT : a.tile_q + (tb < a.tile_r ? 1 : 0);
     const int nb = static_cast<int>(a.n_cols >> 8);
-    const int b_lo = static_cast<int>(static_cast<int64_t>(blockIdx.y) * nb / a.ksplit);
-    const int b_hi = static_cast<int>(static_cast<int64_t>(blockIdx.y + 1) * nb / a.ksplit); // > b_lo: the host keeps ksplit <= nb
-    const int tile0 = tb * 2 * WT;
-    const int wr = wave & 1, wt = wave >> 1; // this wave's half of the rows and of the token tiles
+    const int b_lo = share * a.share_q + min(share, a.share_r), b_hi = b_lo + a.share_q + (share < a.share_r ? 1 : 0); // (not empty: the host keeps ksplit <= nb)
+    // this wave's half of the rows and of the tiles (every other one)
+    const int wr = wave & 1, wt = wave >> 1, my_tiles = FULL ? WT : (tiles - wt + 1) / 2;
 
     // ---- this thread's row of the workgroup's weights and its half h (16 weights) of every sub-block ----
     const int drow = threadIdx.x >> 1, h = threadIdx.x & 1;
@@ -256,21 +257,20 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
     const uint8_t *abase[WT];
 #pragma unroll
     for (int j = 0; j < WT; ++j) {
-        const int slab = wave * WT + j, tile = min(tile0 + (slab >> 1), a.n_tiles - 1); // past the last tile: a valid one, not stored
+        const int slab = wave * WT + j, tile = min(tile0 + (slab >> 1), a.n_tiles - 1);
         abase[j] = a.A + (static_cast<int64_t>(tile) * nb * GM_SLABS + (slab & 1)) * 1024;
     }
     auto issue = [&](int b, int s, int buf) __attribute__((always_inline)) {
         const int64_t off = (static_cast<int64_t>(b) * GM_SLABS + 2 * s) * 1024;
 #pragma unroll
-        for (int j = 0; j < WT; ++j) dma16_base(abase[j] + off, lane16, lds0 + buf * L::A_SLOT + (wave * WT + j) * 1024);
+        for (int j = 0; j < WT; ++j)
+            if (FULL || wave * WT + j < 2 * tiles) dma16_base(abase[j] + off, lane16, lds0 + buf * L::A_SLOT + (wave * WT + j) * 1024);
     };
     auto issue_sums = [&](int b) __attribute__((always_inline)) {
         if constexpr (Q5) {
 #pragma unroll
-            for (int j = wave; j < 2 * WT; j += 4) {
-                const int tile = min(tile0 + j, a.n_tiles - 1);
-                dma16_base(a.A + ((static_cast<int64_t>(tile) * nb + b) * GM_SLABS + 16) * 1024, lane16, lds0 + L::M0 + j * 1024);
-            }
+            for (int j = wave; j < 2 * WT; j += 4)
+                if (FULL || j < tiles) dma16_base(a.A + ((static_cast<int64_t>(min(tile0 + j, a.n_tiles - 1)) * nb + b) * GM_SLABS + 16) * 1024, lane16, lds0 + L::M0 + j * 1024);
         }
     };
 
@@ -321,7 +321,7 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
             if (s < 7) decode(qc, hd, hx, s + 1, buf ^ 1);
             else if (more) decode(qc, hd_next, hx_next, 0, buf ^ 1);
 
-            const uint8_t *ab = smem + buf * L::A_SLOT + wt * (WT * 2048) + lane * 16;
+            const uint8_t *ab = smem + buf * L::A_SLOT + wt * 2048 + lane * 16;
             const uint8_t *bb = smem + L::B0 + buf * L::B_SLOT + wr * 4096 + lane * 16;
             half8 B[FM_RT], Bl[FM_RT];
 #pragma unroll
@@ -336,8 +336,9 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
             }
 #pragma unroll
             for (int tt = 0; tt < WT; ++tt) {
-                const half8 ah = *reinterpret_cast<const half8 *>(ab + tt * 2048);
-                const half8 al = *reinterpret_cast<const half8 *>(ab + tt * 2048 + 1024);
+                if (!FULL && tt >= my_tiles) break;
+                const half8 ah = *reinterpret_cast<const half8 *>(ab + tt * 4096);
+                const half8 al = *reinterpret_cast<const half8 *>(ab + tt * 4096 + 1024);
 #pragma unroll
                 for (int rt = 0; rt < FM_RT; ++rt) {
                     gm_v4f c = zero;
@@ -374,7 +375,7 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
                         gm_v4f am = zero, t = acc[tt][rt];
                         if constexpr (Q5) {
                             // the sums slabs were requested a position ago by all waves and have landed before this position's barrier
-                            const half8 ax = *reinterpret_cast<const half8 *>(l_xs + (wt * WT + tt) * 1024 + lane * 16);
+                            const half8 ax = *reinterpret_cast<const half8 *>(l_xs + (2 * tt + wt) * 1024 + lane * 16);
                             am = __builtin_amdgcn_mfma_f32_16x16x32_f16(ax, m, zero, 0, 0, 0);
                             t = __builtin_amdgcn_mfma_f32_16x16x32_f16(ax, sc16, t, 0, 0, 0);
                         }
@@ -408,11 +409,11 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
         for (int tt = 0; tt < WT; ++tt)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int t = (tile0 + wt * WT + tt) * 16 + 4 * g + i;
-                if (t < a.T) {
+                const int t = (tile0 + 2 * tt + wt) * 16 + 4 * g + i;
+                if ((FULL || tt < my_tiles) && t < a.T) {
                     float v = ysum[tt][rt][i] * a.stat[t].y;
                     if (a.ksplit > 1) {
-                        a.part[(static_cast<int64_t>(blockIdx.y) * a.T + t) * a.n_rows + row] = v;
+                        a.part[(static_cast<int64_t>(share) * a.T + t) * a.n_rows + row] = v;
                     } else {
                         if (a.resid) v += a.resid[t * a.ldr + row];
                         a.y[t * a.ldy + row] = v;
@@ -433,17 +434,17 @@ __global__ void __launch_bounds__(256) fmt_gemm_reduce_kernel(FmtGemmArgs a)
     a.y[t * a.ldy + row] = a.resid ? v + r : v;
 }
 
-template <int FMT, int WT>
+template <int FMT, int WT, bool FULL>
 prima_status launch_wt(const FmtGemmArgs &a, unsigned grid, hipStream_t st)
 {
     static std::atomic<bool> attr_set{false}; // set twice by two threads at worst: the attribute call is idempotent
     if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(fmt_gemm_kernel<FMT, WT>), hipFuncAttributeMaxDynamicSharedMemorySize,
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(fmt_gemm_kernel<FMT, WT, FULL>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 FmLds<FMT, WT>::TOTAL) != hipSuccess)
             return PRIMA_E_DEVICE;
         attr_set = true;
     }
-    hipLaunchKernelGGL((fmt_gemm_kernel<FMT, WT>), dim3(grid, a.ksplit), dim3(FM_THREADS), (FmLds<FMT, WT>::TOTAL), st, a);
+    hipLaunchKernelGGL((fmt_gemm_kernel<FMT, WT, FULL>), dim3(grid), dim3(FM_THREADS), (FmLds<FMT, WT>::TOTAL), st, a);
     return last_launch_status();
 }
 
@@ -476,9 +477,15 @@ prima_status launch_fm(FmtGemmArgs a, void *part, size_t part_bytes, hipStream_t
         }
     }
     a.part = static_cast<float *>(part);
-    const int64_t grid = (a.n_rb + GM_XCDS - 1) / GM_XCDS * static_cast<int64_t>(GM_XCDS) * a.n_tb;
-    if (grid >= (int64_t{1} << 31)) return PRIMA_E_SHAPE;
-    const prima_status s = narrow ? launch_wt<FMT, 2>(a, static_cast<unsigned>(grid), st) : launch_wt<FMT, 4>(a, static_cast<unsigned>(grid), st);
+    if (wgs * a.ksplit >= (int64_t{1} << 31) - GM_XCDS) return PRIMA_E_SHAPE;
+    a.band = gemm_band(a.n_tb);
+    a.share_q = static_cast<int>(nb / a.ksplit); a.share_r = static_cast<int>(nb % a.ksplit);
+    a.tile_q = a.n_tiles / a.n_tb; a.tile_r = a.n_tiles % a.n_tb;
+    const unsigned grid = gemm_grid(wgs * a.ksplit);
+    // full workgroups where that leaves less than a twentieth of padding
+    const bool full = (a.n_tb * (narrow ? 4 : 8) - a.n_tiles) * 20 < a.n_tiles;
+    const prima_status s = narrow ? (full ? launch_wt<FMT, 2, true>(a, grid, st) : launch_wt<FMT, 2, false>(a, grid, st))
+                                  : (full ? launch_wt<FMT, 4, true>(a, grid, st) : launch_wt<FMT, 4, false>(a, grid, st));
     if (s != PRIMA_OK || a.ksplit == 1) return s;
     hipLaunchKernelGGL(fmt_gemm_reduce_kernel, dim3(static_cast<unsigned>((a.n_rows + 255) / 256), a.T), dim3(256), 0, st, a);
     return last_launch_status();

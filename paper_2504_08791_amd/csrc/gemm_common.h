@@ -18,6 +18,26 @@ constexpr size_t GM_STAT_ALIGN = 1024;
 constexpr int GM_XCDS = 8;
 constexpr int GM_CUS = 256;
 
+// Which (row block, token block, share of K) workgroup `wg` takes.  Consecutive workgroup numbers go to consecutive XCDs; each XCD
+// takes an equal run of the units in an order in which neighbours share weights and activations in its L2: shares outermost, then bands
+// of `band` row blocks, a band's row blocks of one token block one after the other (32 units at a time: 4 row blocks x 8 token blocks).
+// False: none left.  (An XCD that took the row blocks xcd, xcd + 8, .. had three of 20 where others had two, 72 workgroups for 64 slots: 5120 rows, 512
+// tokens, three shares 241 us.)
+__device__ __forceinline__ bool gemm_unit(unsigned wg, int n_rb, int n_tb, int n_shares, int band, int &rb, int &tb, int &share)
+{
+    const int xcd = wg % GM_XCDS, seq = wg / GM_XCDS, plane = n_rb * n_tb;
+    const int64_t units = static_cast<int64_t>(plane) * n_shares;
+    const int first = static_cast<int>(units * xcd / GM_XCDS), u = first + seq;
+    if (u >= static_cast<int>(units * (xcd + 1) / GM_XCDS)) return false;
+    share = u / plane;
+    const int v = u - share * plane, r0 = v / (band * n_tb) * band, h = min(band, n_rb - r0), w = v - r0 * n_tb;
+    tb = w / h;
+    rb = r0 + w - tb * h;
+    return true;
+}
+inline unsigned gemm_grid(int64_t units) { return static_cast<unsigned>((units + GM_XCDS - 1) / GM_XCDS * GM_XCDS); }
+inline int gemm_band(int n_tb) { return 32 / (n_tb < 8 ? n_tb : 8); }
+
 // the split activations and the per-token (2^p [* 1/rms], 2^-p) inside the scratch of gemm_ws_bytes(T, n_cols)
 inline float2 *gemm_stat(void *ws) { return static_cast<float2 *>(ws); }
 inline uint8_t *gemm_split(void *ws, int T)

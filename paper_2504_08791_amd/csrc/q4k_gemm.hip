@@ -49,12 +49,6 @@ constexpr int GM_NS = 3;                        // ring slots: positions whose a
 constexpr int GM_SLOT = GM_TT * 2048;                                     // 8 KiB of activations
 constexpr int GM_WQ = 2 * 4096;                                           // per wave: the quants of half a super-block, twice
 constexpr int GM_LDS_BYTES = GM_NS * GM_SLOT + GM_WAVES * (GM_WQ + 2 * 1024); // 64 KiB: two workgroups per compute unit
-// Workgroups that share an XCD at a time: a patch of 4 row blocks x 8 token blocks; with fewer than 8 token blocks all of
-// them and more row blocks, with few row blocks per XCD only those.  A workgroup number that falls outside the matrix
-// costs its dispatch (about 0.1 us): with one token block and patches of 4 x 8, seven numbers in eight were idle and a
-// launch took no less than 260 us whatever its work.
-constexpr int GM_PATCH = 32, GM_PATCH_C = 8;
-
 struct GemmSegDev {
     const uint8_t *W;
     float *y;
@@ -74,11 +68,12 @@ struct GemmArgs {
     const float *resid; // null: none (added to every stored row; launches with a residual have one matrix)
     int64_t ldr;
     int T, n_tiles, n_rb, n_tb; // 16-token tiles, row blocks, token blocks
-    int patch_r, patch_c;       // row blocks x token blocks of a patch
-    // K divided among ksplit workgroups per (row block, token block): workgroup blockIdx.y walks its share of the
+    int band;                   // gemm_band()
+    // K divided among ksplit workgroups per (row block, token block): each walks its share of the
     // super-blocks and stores its sums to part[split][token][ldp] (column: row block * GM_ROWS + row in the block);
     // gemm_ksplit_reduce_kernel adds the shares in order.  ksplit == 1: the sums go straight to y.
     int ksplit;
+    int share_q, share_r, tile_q, tile_r; // super-blocks of a share and tiles of a token block: quotients, and how many have one more
     float *part;
     int64_t ldp;
 };
@@ -206,26 +201,21 @@ __device__ __forceinline__ void dma16_off(const void *gptr, uint32_t lds_addr)
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off offset:%2" : : "v"(gptr), "s"(lds_addr - OFF), "n"(OFF) : "memory");
 }
 
-// Requests a wave makes at the positions p - 3 .. p - 1 behind position p = (b, s) of the product kernel's schedule
-// (activations four positions ahead: 2, or 1 where the target is the sums position; at s == 3, 4, 7 of a super-block with
+// Requests a wave makes at the positions p - GM_AHEAD + 1 .. p - 1 behind position p = (b, s) of the product kernel's schedule
+// (activations GM_AHEAD positions ahead: dm, or 1 where the target is the sums position; at s == 3, 4, 7 of a super-block with
 // a successor 4, 1, 4 weight requests).  successor: whether super-block b has one; the one before b always had.
 constexpr int GM_AHEAD = GM_NS - 1; // positions between an activation request and its use
-constexpr int requests_at(int sk, bool successor) // sk < 0: a position of the super-block before (or the prologue)
+constexpr int requests_at(int sk, bool successor, int dm) // sk < 0: a position of the super-block before (or the prologue)
 {
     const int sp = sk < 0 ? sk + 9 : sk;
-    return ((sp + GM_AHEAD) % 9 < 8 ? 2 : 1) + ((sk < 0 || successor) ? (sp == 3 ? 4 : (sp == 4 ? 1 : (sp == 7 ? 4 : 0))) : 0);
+    return ((sp + GM_AHEAD) % 9 < 8 ? dm : 1) + ((sk < 0 || successor) ? (sp == 3 ? 4 : (sp == 4 ? 1 : (sp == 7 ? 4 : 0))) : 0);
 }
-constexpr int requests_behind(int s, bool successor)
+constexpr int requests_behind(int s, bool successor, int dm)
 {
     int n = 0;
-    for (int k = 1; k < GM_AHEAD; ++k) n += requests_at(s - k, successor);
+    for (int k = 1; k < GM_AHEAD; ++k) n += requests_at(s - k, successor, dm);
     return n;
 }
-static_assert(GM_AHEAD != 4 ||
-                  (requests_behind(0, true) == 10 && requests_behind(0, false) == 10 && requests_behind(2, true) == 6 &&
-                   requests_behind(4, true) == 10 && requests_behind(4, false) == 6 && requests_behind(5, false) == 5 &&
-                   requests_behind(7, true) == 6 && requests_behind(8, true) == 10 && requests_behind(8, false) == 6),
-              "request counts of the product kernel's schedule");
 static_assert(GM_AHEAD >= 2 && GM_AHEAD <= 4, "the weight requests at s == 3, 4, 7 must be older than the activation requests a wait lets pass");
 
 // One workgroup: 4 waves, one per SIMD; a wave owns 64 rows (four B tiles) x 64 tokens, i.e. 16 accumulator tiles for the
@@ -245,31 +235,20 @@ static_assert(GM_AHEAD >= 2 && GM_AHEAD <= 4, "the weight requests at s == 3, 4,
 // to wait on.  Measured with parts of the work switched off (8192 x 28672 weights, 1024 tokens): the LDS reads of the
 // activations cost 30 % of the time, the requests 12 %, the B tiles 10 %, the barrier 3 %: a wave reads every
 // activation of its 64 tokens once per position, whatever the tiling, so LDS bandwidth is met before the MFMA rate.
-__global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
+// TT: the token tiles of this workgroup.  The tiles are shared out evenly, so that one of 21 tiles (333 tokens) is three workgroups
+// of four and three of three; a tile past the last one was multiplied and thrown away.
+template <int TT>
+__device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem, int rb, int share, int tile0)
 {
-    extern __shared__ __align__(16) uint8_t smem[];
-    constexpr int TT = GM_TT;
     constexpr int SLOT = GM_SLOT;
     constexpr int WQ_BASE = GM_NS * SLOT;            // per wave two buffers of 4 KiB: quants of sub-blocks 0-3, of 4-7
     constexpr int HDR_RING = WQ_BASE + GM_WAVES * GM_WQ; // two entries of GM_WAVES KiB
-    constexpr int DM = TT / 2, DMS = TT / 4;         // activation requests per wave: a sub-block position, the sums position
-    static_assert(TT == 4 && GM_WAVES == 4, "requests per wave and position are counted for 4 tiles and 4 waves");
+    constexpr int DM = (TT + 1) / 2;                 // activation requests per wave at a sub-block position (one at the sums position)
+    static_assert(TT >= 1 && TT <= GM_WAVES && GM_WAVES == 4, "requests per wave and position are counted for up to 4 tiles and 4 waves");
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, g = lane >> 4;
-    // Consecutive workgroup numbers go to consecutive XCDs.  32 consecutive workgroups of one XCD (one L2) are 4 row
-    // blocks x 8 token blocks: per super-block step they fetch 4 x 36 KiB of weights and 8 x 68 KiB of activations
-    // between them instead of 32 of either.  An XCD owns the row blocks xcd, xcd + 8, ...  (The shape of the patch
-    // makes no measurable difference at 1024 tokens; this one is the best of four at 512.  The host narrows the patch
-    // when there are fewer token blocks or row blocks than that, so that few workgroup numbers fall outside.)
-    const int xcd = blockIdx.x % GM_XCDS, seq = blockIdx.x / GM_XCDS;
-    const int patch_c = a.patch_c, patch_r = a.patch_r;
-    const int patch = seq / (patch_r * patch_c), within = seq % (patch_r * patch_c);
-    const int patches_tb = (a.n_tb + patch_c - 1) / patch_c;
-    const int rb = ((patch / patches_tb) * patch_r + within / patch_c) * GM_XCDS + xcd;
-    const int tb = (patch % patches_tb) * patch_c + within % patch_c;
-    if (rb >= a.n_rb || tb >= a.n_tb) return; // the whole workgroup, before any barrier
     const int nb = static_cast<int>(a.n_cols >> 8);
     const int sg = a.pair ? 0 : (rb >= a.seg[2].rb0 ? 2 : (rb >= a.seg[1].rb0 ? 1 : 0));
     const GemmSegDev &my = a.seg[sg];
@@ -291,31 +270,25 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
     const uint8_t *wq[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) wq[k] = row_ptr(16 * k + (lane >> 2)) + 16 + ((lane & 3) ^ (lane >> 4)) * 16;
-    const int tile0 = tb * TT;
     const uint32_t lds0 = lds_address(smem);
     // this workgroup's share of K: super-blocks [b_lo, b_lo + nbl) (all of them unless K is divided; never empty: the
     // host keeps ksplit <= nb); below, `b` counts from b_lo
-    const int b_lo = static_cast<int>(static_cast<int64_t>(blockIdx.y) * nb / a.ksplit);
-    const int nbl = static_cast<int>(static_cast<int64_t>(blockIdx.y + 1) * nb / a.ksplit) - b_lo;
+    const int b_lo = share * a.share_q + min(share, a.share_r);
+    const int nbl = a.share_q + (share < a.share_r ? 1 : 0);
     wsrc += static_cast<int64_t>(b_lo) * 144;
 #pragma unroll
     for (int k = 0; k < 4; ++k) wq[k] += static_cast<int64_t>(b_lo) * 144;
     const int total = 9 * nbl; // positions (n_cols < 2^32: no overflow)
 
     // Wave-uniform bases of this wave's activation requests: request jj of a sub-block position is slab (part, tile)
-    // with part = wave & 1, tile = 2 jj + (wave >> 1); request jj of a sums position is tile wave + 4 jj.  Past the
-    // last tile: a valid one, not stored.
-    const uint8_t *abase[DM], *xbase[DMS];
+    // with part = wave & 1, tile = 2 jj + (wave >> 1); that of a sums position is tile `wave`.  Past the workgroup's
+    // last tile: that one again, the same bytes to the same place.
+    const uint8_t *abase[DM];
+    auto tile_of = [&](int jj) __attribute__((always_inline)) { return TT % 2 == 0 ? 2 * jj + (wave >> 1) : min(2 * jj + (wave >> 1), TT - 1); };
 #pragma unroll
-    for (int jj = 0; jj < DM; ++jj) {
-        const int tg = min(tile0 + 2 * jj + (wave >> 1), a.n_tiles - 1);
-        abase[jj] = a.A + ((static_cast<int64_t>(tg) * nb + b_lo) * GM_SLABS + (wave & 1)) * 1024;
-    }
-#pragma unroll
-    for (int jj = 0; jj < DMS; ++jj) {
-        const int tg = min(tile0 + wave + GM_WAVES * jj, a.n_tiles - 1);
-        xbase[jj] = a.A + ((static_cast<int64_t>(tg) * nb + b_lo) * GM_SLABS + 16) * 1024;
-    }
+    for (int jj = 0; jj < DM; ++jj) abase[jj] = a.A + ((static_cast<int64_t>(tile0 + tile_of(jj)) * nb + b_lo) * GM_SLABS + (wave & 1)) * 1024;
+    const int xtile = TT == GM_WAVES ? wave : min(wave, TT - 1);
+    const uint8_t *const xbase = a.A + ((static_cast<int64_t>(tile0 + xtile) * nb + b_lo) * GM_SLABS + 16) * 1024;
     const uint32_t lane16 = lane * 16;
 
     // the quants of half `half` (sub-blocks 4 half .. 4 half + 3) of super-block b: four requests; its headers: one
@@ -344,10 +317,9 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
         if (s < 8) {
 #pragma unroll
             for (int jj = 0; jj < DM; ++jj)
-                dma16_base(abase[jj] + boff + 2048 * s, lane16, base + (2 * jj + (wave >> 1)) * 2048 + (wave & 1) * 1024);
+                dma16_base(abase[jj] + boff + 2048 * s, lane16, base + tile_of(jj) * 2048 + (wave & 1) * 1024);
         } else {
-#pragma unroll
-            for (int jj = 0; jj < DMS; ++jj) dma16_base(xbase[jj] + boff, lane16, base + (wave + GM_WAVES * jj) * 1024);
+            dma16_base(xbase + boff, lane16, base + xtile * 1024);
         }
     };
 
@@ -441,8 +413,8 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
             // target is a sums position) and, where they fall on s == 3, 4, 7 of a super-block that has a successor,
             // 4, 1, 4 weight requests.  The last three positions wait for everything.
             if (p + GM_AHEAD - 1 >= total) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            else if (b + 1 < nbl) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(requests_behind(s, true)) : "memory");
-            else asm volatile("s_waitcnt vmcnt(%0)" : : "n"(requests_behind(s, false)) : "memory"); // the last super-block requests no weights
+            else if (b + 1 < nbl) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(requests_behind(s, true, DM)) : "memory");
+            else asm volatile("s_waitcnt vmcnt(%0)" : : "n"(requests_behind(s, false, DM)) : "memory"); // the last super-block requests no weights
             gm_barrier();
             {
                 // position p + NS - 1 goes into the slot that position p - 1 has just left
@@ -470,12 +442,15 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
                 // LDS reads run two tiles ahead of their MFMAs (one tile, 8 MFMAs, is shorter than the LDS latency
                 // while four waves and the incoming requests share the LDS)
                 half8 ah[3], al[3];
-                uint32_t wn[2];
-                if (s < 7) wn[0] = quants_of(0, s + 1);
-                ah[0] = *reinterpret_cast<const half8 *>(base);
-                al[0] = *reinterpret_cast<const half8 *>(base + 1024);
-                ah[1] = *reinterpret_cast<const half8 *>(base + 2048);
-                al[1] = *reinterpret_cast<const half8 *>(base + 2048 + 1024);
+                uint32_t wn[GM_RT];
+#pragma unroll
+                for (int rt = 0; rt < GM_RT; ++rt)
+                    if (s < 7 && rt * TT < GM_RT) wn[rt] = quants_of(rt, s + 1);
+#pragma unroll
+                for (int tt = 0; tt < (TT < 2 ? TT : 2); ++tt) {
+                    ah[tt] = *reinterpret_cast<const half8 *>(base + tt * 2048);
+                    al[tt] = *reinterpret_cast<const half8 *>(base + tt * 2048 + 1024);
+                }
 #pragma unroll
                 for (int tt = 0; tt < TT; ++tt) {
                     const half8 ch = ah[tt % 3], cl = al[tt % 3];
@@ -488,20 +463,25 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
                         acch[tt][rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ch, Bc[rt], s == 0 ? zero : acch[tt][rt], 0, 0, 0);
                         acch[tt][rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(cl, Bc[rt], acch[tt][rt], 0, 0, 0);
                     }
-                    if (s < 7 && tt + 1 < TT) wn[(tt + 1) & 1] = quants_of(tt + 1, s + 1);
-                    if (tt < GM_RT) {
-                        if (s < 7) build_b(Bn[tt], wn[tt & 1], tt, s + 1);
-                        else build_m(Bn[tt], dd[tt], dm[tt], tt, b);
-                        __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+                    // the B tiles of the next position are shared out over the token tiles
 #pragma unroll
-                        for (int k = 0; k < 2 * GM_RT; ++k) { // one MFMA, then up to four VALU instructions of the build
-                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                            __builtin_amdgcn_sched_group_barrier(0x002, s < 7 ? 2 : 4, 0);
-                        }
-                        // built here, not where it is used: the compiler moved the unpacking into the next position, in front of its
-                        // first matrix instruction
-                        asm volatile("" : "+v"(Bn[tt]));
+                    for (int rt = 0; rt < GM_RT; ++rt) {
+                        if (s < 7 && rt * TT / GM_RT == tt + 1) wn[rt] = quants_of(rt, s + 1);
+                        if (rt * TT / GM_RT != tt) continue;
+                        if (s < 7) build_b(Bn[rt], wn[rt], rt, s + 1);
+                        else build_m(Bn[rt], dd[rt], dm[rt], rt, b);
                     }
+                    __builtin_amdgcn_sched_group_barrier(0x100, TT == 4 ? 3 : 2 + GM_RT, 0);
+#pragma unroll
+                    for (int k = 0; k < 2 * GM_RT; ++k) { // one MFMA, then up to so many VALU instructions of the builds
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, (s < 7 ? 2 : 4) * ((GM_RT + TT - 1) / TT), 0);
+                    }
+                    // built here, not where it is used: the compiler moved the unpacking into the next position, in front of its
+                    // first matrix instruction
+#pragma unroll
+                    for (int rt = 0; rt < GM_RT; ++rt)
+                        if (rt * TT / GM_RT == tt) asm volatile("" : "+v"(Bn[rt]));
                     __builtin_amdgcn_sched_barrier(0);
                 }
             } else {
@@ -521,9 +501,11 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
                         for (int i = 0; i < 4; ++i)
                             yacc[tt][rt][i] += fmaf(dd[rt], acch[tt][rt][i], -(dm[rt] * am[i]));
                     }
-                    if (tt < GM_RT) {
-                        if (b + 1 < nbl) { load_scales(tt, b + 1); build_b(Bn[tt], quants_of(tt, 0), tt, 0); }
-                        else Bn[tt] = Bc[tt];
+#pragma unroll
+                    for (int rt = 0; rt < GM_RT; ++rt) {
+                        if (rt * TT / GM_RT != tt) continue;
+                        if (b + 1 < nbl) { load_scales(rt, b + 1); build_b(Bn[rt], quants_of(rt, 0), rt, 0); }
+                        else Bn[rt] = Bc[rt];
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -553,7 +535,7 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int t = (tile0 + tt) * 16 + 4 * g + i;
-                    if (t < a.T) dst[(static_cast<int64_t>(blockIdx.y) * a.T + t) * a.ldp] = yacc[tt][rt][i] * a.stat[t].y;
+                    if (t < a.T) dst[(static_cast<int64_t>(share) * a.T + t) * a.ldp] = yacc[tt][rt][i] * a.stat[t].y;
                 }
         }
         return;
@@ -592,6 +574,20 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
                     my.y[t * my.ldy + out_row] = v;
                 }
             }
+    }
+}
+
+__global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    int rb, tb, share;
+    if (!gemm_unit(blockIdx.x, a.n_rb, a.n_tb, a.ksplit, a.band, rb, tb, share)) return; // the whole workgroup, before any barrier
+    const int tile0 = tb * a.tile_q + min(tb, a.tile_r);
+    switch (a.tile_q + (tb < a.tile_r ? 1 : 0)) {
+    case 1: q4k_gemm_block<1>(a, smem, rb, share, tile0); break;
+    case 2: q4k_gemm_block<2>(a, smem, rb, share, tile0); break;
+    case 3: q4k_gemm_block<3>(a, smem, rb, share, tile0); break;
+    default: q4k_gemm_block<4>(a, smem, rb, share, tile0); break;
     }
 }
 
@@ -693,11 +689,7 @@ prima_status launch_q4k_gemm_multi(const GemmMat *mats, int n_mats, bool pair, i
     const int64_t nb = n_cols / QK;
     const int n_tiles = (T + 15) / 16;
     const int n_tb = (n_tiles + GM_TT - 1) / GM_TT;
-    const int64_t rb_per_xcd = (n_rb + GM_XCDS - 1) / GM_XCDS;
-    const int patch_c = std::min(n_tb, GM_PATCH_C);
-    const int patch_r = static_cast<int>(std::min<int64_t>(std::max(1, GM_PATCH / patch_c), rb_per_xcd));
-    const int64_t grid = (rb_per_xcd + patch_r - 1) / patch_r * ((n_tb + patch_c - 1) / patch_c) * (patch_r * patch_c) * GM_XCDS;
-    if (grid >= (int64_t{1} << 31) || n_tiles > 65535 || nb >= (int64_t{1} << 31)) return PRIMA_E_SHAPE;
+    if (n_rb * n_tb >= (int64_t{1} << 31) - GM_XCDS || n_tiles > 65535 || nb >= (int64_t{1} << 31)) return PRIMA_E_SHAPE;
     static std::atomic<bool> attr_set{false}; // set twice by two threads at worst: the attribute call is idempotent
     if (!attr_set) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(q4k_gemm_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, GM_LDS_BYTES) != hipSuccess)
@@ -713,13 +705,15 @@ prima_status launch_q4k_gemm_multi(const GemmMat *mats, int n_mats, bool pair, i
     }
     a.pair = pair ? 1 : 0;
     a.n_cols = n_cols; a.A = A; a.stat = stat; a.resid = resid; a.ldr = ldr;
-    a.T = T; a.n_tiles = n_tiles; a.n_rb = static_cast<int>(n_rb); a.n_tb = n_tb; a.patch_r = patch_r; a.patch_c = patch_c;
+    a.T = T; a.n_tiles = n_tiles; a.n_rb = static_cast<int>(n_rb); a.n_tb = n_tb; a.band = gemm_band(n_tb);
     // K is divided when that fills the device and the caller's scratch holds the shares
     a.ksplit = part && T <= 65535 ? ksplit_for(n_rb, n_tb, nb) : 1; // (the shares are added by a launch with T as a grid dimension)
     a.ldp = n_rb * GM_ROWS;
     if (a.ksplit > 1 && part_bytes < static_cast<size_t>(a.ksplit) * static_cast<size_t>(T) * static_cast<size_t>(a.ldp) * sizeof(float)) a.ksplit = 1;
+    a.share_q = static_cast<int>(nb / a.ksplit); a.share_r = static_cast<int>(nb % a.ksplit);
+    a.tile_q = n_tiles / n_tb; a.tile_r = n_tiles % n_tb;
     a.part = a.ksplit > 1 ? static_cast<float *>(part) : nullptr;
-    hipLaunchKernelGGL(q4k_gemm_kernel, dim3(static_cast<unsigned>(grid), a.ksplit), dim3(GM_THREADS), GM_LDS_BYTES, st, a);
+    hipLaunchKernelGGL(q4k_gemm_kernel, dim3(gemm_grid(n_rb * n_tb * a.ksplit)), dim3(GM_THREADS), GM_LDS_BYTES, st, a);
     if (a.ksplit > 1) {
         const prima_status ps = last_launch_status();
         if (ps != PRIMA_OK) return ps;

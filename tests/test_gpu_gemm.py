@@ -50,6 +50,20 @@ def test_gemm_shapes(gpu_lib):
         assert np.array_equal(got.view(np.uint32), again.view(np.uint32))
 
 
+@pytest.mark.parametrize("rows,nb,T", [(2600, 2, 333), (300, 1, 65), (5000, 1, 48), (700, 3, 1100), (260, 9, 17)])
+def test_gemm_row_and_token_blocks_shared_out_unevenly(gpu_lib, rows, nb, T):
+    """Row blocks that do not divide among the 8 XCDs, token tiles (21, 5, 3, 69, 2) that do not divide among the workgroups' four, more
+    than one band of row blocks and token blocks, K whole and divided."""
+    rng = np.random.default_rng(38)
+    W = _rand_q4k(rng, rows, nb)
+    x = rng.standard_normal((T, nb * 256)).astype(np.float32)
+    ref = _oracle_product(W, x.astype(np.float64))
+    for split in (False, True):
+        ws = torch.empty(gpu_lib.gemm_workspace_bytes(T, rows, nb * 256, ksplit=split), dtype=torch.uint8, device="cuda")
+        got = gpu_lib.q4k_gemm(_dev(W), _dev(x), workspace=ws).cpu().numpy()
+        assert rel_err(got, ref) < ARITH_TOL, (split, rel_err(got, ref))
+
+
 def test_gemm_rmsnorm_and_residual(gpu_lib):
     """RMSNorm in front, residual behind, strided rows of x, y and the residual."""
     rng = np.random.default_rng(32)

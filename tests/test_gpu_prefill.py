@@ -231,6 +231,12 @@ def test_products_of_the_other_formats_are_no_less_exact_than_the_mat_vec(gpu_li
     assert err[0] <= 1.02 * err[1] and (dist == "spread" or err[1] < 1e-6), err
 
 
+@pytest.mark.parametrize("fmt", ["q5_k", "q6_k", "q8_0", "f16"])
+def test_workgroups_of_128_tokens_that_lack_some(gpu_lib, fmt):
+    """22 token tiles: three workgroups of 128 tokens with seven or eight tiles each, the absent ones skipped."""
+    test_products_of_the_other_formats_are_no_less_exact_than_the_mat_vec(gpu_lib, fmt, 350, "normal")
+
+
 def test_prefill_then_decode_continues(gpu_lib, route):
     """A prompt through the prefill call, the next token through the decode call: against the oracle doing the same."""
     cfg = TINY["t1"].with_(T=40, n_past=0)
