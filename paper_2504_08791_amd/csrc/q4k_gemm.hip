@@ -351,12 +351,11 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
     auto load_scales = [&](int rt, int bb) __attribute__((always_inline)) {
         hsc[rt] = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint32_t *>(smem + HDR_RING + ((bb & 1) * GM_WAVES + wave) * 1024 + (16 * rt + n) * 16) + 1);
     };
-    // an exponent in a vector register: an and-or takes one scalar operand, which the mask is
-    uint32_t e1024 = 0x64006400u;
-    asm("" : "+v"(e1024));
-    // B tile `rt` of sub-block s from this wave's quants and the sub-scales in hsc: sc_s * q as binary16 (exact).  A dword
-    // holds the eight weights of lane (n, g); masked in pairs (0,4) (1,5) (2,6) (3,7) into the mantissas of 1024 + q, the odd
-    // pairs (bits 4..7 of a half) of 64 + q without a shift, then one fused multiply-add per pair: (1024 + q) sc - 1024 sc
+    // B tile `rt` of sub-block s from this wave's quants and the sub-scales in hsc: 2^-14 sc_s q as binary16 (exact: 10 bits, 2^-14 at the
+    // least).  A dword holds the eight weights of lane (n, g).  Masked in pairs (0,4) (1,5) (2,6) (3,7) they are subnormal binary16 numbers as
+    // they stand, 2^-24 q and, the odd pairs (bits 4..7 of a half), 2^-20 q: one multiplication by 2^10 sc or 2^6 sc each.  (With an exponent
+    // put in, 1024 + q, a fused multiply-add that took 1024 sc off again: four vector instructions more per tile pair; 70B 1024 tokens 3920 -> 3860 us, 8B
+    // 333 489 -> 483.)
     // The quants are read a tile ahead of their use, with two VALU instructions a matrix instruction while they are unpacked.  This, the order of the
     // pieces above and the tiles pinned where they are built, one layer, us: 14B 333 tokens 700.6 -> 689.4, 64: 223.8 -> 218.9, 8B 333 490.4 -> 483.3; 70B
     // 256: 1030 -> 1020, 1024: 3648 -> 3620, 8B 2000 2098 -> 2087 (the last two within twice the spread of the runs)
@@ -367,14 +366,12 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
     };
     auto build_b = [&](half8 &B, uint32_t w, int rt, int s) __attribute__((always_inline)) {
         const _Float16 sc = static_cast<_Float16>(static_cast<unsigned short>(hdr_field(make_uint4(0u, hsc[rt].x, hsc[rt].y, 0u), s)));
-        const half2v sc2 = {sc, sc};
-        const _Float16 offa = static_cast<_Float16>(-1024.f) * sc, offb = static_cast<_Float16>(-64.f) * sc; // exact: at most 64512 in magnitude
-        const half2v off2[2] = {{offa, offa}, {offb, offb}};
+        const half2v sc2 = half2v{sc, sc} * half2v{static_cast<_Float16>(1024.f), static_cast<_Float16>(64.f)};
+        const half2v sca = {sc2[0], sc2[0]}, scb = {sc2[1], sc2[1]};
 #pragma unroll
         for (int pr = 0; pr < 4; ++pr) {
             const uint32_t v = pr < 2 ? w : w >> 8;
-            const uint32_t bits = (pr & 1) == 0 ? ((v & 0x000f000fu) | e1024) : ((v & 0x00f000f0u) | (e1024 ^ 0x30003000u));
-            const half2v r = __builtin_elementwise_fma(__builtin_bit_cast(half2v, bits), sc2, off2[pr & 1]);
+            const half2v r = __builtin_bit_cast(half2v, v & (pr & 1 ? 0x00f000f0u : 0x000f000fu)) * (pr & 1 ? scb : sca);
             B[2 * pr] = r[0];
             B[2 * pr + 1] = r[1];
         }
@@ -382,7 +379,7 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
     // ... and of the sums position: the m_s as B operand, with d and dmin
     auto build_m = [&](half8 &B, float &d_, float &dm_, int rt, int bb) __attribute__((always_inline)) {
         const uint4 hdr = *reinterpret_cast<const uint4 *>(smem + HDR_RING + ((bb & 1) * GM_WAVES + wave) * 1024 + (16 * rt + n) * 16);
-        d_ = hdr_d(hdr);
+        d_ = hdr_d(hdr) * 16384.f; // (the B tiles are 2^-14 of sc q)
         dm_ = hdr_dmin(hdr);
 #pragma unroll
         for (int s8 = 0; s8 < 8; ++s8) B[s8] = static_cast<_Float16>(static_cast<unsigned short>(hdr_field(hdr, 8 + s8)));
