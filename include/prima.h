@@ -359,9 +359,9 @@ prima_status prima_window_plan_status(const prima_dims *d, int32_t kv_cap, int32
  * 1 <= T <= PRIMA_GEMM_MAX_TOK.  W: Q4_K layout v1, device, 16-byte aligned.  x: fp32 [T][ldx], 16-byte aligned,
  * ldx >= n_cols, ldx % 4 == 0.  gain: fp32 [n_cols], 16-byte aligned, or null.  resid: fp32 [T][ldr] or null (may be y).
  * y: fp32 [T][ldy], ldy >= n_rows, must not overlap x.  workspace: device, 256-byte aligned, at least
- * prima_gemm_workspace_bytes(T, n_cols) bytes (per-token scales and the activations laid out for the matrix cores,
- * about 4.25 bytes per activation; contents need not be kept).  The activations enter the matrix cores as the sum of
- * two binary16 numbers (22 bits after a per-token power-of-two scale), products and sums are fp32; the same arguments
+ * prima_gemm_workspace_bytes(T, n_cols) bytes (the activations laid out for the matrix cores, about 4.25 bytes per activation,
+ * and their sums of squares; contents need not be kept).  The activations enter the matrix cores as the sum of
+ * two binary16 numbers (22 bits after a power-of-two scale per token and super-block), products and sums are fp32; the same arguments
  * always give the same bits.  All pointers device; asynchronous on hip_stream.
  *
  * Few rows and few tokens (an output projection against a prompt of a hundred tokens) give fewer workgroups than the

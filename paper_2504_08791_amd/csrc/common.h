@@ -104,11 +104,44 @@ prima_status launch_zero_arrivals(void *ws, size_t bytes, hipStream_t st);
 // host only: whether every pass of this launch finds a plan and fits the scratch (nothing is launched)
 prima_status gemv_plan_status(const GemvArgs &a, void *ws, size_t ws_bytes, size_t arrivals_region);
 
-// many tokens (q4k_gemm.hip): ws holds gemm_ws_bytes(T, n_cols) bytes (per-token scales, the activations split for the matrix cores)
-size_t gemm_ws_bytes(int T, int64_t n_cols);
-prima_status launch_q4k_gemm(const uint8_t *W, int64_t n_rows, int64_t n_cols, const float *x, int64_t ldx, int T,
-                             const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy,
-                             void *ws, hipStream_t st, bool split_ready = false, void *part = nullptr, size_t part_bytes = 0);
+// ---- many tokens (gemm_prepare.hip, q4k_gemm.hip, fmt_gemm.hip) ----
+// The activations of a product: split and laid out for the matrix cores (gemm_common.h) by launch_gemm_prepare(), without 1/rms: that multiplies the
+// finished sums, from the sums of squares ss[super-block][ld] of the tokens (ss null: no norm).
+struct GemmNorm {
+    const float *ss;
+    int nb, ld; // ld: tokens rounded up to 16
+    float eps;
+};
+struct GemmActs {
+    const uint8_t *A;
+    GemmNorm norm;
+};
+// K divided among workgroups leaves shares of the sums, without 1/rms: share s of token t, row r of matrix i at part[s * stride + t * ld + col[i] + r].
+// (gate, up) pair: row r of the gate at r / 128 * 256 + r % 128 / 32 * 64 + r % 32 instead, of the up matrix 32 further.  n 0: there are none, the product is complete.
+struct GemmShares {
+    const float *part;
+    int n;
+    int64_t stride, ld, col[3];
+};
+enum { GEMM_PLAIN = 0, GEMM_RESIDUAL = 1, GEMM_SWIGLU = 2 };
+struct GemmPrepare {
+    int mode, T, n_tiles, nb; // v: [T][256 nb]
+    const float *x;           // GEMM_PLAIN: v; GEMM_RESIDUAL: added to the shares p
+    int64_t ldx;
+    GemmShares p;             // GEMM_SWIGLU: of a pair
+    GemmNorm norm;            // GEMM_SWIGLU: of the pair's activations
+    float *out;               // v stored (null: not); may be x
+    int64_t ldo;
+    const float *gain; // null: none; else ss gets the sums of squares of v, and v * gain is laid out
+    float *ss;
+    uint8_t *A; // null: not laid out
+};
+prima_status launch_gemm_prepare(GemmPrepare a, hipStream_t st);
+size_t gemm_acts_bytes(int T, int64_t n_cols); // A
+size_t gemm_ss_bytes(int T, int64_t n_cols);   // ss
+// y = 1/rms * the shares of one matrix (+ resid)
+prima_status launch_gemm_sum(const GemmShares &p, const GemmNorm &norm, const float *resid, int64_t ldr, float *y, int64_t ldy, int64_t n_rows, int T,
+                             hipStream_t st);
 // K divided among workgroups (a launch whose rows and tokens alone would leave most of the device idle): the number of
 // shares for T tokens and n_mats matrices of these rows sharing a launch, or (pair) a gate and an up matrix of n_rows[0]
 // each (1: none), and the bytes of `part` that hold the shares' sums (0: none).  A launch divides K only if it is given
@@ -116,21 +149,33 @@ prima_status launch_q4k_gemm(const uint8_t *W, int64_t n_rows, int64_t n_cols, c
 int gemm_ksplit(int T, const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair = false);
 size_t gemm_part_bytes(int T, const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair = false);
 // up to three matrices with the same columns against the same activations (Q / K / V), or, with pair set, two of equal
-// shape (gate, up) with silu(gate) * up stored to mats[0].y; the residual only with one matrix
+// shape (gate, up) with silu(gate) * up stored to mats[0].y; the residual only with one matrix.  later: the shares of K, if there are any, are left to
+// the caller's next launch (resid and y then unused); null: one matrix, they are added here.
 struct GemmMat {
     const uint8_t *W;
     float *y;
     int64_t n_rows, ldy;
 };
-prima_status launch_q4k_gemm_multi(const GemmMat *mats, int n_mats, bool pair, int64_t n_cols, const float *x, int64_t ldx, int T,
-                                   const float *gain, float eps, const float *resid, int64_t ldr, void *ws, hipStream_t st,
-                                   bool split_ready = false, void *part = nullptr, size_t part_bytes = 0);
+prima_status launch_q4k_gemm(const GemmMat *mats, int n_mats, bool pair, int64_t n_cols, const GemmActs &x, int T, const float *resid, int64_t ldr,
+                             void *part, size_t part_bytes, GemmShares *later, hipStream_t st);
 // the same for one matrix in another format (fmt_gemm.hip), where fmt_gemm_takes(fmt) (all of them but FP32, whose weights
-// are not exact in binary16); split_ready as above: ws may hold the split a Q4_K product of the group made, and vice versa
+// are not exact in binary16)
 bool fmt_gemm_takes(int fmt);
-prima_status launch_fmt_gemm(int fmt, const uint8_t *W, int64_t n_rows, int64_t n_cols, const float *x, int64_t ldx, int T,
-                             const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy,
-                             void *ws, hipStream_t st, bool split_ready, void *part, size_t part_bytes);
+size_t fmt_gemm_part_bytes(int T, int64_t n_rows, int64_t n_cols); // what its shares take where the scratch does not limit them
+prima_status launch_fmt_gemm(int fmt, const GemmMat &m, int64_t n_cols, const GemmActs &x, int T, const float *resid, int64_t ldr, void *part,
+                             size_t part_bytes, GemmShares *later, hipStream_t st);
+// RoPE on q and k, k and v appended to the caches as rows n_past .. n_past + T - 1; p: shares of q, k, v (n 0: complete, at part); q: where the rotated
+// queries go; tab from launch_rope_table
+struct RopeAppend {
+    GemmShares p[3];
+    GemmNorm norm;
+    const float *tab;
+    float *q;
+    __half *K, *V;
+    int kv_cap, n_past;
+    int Hq, Hkv, D, mode; // (filled in by the launch)
+};
+prima_status launch_rope_append(RopeAppend a, const prima_dims &d, int T, hipStream_t st);
 // RoPE table [T][D/2] of (cos, sin) for the positions n_past .. n_past + T - 1 (any T)
 prima_status launch_rope_table(float *tab, int T, int D, int n_past, float theta, hipStream_t st);
 
@@ -172,11 +217,6 @@ AttnRecords attn_records(const prima_dims &d, int n_past, int T, void *ws, const
 // a prompt: rotated K / V rows already in the caches, q rotated; pieces of PRIMA_MAX_TOK tokens in one launch
 prima_status launch_attn_prompt(const prima_dims &d, const float *q, __half *K, __half *V, int kv_cap, int n_past, int T,
                                 float *o, hipStream_t st);
-// RoPE on q (in place) and k, and k, v appended to the caches as rows n_past .. n_past + T - 1, for any T; tab from
-// launch_rope_table
-prima_status launch_rope_append(const prima_dims &d, float *q, const float *k, const float *v, const float *tab,
-                                __half *K, __half *V, int kv_cap, int n_past, int T, hipStream_t st);
-
 // 16 bytes per lane from global memory straight into LDS: lane l writes bytes [16 l, 16 l + 16) of the
 // 1 KiB at LDS byte address lds_addr (wave-uniform, goes through M0).  Written as inline assembly on
 // purpose: the compiler then does not know these loads write LDS and leaves the ordering against the

@@ -44,15 +44,16 @@ struct FmtGemmArgs {
     const uint8_t *W;
     int64_t n_rows, n_cols;
     const uint8_t *A;   // split activations
-    const float2 *stat; // per token: (2^p [* 1/rms], 2^-p)
+    GemmNorm norm;
     const float *resid;
     int64_t ldr;
     float *y;
     int64_t ldy;
     int T, n_tiles, n_rb, n_tb, band;
     int share_q, share_r, tile_q, tile_r; // as in q4k_gemm.hip
-    int ksplit; // as in q4k_gemm.hip: shares of K, each share's sums in part[share][token][n_rows]
+    int ksplit; // as in q4k_gemm.hip: shares of K, each share's sums in part[share][token][ldp]
     float *part;
+    int64_t ldp;
 };
 
 // value of the neighbouring lane (lane ^ 1)
@@ -84,8 +85,8 @@ struct FmLds {
     static constexpr int B_SLOT = B_PARTS * FM_ROWS * 64;   // [part][16-row tile][lane][16 bytes]
     static constexpr int B0 = 2 * A_SLOT;
     static constexpr int D0 = B0 + 2 * B_SLOT;              // d: [2][128] floats (Q8_0: per position; Q5_K: d, dmin)
-    static constexpr int M0 = D0 + 2 * FM_ROWS * 4;         // Q5_K: sums slabs of the tokens, then the m_s and the 16 sc_s of every row
-    static constexpr int TOTAL = FMT == PRIMA_FMT_Q5_K ? M0 + 2 * WT * 1024 + 2 * FM_ROWS * 16 : M0;
+    static constexpr int M0 = D0 + 2 * FM_ROWS * 4;         // sums slabs of the tokens; Q5_K: then the m_s and the 16 sc_s of every row
+    static constexpr int TOTAL = M0 + 2 * WT * 1024 + (FMT == PRIMA_FMT_Q5_K ? 2 * FM_ROWS * 16 : 0);
     static_assert(TOTAL <= 81920, "two workgroups per compute unit");
 };
 
@@ -252,7 +253,7 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
         }
     };
 
-    // ---- activation requests: 4 WT slabs of 1 KiB per position, WT per wave; a sums slab per token tile (Q5_K) ----
+    // ---- activation requests: 4 WT slabs of 1 KiB per position, WT per wave; a sums slab per token tile and super-block ----
     const uint32_t lds0 = lds_address(smem), lane16 = lane * 16;
     const uint8_t *abase[WT];
 #pragma unroll
@@ -267,7 +268,7 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
             if (FULL || wave * WT + j < 2 * tiles) dma16_base(abase[j] + off, lane16, lds0 + buf * L::A_SLOT + (wave * WT + j) * 1024);
     };
     auto issue_sums = [&](int b) __attribute__((always_inline)) {
-        if constexpr (Q5) {
+        {
 #pragma unroll
             for (int j = wave; j < 2 * WT; j += 4)
                 if (FULL || j < tiles) dma16_base(a.A + ((static_cast<int64_t>(min(tile0 + j, a.n_tiles - 1)) * nb + b) * GM_SLABS + 16) * 1024, lane16, lds0 + L::M0 + j * 1024);
@@ -373,18 +374,22 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
 #pragma unroll
                     for (int tt = 0; tt < WT; ++tt) {
                         gm_v4f am = zero, t = acc[tt][rt];
+                        // the sums slabs were requested a position ago by all waves and have landed before this position's barrier
+                        const uint8_t *const sums = l_xs + (2 * tt + wt) * 1024;
+                        unsigned off = GM_SCALES + 16 * g;
+                        asm volatile("" : "+v"(off)); // read again for every tile of rows: kept, they spill
+                        const gm_v4f scale = *reinterpret_cast<const gm_v4f *>(sums + off); // of this lane's tokens: powers of two
                         if constexpr (Q5) {
-                            // the sums slabs were requested a position ago by all waves and have landed before this position's barrier
-                            const half8 ax = *reinterpret_cast<const half8 *>(l_xs + (2 * tt + wt) * 1024 + lane * 16);
+                            const half8 ax = gemm_sums_operand(*reinterpret_cast<const half8 *>(sums + lane * 16), g);
                             am = __builtin_amdgcn_mfma_f32_16x16x32_f16(ax, m, zero, 0, 0, 0);
                             t = __builtin_amdgcn_mfma_f32_16x16x32_f16(ax, sc16, t, 0, 0, 0);
                         }
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             if constexpr (Q6) {
-                                ysum[tt][rt][i] = fmaf(d, t[i], ysum[tt][rt][i]);
+                                ysum[tt][rt][i] = fmaf(d * scale[i], t[i], ysum[tt][rt][i]);
                             } else {
-                                const float term = Q5 ? fmaf(d, t[i], -(dm * am[i])) : t[i];
+                                const float term = (Q5 ? fmaf(d, t[i], -(dm * am[i])) : t[i]) * scale[i];
                                 unsigned &cw = comp[tt][rt][i >> 1];
                                 const float c0 = __builtin_bit_cast(float, i & 1 ? cw & 0xffff0000u : cw << 16);
                                 const float v = term - c0, yn = ysum[tt][rt][i] + v;
@@ -401,6 +406,13 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
         hx = hx_next;
     }
 
+    const float *inv = nullptr; // 1/rms of the workgroup's tokens
+    if (a.norm.ss && a.ksplit == 1) {
+        float *const red = reinterpret_cast<float *>(smem);
+        gm_barrier(); // (the last operands have been read)
+        gemm_inv_rms_tokens<32 * WT>(a.norm, tile0 * 16, red, red + 256);
+        inv = red + 256;
+    }
 #pragma unroll
     for (int rt = 0; rt < FM_RT; ++rt) {
         const int64_t row = static_cast<int64_t>(rb) * FM_ROWS + wr * 64 + rt * 16 + n;
@@ -411,27 +423,17 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
             for (int i = 0; i < 4; ++i) {
                 const int t = (tile0 + 2 * tt + wt) * 16 + 4 * g + i;
                 if ((FULL || tt < my_tiles) && t < a.T) {
-                    float v = ysum[tt][rt][i] * a.stat[t].y;
+                    float v = ysum[tt][rt][i];
                     if (a.ksplit > 1) {
-                        a.part[(static_cast<int64_t>(share) * a.T + t) * a.n_rows + row] = v;
+                        a.part[(static_cast<int64_t>(share) * a.T + t) * a.ldp + row] = v;
                     } else {
+                        if (inv) v *= inv[16 * (2 * tt + wt) + 4 * g + i];
                         if (a.resid) v += a.resid[t * a.ldr + row];
                         a.y[t * a.ldy + row] = v;
                     }
                 }
             }
     }
-}
-
-// y = the shares of K added in order (+ resid)
-__global__ void __launch_bounds__(256) fmt_gemm_reduce_kernel(FmtGemmArgs a)
-{
-    const int64_t row = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    const int t = blockIdx.y;
-    if (row >= a.n_rows) return;
-    const float r = a.resid ? a.resid[t * a.ldr + row] : 0.f;
-    const float v = gemm_add_shares(a.part + static_cast<int64_t>(t) * a.n_rows + row, static_cast<int64_t>(a.T) * a.n_rows, a.ksplit);
-    a.y[t * a.ldy + row] = a.resid ? v + r : v;
 }
 
 template <int FMT, int WT, bool FULL>
@@ -448,75 +450,97 @@ prima_status launch_wt(const FmtGemmArgs &a, unsigned grid, hipStream_t st)
     return last_launch_status();
 }
 
-template <int FMT>
-prima_status launch_fm(FmtGemmArgs a, void *part, size_t part_bytes, hipStream_t st)
+// Token blocks and shares of K
+struct FmPlan {
+    bool narrow;
+    int n_tb, ksplit;
+};
+FmPlan plan_fm(int T, int64_t n_rows, int64_t n_cols, int64_t part_bytes)
 {
+    const int64_t n_rb = (n_rows + FM_ROWS - 1) / FM_ROWS, nb = n_cols / QK;
+    const int n_tiles = (T + 15) / 16;
+    FmPlan p{};
     // 128 tokens per workgroup, 64 where that leaves fewer tokens of padding or twice the workgroups on an idle device
-    const bool narrow = (a.n_tiles + 3) / 4 * 4 < (a.n_tiles + 7) / 8 * 8 || static_cast<int64_t>(a.n_rb) * ((a.n_tiles + 7) / 8) * 2 <= 2 * GM_CUS;
-    a.n_tb = narrow ? (a.n_tiles + 3) / 4 : (a.n_tiles + 7) / 8;
-    const int64_t wgs = static_cast<int64_t>(a.n_rb) * a.n_tb, slots = 2 * GM_CUS;
-    const int64_t nb = a.n_cols / QK;
+    p.narrow = (n_tiles + 3) / 4 * 4 < (n_tiles + 7) / 8 * 8 || n_rb * ((n_tiles + 7) / 8) * 2 <= 2 * GM_CUS;
+    p.n_tb = p.narrow ? (n_tiles + 3) / 4 : (n_tiles + 7) / 8;
+    const int64_t wgs = n_rb * p.n_tb, slots = 2 * GM_CUS;
     // Shares of K (at least 4 super-blocks each, as far as the scratch holds them): rounds of workgroups times a share's super-blocks, about
     // 7 us each at 64 tokens and 14 at 128, against the shares' way to memory and back (4 TB/s).  (As many as fit the device at once
     // left a quarter of it idle where they do not come out even: 4096 x 14336 in Q6_K, 333 tokens, two shares 227 us and 6 for their sum, five 200 and 7.)
     // The two figures serve every format: one layer of 8B, 14B and 70B shapes, 40 to 900 tokens, us, that rule / this one where they differ: down in Q5_K 8B 333
     // tokens (two shares / five) 576 / 553, Q8_0 576 / 561, FP16 604 / 587; 14B 400 (one / three) Q5_K 934 / 837, Q6_K 958 / 855, Q8_0 920 / 834, FP16 949 / 848; 70B
     // 180 (two / five) Q5_K 1034 / 971, FP16 1057 / 1018; every matrix, 14B, 180 tokens Q5_K 623 / 581, Q8_0 652 / 602, 512 tokens 1364 / 1197, 1357 / 1202.
-    a.ksplit = 1;
-    if (part && a.T <= 65535) {
-        const int64_t share_bytes = static_cast<int64_t>(a.T) * a.n_rows * static_cast<int64_t>(sizeof(float));
-        const int64_t most = std::min<int64_t>({nb / 4, 16, static_cast<int64_t>(part_bytes) / share_bytes});
+    p.ksplit = 1;
+    if (part_bytes > 0 && T <= 65535) {
+        const int64_t share_bytes = static_cast<int64_t>(T) * n_rows * static_cast<int64_t>(sizeof(float));
+        const int64_t most = std::min<int64_t>({nb / 4, 16, part_bytes / share_bytes});
         double best = 0.;
         for (int64_t ks = 1; ks <= std::max<int64_t>(1, most); ++ks) {
-            const double us = static_cast<double>((wgs * ks + slots - 1) / slots) * static_cast<double>((nb + ks - 1) / ks) * (narrow ? 7. : 14.) +
+            const double us = static_cast<double>((wgs * ks + slots - 1) / slots) * static_cast<double>((nb + ks - 1) / ks) * (p.narrow ? 7. : 14.) +
                               (ks > 1 ? 4. + static_cast<double>(ks * share_bytes) * 2. / 4e6 : 0.);
             if (ks == 1 || us < best) {
                 best = us;
-                a.ksplit = static_cast<int>(ks);
+                p.ksplit = static_cast<int>(ks);
             }
         }
     }
-    a.part = static_cast<float *>(part);
-    if (wgs * a.ksplit >= (int64_t{1} << 31) - GM_XCDS) return PRIMA_E_SHAPE;
+    return p;
+}
+
+template <int FMT>
+prima_status launch_fm(FmtGemmArgs a, const FmPlan &p, hipStream_t st)
+{
+    const int64_t wgs = static_cast<int64_t>(a.n_rb) * p.n_tb, nb = a.n_cols / QK;
+    if (wgs * p.ksplit >= (int64_t{1} << 31) - GM_XCDS) return PRIMA_E_SHAPE;
+    a.n_tb = p.n_tb;
+    a.ksplit = p.ksplit;
     a.band = gemm_band(a.n_tb);
     a.share_q = static_cast<int>(nb / a.ksplit); a.share_r = static_cast<int>(nb % a.ksplit);
     a.tile_q = a.n_tiles / a.n_tb; a.tile_r = a.n_tiles % a.n_tb;
     const unsigned grid = gemm_grid(wgs * a.ksplit);
     // full workgroups where that leaves less than a twentieth of padding
-    const bool full = (a.n_tb * (narrow ? 4 : 8) - a.n_tiles) * 20 < a.n_tiles;
-    const prima_status s = narrow ? (full ? launch_wt<FMT, 2, true>(a, grid, st) : launch_wt<FMT, 2, false>(a, grid, st))
-                                  : (full ? launch_wt<FMT, 4, true>(a, grid, st) : launch_wt<FMT, 4, false>(a, grid, st));
-    if (s != PRIMA_OK || a.ksplit == 1) return s;
-    hipLaunchKernelGGL(fmt_gemm_reduce_kernel, dim3(static_cast<unsigned>((a.n_rows + 255) / 256), a.T), dim3(256), 0, st, a);
-    return last_launch_status();
+    const bool full = (a.n_tb * (p.narrow ? 4 : 8) - a.n_tiles) * 20 < a.n_tiles;
+    if (p.narrow) return full ? launch_wt<FMT, 2, true>(a, grid, st) : launch_wt<FMT, 2, false>(a, grid, st);
+    return full ? launch_wt<FMT, 4, true>(a, grid, st) : launch_wt<FMT, 4, false>(a, grid, st);
 }
 
 } // namespace
 
 bool fmt_gemm_takes(int fmt) { return fmt == PRIMA_FMT_Q5_K || fmt == PRIMA_FMT_Q6_K || fmt == PRIMA_FMT_Q8_0 || fmt == PRIMA_FMT_F16; }
 
-prima_status launch_fmt_gemm(int fmt, const uint8_t *W, int64_t n_rows, int64_t n_cols, const float *x, int64_t ldx, int T,
-                             const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy,
-                             void *ws, hipStream_t st, bool split_ready, void *part, size_t part_bytes)
+size_t fmt_gemm_part_bytes(int T, int64_t n_rows, int64_t n_cols)
 {
-    if (T == 0 || n_rows == 0) return PRIMA_OK;
-    const int64_t n_rb = (n_rows + FM_ROWS - 1) / FM_ROWS;
+    const int ks = plan_fm(T, n_rows, n_cols, int64_t{1} << 62).ksplit;
+    return ks == 1 ? 0 : static_cast<size_t>(ks) * static_cast<size_t>(T) * static_cast<size_t>(n_rows) * sizeof(float);
+}
+
+prima_status launch_fmt_gemm(int fmt, const GemmMat &m, int64_t n_cols, const GemmActs &x, int T, const float *resid, int64_t ldr, void *part,
+                             size_t part_bytes, GemmShares *later, hipStream_t st)
+{
+    if (later) *later = GemmShares{};
+    if (T == 0 || m.n_rows == 0) return PRIMA_OK;
+    const int64_t n_rb = (m.n_rows + FM_ROWS - 1) / FM_ROWS;
     const int n_tiles = (T + 15) / 16;
     if (n_rb >= (int64_t{1} << 30) || n_tiles > 65535 || n_cols / QK >= (int64_t{1} << 31)) return PRIMA_E_SHAPE;
-    if (!split_ready) {
-        const prima_status s = launch_gemm_split(n_cols, x, ldx, T, gain, eps, ws, st);
-        if (s != PRIMA_OK) return s;
-    }
+    const FmPlan p = plan_fm(T, m.n_rows, n_cols, part ? static_cast<int64_t>(part_bytes) : 0);
     FmtGemmArgs a{};
-    a.W = W; a.n_rows = n_rows; a.n_cols = n_cols; a.A = gemm_split(ws, T); a.stat = gemm_stat(ws);
-    a.resid = resid; a.ldr = ldr; a.y = y; a.ldy = ldy; a.T = T; a.n_tiles = n_tiles; a.n_rb = static_cast<int>(n_rb);
+    a.W = m.W; a.n_rows = m.n_rows; a.n_cols = n_cols; a.A = x.A; a.norm = x.norm;
+    a.resid = resid; a.ldr = ldr; a.y = m.y; a.ldy = m.ldy; a.T = T; a.n_tiles = n_tiles; a.n_rb = static_cast<int>(n_rb);
+    a.part = static_cast<float *>(part);
+    a.ldp = m.n_rows;
+    prima_status s;
     switch (fmt) {
-    case PRIMA_FMT_Q5_K: return launch_fm<PRIMA_FMT_Q5_K>(a, part, part_bytes, st);
-    case PRIMA_FMT_Q6_K: return launch_fm<PRIMA_FMT_Q6_K>(a, part, part_bytes, st);
-    case PRIMA_FMT_Q8_0: return launch_fm<PRIMA_FMT_Q8_0>(a, part, part_bytes, st);
-    case PRIMA_FMT_F16: return launch_fm<PRIMA_FMT_F16>(a, part, part_bytes, st);
+    case PRIMA_FMT_Q5_K: s = launch_fm<PRIMA_FMT_Q5_K>(a, p, st); break;
+    case PRIMA_FMT_Q6_K: s = launch_fm<PRIMA_FMT_Q6_K>(a, p, st); break;
+    case PRIMA_FMT_Q8_0: s = launch_fm<PRIMA_FMT_Q8_0>(a, p, st); break;
+    case PRIMA_FMT_F16: s = launch_fm<PRIMA_FMT_F16>(a, p, st); break;
     default: return PRIMA_E_SHAPE;
     }
+    if (s != PRIMA_OK || p.ksplit == 1) return s;
+    const GemmShares sh{a.part, p.ksplit, static_cast<int64_t>(T) * a.ldp, a.ldp, {0, 0, 0}};
+    if (!later) return launch_gemm_sum(sh, x.norm, resid, ldr, m.y, m.ldy, m.n_rows, T, st);
+    *later = sh;
+    return PRIMA_OK;
 }
 
 } // namespace prima

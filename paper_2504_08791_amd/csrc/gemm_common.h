@@ -10,11 +10,13 @@ typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float gm_v4f __attribute__((ext_vector_type(4)));
 
 // Split activations: [token tile of 16][super-block][17 slabs][64 lanes] x 16 bytes; slabs 2 s and 2 s + 1 are the hi and lo
-// parts of sub-block s (lane (m, g): token m, columns 8g .. 8g+7 of the sub-block in the order 0 4 1 5 2 6 3 7), slab 16
-// the sub-block sums (lane (m, 0) their hi parts, lane (m, 1) their lo parts).
+// parts of sub-block s (lane (m, g): token m, columns 8g .. 8g+7 of the sub-block in the order 0 4 1 5 2 6 3 7: that in which a dword of
+// eight 4-bit weights unpacks into pairs), scaled by a power of two per token and super-block to less than 1024.  Slab 16: the sub-block sums, lane (m, 0)
+// their hi parts, lane (m, 1) their lo parts; behind them, at GM_SCALES, the 16 tokens' scales as floats, 2^-p, and then nothing that was written: the
+// lanes (m, 2) and (m, 3) of that operand have to be zeros (gemm_sums_operand()).
 constexpr int GM_SLABS = 17;
 constexpr int GM_TILE_BYTES = GM_SLABS * 1024;
-constexpr size_t GM_STAT_ALIGN = 1024;
+constexpr int GM_SCALES = 512;
 constexpr int GM_XCDS = 8;
 constexpr int GM_CUS = 256;
 
@@ -36,16 +38,53 @@ __device__ __forceinline__ bool gemm_unit(unsigned wg, int n_rb, int n_tb, int n
     return true;
 }
 inline unsigned gemm_grid(int64_t units) { return static_cast<unsigned>((units + GM_XCDS - 1) / GM_XCDS * GM_XCDS); }
-inline int gemm_band(int n_tb) { return 32 / (n_tb < 8 ? n_tb : 8); }
+inline int gemm_band(int n_tb) { return n_tb <= 8 ? 1 : 8; }
 
-// the split activations and the per-token (2^p [* 1/rms], 2^-p) inside the scratch of gemm_ws_bytes(T, n_cols)
-inline float2 *gemm_stat(void *ws) { return static_cast<float2 *>(ws); }
-inline uint8_t *gemm_split(void *ws, int T)
+__device__ __forceinline__ half8 gemm_sums_operand(half8 v, int g)
 {
-    return static_cast<uint8_t *>(ws) + round_up(static_cast<size_t>(T) * sizeof(float2), GM_STAT_ALIGN);
+    const half8 none = {};
+    return g < 2 ? v : none;
 }
-// fills both (two launches)
-prima_status launch_gemm_split(int64_t n_cols, const float *x, int64_t ldx, int T, const float *gain, float eps, void *ws, hipStream_t st);
+
+// 1/rms of token t from its sums of squares over super-blocks, added by a wave, by 16 lanes, or by a workgroup of 256 threads for the NT
+// tokens from t0 on (into inv[NT]; red[256]: scratch; both in LDS, a barrier in between and behind)
+__device__ __forceinline__ float gemm_inv_rms(const GemmNorm &n, float squares) { return 1.0f / sqrtf(squares / (static_cast<float>(n.nb) * 256.f) + n.eps); }
+__device__ __forceinline__ float gemm_squares64(const GemmNorm &n, int t, int lane)
+{
+    float s = 0.f;
+    for (int b = lane; b < n.nb; b += 64) s += n.ss[static_cast<int64_t>(b) * n.ld + t];
+    return s;
+}
+__device__ __forceinline__ float gemm_inv_rms16(const GemmNorm &n, int t, int j)
+{
+    float s = 0.f;
+    for (int b = j; b < n.nb; b += 16) s += n.ss[static_cast<int64_t>(b) * n.ld + t];
+    return gemm_inv_rms(n, row_sum16(s));
+}
+template <int NT>
+__device__ __forceinline__ void gemm_inv_rms_tokens(const GemmNorm &n, int t0, float *red, float *inv)
+{
+    constexpr int P = 256 / NT;
+    const int k = threadIdx.x % NT, t = min(t0 + k, n.ld - 1);
+    float s = 0.f;
+    for (int b = threadIdx.x / NT; b < n.nb; b += P) s += n.ss[static_cast<int64_t>(b) * n.ld + t];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    if (threadIdx.x < NT) {
+#pragma unroll
+        for (int i = 1; i < P; ++i) s += red[i * NT + k];
+        inv[k] = gemm_inv_rms(n, s);
+    }
+    __syncthreads();
+}
+
+// The lane's number, made anew: what is addressed with it is formed where it is used (kept over a kernel's loop it spills).
+__device__ __forceinline__ int lane_anew()
+{
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+}
 
 // 16 bytes per lane from global memory straight into LDS (as dma16), with the address as a wave-uniform base plus a
 // 32-bit lane offset: the bases live in scalar registers and cost no vector register per request in flight

@@ -8,15 +8,14 @@
 // token group and stops scaling at 8 tokens.  Here:
 //   * the B operand is the weight tile itself: per sub-block of 32 weights the integers sc_s * q (at most 945:
 //     exact in binary16), built in registers once per super-block and used for every token of the workgroup;
-//   * the A operand is the activations as two binary16 numbers hi + lo (22 bits), scaled per token by a power
-//     of two so that |a| < 1024; products of two binary16 numbers are exact in fp32, the MFMA adds in fp32;
+//   * the A operand is the activations as two binary16 numbers hi + lo (22 bits), scaled per token and super-block by a
+//     power of two so that |a| < 1024; products of two binary16 numbers are exact in fp32, the MFMA adds in fp32;
 //   * one accumulator per super-block (256 weights, 8 MFMA steps x 2); the min term sum_s m_s * xs_s (xs_s: the
 //     sub-block sums of the scaled activations, again as hi + lo) is one more MFMA step with the m_s as B operand;
 //     then  y += d * acc - dmin * acc_m  in fp32.
-// Three kernels.  (1) per token: 1/rms (RMSNorm in front) and the power of two.  (2) the activations, split and
-// laid out in A-operand order per (16-token tile, super-block): 17 slabs of 1 KiB (8 sub-blocks x (hi, lo), and
-// the sums), so that the product kernel moves them into LDS with 16-byte global->LDS loads and no arithmetic; the
-// split is done once, not once per row block.  (3) the product: a workgroup of 4 waves owns 256 rows x 64 tokens,
+// gemm_prepare.hip splits the activations and lays them out in A-operand order per (16-token tile, super-block): 17 slabs of 1 KiB
+// (8 sub-blocks x (hi, lo), and the sums), so that the product kernel moves them into LDS with 16-byte global->LDS loads and no
+// arithmetic; the split is done once, not once per row block.  The product: a workgroup of 4 waves owns 256 rows x 64 tokens,
 // a wave 64 rows (four B tiles in registers: every A tile read from LDS feeds four MFMAs per part); two workgroups
 // share a compute unit, so that one's VALU and LDS phases run under the other's MFMAs.  The super-block is walked
 // sub-block by sub-block; global->LDS loads fill a ring of activation slots two positions ahead and, per wave,
@@ -48,7 +47,11 @@ constexpr int GM_NS = 3;                        // ring slots: positions whose a
                                                 // and 5 slots measured the same)
 constexpr int GM_SLOT = GM_TT * 2048;                                     // 8 KiB of activations
 constexpr int GM_WQ = 2 * 4096;                                           // per wave: the quants of half a super-block, twice
-constexpr int GM_LDS_BYTES = GM_NS * GM_SLOT + GM_WAVES * (GM_WQ + 2 * 1024); // 64 KiB: two workgroups per compute unit
+// per wave: a super-block's headers as they come, and what its 64 rows need of them: the sub-scales as binary16 pairs [sub-block][row], the m_s [row], d and dmin
+// [row] twice, of super-blocks in turn
+constexpr int GM_HDR = 1024, GM_SC = 8 * 256, GM_M = 1024, GM_D = 512, GM_DEC = GM_SC + GM_M + 2 * GM_D;
+constexpr int GM_LDS_BYTES = GM_NS * GM_SLOT + GM_WAVES * (GM_WQ + GM_HDR + GM_DEC); // 76 KiB: two workgroups per compute unit
+static_assert(2 * GM_LDS_BYTES <= 160 * 1024, "two workgroups per compute unit");
 struct GemmSegDev {
     const uint8_t *W;
     float *y;
@@ -63,134 +66,20 @@ struct GemmArgs {
     GemmSegDev seg[3];
     int pair;
     int64_t n_cols;
-    const uint8_t *A;   // split activations: [token tile][super-block][17][64 lanes] x 16 bytes
-    const float2 *stat; // per token: (2^p [* 1/rms], 2^-p)
+    const uint8_t *A; // split activations: [token tile][super-block][17][64 lanes] x 16 bytes
+    GemmNorm norm;
     const float *resid; // null: none (added to every stored row; launches with a residual have one matrix)
     int64_t ldr;
     int T, n_tiles, n_rb, n_tb; // 16-token tiles, row blocks, token blocks
     int band;                   // gemm_band()
     // K divided among ksplit workgroups per (row block, token block): each walks its share of the
-    // super-blocks and stores its sums to part[split][token][ldp] (column: row block * GM_ROWS + row in the block);
-    // gemm_ksplit_reduce_kernel adds the shares in order.  ksplit == 1: the sums go straight to y.
+    // super-blocks and stores its sums to part[split][token][ldp] (column: row block * GM_ROWS + row in the block); a
+    // launch of gemm_prepare.hip adds them.  ksplit == 1: the sums go straight to y.
     int ksplit;
     int share_q, share_r, tile_q, tile_r; // super-blocks of a share and tiles of a token block: quotients, and how many have one more
     float *part;
     int64_t ldp;
 };
-
-// per token: 1/rms (RMSNorm in front) and the power of two that brings max |a| below 1024
-__global__ void __launch_bounds__(256) gemm_token_scale_kernel(const float *__restrict__ x, int64_t ldx, int64_t K, const float *__restrict__ gain,
-                                                               float eps, float2 *__restrict__ stat)
-{
-    __shared__ float red[2][4];
-    const int t = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float ss = 0.f, amax = 0.f;
-    // eight pieces of the row requested at a time: one by one they were a chain of K / 1024 trips through memory (1024 tokens of 28672 columns 23.7 -> 20 us, of 8192 7 to 8.4 -> 6.5 to 7.8)
-    constexpr int AT = 8;
-    for (int64_t k0 = static_cast<int64_t>(threadIdx.x) * 4; k0 < K; k0 += AT * 1024) {
-        float4 v[AT], g[AT];
-#pragma unroll
-        for (int j = 0; j < AT; ++j) { // (past the end: the thread's first piece again, not counted)
-            const int64_t k = k0 + j * 1024 < K ? k0 + j * 1024 : k0;
-            v[j] = *reinterpret_cast<const float4 *>(x + t * ldx + k);
-            g[j] = make_float4(1.f, 1.f, 1.f, 1.f);
-            if (gain) g[j] = *reinterpret_cast<const float4 *>(gain + k);
-        }
-#pragma unroll
-        for (int j = 0; j < AT; ++j) {
-            if (k0 + j * 1024 >= K) break;
-            ss += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
-            amax = fmaxf(fmaxf(amax, fmaxf(fabsf(v[j].x * g[j].x), fabsf(v[j].y * g[j].y))), fmaxf(fabsf(v[j].z * g[j].z), fabsf(v[j].w * g[j].w)));
-        }
-    }
-    ss = wave_sum(ss);
-    amax = wave_max(amax);
-    if (lane == 0) { red[0][wave] = ss; red[1][wave] = amax; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        ss = ((red[0][0] + red[0][1]) + red[0][2]) + red[0][3];
-        amax = fmaxf(fmaxf(red[1][0], red[1][1]), fmaxf(red[1][2], red[1][3]));
-        const float inv_rms = gain ? 1.0f / sqrtf(ss / static_cast<float>(K) + eps) : 1.f;
-        amax *= inv_rms;
-        int ex = 0;
-        if (amax > 0.f) frexpf(amax, &ex); // amax < 2^ex
-        int p = 10 - ex;
-        p = p > 100 ? 100 : (p < -100 ? -100 : p);
-        stat[t] = make_float2(ldexpf(inv_rms, p), ldexpf(1.0f, -p));
-    }
-}
-
-// The activations of one (16-token tile, super-block) in A-operand order.  Lane (m, g) of an MFMA step holds, for
-// token m, the columns 8g .. 8g+7 of a sub-block in the order 0 4 1 5 2 6 3 7 (the order in which the product
-// kernel unpacks a dword of eight 4-bit weights into four binary16 pairs).  Tokens past T are zeros.
-__global__ void __launch_bounds__(256) gemm_split_kernel(const float *__restrict__ x, int64_t ldx, const float *__restrict__ gain,
-                                                         const float2 *__restrict__ stat, int T, int64_t nb, uint8_t *__restrict__ A)
-{
-    __shared__ float xs[16][8];
-    const int64_t b = blockIdx.x;
-    const int tile = blockIdx.y;
-    const int m = threadIdx.x >> 4, c0 = (threadIdx.x & 15) * 16;
-    const int t = tile * 16 + m;
-    const bool valid = t < T;
-    const int ts = valid ? t : T - 1;
-    const float scale = stat[ts].x;
-    const float *xp = x + ts * ldx + b * 256 + c0;
-    float v[16];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float4 q = *reinterpret_cast<const float4 *>(xp + 4 * i);
-        v[4 * i] = q.x; v[4 * i + 1] = q.y; v[4 * i + 2] = q.z; v[4 * i + 3] = q.w;
-    }
-    if (gain) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float4 q = *reinterpret_cast<const float4 *>(gain + b * 256 + c0 + 4 * i);
-            v[4 * i] *= q.x; v[4 * i + 1] *= q.y; v[4 * i + 2] *= q.z; v[4 * i + 3] *= q.w;
-        }
-    }
-    float sum = 0.f;
-    _Float16 hh[16], ll[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        float sv = valid ? v[i] * scale : 0.f;
-        // the product as an opaque fp32 number: left visible, the compiler formed the stored hi from the rounded
-        // product and the hi that lo is taken against from the exact one (fused multiply-convert); the two differ
-        // now and then by one binary16 step, which lo then does not make up for
-        asm volatile("" : "+v"(sv));
-        hh[i] = static_cast<_Float16>(sv);
-        ll[i] = static_cast<_Float16>(sv - static_cast<float>(hh[i]));
-        sum += static_cast<float>(hh[i]) + static_cast<float>(ll[i]); // what the MFMAs will see
-    }
-    const int s8 = c0 >> 5, g0 = (c0 & 31) >> 3; // sub-block, and the first of this thread's two 8-column groups
-    uint8_t *dst = A + (static_cast<int64_t>(tile) * nb + b) * GM_TILE_BYTES;
-#pragma unroll
-    for (int gi = 0; gi < 2; ++gi) {
-        half8 h, l;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int c = 8 * gi + (j & 1) * 4 + (j >> 1);
-            h[j] = hh[c];
-            l[j] = ll[c];
-        }
-        *reinterpret_cast<half8 *>(dst + (2 * s8) * 1024 + (m + 16 * (g0 + gi)) * 16) = h;
-        *reinterpret_cast<half8 *>(dst + (2 * s8 + 1) * 1024 + (m + 16 * (g0 + gi)) * 16) = l;
-    }
-    sum += __shfl_xor(sum, 1, 64); // the two threads of a sub-block are neighbours
-    if ((threadIdx.x & 1) == 0) xs[m][s8] = sum;
-    __syncthreads();
-    if (threadIdx.x < 64) { // slab 16: lane (m, 0) the sums' hi parts, lane (m, 1) their lo parts, lanes (m, 2..3) zeros
-        const int mm = threadIdx.x & 15, gg = threadIdx.x >> 4;
-        half8 o;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float s = xs[mm][j];
-            const _Float16 sh = static_cast<_Float16>(s);
-            const _Float16 sl = static_cast<_Float16>(s - static_cast<float>(sh));
-            o[j] = gg == 0 ? sh : (gg == 1 ? sl : static_cast<_Float16>(0.f));
-        }
-        *reinterpret_cast<half8 *>(dst + 16 * 1024 + threadIdx.x * 16) = o;
-    }
-}
 
 // dma16_base with a per-lane pointer plus a constant byte offset (0 .. 4095) in the instruction instead.  The instruction adds
 // its offset to the LDS address as well as to the global one, so M0 gets the LDS address less the offset.
@@ -219,14 +108,14 @@ constexpr int requests_behind(int s, bool successor, int dm)
 static_assert(GM_AHEAD >= 2 && GM_AHEAD <= 4, "the weight requests at s == 3, 4, 7 must be older than the activation requests a wait lets pass");
 
 // One workgroup: 4 waves, one per SIMD; a wave owns 64 rows (four B tiles) x 64 tokens, i.e. 16 accumulator tiles for the
-// super-block in hand and as many running sums; two workgroups share a compute unit (237 registers per wave, 64 KiB of
+// super-block in hand and as many running sums; two workgroups share a compute unit (up to 256 registers per wave, 76 KiB of
 // LDS per workgroup) and run out of step with each other.  The super-block is walked sub-block by sub-block ("positions"
 // 0..7, then position 8: the sums slab and the min term).  Everything comes through LDS by 16-byte global->LDS loads:
 //   activations: a ring of NS slots of 8 KiB, [4 token tiles][hi 1 KiB | lo 1 KiB] of a sub-block, shared by the four
 //     waves, requested NS - 1 positions ahead (position 8 uses the slot's first 4 KiB for the sums slabs);
 //   quants: per wave two buffers of 4 KiB, sub-blocks 0-3 and 4-7 of its 64 rows, each filled by four requests of 64
 //     bytes x 16 rows as soon as the B tiles of the half super-block before have been built from it;
-//   headers: 64 rows x 16 bytes per wave and super-block, a ring of two.
+//   headers: 64 rows x 16 bytes per wave and super-block, decoded into LDS of the wave.
 // Per position: wait until everything this wave requested four positions ago or earlier has landed (requests complete
 // in order; the wait names the number of requests made since, which the schedule fixes), barrier (everyone's share of
 // the activations is there, and everyone has finished reading the slot of the position before, which is the slot
@@ -242,7 +131,7 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
 {
     constexpr int SLOT = GM_SLOT;
     constexpr int WQ_BASE = GM_NS * SLOT;            // per wave two buffers of 4 KiB: quants of sub-blocks 0-3, of 4-7
-    constexpr int HDR_RING = WQ_BASE + GM_WAVES * GM_WQ; // two entries of GM_WAVES KiB
+    constexpr int HDR = WQ_BASE + GM_WAVES * GM_WQ, DEC = HDR + GM_WAVES * GM_HDR;
     constexpr int DM = (TT + 1) / 2;                 // activation requests per wave at a sub-block position (one at the sums position)
     static_assert(TT >= 1 && TT <= GM_WAVES && GM_WAVES == 4, "requests per wave and position are counted for up to 4 tiles and 4 waves");
 
@@ -260,24 +149,18 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
     // (lane & 3) of row 16k + (lane >> 2): 16 runs of 64 bytes per request (16 bytes of each of 64 rows per request cost
     // about 12 % at 1024 tokens and more).  Local row r: row0 + r of the matrix, or (pair) row0 + (r & 31) of the gate
     // (r < 32) or the up matrix; past the end: a valid row, not stored.
-    auto row_ptr = [&](int r) __attribute__((always_inline)) -> const uint8_t * {
-        const int64_t gr = min<int64_t>(row0 + (a.pair ? (r & 31) : r), my.n_rows - 1);
-        return (a.pair ? a.seg[r >> 5].W : my.W) + gr * nb * 144;
-    };
-    const uint8_t *wsrc = row_ptr(lane);
+    const uint32_t stride = static_cast<uint32_t>(nb) * 144; // of a row (the host refuses more)
+    const int64_t row_c = min<int64_t>(row0, my.n_rows - 1);
+    const int left = static_cast<int>(min<int64_t>(my.n_rows - 1 - row_c, 63)); // rows of this wave behind its first
     // The four 16-byte pieces of a row's half lie in LDS in an order of their own for every fourth row, which the requests bring about: read in
     // the file's order, rows n and n + 4 share the banks (a row is 64 bytes), four lanes to each.
-    const uint8_t *wq[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) wq[k] = row_ptr(16 * k + (lane >> 2)) + 16 + ((lane & 3) ^ (lane >> 4)) * 16;
     const uint32_t lds0 = lds_address(smem);
     // this workgroup's share of K: super-blocks [b_lo, b_lo + nbl) (all of them unless K is divided; never empty: the
     // host keeps ksplit <= nb); below, `b` counts from b_lo
     const int b_lo = share * a.share_q + min(share, a.share_r);
     const int nbl = a.share_q + (share < a.share_r ? 1 : 0);
-    wsrc += static_cast<int64_t>(b_lo) * 144;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) wq[k] += static_cast<int64_t>(b_lo) * 144;
+    const int64_t w_off = row_c * stride + static_cast<int64_t>(b_lo) * 144;
+    const uint8_t *const w0 = my.W + w_off, *const w1 = (a.pair ? a.seg[1].W : my.W) + w_off; // local rows 0 .. 31, 32 .. 63
     const int total = 9 * nbl; // positions (n_cols < 2^32: no overflow)
 
     // Wave-uniform bases of this wave's activation requests: request jj of a sub-block position is slab (part, tile)
@@ -295,20 +178,28 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
     auto issue_quants = [&](int b, int half) __attribute__((always_inline)) {
         const uint32_t dst = lds0 + WQ_BASE + wave * GM_WQ + half * 4096;
         const int64_t off = static_cast<int64_t>(b) * 144;
+        const int l = lane_anew(), r = l >> 2;
+        const uint32_t c = 16 + ((l & 3) ^ (l >> 4)) * 16;
+        auto from = [&](int k) __attribute__((always_inline)) {
+            const uint32_t rk = min((a.pair ? 16 * (k & 1) : 16 * k) + r, left);
+            return (k < 2 ? w0 : w1) + off + (static_cast<uint64_t>(rk) * stride + c);
+        };
         if (half == 0) {
-            dma16_off<0>(wq[0] + off, dst);
-            dma16_off<0>(wq[1] + off, dst + 1024);
-            dma16_off<0>(wq[2] + off, dst + 2048);
-            dma16_off<0>(wq[3] + off, dst + 3072);
+            dma16_off<0>(from(0), dst);
+            dma16_off<0>(from(1), dst + 1024);
+            dma16_off<0>(from(2), dst + 2048);
+            dma16_off<0>(from(3), dst + 3072);
         } else {
-            dma16_off<64>(wq[0] + off, dst);
-            dma16_off<64>(wq[1] + off, dst + 1024);
-            dma16_off<64>(wq[2] + off, dst + 2048);
-            dma16_off<64>(wq[3] + off, dst + 3072);
+            dma16_off<64>(from(0), dst);
+            dma16_off<64>(from(1), dst + 1024);
+            dma16_off<64>(from(2), dst + 2048);
+            dma16_off<64>(from(3), dst + 3072);
         }
     };
     auto issue_headers = [&](int b) __attribute__((always_inline)) {
-        dma16_off<0>(wsrc + static_cast<int64_t>(b) * 144, lds0 + HDR_RING + ((b & 1) * GM_WAVES + wave) * 1024);
+        const int r = lane_anew();
+        const uint32_t rr = min(a.pair ? r & 31 : r, left);
+        dma16_off<0>((r < 32 ? w0 : w1) + static_cast<int64_t>(b) * 144 + static_cast<uint64_t>(rr) * stride, lds0 + HDR + wave * GM_HDR);
     };
     // the activation requests of position (b, s), into ring slot `slot` (s is a constant wherever this is called)
     auto issue = [&](int b, int s, int slot) __attribute__((always_inline)) {
@@ -343,15 +234,30 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
         if (q == GM_AHEAD - 2) issue_quants(0, 1); // as position (b - 1, 7) would have
     }
 
-    // Words 1 and 2 of the headers (stream bits 0 .. 63: the eight sub-scales) of the super-block whose B tiles are being built,
-    // this lane's row of each tile: read once per super-block.  (Read with the rest of the header for every tile and position
-    // they were 4 of the 13 KiB that a wave took out of LDS per position.  With the shorter unpacking below: 28672 x 8192 at 1024
-    // tokens 1175 -> 1151 us, 14336 x 4096 at 333 tokens 155 -> 149.)
-    uint2 hsc[GM_RT];
-    auto load_scales = [&](int rt, int bb) __attribute__((always_inline)) {
-        hsc[rt] = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint32_t *>(smem + HDR_RING + ((bb & 1) * GM_WAVES + wave) * 1024 + (16 * rt + n) * 16) + 1);
+    // A super-block's headers are decoded once, a lane a row, into LDS of the wave's own, at the last sub-block position of the super-block before
+    // (the sub-scales there have been read then, and its m_s are read first).  (Decoded where they are used, by the four lanes
+    // that share a row, for every tile, they were 18 of the 52 vector instructions of a position and 80 of those in front of the sums.)
+    uint8_t *const dec = smem + DEC + wave * GM_DEC;
+    auto decode_scales = [&](const uint4 &hd, int l, int from, int to) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s8 = 0; s8 < 8; ++s8) {
+            if (s8 < from || s8 >= to) continue;
+            const _Float16 sc = static_cast<_Float16>(static_cast<unsigned short>(hdr_field(hd, s8)));
+            *reinterpret_cast<half2v *>(dec + s8 * 256 + l * 4) = half2v{sc, sc} * half2v{static_cast<_Float16>(1024.f), static_cast<_Float16>(64.f)};
+        }
     };
-    // B tile `rt` of sub-block s from this wave's quants and the sub-scales in hsc: 2^-14 sc_s q as binary16 (exact: 10 bits, 2^-14 at the
+    auto decode_m = [&](const uint4 &hd, int l) __attribute__((always_inline)) {
+        half8 m;
+#pragma unroll
+        for (int s8 = 0; s8 < 8; ++s8) m[s8] = static_cast<_Float16>(static_cast<unsigned short>(hdr_field(hd, 8 + s8)));
+        *reinterpret_cast<half8 *>(dec + GM_SC + l * 16) = m;
+    };
+    auto decode_d = [&](const uint4 &hd, int l, int bb) __attribute__((always_inline)) {
+        *reinterpret_cast<float2 *>(dec + GM_SC + GM_M + (bb & 1) * GM_D + l * 8) = make_float2(hdr_d(hd) * 16384.f, hdr_dmin(hd)); // (the B tiles are 2^-14 of sc q)
+    };
+    auto header = [&](int l) __attribute__((always_inline)) { return *reinterpret_cast<const uint4 *>(smem + HDR + wave * GM_HDR + l * 16); };
+    auto scale_of = [&](int rt, int s) __attribute__((always_inline)) { return *reinterpret_cast<const half2v *>(dec + s * 256 + (16 * rt + n) * 4); };
+    // B tile `rt` of sub-block s from this wave's quants and sub-scales: 2^-14 sc_s q as binary16 (exact: 10 bits, 2^-14 at the
     // least).  A dword holds the eight weights of lane (n, g).  Masked in pairs (0,4) (1,5) (2,6) (3,7) they are subnormal binary16 numbers as
     // they stand, 2^-24 q and, the odd pairs (bits 4..7 of a half), 2^-20 q: one multiplication by 2^10 sc or 2^6 sc each.  (With an exponent
     // put in, 1024 + q, a fused multiply-add that took 1024 sc off again: four vector instructions more per tile pair; 70B 1024 tokens 3920 -> 3860 us, 8B
@@ -364,9 +270,7 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
         // request rt of the half brought rows 16 rt .. 16 rt + 15: [row][sub-block of the half][16 bytes]
         return *reinterpret_cast<const uint32_t *>(smem + WQ_BASE + wave * GM_WQ + (s >> 2) * 4096 + rt * 1024 + (lane_q ^ ((s & 3) << 4)));
     };
-    auto build_b = [&](half8 &B, uint32_t w, int rt, int s) __attribute__((always_inline)) {
-        const _Float16 sc = static_cast<_Float16>(static_cast<unsigned short>(hdr_field(make_uint4(0u, hsc[rt].x, hsc[rt].y, 0u), s)));
-        const half2v sc2 = half2v{sc, sc} * half2v{static_cast<_Float16>(1024.f), static_cast<_Float16>(64.f)};
+    auto build_b = [&](half8 &B, uint32_t w, half2v sc2) __attribute__((always_inline)) {
         const half2v sca = {sc2[0], sc2[0]}, scb = {sc2[1], sc2[1]};
 #pragma unroll
         for (int pr = 0; pr < 4; ++pr) {
@@ -376,13 +280,10 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
             B[2 * pr + 1] = r[1];
         }
     };
-    // ... and of the sums position: the m_s as B operand, with d and dmin
-    auto build_m = [&](half8 &B, float &d_, float &dm_, int rt, int bb) __attribute__((always_inline)) {
-        const uint4 hdr = *reinterpret_cast<const uint4 *>(smem + HDR_RING + ((bb & 1) * GM_WAVES + wave) * 1024 + (16 * rt + n) * 16);
-        d_ = hdr_d(hdr) * 16384.f; // (the B tiles are 2^-14 of sc q)
-        dm_ = hdr_dmin(hdr);
-#pragma unroll
-        for (int s8 = 0; s8 < 8; ++s8) B[s8] = static_cast<_Float16>(static_cast<unsigned short>(hdr_field(hdr, 8 + s8)));
+    // the m_s, B operand of the sums position, and d and dmin
+    auto m_of = [&](int l, int rt) __attribute__((always_inline)) { return *reinterpret_cast<const half8 *>(dec + GM_SC + (16 * rt + (l & 15)) * 16); };
+    auto d_of = [&](int l, int rt, int bb) __attribute__((always_inline)) {
+        return *reinterpret_cast<const float2 *>(dec + GM_SC + GM_M + (bb & 1) * GM_D + (16 * rt + (l & 15)) * 8);
     };
 
     // The wave is alone on its SIMD and issues in order: an MFMA occupies the matrix pipe for 16 cycles, during which
@@ -391,10 +292,15 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
     // built in front of their own MFMAs they would cost their full issue time with the matrix pipe idle.  The quants
     // and headers that position p + 1 needs are this wave's own requests; the wait below covers them.
     half8 Bc[GM_RT];     // B tiles of the current position (at the sums position: the m_s)
-    float dd[GM_RT], dm[GM_RT];
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"(GM_AHEAD * DM + 4) : "memory"); // headers and first half of super-block 0 have landed
+    {
+        const uint4 hd = header(lane);
+        decode_scales(hd, lane, 0, 8);
+        decode_m(hd, lane);
+        decode_d(hd, lane, 0);
 #pragma unroll
-    for (int rt = 0; rt < GM_RT; ++rt) { load_scales(rt, 0); build_b(Bc[rt], quants_of(rt, 0), rt, 0); }
+        for (int rt = 0; rt < GM_RT; ++rt) build_b(Bc[rt], quants_of(rt, 0), scale_of(rt, 0));
+    }
 
     for (int b = 0; b < nbl; ++b) {
         // one position; s as a constant of the type system (a loop over s with "#pragma unroll" is refused by the
@@ -440,9 +346,11 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
                 // while four waves and the incoming requests share the LDS)
                 half8 ah[3], al[3];
                 uint32_t wn[GM_RT];
+                half2v sn[GM_RT];
+                uint4 hd;
 #pragma unroll
                 for (int rt = 0; rt < GM_RT; ++rt)
-                    if (s < 7 && rt * TT < GM_RT) wn[rt] = quants_of(rt, s + 1);
+                    if (s < 7 && rt * TT < GM_RT) { wn[rt] = quants_of(rt, s + 1); sn[rt] = scale_of(rt, s + 1); }
 #pragma unroll
                 for (int tt = 0; tt < (TT < 2 ? TT : 2); ++tt) {
                     ah[tt] = *reinterpret_cast<const half8 *>(base + tt * 2048);
@@ -463,16 +371,25 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
                     // the B tiles of the next position are shared out over the token tiles
 #pragma unroll
                     for (int rt = 0; rt < GM_RT; ++rt) {
-                        if (s < 7 && rt * TT / GM_RT == tt + 1) wn[rt] = quants_of(rt, s + 1);
-                        if (rt * TT / GM_RT != tt) continue;
-                        if (s < 7) build_b(Bn[rt], wn[rt], rt, s + 1);
-                        else build_m(Bn[rt], dd[rt], dm[rt], rt, b);
+                        if (s < 7 && rt * TT / GM_RT == tt + 1) { wn[rt] = quants_of(rt, s + 1); sn[rt] = scale_of(rt, s + 1); }
+                        if (s < 7 && rt * TT / GM_RT == tt) build_b(Bn[rt], wn[rt], sn[rt]);
+                        if (s == 7 && rt * TT / GM_RT == tt) Bn[rt] = m_of(lane_anew(), rt);
                     }
-                    __builtin_amdgcn_sched_group_barrier(0x100, TT == 4 ? 3 : 2 + GM_RT, 0);
+                    if (s == 7) { // the headers of the next super-block (past the last: the last ones again)
+                        const int l = lane_anew();
+                        if (tt == 0) hd = header(l);
+                        if (tt == (TT > 1 ? 1 : 0)) decode_scales(hd, l, 0, TT > 2 ? 4 : 8);
+                        if (TT > 2 && tt == 2) decode_scales(hd, l, 4, 8);
+                        if (tt == TT - 1) {
+                            decode_m(hd, l);
+                            decode_d(hd, l, b + 1);
+                        }
+                    }
+                    __builtin_amdgcn_sched_group_barrier(0x100, TT == 4 ? 4 : 2 + 2 * GM_RT, 0);
 #pragma unroll
                     for (int k = 0; k < 2 * GM_RT; ++k) { // one MFMA, then up to so many VALU instructions of the builds
                         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x002, (s < 7 ? 2 : 4) * ((GM_RT + TT - 1) / TT), 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, (s < 7 ? 2 : 5) * ((GM_RT + TT - 1) / TT), 0);
                     }
                     // built here, not where it is used: the compiler moved the unpacking into the next position, in front of its
                     // first matrix instruction
@@ -483,25 +400,29 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
                 }
             } else {
                 // the min term: sum_s m_s * xs_s, one MFMA step with the m_s as B operand; then the super-block's term
-                // is formed at its own magnitude and added in one step (one rounding per super-block at the magnitude
-                // of the running sum)
-                half8 ax = *reinterpret_cast<const half8 *>(base);
+                // is formed at its own magnitude, scaled back (a power of two) and added in one step (one rounding per super-block
+                // at the magnitude of the running sum)
+                const uint8_t *const scales = smem + slot * SLOT + GM_SCALES + (lane_anew() >> 4) * 16;
+                float2 dd[GM_RT];
+                const int l = lane_anew();
+#pragma unroll
+                for (int rt = 0; rt < GM_RT; ++rt) dd[rt] = d_of(l, rt, b);
 #pragma unroll
                 for (int tt = 0; tt < TT; ++tt) {
-                    const half8 cx = ax;
-                    if (tt + 1 < TT) ax = *reinterpret_cast<const half8 *>(base + (tt + 1) * 1024);
+                    const half8 cx = gemm_sums_operand(*reinterpret_cast<const half8 *>(base + tt * 1024), g);
+                    const v4f cs = *reinterpret_cast<const v4f *>(scales + tt * 1024);
 #pragma unroll
                     for (int rt = 0; rt < GM_RT; ++rt) {
                         const v4f am = __builtin_amdgcn_mfma_f32_16x16x32_f16(cx, Bc[rt], zero, 0, 0, 0);
                         // this lane: row n of row tile rt, tokens 4g .. 4g+3 of the tile
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
-                            yacc[tt][rt][i] += fmaf(dd[rt], acch[tt][rt][i], -(dm[rt] * am[i]));
+                            yacc[tt][rt][i] = fmaf(fmaf(dd[rt].x, acch[tt][rt][i], -(dd[rt].y * am[i])), cs[i], yacc[tt][rt][i]);
                     }
 #pragma unroll
                     for (int rt = 0; rt < GM_RT; ++rt) {
                         if (rt * TT / GM_RT != tt) continue;
-                        if (b + 1 < nbl) { load_scales(rt, b + 1); build_b(Bn[rt], quants_of(rt, 0), rt, 0); }
+                        if (b + 1 < nbl) build_b(Bn[rt], quants_of(rt, 0), scale_of(rt, 0));
                         else Bn[rt] = Bc[rt];
                     }
                     __builtin_amdgcn_sched_barrier(0);
@@ -521,7 +442,7 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
         position(std::integral_constant<int, 8>{});
     }
 
-    if (a.ksplit > 1) { // this share's sums, scaled back, for gemm_ksplit_reduce_kernel
+    if (a.ksplit > 1) { // this share's sums
 #pragma unroll
         for (int rt = 0; rt < GM_RT; ++rt) {
             const int64_t out_row = row0 + (a.pair ? 16 * (rt & 1) : 16 * rt) + n;
@@ -532,11 +453,19 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int t = (tile0 + tt) * 16 + 4 * g + i;
-                    if (t < a.T) dst[(static_cast<int64_t>(share) * a.T + t) * a.ldp] = yacc[tt][rt][i] * a.stat[t].y;
+                    if (t < a.T) dst[(static_cast<int64_t>(share) * a.T + t) * a.ldp] = yacc[tt][rt][i];
                 }
         }
         return;
     }
+    const float *inv = nullptr; // 1/rms of the workgroup's tokens
+    if (a.norm.ss) {
+        float *const red = reinterpret_cast<float *>(smem);
+        gm_barrier(); // (the ring's last slots have been read)
+        gemm_inv_rms_tokens<GM_TM>(a.norm, tile0 * 16, red, red + 256);
+        inv = red + 256;
+    }
+    auto of = [&](int tt, int i) __attribute__((always_inline)) { return inv ? inv[16 * tt + 4 * g + i] : 1.f; };
     if (a.pair) { // row tiles 0, 1: rows of the gate matrix; 2, 3: the same rows of the up matrix
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt) {
@@ -548,7 +477,7 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
                 for (int i = 0; i < 4; ++i) {
                     const int t = (tile0 + tt) * 16 + 4 * g + i;
                     if (t < a.T) {
-                        const float sc = a.stat[t].y;
+                        const float sc = of(tt, i);
                         const float gt = yacc[tt][rt][i] * sc, up = yacc[tt][rt + 2][i] * sc;
                         my.y[t * my.ldy + out_row] = gt / (1.0f + expf(-gt)) * up;
                     }
@@ -566,7 +495,7 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
             for (int i = 0; i < 4; ++i) {
                 const int t = (tile0 + tt) * 16 + 4 * g + i;
                 if (t < a.T) {
-                    float v = yacc[tt][rt][i] * a.stat[t].y;
+                    float v = yacc[tt][rt][i] * of(tt, i);
                     if (a.resid) v += a.resid[t * a.ldr + out_row];
                     my.y[t * my.ldy + out_row] = v;
                 }
@@ -586,33 +515,6 @@ __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
     case 3: q4k_gemm_block<3>(a, smem, rb, share, tile0); break;
     default: q4k_gemm_block<4>(a, smem, rb, share, tile0); break;
     }
-}
-
-// y = the shares of K added in order (+ resid): one thread per (token, column of the shares)
-__global__ void __launch_bounds__(256) gemm_ksplit_reduce_kernel(GemmArgs a)
-{
-    const int64_t col = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    const int t = blockIdx.y;
-    if (a.pair) {
-        // output row `col` of silu(gate) * up: its gate sums sit at column (row block, wave, row in the wave's 32) of the
-        // shares, its up sums 32 columns further
-        if (col >= a.seg[0].n_rows) return;
-        const int64_t gc = (col / (GM_ROWS / 2)) * GM_ROWS + ((col % (GM_ROWS / 2)) / 32) * 64 + col % 32;
-        const float *const p = a.part + static_cast<int64_t>(t) * a.ldp + gc;
-        const float gt = gemm_add_shares(p, static_cast<int64_t>(a.T) * a.ldp, a.ksplit);
-        const float up = gemm_add_shares(p + 32, static_cast<int64_t>(a.T) * a.ldp, a.ksplit);
-        a.seg[0].y[t * a.seg[0].ldy + col] = gt / (1.0f + expf(-gt)) * up;
-        return;
-    }
-    if (col >= a.ldp) return;
-    const int rb = static_cast<int>(col / GM_ROWS);
-    const int sg = rb >= a.seg[2].rb0 ? 2 : (rb >= a.seg[1].rb0 ? 1 : 0);
-    const GemmSegDev &my = a.seg[sg];
-    const int64_t row = col - static_cast<int64_t>(my.rb0) * GM_ROWS;
-    if (row >= my.n_rows) return;
-    const float r = a.resid ? a.resid[t * a.ldr + row] : 0.f;
-    const float v = gemm_add_shares(a.part + static_cast<int64_t>(t) * a.ldp + col, static_cast<int64_t>(a.T) * a.ldp, a.ksplit);
-    my.y[t * my.ldy + row] = a.resid ? v + r : v;
 }
 
 // Into how many shares K is cut: none while the row and token blocks alone give every compute unit a workgroup; else as
@@ -647,27 +549,13 @@ size_t gemm_part_bytes(int T, const int64_t *n_rows, int n_mats, int64_t n_cols,
     return static_cast<size_t>(s) * static_cast<size_t>(T) * static_cast<size_t>(n_rb) * GM_ROWS * sizeof(float);
 }
 
-size_t gemm_ws_bytes(int T, int64_t n_cols)
-{
-    const size_t tiles = (static_cast<size_t>(T) + 15) / 16;
-    return round_up(static_cast<size_t>(T) * sizeof(float2), GM_STAT_ALIGN) + tiles * static_cast<size_t>(n_cols / QK) * GM_TILE_BYTES;
-}
+size_t gemm_acts_bytes(int T, int64_t n_cols) { return (static_cast<size_t>(T) + 15) / 16 * static_cast<size_t>(n_cols / QK) * GM_TILE_BYTES; }
+size_t gemm_ss_bytes(int T, int64_t n_cols) { return round_up((static_cast<size_t>(T) + 15) / 16 * 16 * static_cast<size_t>(n_cols / QK) * sizeof(float), 1024); }
 
-prima_status launch_gemm_split(int64_t n_cols, const float *x, int64_t ldx, int T, const float *gain, float eps, void *ws, hipStream_t st)
+prima_status launch_q4k_gemm(const GemmMat *mats, int n_mats, bool pair, int64_t n_cols, const GemmActs &x, int T, const float *resid, int64_t ldr,
+                             void *part, size_t part_bytes, GemmShares *later, hipStream_t st)
 {
-    const int64_t nb = n_cols / QK;
-    const int n_tiles = (T + 15) / 16;
-    if (n_tiles > 65535 || nb >= (int64_t{1} << 31)) return PRIMA_E_SHAPE;
-    hipLaunchKernelGGL(gemm_token_scale_kernel, dim3(T), dim3(256), 0, st, x, ldx, n_cols, gain, eps, gemm_stat(ws));
-    hipLaunchKernelGGL(gemm_split_kernel, dim3(static_cast<unsigned>(nb), n_tiles), dim3(256), 0, st, x, ldx, gain, gemm_stat(ws), T, nb,
-                       gemm_split(ws, T));
-    return last_launch_status();
-}
-
-prima_status launch_q4k_gemm_multi(const GemmMat *mats, int n_mats, bool pair, int64_t n_cols, const float *x, int64_t ldx, int T,
-                                   const float *gain, float eps, const float *resid, int64_t ldr, void *ws, hipStream_t st, bool split_ready,
-                                   void *part, size_t part_bytes)
-{
+    if (later) *later = GemmShares{};
     if (n_mats < 1 || n_mats > 3 || (pair && (n_mats != 2 || mats[0].n_rows != mats[1].n_rows || resid))) return PRIMA_E_SHAPE;
     if (T == 0) return PRIMA_OK;
     GemmArgs a{};
@@ -686,6 +574,7 @@ prima_status launch_q4k_gemm_multi(const GemmMat *mats, int n_mats, bool pair, i
     const int64_t nb = n_cols / QK;
     const int n_tiles = (T + 15) / 16;
     const int n_tb = (n_tiles + GM_TT - 1) / GM_TT;
+    if (nb >= (int64_t{1} << 32) / 144) return PRIMA_E_SHAPE; // (a row of 4 GiB: its activations laid out would be 500)
     if (n_rb * n_tb >= (int64_t{1} << 31) - GM_XCDS || n_tiles > 65535 || nb >= (int64_t{1} << 31)) return PRIMA_E_SHAPE;
     static std::atomic<bool> attr_set{false}; // set twice by two threads at worst: the attribute call is idempotent
     if (!attr_set) {
@@ -693,38 +582,25 @@ prima_status launch_q4k_gemm_multi(const GemmMat *mats, int n_mats, bool pair, i
             return PRIMA_E_DEVICE;
         attr_set = true;
     }
-    const float2 *stat = gemm_stat(ws);
-    const uint8_t *A = gemm_split(ws, T);
-    // split_ready: ws holds the split of these very activations (the call before this one had the same x, gain, eps, T)
-    if (!split_ready) {
-        const prima_status ps = launch_gemm_split(n_cols, x, ldx, T, gain, eps, ws, st);
-        if (ps != PRIMA_OK) return ps;
-    }
     a.pair = pair ? 1 : 0;
-    a.n_cols = n_cols; a.A = A; a.stat = stat; a.resid = resid; a.ldr = ldr;
+    a.n_cols = n_cols; a.A = x.A; a.norm = x.norm; a.resid = resid; a.ldr = ldr;
     a.T = T; a.n_tiles = n_tiles; a.n_rb = static_cast<int>(n_rb); a.n_tb = n_tb; a.band = gemm_band(n_tb);
     // K is divided when that fills the device and the caller's scratch holds the shares
-    a.ksplit = part && T <= 65535 ? ksplit_for(n_rb, n_tb, nb) : 1; // (the shares are added by a launch with T as a grid dimension)
+    a.ksplit = part && T <= 65535 && (later || (n_mats == 1 && !pair)) ? ksplit_for(n_rb, n_tb, nb) : 1; // (shares: T a grid dimension of the launch that adds them)
     a.ldp = n_rb * GM_ROWS;
     if (a.ksplit > 1 && part_bytes < static_cast<size_t>(a.ksplit) * static_cast<size_t>(T) * static_cast<size_t>(a.ldp) * sizeof(float)) a.ksplit = 1;
     a.share_q = static_cast<int>(nb / a.ksplit); a.share_r = static_cast<int>(nb % a.ksplit);
     a.tile_q = n_tiles / n_tb; a.tile_r = n_tiles % n_tb;
     a.part = a.ksplit > 1 ? static_cast<float *>(part) : nullptr;
     hipLaunchKernelGGL(q4k_gemm_kernel, dim3(gemm_grid(n_rb * n_tb * a.ksplit)), dim3(GM_THREADS), GM_LDS_BYTES, st, a);
-    if (a.ksplit > 1) {
-        const prima_status ps = last_launch_status();
-        if (ps != PRIMA_OK) return ps;
-        hipLaunchKernelGGL(gemm_ksplit_reduce_kernel, dim3(static_cast<unsigned>((a.ldp + 255) / 256), T), dim3(256), 0, st, a);
-    }
-    return last_launch_status();
-}
-
-prima_status launch_q4k_gemm(const uint8_t *W, int64_t n_rows, int64_t n_cols, const float *x, int64_t ldx, int T,
-                             const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy,
-                             void *ws, hipStream_t st, bool split_ready, void *part, size_t part_bytes)
-{
-    const GemmMat m{W, y, n_rows, ldy};
-    return launch_q4k_gemm_multi(&m, 1, false, n_cols, x, ldx, T, gain, eps, resid, ldr, ws, st, split_ready, part, part_bytes);
+    const prima_status ps = last_launch_status();
+    if (ps != PRIMA_OK || a.ksplit == 1) return ps;
+    GemmShares p{a.part, a.ksplit, static_cast<int64_t>(T) * a.ldp, a.ldp, {0, 0, 0}};
+    for (int i = 0; i < 3; ++i)
+        if (a.seg[i].rb0 != 0x7fffffff) p.col[i] = static_cast<int64_t>(a.seg[i].rb0) * GM_ROWS;
+    if (!later) return launch_gemm_sum(p, x.norm, resid, ldr, mats[0].y, mats[0].ldy, mats[0].n_rows, T, st);
+    *later = p;
+    return PRIMA_OK;
 }
 
 } // namespace prima

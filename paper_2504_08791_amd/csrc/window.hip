@@ -488,7 +488,7 @@ prima_status check_window_args(const prima_dims *d, int32_t kv_cap, int32_t n_pa
 }
 
 struct PrefillWs {
-    size_t q, k, v, o, h, a, u, xb0, xb1, rope, attn, stat, part, part_bytes, total;
+    size_t q, k, v, o, h, a, u, xb0, xb1, rope, attn, ss, acts, part, part_bytes, total;
     size_t dec_base; // short prompts: the scratch of a decode call of PRIMA_MAX_TOK tokens, carved from here
     WindowWs dec;
 };
@@ -513,12 +513,15 @@ PrefillWs carve_prefill(const prima_dims &d, int kv_cap, int T)
     w.xb1 = take(t * static_cast<size_t>(d.e) * f);
     w.rope = take(t * static_cast<size_t>(d.head_dim) * f);
     w.attn = take(attn_ws_bytes(d, kv_cap, PRIMA_MAX_TOK));
-    w.stat = take(gemm_ws_bytes(T, std::max<int64_t>({d.e, static_cast<int64_t>(qd), d.ffn})));
+    w.ss = take(gemm_ss_bytes(T, d.e));
+    w.acts = take(gemm_acts_bytes(T, std::max<int64_t>({d.e, static_cast<int64_t>(qd), d.ffn})));
     {
         // the shares of K of the launches that divide it (few rows, few tokens): the largest of the layer's products
         const int64_t r_qkv[3] = {static_cast<int64_t>(qd), static_cast<int64_t>(kvd), static_cast<int64_t>(kvd)}, r_e[1] = {d.e}, r_f[1] = {d.ffn};
-        size_t pb = gemm_part_bytes(T, r_qkv, 3, d.e);
-        for (int i = 0; i < 3; ++i) pb = std::max(pb, gemm_part_bytes(T, r_qkv + i, 1, d.e)); // one by one when the formats differ
+        size_t pb = gemm_part_bytes(T, r_qkv, 3, d.e), apart = 0;
+        for (int i = 0; i < 3; ++i) // one by one when the formats differ, all there until the launch behind them
+            apart += round_up(std::max(gemm_part_bytes(T, r_qkv + i, 1, d.e), fmt_gemm_part_bytes(T, r_qkv[i], d.e)), 256);
+        pb = std::max(pb, apart);
         pb = std::max({pb, gemm_part_bytes(T, r_e, 1, static_cast<int64_t>(qd)), gemm_part_bytes(T, r_e, 1, d.ffn), gemm_part_bytes(T, r_f, 1, d.e),
                        gemm_part_bytes(T, r_f, 1, d.e, true)});
         w.part_bytes = pb;
@@ -530,73 +533,143 @@ PrefillWs carve_prefill(const prima_dims &d, int kv_cap, int T)
     return w;
 }
 
-// one decoder layer for T prompt tokens: the projections as matrix products over all tokens, attention for pieces of
-// PRIMA_MAX_TOK tokens (each sees the rows cached before it and, causally, its own), all pieces in one launch
-prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv_cap, int n_past, int T,
-                               const float *x, float *y, void *ws, const PrefillWs &w, hipStream_t st,
-                               const prima_layer_formats *fm = nullptr)
+// One decoder layer for T prompt tokens: the projections as matrix products over all tokens, attention for pieces of PRIMA_MAX_TOK tokens (each sees
+// the rows cached before it and, causally, its own), all pieces in one launch; between them the launches of gemm_prepare.hip.  prepared: the layer
+// before this one has laid out x for this one's Q/K/V; next: the layer after it, whose Q/K/V activations the last launch may lay out (null: none), and
+// then sets next_prepared.
+// fm: formats of the seven matrices (null: all Q4_K).  Each goes through the matrix product of its format; FP32 (whose
+// weights are not exact in the product's binary16 operands) through the format mat-vec, PRIMA_MAX_TOK tokens a launch
+prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv_cap, int n_past, int T, const float *x, float *y, void *ws,
+                               const PrefillWs &w, hipStream_t st, const prima_layer_formats *fm, bool prepared, const prima_layer *next,
+                               const prima_layer_formats *next_fm, bool *next_prepared)
 {
-    // fm: formats of the seven matrices (null: all Q4_K).  Each goes through the matrix product of its format; FP32 (whose
-    // weights are not exact in the product's binary16 operands) through the format mat-vec, PRIMA_MAX_TOK tokens a launch
-    const int f_q = fm ? fm->wq : 0, f_k = fm ? fm->wk : 0, f_v = fm ? fm->wv : 0, f_o = fm ? fm->wo : 0;
-    const int f_g = fm ? fm->wgate : 0, f_u = fm ? fm->wup : 0, f_d = fm ? fm->wdown : 0;
+    static constexpr prima_layer_formats ALL_Q4_K = {0, 0, 0, 0, 0, 0, 0};
+    const prima_layer_formats &f = fm ? *fm : ALL_Q4_K, &nf = next_fm ? *next_fm : ALL_Q4_K;
     const int64_t e = d.e, qd = static_cast<int64_t>(d.n_q_heads) * d.head_dim, kvd = static_cast<int64_t>(d.n_kv_heads) * d.head_dim, F = d.ffn;
     float *q = at<float>(ws, w.q), *k = at<float>(ws, w.k), *v = at<float>(ws, w.v);
-    float *o = at<float>(ws, w.o), *h = at<float>(ws, w.h), *act = at<float>(ws, w.a);
-    void *stat = at<char>(ws, w.stat), *part = at<char>(ws, w.part);
-    auto W = [](const void *p) { return static_cast<const uint8_t *>(p); };
+    float *o = at<float>(ws, w.o), *h = at<float>(ws, w.h), *act = at<float>(ws, w.a), *ss = at<float>(ws, w.ss);
+    uint8_t *const acts = at<uint8_t>(ws, w.acts);
+    char *const part = at<char>(ws, w.part);
     prima_status s;
 #define PRIMA_TRY(call) do { s = (call); if (s != PRIMA_OK) return s; } while (0)
-    // one projection: out = W a (+ resid), a = xin or RMSNorm(xin; gain); split_ready as for the matrix product.  A small matrix alone in
-    // its group and few tokens: two mat-vecs are fewer launches than the split, the product and its shares' sum (two layers of hidden
-    // size 512, down in Q8_0, us, product / mat-vecs: 17 tokens 255 / 212, 33 tokens 288 / 278).
-    auto product = [&](int fmt, const void *Wm, int64_t rows, int64_t cols, const float *xin, const float *gain, const float *resid,
-                       float *out, bool split_ready, bool alone = false) -> prima_status {
-        if (fmt == PRIMA_FMT_Q4_K)
-            return launch_q4k_gemm(W(Wm), rows, cols, xin, cols, T, gain, d.rms_eps, resid, rows, out, rows, stat, st, split_ready, part,
-                                   w.part_bytes);
-        if (fmt_gemm_takes(fmt) && !(alone && T <= 2 * PRIMA_MAX_TOK && rows * cols < (int64_t{1} << 20)))
-            return launch_fmt_gemm(fmt, W(Wm), rows, cols, xin, cols, T, gain, d.rms_eps, resid, rows, out, rows, stat, st, split_ready, part,
-                                   w.part_bytes);
+    const GemmActs plain{acts, GemmNorm{}};
+    const GemmActs normed{acts, GemmNorm{ss, static_cast<int>(e / QK), (T + 15) / 16 * 16, d.rms_eps}};
+    auto mat = [](const void *W, float *out, int64_t rows) { return GemmMat{static_cast<const uint8_t *>(W), out, rows, rows}; };
+    // Whether a matrix goes through a matrix product.  A small one alone in its group and few tokens: two mat-vecs are fewer launches than the
+    // split, the product and its shares' sum (two layers of hidden size 512, down in Q8_0, us, product / mat-vecs: 17 tokens 255 / 212, 33 tokens 288 / 278).
+    auto takes = [](int fmt) { return fmt == PRIMA_FMT_Q4_K || fmt_gemm_takes(fmt); };
+    auto takes_alone = [&](int fmt, int64_t rows, int64_t cols) {
+        return fmt == PRIMA_FMT_Q4_K || (fmt_gemm_takes(fmt) && !(T <= 2 * PRIMA_MAX_TOK && rows * cols < (int64_t{1} << 20)));
+    };
+    // one matrix: out = W a (+ resid); its shares of K left to the next launch, or added
+    auto product = [&](int fmt, const GemmMat &m, int64_t cols, const GemmActs &a, const float *resid, char *to, size_t to_bytes, GemmShares *later) {
+        return fmt == PRIMA_FMT_Q4_K ? launch_q4k_gemm(&m, 1, false, cols, a, T, resid, m.n_rows, to, to_bytes, later, st)
+                                     : launch_fmt_gemm(fmt, m, cols, a, T, resid, m.n_rows, to, to_bytes, later, st);
+    };
+    auto mat_vecs = [&](int fmt, const GemmMat &m, int64_t cols, const float *xin, const float *gain, const float *resid) -> prima_status {
         for (int t0 = 0; t0 < T; t0 += PRIMA_MAX_TOK) {
-            const int Tc = std::min<int>(PRIMA_MAX_TOK, T - t0);
-            const prima_status ps = launch_fmt_gemv(fmt, W(Wm), rows, cols, xin + t0 * cols, cols, Tc, gain, d.rms_eps,
-                                                    resid ? resid + t0 * rows : nullptr, rows, out + t0 * rows, rows, st);
+            const prima_status ps = launch_fmt_gemv(fmt, m.W, m.n_rows, cols, xin + t0 * cols, cols, std::min<int>(PRIMA_MAX_TOK, T - t0), gain, d.rms_eps,
+                                                    resid ? resid + t0 * m.n_rows : nullptr, m.n_rows, m.y + t0 * m.n_rows, m.n_rows, st);
             if (ps != PRIMA_OK) return ps;
         }
         return PRIMA_OK;
     };
+    // v (x, or the shares + x, or SwiGLU of the shares), stored to out and laid out as activations (lay), its gain applied
+    auto prepare = [&](int mode, int64_t cols, const float *xin, const GemmShares &p, float *out, const float *gain, bool lay) -> prima_status {
+        if (!lay && !out) return PRIMA_OK;
+        GemmPrepare a{};
+        a.mode = mode; a.T = T; a.nb = static_cast<int>(cols / QK); a.x = xin; a.ldx = cols; a.p = p; a.norm = normed.norm;
+        a.out = out; a.ldo = cols; a.gain = gain; a.ss = ss; a.A = lay ? acts : nullptr;
+        return launch_gemm_prepare(a, st);
+    };
     const float *g_attn = static_cast<const float *>(L.g_attn), *g_ffn = static_cast<const float *>(L.g_ffn);
-    if (f_q == PRIMA_FMT_Q4_K && f_k == PRIMA_FMT_Q4_K && f_v == PRIMA_FMT_Q4_K) {
-        const GemmMat qkv[3] = {{W(L.wq), q, qd, qd}, {W(L.wk), k, kvd, kvd}, {W(L.wv), v, kvd, kvd}};
-        PRIMA_TRY(launch_q4k_gemm_multi(qkv, 3, false, e, x, e, T, g_attn, d.rms_eps, nullptr, 0, stat, st, false, part, w.part_bytes));
-    } else {
-        auto splits = [](int f) { return f == PRIMA_FMT_Q4_K || fmt_gemm_takes(f); };
-        bool ready = false; // the first matrix of the group that goes through a matrix product splits the activations for the others
-        PRIMA_TRY(product(f_q, L.wq, qd, e, x, g_attn, nullptr, q, ready));
-        ready = ready || splits(f_q);
-        PRIMA_TRY(product(f_k, L.wk, kvd, e, x, g_attn, nullptr, k, ready));
-        ready = ready || splits(f_k);
-        PRIMA_TRY(product(f_v, L.wv, kvd, e, x, g_attn, nullptr, v, ready));
+
+    { // Q, K, V: those in Q4_K in one launch, each of the others in one of its own
+        const int fmts[3] = {f.wq, f.wk, f.wv};
+        const GemmMat m[3] = {mat(L.wq, q, qd), mat(L.wk, k, kvd), mat(L.wv, v, kvd)};
+        RopeAppend r{};
+        if (takes(f.wq) || takes(f.wk) || takes(f.wv)) {
+            if (!prepared) PRIMA_TRY(prepare(GEMM_PLAIN, e, x, GemmShares{}, nullptr, g_attn, true));
+            r.norm = normed.norm;
+        }
+        size_t used = 0;
+        auto used_by = [&](const GemmShares &p) { used += round_up(static_cast<size_t>(p.n) * static_cast<size_t>(p.stride) * sizeof(float), 256); };
+        GemmMat q4[3];
+        int at_q4[3], n_q4 = 0;
+        for (int i = 0; i < 3; ++i)
+            if (fmts[i] == PRIMA_FMT_Q4_K) { at_q4[n_q4] = i; q4[n_q4++] = m[i]; }
+        if (n_q4) {
+            GemmShares p;
+            PRIMA_TRY(launch_q4k_gemm(q4, n_q4, false, e, normed, T, nullptr, 0, part, w.part_bytes, &p, st));
+            used_by(p);
+            for (int i = 0; i < n_q4; ++i) {
+                r.p[at_q4[i]] = p;
+                r.p[at_q4[i]].col[0] = p.col[i];
+            }
+        }
+        for (int i = 0; i < 3; ++i) {
+            if (fmts[i] == PRIMA_FMT_Q4_K) continue;
+            if (!takes(fmts[i])) {
+                PRIMA_TRY(mat_vecs(fmts[i], m[i], e, x, g_attn, nullptr));
+                continue;
+            }
+            PRIMA_TRY(product(fmts[i], m[i], e, normed, nullptr, part + used, w.part_bytes > used ? w.part_bytes - used : 0, &r.p[i]));
+            used_by(r.p[i]);
+        }
+        for (int i = 0; i < 3; ++i)
+            if (r.p[i].n == 0) r.p[i] = GemmShares{m[i].y, 0, 0, m[i].n_rows, {0, 0, 0}};
+        // RoPE and the cache rows of all T tokens first; then the pieces of PRIMA_MAX_TOK tokens in one launch, or fewer tokens
+        // than that in a launch of the decode kind (caches complete, queries rotated)
+        r.tab = at<float>(ws, w.rope); r.q = q; r.kv_cap = kv_cap; r.n_past = n_past;
+        r.K = static_cast<__half *>(L.k_cache); r.V = static_cast<__half *>(L.v_cache);
+        PRIMA_TRY(launch_rope_append(r, d, T, st));
+        if (T >= PRIMA_MAX_TOK) PRIMA_TRY(launch_attn_prompt(d, q, r.K, r.V, kv_cap, n_past, T, o, st));
+        else PRIMA_TRY(launch_attn(d, q, nullptr, nullptr, nullptr, nullptr, r.K, r.V, kv_cap, n_past, T, o, at<char>(ws, w.attn), st, nullptr,
+                                   ATTN_MERGE_INSIDE));
     }
-    // RoPE and the cache rows of all T tokens first; then the pieces of PRIMA_MAX_TOK tokens in one launch, or fewer tokens
-    // than that in a launch of the decode kind (caches complete, queries rotated)
-    __half *Kc = static_cast<__half *>(L.k_cache), *Vc = static_cast<__half *>(L.v_cache);
-    PRIMA_TRY(launch_rope_append(d, q, k, v, at<float>(ws, w.rope), Kc, Vc, kv_cap, n_past, T, st));
-    if (T >= PRIMA_MAX_TOK) PRIMA_TRY(launch_attn_prompt(d, q, Kc, Vc, kv_cap, n_past, T, o, st));
-    else PRIMA_TRY(launch_attn(d, q, nullptr, nullptr, nullptr, nullptr, Kc, Vc, kv_cap, n_past, T, o, at<char>(ws, w.attn), st, nullptr,
-                               ATTN_MERGE_INSIDE));
-    PRIMA_TRY(product(f_o, L.wo, e, qd, o, nullptr, x, h, false, true));
-    if (f_g == PRIMA_FMT_Q4_K && f_u == PRIMA_FMT_Q4_K) {
-        const GemmMat gate_up[2] = {{W(L.wgate), act, F, F}, {W(L.wup), nullptr, F, F}};
-        PRIMA_TRY(launch_q4k_gemm_multi(gate_up, 2, true, e, h, e, T, g_ffn, d.rms_eps, nullptr, 0, stat, st, false, part, w.part_bytes));
+    { // output projection, h = x + ..
+        GemmShares p{};
+        const bool lay = takes(f.wgate) || takes(f.wup);
+        if (takes_alone(f.wo, e, qd)) {
+            PRIMA_TRY(prepare(GEMM_PLAIN, qd, o, GemmShares{}, nullptr, nullptr, true));
+            PRIMA_TRY(product(f.wo, mat(L.wo, h, e), qd, plain, x, part, w.part_bytes, &p));
+        } else {
+            PRIMA_TRY(mat_vecs(f.wo, mat(L.wo, h, e), qd, o, nullptr, x));
+        }
+        if (p.n) PRIMA_TRY(prepare(GEMM_RESIDUAL, e, x, p, h, g_ffn, lay));
+        else PRIMA_TRY(prepare(GEMM_PLAIN, e, h, p, nullptr, g_ffn, lay));
+    }
+    const bool down = takes_alone(f.wdown, e, F);
+    if (f.wgate == PRIMA_FMT_Q4_K && f.wup == PRIMA_FMT_Q4_K) {
+        const GemmMat gate_up[2] = {mat(L.wgate, act, F), mat(L.wup, nullptr, F)};
+        GemmShares p;
+        PRIMA_TRY(launch_q4k_gemm(gate_up, 2, true, e, normed, T, nullptr, 0, part, w.part_bytes, &p, st));
+        if (p.n) PRIMA_TRY(prepare(GEMM_SWIGLU, F, nullptr, p, down ? nullptr : act, nullptr, down));
+        else PRIMA_TRY(prepare(GEMM_PLAIN, F, act, p, nullptr, nullptr, down));
     } else {
         float *up = at<float>(ws, w.u);
-        PRIMA_TRY(product(f_g, L.wgate, F, e, h, g_ffn, nullptr, act, false));
-        PRIMA_TRY(product(f_u, L.wup, F, e, h, g_ffn, nullptr, up, f_g == PRIMA_FMT_Q4_K || fmt_gemm_takes(f_g)));
+        const GemmMat m[2] = {mat(L.wgate, act, F), mat(L.wup, up, F)};
+        const int fmts[2] = {f.wgate, f.wup};
+        for (int i = 0; i < 2; ++i) {
+            if (takes(fmts[i])) PRIMA_TRY(product(fmts[i], m[i], e, normed, nullptr, part, w.part_bytes, nullptr));
+            else PRIMA_TRY(mat_vecs(fmts[i], m[i], e, h, g_ffn, nullptr));
+        }
         PRIMA_TRY(launch_swiglu(act, up, static_cast<int64_t>(T) * F, st));
+        PRIMA_TRY(prepare(GEMM_PLAIN, F, act, GemmShares{}, nullptr, nullptr, down));
     }
-    PRIMA_TRY(product(f_d, L.wdown, e, F, act, nullptr, h, y, false, true));
+    *next_prepared = false;
+    if (!down) {
+        PRIMA_TRY(mat_vecs(f.wdown, mat(L.wdown, y, e), F, act, nullptr, h));
+    } else {
+        GemmShares p;
+        PRIMA_TRY(product(f.wdown, mat(L.wdown, y, e), F, plain, h, part, w.part_bytes, &p));
+        if (p.n && next && (takes(nf.wq) || takes(nf.wk) || takes(nf.wv))) {
+            PRIMA_TRY(prepare(GEMM_RESIDUAL, e, h, p, y, static_cast<const float *>(next->g_attn), true));
+            *next_prepared = true;
+        } else if (p.n) {
+            PRIMA_TRY(launch_gemm_sum(p, GemmNorm{}, h, e, y, e, e, T, st));
+        }
+    }
 #undef PRIMA_TRY
     return PRIMA_OK;
 }
@@ -724,6 +797,9 @@ prima_status prima_q4k_gemv_noalloc(const void *W, int64_t n_rows, int64_t n_col
     return launch_gemv_mfma(ga, ws, PRIMA_NOALLOC_SCRATCH_BYTES, gemv_arrivals_bytes(n_rows), st, true);
 }
 
+// scratch of a product on its own: the sums of squares, the activations laid out, then the shares of K
+static size_t gemm_ws_bytes(int T, int64_t n_cols) { return gemm_ss_bytes(T, n_cols) + gemm_acts_bytes(T, n_cols); }
+
 size_t prima_gemm_workspace_bytes(int32_t T, int64_t n_cols) { return (T < 1 || n_cols <= 0 || n_cols % QK) ? 0 : gemm_ws_bytes(T, n_cols); }
 
 int32_t prima_gemm_ksplit(int32_t T, int64_t n_rows, int64_t n_cols)
@@ -751,8 +827,19 @@ prima_status prima_q4k_gemm(const void *W, int64_t n_rows, int64_t n_cols, const
     // what lies behind the minimum holds the shares of K, if it holds them all
     const size_t part_off = round_up(gemm_ws_bytes(T, n_cols), 256);
     void *part = workspace_bytes > part_off ? static_cast<char *>(workspace) + part_off : nullptr;
-    return launch_q4k_gemm(static_cast<const uint8_t *>(W), n_rows, n_cols, x, ldx, T, gain, eps, resid, ldr, y, ldy, workspace,
-                           static_cast<hipStream_t>(hip_stream), false, part, part ? workspace_bytes - part_off : 0);
+    hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    if (n_rows == 0) return PRIMA_OK;
+    GemmPrepare a{};
+    a.mode = GEMM_PLAIN; a.T = T; a.nb = static_cast<int>(n_cols / QK); a.x = x; a.ldx = ldx; a.gain = gain;
+    a.ss = static_cast<float *>(workspace);
+    a.A = static_cast<uint8_t *>(workspace) + gemm_ss_bytes(T, n_cols);
+    if (n_cols / QK >= (int64_t{1} << 31)) return PRIMA_E_SHAPE;
+    const prima_status s = launch_gemm_prepare(a, st);
+    if (s != PRIMA_OK) return s;
+    GemmActs acts{a.A, GemmNorm{}};
+    if (gain) acts.norm = GemmNorm{a.ss, a.nb, (T + 15) / 16 * 16, eps};
+    const GemmMat m{static_cast<const uint8_t *>(W), y, n_rows, ldy};
+    return launch_q4k_gemm(&m, 1, false, n_cols, acts, T, resid, ldr, part, part ? workspace_bytes - part_off : 0, nullptr, st);
 }
 
 size_t prima_attn_workspace_bytes(const prima_dims *d, int32_t kv_cap, int32_t T)
@@ -1017,9 +1104,12 @@ prima_status prima_layer_window_prefill_mixed(const prima_dims *d, const prima_l
         if (s != PRIMA_OK) return s;
     }
     const float *cur = x_in;
+    bool prepared = false;
     for (int i = 0; i < L; ++i) {
         float *dst = (i == L - 1) ? x_out : at<float>(workspace, (i & 1) ? w.xb1 : w.xb0);
-        s = run_layer_prefill(*d, layers[i], kv_cap, n_past, T, cur, dst, workspace, w, st, formats ? &formats[i] : nullptr);
+        const bool more = i + 1 < L;
+        s = run_layer_prefill(*d, layers[i], kv_cap, n_past, T, cur, dst, workspace, w, st, formats ? &formats[i] : nullptr, prepared,
+                              more ? &layers[i + 1] : nullptr, formats && more ? &formats[i + 1] : nullptr, &prepared);
         if (s != PRIMA_OK) return s;
         cur = dst;
     }

@@ -64,6 +64,26 @@ def test_gemm_row_and_token_blocks_shared_out_unevenly(gpu_lib, rows, nb, T):
         assert rel_err(got, ref) < ARITH_TOL, (split, rel_err(got, ref))
 
 
+@pytest.mark.parametrize("T", [3, 40])
+def test_gemm_super_blocks_of_very_different_magnitude(gpu_lib, T):
+    """Every super-block of a token has a scale of its own: magnitudes from 1e-12 to 1e12, a super-block of zeros, a column each that is the
+    largest by far.  The error is the largest super-block's alone.  An infinite activation spoils its own token only."""
+    rng = np.random.default_rng(39 + T)
+    rows, nb = 300, 6
+    W = _rand_q4k(rng, rows, nb)
+    x = (rng.standard_normal((T, nb, 256)) * 10 ** rng.uniform(-12, 12, (T, nb, 1))).astype(np.float32)
+    x[:, 2] = 0
+    x[:, 3, 77] *= 1e4
+    x = x.reshape(T, nb * 256)
+    ref = _oracle_product(W, x.astype(np.float64))
+    got = gpu_lib.q4k_gemm(_dev(W), _dev(x)).cpu().numpy()
+    assert max(rel_err(got[t], ref[t]) for t in range(T)) < ARITH_TOL
+    x[1, 300] = np.inf
+    bad = gpu_lib.q4k_gemm(_dev(W), _dev(x)).cpu().numpy()
+    assert not np.isfinite(bad[1]).any()
+    assert np.array_equal(np.delete(bad, 1, 0), np.delete(got, 1, 0))
+
+
 def test_gemm_rmsnorm_and_residual(gpu_lib):
     """RMSNorm in front, residual behind, strided rows of x, y and the residual."""
     rng = np.random.default_rng(32)

@@ -292,6 +292,25 @@ def test_prefill_model_shape_one_layer(gpu_lib, matrix_product_route, T):
     assert rel_err(y, ref) < HID_TOL, rel_err(y, ref)
 
 
+@pytest.mark.parametrize("mode,T,n_past", [(0, 17, 0), (1, 20, 33), (1, 260, 5)])
+def test_the_launches_between_the_products(gpu_lib, matrix_product_route, mode, T, n_past):
+    """Three layers of several formats whose products divide K (but for 260 tokens' gate and up): shares added into the rotation, the residual and SwiGLU, and
+    laid out for the next layer or not (its Q, K and V in FP32); few and many waves a launch; 20 super-blocks, more than the 16 lanes that add a token's
+    sums of squares."""
+    d = ModelDims(5120, 10, 5, 128, 2560, 1e4, rope_mode=mode) if mode else ModelDims(5120, 10, 5, 128, 2560, 1e4)
+    cfg = WindowConfig("between", 81, d, 3, T, n_past)
+    formats = [{"wv": "q6_k", "wk": "q8_0"}, {"wq": "f32", "wk": "f32", "wv": "f32", "wo": "q5_k"}, {"wdown": "f32"}]
+    cap = n_past + T
+    host = [synth.layer_tensors(cfg, l, kv_cap=cap, formats=formats[l]) for l in range(3)]
+    win = gpu_lib.Window(d, [{k: _dev(v) for k, v in t.items()} for t in host], cap, T_max=16, formats=formats)
+    x = synth.window_input(cfg)
+    print("case", mode, T, n_past, flush=True)
+    y = win.prefill(_dev(x), n_past)
+    assert torch.equal(y, win.prefill(_dev(x), n_past))
+    ref = _oracle_prompt(d, host, x, n_past, formats)
+    check_hidden(f"launches between mode={mode} T={T}", rel_err(y.cpu().numpy(), ref), d, host, x.astype(np.float64), n_past, formats=formats, eps=EPS_FP32)
+
+
 def test_prefill_at_the_largest_token_count(gpu_lib):
     """8192 prompt tokens (the call's limit) through one 8B-shaped layer, filling the cache to its last row.  The oracle
     would take hours; checked instead: the first 8176 tokens' outputs are, bit for bit, those of a call with only them
