@@ -97,6 +97,9 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     typedef FmLds<FMT, WT> L;
+    // Q5_K has no registers left for its unpacking between the products (all seven matrices, 8B 1024 tokens: 1739 us in front, 1785 woven; Q8_0 1697 / 1648, Q6_K
+    // 1867 / 1783), and workgroups that lack tiles have branches there.
+    constexpr bool WOVEN = FULL && FMT != PRIMA_FMT_Q5_K;
     constexpr bool Q5 = FMT == PRIMA_FMT_Q5_K, Q6 = FMT == PRIMA_FMT_Q6_K, Q8 = FMT == PRIMA_FMT_Q8_0, H = FMT == PRIMA_FMT_F16;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -147,89 +150,77 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
     auto h2f = [](unsigned v) { return __half2float(__ushort_as_half(static_cast<unsigned short>(v & 0xffffu))); };
     auto word = [](const uint4 &v, int i) __attribute__((always_inline)) { return i == 0 ? v.x : (i == 1 ? v.y : (i == 2 ? v.z : v.w)); };
 
-    // this thread's 16 weights of sub-block s as operand bytes in buffer `buf`; of an odd sub-block their negatives, whose sums
+    // Half c (8) of this thread's 16 weights of sub-block s as operand bytes in buffer `buf`; of an odd sub-block their negatives, whose sums
     // are subtracted (see the top of the file)
-    auto decode = [&](const Quants<FMT> &q, const uint4 &hd, unsigned hx, int s, int buf) __attribute__((always_inline)) {
-        half2v hi[8], lo[8];
+    auto decode = [&](const Quants<FMT> &q, const uint4 &hd, unsigned hx, int s, int buf, int c) __attribute__((always_inline)) {
+        half2v hi[4], lo[4];
         if constexpr (Q5 || Q6) {
             // thread s & 1 of the row holds the sub-block; its neighbour takes its own half from there
             const bool own = (s & 1) == h;
-            unsigned w0, w1;
+            unsigned w;
             if ((s & 1) == 0) {
-                const unsigned t0 = swap1(q.lo.z), t1 = swap1(q.lo.w);
-                w0 = own ? q.lo.x : t0; w1 = own ? q.lo.y : t1;
+                const unsigned t = swap1(c ? q.lo.w : q.lo.z);
+                w = own ? (c ? q.lo.y : q.lo.x) : t;
             } else {
-                const unsigned t0 = swap1(q.lo.x), t1 = swap1(q.lo.y);
-                w0 = own ? q.lo.z : t0; w1 = own ? q.lo.w : t1;
+                const unsigned t = swap1(c ? q.lo.y : q.lo.x);
+                w = own ? (c ? q.lo.w : q.lo.z) : t;
             }
-            unsigned u[4];
+            unsigned u, v;
             if constexpr (Q6) {
                 unsigned hb;
                 if ((s & 1) == 0) { const unsigned t = swap1(q.hi.y); hb = own ? q.hi.x : t; }
                 else { const unsigned t = swap1(q.hi.x); hb = own ? q.hi.y : t; }
-                u[0] = (w0 & 0x0F0F0F0Fu) | ((hb << 4) & 0x30303030u);
-                u[1] = ((w0 >> 4) & 0x0F0F0F0Fu) | ((hb << 2) & 0x30303030u);
-                u[2] = (w1 & 0x0F0F0F0Fu) | (hb & 0x30303030u);
-                u[3] = ((w1 >> 4) & 0x0F0F0F0Fu) | ((hb >> 2) & 0x30303030u);
+                u = (w & 0x0F0F0F0Fu) | ((c ? hb : hb << 4) & 0x30303030u);
+                v = ((w >> 4) & 0x0F0F0F0Fu) | ((c ? hb >> 2 : hb << 2) & 0x30303030u);
             } else {
                 const unsigned t = swap1(q.hi);
                 const unsigned hb = (own ? q.hi : t) >> (4 * h); // bits 4 h .. 4 h + 3 of every byte: this half's groups of four
-                u[0] = (w0 & 0x0F0F0F0Fu) | ((hb << 4) & 0x10101010u);
-                u[1] = ((w0 >> 4) & 0x0F0F0F0Fu) | ((hb << 3) & 0x10101010u);
-                u[2] = (w1 & 0x0F0F0F0Fu) | ((hb << 2) & 0x10101010u);
-                u[3] = ((w1 >> 4) & 0x0F0F0F0Fu) | ((hb << 1) & 0x10101010u);
+                u = (w & 0x0F0F0F0Fu) | ((c ? hb << 2 : hb << 4) & 0x10101010u);
+                v = ((w >> 4) & 0x0F0F0F0Fu) | ((c ? hb << 1 : hb << 3) & 0x10101010u);
             }
-            bytes_to_pairs(u[0], u[1], hi);
-            bytes_to_pairs(u[2], u[3], hi + 4);
+            bytes_to_pairs(u, v, hi);
             if constexpr (Q6) {
-                const unsigned w = word(hd, s >> 1);
-                const int sc = static_cast<int>(w << (24 - 16 * (s & 1) - 8 * h)) >> 24; // byte 2 s + h, signed
+                const unsigned sw = word(hd, s >> 1);
+                const int sc = static_cast<int>(sw << (24 - 16 * (s & 1) - 8 * h)) >> 24; // byte 2 s + h, signed
                 const _Float16 f = static_cast<_Float16>(static_cast<float>(s & 1 ? -sc : sc));
                 const half2v sc2 = {f, f}, off = {static_cast<_Float16>(-1056.f), static_cast<_Float16>(-1056.f)};
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const half2v v = hi[i] + off; // q - 32, exact
-                    hi[i] = v * sc2;              // rounded to 11 bits
-                    lo[i] = __builtin_elementwise_fma(v, sc2, -hi[i]); // the remainder, exact
+                for (int i = 0; i < 4; ++i) {
+                    const half2v x = hi[i] + off; // q - 32, exact
+                    hi[i] = x * sc2;              // rounded to 11 bits
+                    lo[i] = __builtin_elementwise_fma(x, sc2, -hi[i]); // the remainder, exact
                 }
             } else {
                 const float fs = static_cast<float>(hdr_field(hd, s));
                 const _Float16 f = static_cast<_Float16>(s & 1 ? -fs : fs);
                 const half2v sc2 = {f, f}, off = {static_cast<_Float16>(-1040.f), static_cast<_Float16>(-1040.f)};
 #pragma unroll
-                for (int i = 0; i < 8; ++i) hi[i] = (hi[i] + off) * sc2; // (q - 16) sc: both steps exact
+                for (int i = 0; i < 4; ++i) hi[i] = (hi[i] + off) * sc2; // (q - 16) sc: both steps exact
             }
         } else if constexpr (Q8) {
-            bytes_to_pairs(q.q.x ^ 0x80808080u, q.q.y ^ 0x80808080u, hi);
-            bytes_to_pairs(q.q.z ^ 0x80808080u, q.q.w ^ 0x80808080u, hi + 4);
+            bytes_to_pairs((c ? q.q.z : q.q.x) ^ 0x80808080u, (c ? q.q.w : q.q.y) ^ 0x80808080u, hi);
             const half2v off = {static_cast<_Float16>(-1152.f), static_cast<_Float16>(-1152.f)};
 #pragma unroll
-            for (int i = 0; i < 8; ++i) hi[i] = s & 1 ? -off - hi[i] : hi[i] + off;
+            for (int i = 0; i < 4; ++i) hi[i] = s & 1 ? -off - hi[i] : hi[i] + off;
         } else {
             // numbers 0..7 as pairs (0,4) (1,5) (2,6) (3,7)
             const unsigned neg = s & 1 ? 0x80008000u : 0u;
-            const unsigned v[8] = {q.a.x ^ neg, q.a.y ^ neg, q.a.z ^ neg, q.a.w ^ neg, q.b.x ^ neg, q.b.y ^ neg, q.b.z ^ neg, q.b.w ^ neg};
+            const uint4 &x = c ? q.b : q.a;
+            const unsigned v[4] = {x.x ^ neg, x.y ^ neg, x.z ^ neg, x.w ^ neg};
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    hi[4 * c + i] = __builtin_bit_cast(half2v, __builtin_amdgcn_perm(v[4 * c + 2 + (i >> 1)], v[4 * c + (i >> 1)],
-                                                                                     (i & 1) ? 0x07060302u : 0x05040100u));
+            for (int i = 0; i < 4; ++i)
+                hi[i] = __builtin_bit_cast(half2v, __builtin_amdgcn_perm(v[2 + (i >> 1)], v[i >> 1], (i & 1) ? 0x07060302u : 0x05040100u));
         }
-        uint8_t *dst = bdst + buf * L::B_SLOT;
+        uint8_t *dst = bdst + buf * L::B_SLOT + c * 256;
         auto store = [&](uint8_t *to, const half2v *p) __attribute__((always_inline)) {
             *reinterpret_cast<uint4 *>(to) = make_uint4(__builtin_bit_cast(unsigned, p[0]), __builtin_bit_cast(unsigned, p[1]),
                                                         __builtin_bit_cast(unsigned, p[2]), __builtin_bit_cast(unsigned, p[3]));
         };
         store(dst, hi);
-        store(dst + 256, hi + 4);
-        if constexpr (Q6) {
-            store(dst + FM_ROWS * 64, lo);
-            store(dst + FM_ROWS * 64 + 256, lo + 4);
-        }
+        if constexpr (Q6) store(dst + FM_ROWS * 64, lo);
         if constexpr (Q8) {
             const unsigned w = word(hd, s >> 1);
-            if (h == 0) l_d[buf * FM_ROWS + drow] = h2f(s & 1 ? w >> 16 : w);
+            if (c == 0 && h == 0) l_d[buf * FM_ROWS + drow] = h2f(s & 1 ? w >> 16 : w);
         }
     };
     // what the fold of a super-block needs of its rows: d (Q6_K), d, dmin and the m_s (Q5_K)
@@ -292,7 +283,8 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
     load_quants(qc, b_lo, 0);
     if constexpr (fm_pairwise<FMT>) load_quants(qn, b_lo, 2);
     else load_quants(qn, b_lo, 1);
-    decode(qc, hd, hx, 0, 0);
+    decode(qc, hd, hx, 0, 0, 0);
+    decode(qc, hd, hx, 0, 0, 1);
     hd_next = hd; hx_next = hx;
 
     for (int b = b_lo; b < b_hi; ++b) {
@@ -319,8 +311,15 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
                 if (s + 2 < 8 || more) load_quants(qn, s + 2 < 8 ? b : b + 1, (s + 2) & 7);
             }
             if (s == 5 && more) load_header(hd_next, hx_next, b + 1);
-            if (s < 7) decode(qc, hd, hx, s + 1, buf ^ 1);
-            else if (more) decode(qc, hd_next, hx_next, 0, buf ^ 1);
+            // The operands of the next position.  WOVEN: unpacked between the matrix instructions of the first two tiles, a half each; else in
+            // front.  (Past the last position those of the last super-block again, unused.)
+            auto decode_next = [&](int c) __attribute__((always_inline)) {
+                decode(qc, s < 7 ? hd : hd_next, s < 7 ? hx : hx_next, (s + 1) & 7, buf ^ 1, c);
+            };
+            if constexpr (!WOVEN) {
+                decode_next(0);
+                decode_next(1);
+            }
 
             const uint8_t *ab = smem + buf * L::A_SLOT + wt * 2048 + lane * 16;
             const uint8_t *bb = smem + L::B0 + buf * L::B_SLOT + wr * 4096 + lane * 16;
@@ -353,6 +352,16 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
                         else acc[tt][rt][i] = s == 0 ? ci : acc[tt][rt][i] + ci;
                     }
                 }
+                if constexpr (WOVEN) {
+                    if (tt == 0) decode_next(0);
+                    if (tt == (WT > 1 ? 1 : 0)) decode_next(1);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 12, 0);
+#pragma unroll
+                    for (int k = 0; k < (Q6 ? 3 : 2) * FM_RT; ++k) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
+                    }
+                }
                 // the sums are made here (the compiler would move products and additions into the next position's block, where
                 // they are used, and spill their operands), tile by tile
 #pragma unroll
@@ -376,11 +385,10 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
                         gm_v4f am = zero, t = acc[tt][rt];
                         // the sums slabs were requested a position ago by all waves and have landed before this position's barrier
                         const uint8_t *const sums = l_xs + (2 * tt + wt) * 1024;
-                        unsigned off = GM_SCALES + 16 * g;
-                        asm volatile("" : "+v"(off)); // read again for every tile of rows: kept, they spill
-                        const gm_v4f scale = *reinterpret_cast<const gm_v4f *>(sums + off); // of this lane's tokens: powers of two
+                        const int l = lane_anew(); // (read again for every tile of rows: kept, they spill)
+                        const gm_v4f scale = *reinterpret_cast<const gm_v4f *>(sums + GM_SCALES + (l >> 4) * 16); // of this lane's tokens: powers of two
                         if constexpr (Q5) {
-                            const half8 ax = gemm_sums_operand(*reinterpret_cast<const half8 *>(sums + lane * 16), g);
+                            const half8 ax = gemm_sums_operand(*reinterpret_cast<const half8 *>(sums + l * 16), g);
                             am = __builtin_amdgcn_mfma_f32_16x16x32_f16(ax, m, zero, 0, 0, 0);
                             t = __builtin_amdgcn_mfma_f32_16x16x32_f16(ax, sc16, t, 0, 0, 0);
                         }
