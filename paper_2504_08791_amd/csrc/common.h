@@ -135,6 +135,7 @@ struct GemmPrepare {
     const float *gain; // null: none; else ss gets the sums of squares of v, and v * gain is laid out
     float *ss;
     uint8_t *A; // null: not laid out
+    int waves;  // of a workgroup (filled in by the launch)
 };
 prima_status launch_gemm_prepare(GemmPrepare a, hipStream_t st);
 size_t gemm_acts_bytes(int T, int64_t n_cols); // A
@@ -148,6 +149,8 @@ prima_status launch_gemm_sum(const GemmShares &p, const GemmNorm &norm, const fl
 // that much.
 int gemm_ksplit(int T, const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair = false);
 size_t gemm_part_bytes(int T, const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair = false);
+// the same where the shares are left to the caller's next launch
+size_t gemm_later_bytes(int T, const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair = false);
 // up to three matrices with the same columns against the same activations (Q / K / V), or, with pair set, two of equal
 // shape (gate, up) with silu(gate) * up stored to mats[0].y; the residual only with one matrix.  later: the shares of K, if there are any, are left to
 // the caller's next launch (resid and y then unused); null: one matrix, they are added here.
@@ -173,7 +176,7 @@ struct RopeAppend {
     float *q;
     __half *K, *V;
     int kv_cap, n_past;
-    int Hq, Hkv, D, mode; // (filled in by the launch)
+    int Hq, Hkv, D, mode, block; // (filled in by the launch)
 };
 prima_status launch_rope_append(RopeAppend a, const prima_dims &d, int T, hipStream_t st);
 // RoPE table [T][D/2] of (cos, sin) for the positions n_past .. n_past + T - 1 (any T)

@@ -472,7 +472,7 @@ FmPlan plan_fm(int T, int64_t n_rows, int64_t n_cols, int64_t part_bytes)
     p.narrow = (n_tiles + 3) / 4 * 4 < (n_tiles + 7) / 8 * 8 || n_rb * ((n_tiles + 7) / 8) * 2 <= 2 * GM_CUS;
     p.n_tb = p.narrow ? (n_tiles + 3) / 4 : (n_tiles + 7) / 8;
     const int64_t wgs = n_rb * p.n_tb, slots = 2 * GM_CUS;
-    // Shares of K (at least 4 super-blocks each, as far as the scratch holds them): rounds of workgroups times a share's super-blocks, about
+    // Shares of K (as far as the scratch holds them; with four super-blocks of each at the least, two 8B layers with V and down in Q6_K took 293 us at 17 tokens, 248 without): rounds of workgroups times a share's super-blocks, about
     // 7 us each at 64 tokens and 14 at 128, against the shares' way to memory and back (4 TB/s).  (As many as fit the device at once
     // left a quarter of it idle where they do not come out even: 4096 x 14336 in Q6_K, 333 tokens, two shares 227 us and 6 for their sum, five 200 and 7.)
     // The two figures serve every format: one layer of 8B, 14B and 70B shapes, 40 to 900 tokens, us, that rule / this one where they differ: down in Q5_K 8B 333
@@ -481,7 +481,7 @@ FmPlan plan_fm(int T, int64_t n_rows, int64_t n_cols, int64_t part_bytes)
     p.ksplit = 1;
     if (part_bytes > 0 && T <= 65535) {
         const int64_t share_bytes = static_cast<int64_t>(T) * n_rows * static_cast<int64_t>(sizeof(float));
-        const int64_t most = std::min<int64_t>({nb / 4, 16, part_bytes / share_bytes});
+        const int64_t most = std::min<int64_t>({nb, 16, part_bytes / share_bytes});
         double best = 0.;
         for (int64_t ks = 1; ks <= std::max<int64_t>(1, most); ++ks) {
             const double us = static_cast<double>((wgs * ks + slots - 1) / slots) * static_cast<double>((nb + ks - 1) / ks) * (p.narrow ? 7. : 14.) +

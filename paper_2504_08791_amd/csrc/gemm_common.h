@@ -46,20 +46,24 @@ __device__ __forceinline__ half8 gemm_sums_operand(half8 v, int g)
     return g < 2 ? v : none;
 }
 
-// 1/rms of token t from its sums of squares over super-blocks, added by a wave, by 16 lanes, or by a workgroup of 256 threads for the NT
+// 1/rms of token t from its sums of squares over super-blocks, added by a wave or by 16 lanes (requested and added apart, so that
+// other requests share the trip through memory), or by a workgroup of 256 threads for the NT
 // tokens from t0 on (into inv[NT]; red[256]: scratch; both in LDS, a barrier in between and behind)
 __device__ __forceinline__ float gemm_inv_rms(const GemmNorm &n, float squares) { return 1.0f / sqrtf(squares / (static_cast<float>(n.nb) * 256.f) + n.eps); }
-__device__ __forceinline__ float gemm_squares64(const GemmNorm &n, int t, int lane)
+struct GemmSquares {
+    float s, u;
+};
+template <int LANES> // 16 or 64: requests the first 2 LANES super-blocks'
+__device__ __forceinline__ GemmSquares gemm_squares(const GemmNorm &n, int t, int lane)
 {
-    float s = 0.f;
-    for (int b = lane; b < n.nb; b += 64) s += n.ss[static_cast<int64_t>(b) * n.ld + t];
-    return s;
+    return {n.ss[static_cast<int64_t>(min(lane, n.nb - 1)) * n.ld + t], n.ss[static_cast<int64_t>(min(lane + LANES, n.nb - 1)) * n.ld + t]};
 }
-__device__ __forceinline__ float gemm_inv_rms16(const GemmNorm &n, int t, int j)
+template <int LANES>
+__device__ __forceinline__ float gemm_inv_rms_of(const GemmNorm &n, int t, int lane, const GemmSquares &q)
 {
-    float s = 0.f;
-    for (int b = j; b < n.nb; b += 16) s += n.ss[static_cast<int64_t>(b) * n.ld + t];
-    return gemm_inv_rms(n, row_sum16(s));
+    float s = (lane < n.nb ? q.s : 0.f) + (lane + LANES < n.nb ? q.u : 0.f);
+    for (int b = lane + 2 * LANES; b < n.nb; b += LANES) s += n.ss[static_cast<int64_t>(b) * n.ld + t];
+    return gemm_inv_rms(n, LANES == 16 ? row_sum16(s) : wave_sum(s));
 }
 template <int NT>
 __device__ __forceinline__ void gemm_inv_rms_tokens(const GemmNorm &n, int t0, float *red, float *inv)
@@ -100,7 +104,7 @@ __device__ __forceinline__ void gm_barrier()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// The shares of K of one number, `stride` numbers apart, added in order.  Eight are requested at a time (one by one, a trip through memory
+// The shares of K of one number, `stride` numbers apart, eight added pairwise and the eights in order.  Eight are requested at a time (one by one, a trip through memory
 // each: 333 tokens of 4096 rows, four or five shares, 8.5 to 9.6 us, now 8 to 8.5).
 __device__ __forceinline__ float gemm_add_shares(const float *p, int64_t stride, int n)
 {
@@ -111,7 +115,10 @@ __device__ __forceinline__ float gemm_add_shares(const float *p, int64_t stride,
 #pragma unroll
         for (int j = 0; j < AT; ++j) a[j] = p[min(i + j, n - 1) * stride]; // (past the last: the last again, not added)
 #pragma unroll
-        for (int j = 0; j < AT; ++j) v = i + j == 0 ? a[j] : (i + j < n ? v + a[j] : v);
+        for (int j = 1; j < AT; ++j)
+            if (i + j >= n) a[j] = 0.f;
+        const float s = ((a[0] + a[4]) + (a[2] + a[6])) + ((a[1] + a[5]) + (a[3] + a[7]));
+        v = i == 0 ? s : v + s;
     }
     return v;
 }

@@ -527,6 +527,29 @@ int ksplit_for(int64_t n_rb, int64_t n_tb, int64_t nb)
     const int64_t s = std::min<int64_t>({slots / wgs, nb / GM_MIN_SHARE, GM_MAX_KSPLIT});
     return s < 2 ? 1 : static_cast<int>(s);
 }
+// Shares that the caller's next launch adds on its way: they cost no launch, so that it takes them for less.  By rounds of workgroups times a
+// share's super-blocks (us each, a token tile a workgroup: 1.7 alone on a compute unit, 2.5 with another), and the shares' way to memory and back.
+// Two layers, us, shares by ksplit_for() (four super-blocks at the least, none from half a device of workgroups on) / here: 8B 17 tokens 248 / 217, 64 332 / 303,
+// 128 424 / 406, 333 865 / 860, 700 1606 / 1508; 14B 48 340 / 308, 333 1032 / 1025; 70B 17 475 / 461, 96 910 / 909, 333 2749 / 2611, 700 5273 / 4996.
+int shares_for(int64_t n_rb, int n_tiles, int64_t nb, int T)
+{
+    const int n_tb = (n_tiles + GM_TT - 1) / GM_TT;
+    const int64_t wgs = n_rb * n_tb, slots = 2 * GM_CUS;
+    const double tiles = (n_tiles + n_tb - 1) / n_tb;
+    double best = 0.;
+    int best_ks = 1;
+    for (int64_t ks = 1; ks <= std::min<int64_t>(GM_MAX_KSPLIT, nb); ++ks) {
+        const int64_t units = wgs * ks, full = units / slots, rest = units - full * slots;
+        const double rounds = full * 2.5 + (rest == 0 ? 0. : (rest <= GM_CUS ? 1.7 : 2.5));
+        const double us = rounds * tiles * static_cast<double>((nb + ks - 1) / ks) +
+                          (ks > 1 ? 1. + static_cast<double>(ks) * T * static_cast<double>(n_rb) * GM_ROWS * 8. / 4e6 : 0.);
+        if (ks == 1 || us < best) {
+            best = us;
+            best_ks = static_cast<int>(ks);
+        }
+    }
+    return best_ks;
+}
 // row blocks of one matrix; of a (gate, up) pair of n_rows each: 128 rows of both per block
 int64_t row_blocks(int64_t n_rows, bool pair = false) { return pair ? (n_rows + GM_ROWS / 2 - 1) / (GM_ROWS / 2) : (n_rows + GM_ROWS - 1) / GM_ROWS; }
 int token_blocks(int T) { return ((T + 15) / 16 + GM_TT - 1) / GM_TT; }
@@ -547,6 +570,14 @@ size_t gemm_part_bytes(int T, const int64_t *n_rows, int n_mats, int64_t n_cols,
     int64_t n_rb = 0;
     for (int i = 0; i < (pair ? 1 : n_mats); ++i) n_rb += row_blocks(n_rows[i], pair);
     return static_cast<size_t>(s) * static_cast<size_t>(T) * static_cast<size_t>(n_rb) * GM_ROWS * sizeof(float);
+}
+
+size_t gemm_later_bytes(int T, const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair)
+{
+    int64_t n_rb = 0;
+    for (int i = 0; i < (pair ? 1 : n_mats); ++i) n_rb += row_blocks(n_rows[i], pair);
+    const int s = shares_for(n_rb, (T + 15) / 16, n_cols / QK, T);
+    return s == 1 ? 0 : static_cast<size_t>(s) * static_cast<size_t>(T) * static_cast<size_t>(n_rb) * GM_ROWS * sizeof(float);
 }
 
 size_t gemm_acts_bytes(int T, int64_t n_cols) { return (static_cast<size_t>(T) + 15) / 16 * static_cast<size_t>(n_cols / QK) * GM_TILE_BYTES; }
@@ -586,9 +617,11 @@ prima_status launch_q4k_gemm(const GemmMat *mats, int n_mats, bool pair, int64_t
     a.n_cols = n_cols; a.A = x.A; a.norm = x.norm; a.resid = resid; a.ldr = ldr;
     a.T = T; a.n_tiles = n_tiles; a.n_rb = static_cast<int>(n_rb); a.n_tb = n_tb; a.band = gemm_band(n_tb);
     // K is divided when that fills the device and the caller's scratch holds the shares
-    a.ksplit = part && T <= 65535 && (later || (n_mats == 1 && !pair)) ? ksplit_for(n_rb, n_tb, nb) : 1; // (shares: T a grid dimension of the launch that adds them)
+    a.ksplit = part && T <= 65535 && (later || (n_mats == 1 && !pair)) ? (later ? shares_for(n_rb, n_tiles, nb, T) : ksplit_for(n_rb, n_tb, nb)) : 1; // (shares: T a grid dimension of the launch that adds them)
     a.ldp = n_rb * GM_ROWS;
-    if (a.ksplit > 1 && part_bytes < static_cast<size_t>(a.ksplit) * static_cast<size_t>(T) * static_cast<size_t>(a.ldp) * sizeof(float)) a.ksplit = 1;
+    const size_t share_bytes = static_cast<size_t>(T) * static_cast<size_t>(a.ldp) * sizeof(float);
+    if (later && a.ksplit > 1) a.ksplit = static_cast<int>(std::max<size_t>(1, std::min<size_t>(a.ksplit, part_bytes / share_bytes)));
+    if (a.ksplit > 1 && part_bytes < a.ksplit * share_bytes) a.ksplit = 1;
     a.share_q = static_cast<int>(nb / a.ksplit); a.share_r = static_cast<int>(nb % a.ksplit);
     a.tile_q = n_tiles / n_tb; a.tile_r = n_tiles % n_tb;
     a.part = a.ksplit > 1 ? static_cast<float *>(part) : nullptr;

@@ -518,12 +518,13 @@ PrefillWs carve_prefill(const prima_dims &d, int kv_cap, int T)
     {
         // the shares of K of the launches that divide it (few rows, few tokens): the largest of the layer's products
         const int64_t r_qkv[3] = {static_cast<int64_t>(qd), static_cast<int64_t>(kvd), static_cast<int64_t>(kvd)}, r_e[1] = {d.e}, r_f[1] = {d.ffn};
-        size_t pb = gemm_part_bytes(T, r_qkv, 3, d.e), apart = 0;
+        size_t pb = std::max(gemm_part_bytes(T, r_f, 1, d.e), gemm_later_bytes(T, r_qkv, 3, d.e)), apart = 0;
         for (int i = 0; i < 3; ++i) // one by one when the formats differ, all there until the launch behind them
-            apart += round_up(std::max(gemm_part_bytes(T, r_qkv + i, 1, d.e), fmt_gemm_part_bytes(T, r_qkv[i], d.e)), 256);
+            apart += round_up(std::max(gemm_later_bytes(T, r_qkv + i, 1, d.e), fmt_gemm_part_bytes(T, r_qkv[i], d.e)), 256);
         pb = std::max(pb, apart);
-        pb = std::max({pb, gemm_part_bytes(T, r_e, 1, static_cast<int64_t>(qd)), gemm_part_bytes(T, r_e, 1, d.ffn), gemm_part_bytes(T, r_f, 1, d.e),
-                       gemm_part_bytes(T, r_f, 1, d.e, true)});
+        for (const int64_t cols : {static_cast<int64_t>(qd), static_cast<int64_t>(d.ffn)})
+            pb = std::max({pb, gemm_later_bytes(T, r_e, 1, cols), fmt_gemm_part_bytes(T, d.e, cols)});
+        pb = std::max(pb, gemm_later_bytes(T, r_f, 1, d.e, true));
         w.part_bytes = pb;
         w.part = take(pb);
     }
