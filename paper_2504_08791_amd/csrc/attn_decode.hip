@@ -71,6 +71,7 @@ struct AttnTileLds {
 template <int D, int MODE> // head size, RoPE pairing (0: i with i + D/2, 1: 2i with 2i + 1)
 __global__ void __launch_bounds__(ATT_THREADS, 4) attn_decode_kernel(AttnArgs a) // 4 waves per SIMD (two workgroups per compute unit): at most 128 VGPRs
 {
+    request_args<sizeof(a)>();
     extern __shared__ __align__(16) uint8_t smem[];
     constexpr int NA = D / 32; // MFMAs (k-steps of 32) per tile of logits and query part
     constexpr int NB = D / 16; // 16-column blocks of the output

@@ -220,6 +220,22 @@ AttnRecords attn_records(const prima_dims &d, int n_past, int T, void *ws, const
 // a prompt: rotated K / V rows already in the caches, q rotated; pieces of PRIMA_MAX_TOK tokens in one launch
 prima_status launch_attn_prompt(const prima_dims &d, const float *q, __half *K, __half *V, int kv_cap, int n_past, int T,
                                 float *o, hipStream_t st);
+// Requests every line of a kernel's `bytes` of arguments at once, as its first thing.  A launch starts with cold scalar caches, and the
+// compiler fetches an argument where it is first needed: two to five trips through memory one after the other (half a microsecond and more
+// each) before the first load of data went out.  With this and the streams' matrices picked without fetches of their own, us, before / now: four 32B layers,
+// 4 tokens 443 / 429, 14B with Q6_K 3 tokens 369 / 354, 16 sequences through three 14B layers 340 / 331, 14B 2 tokens 254 / 250, 8B prompt of 24 227 / 220.
+// (One token's mat-vec requests most of them by itself: 147.7 / 147.3.  Not in the output layer's kernels: no change.)
+template <int BYTES>
+__device__ __forceinline__ void request_args()
+{
+    typedef const __attribute__((address_space(4))) uint32_t Word;
+    Word *const p = (Word *)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t x = p[BYTES / 4 - 1];
+#pragma unroll
+    for (int i = 0; i < BYTES; i += 64) x ^= p[i / 4];
+    asm volatile("" ::"s"(x));
+}
+
 // 16 bytes per lane from global memory straight into LDS: lane l writes bytes [16 l, 16 l + 16) of the
 // 1 KiB at LDS byte address lds_addr (wave-uniform, goes through M0).  Written as inline assembly on
 // purpose: the compiler then does not know these loads write LDS and leaves the ordering against the

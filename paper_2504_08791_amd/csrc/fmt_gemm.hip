@@ -95,6 +95,7 @@ struct FmLds {
 template <int FMT, int WT, bool FULL>
 __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
 {
+    request_args<sizeof(a)>();
     extern __shared__ __align__(16) uint8_t smem[];
     typedef FmLds<FMT, WT> L;
     // Q5_K has no registers left for its unpacking between the products (all seven matrices, 8B 1024 tokens: 1739 us in front, 1785 woven; Q8_0 1697 / 1648, Q6_K

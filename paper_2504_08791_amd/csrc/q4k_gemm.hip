@@ -505,6 +505,7 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
 
 __global__ void __launch_bounds__(GM_THREADS, 2) q4k_gemm_kernel(GemmArgs a)
 {
+    request_args<sizeof(a)>();
     extern __shared__ __align__(16) uint8_t smem[];
     int rb, tb, share;
     if (!gemm_unit(blockIdx.x, a.n_rb, a.n_tb, a.ksplit, a.band, rb, tb, share)) return; // the whole workgroup, before any barrier

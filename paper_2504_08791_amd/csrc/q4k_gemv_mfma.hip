@@ -56,6 +56,7 @@ namespace prima {
 template <int TT>
 __global__ void __launch_bounds__(GEMV_THREADS) gemv_q4k_persistent_kernel(PGemvArgs a)
 {
+    request_args<sizeof(a)>();
     extern __shared__ __align__(16) uint8_t smem[];
     const int wg_index = blockIdx.x;
     const float *const arg_x = a.x, *const arg_gain = a.gain;
@@ -70,6 +71,7 @@ __global__ void __launch_bounds__(GEMV_THREADS) gemv_q4k_persistent_kernel(PGemv
 template <int TT>
 __global__ void __launch_bounds__(256) gemv_slab_reduce_kernel(PGemvArgs a)
 {
+    request_args<sizeof(a)>();
     const bool pairs = a.epi == EPI_SWIGLU;
     const int gran = pairs ? 2 : 1;
     const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;

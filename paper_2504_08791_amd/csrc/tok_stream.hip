@@ -44,11 +44,15 @@ struct StreamArgs {
     int n_slabs, slab; // slabs of K, super-blocks of one (a multiple of the stage's; the last may be shorter)
     int ks_shift;      // a unit is one of 2^ks_shift parts of a (tile, slab)
     int rounds, per_round; // as in tok_gemv.hip, among the workgroups of a slab
+    // a slab has wg_slab workgroups, the first wg_more one more; workgroup / n_slabs by a multiplication (n_slabs 1: not needed)
+    int wg_slab, wg_more;
+    unsigned slab_magic;
 };
 
 template <int FMT, int NT>
 __global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) tok_stream_kernel(StreamArgs a)
 {
+    request_args<sizeof(a)>();
     extern __shared__ __align__(16) uint8_t smem[];
     constexpr int SBS = TkFmt<FMT>::SBS, WAVES = TkFmt<FMT>::WAVES;
     const int lane = threadIdx.x & 63;
@@ -57,8 +61,14 @@ __global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64) __attribute__((amdgpu_
     uint8_t *const l_stage = smem + wave * tk_stage_bytes<FMT>;
     uint8_t *const l_a = smem + WAVES * tk_stage_bytes<FMT>;
 
-    const int rank = static_cast<int>(blockIdx.x) / a.n_slabs, slab = static_cast<int>(blockIdx.x) - rank * a.n_slabs;
-    const int ranks = (static_cast<int>(gridDim.x) - slab + a.n_slabs - 1) / a.n_slabs; // workgroups of this slab
+    // The matrices' fields as one and what the next has more: picked by a number they are fetched through a picked address, each a wait in front
+    // of the first weights.
+    const uint8_t *const W0 = a.seg[0].W;
+    const int64_t W1 = a.seg[1].W - a.seg[0].W, W2 = a.seg[2].W - a.seg[1].W;
+    const int64_t rows0 = a.seg[0].n_rows, rows1 = a.seg[1].n_rows - rows0, rows2 = a.seg[2].n_rows - rows1 - rows0;
+    const int first1 = a.seg[1].tile0, first2 = a.seg[2].tile0;
+    const int rank = a.n_slabs == 1 ? blockIdx.x : static_cast<int>(__umulhi(blockIdx.x, a.slab_magic)), slab = static_cast<int>(blockIdx.x) - rank * a.n_slabs;
+    const int ranks = a.wg_slab + (slab < a.wg_more ? 1 : 0); // workgroups of this slab
     const int nb = a.nb, ks_shift = a.ks_shift, ks = 1 << ks_shift;
     const int sb0 = slab * a.slab, nsb = min(a.slab, nb - sb0);
     const int my_l = wave >> ks_shift, part = wave & (ks - 1);
@@ -70,11 +80,8 @@ __global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64) __attribute__((amdgpu_
         if (my_tile >= a.per_round || tile >= a.n_tiles) return a.rounds;
         return min(k, a.rounds);
     };
-    int n_active = 0;
-    {
-        int tile;
-        for (int k = next_round(0, tile); k < a.rounds; k = next_round(k + 1, tile)) ++n_active;
-    }
+    // (all rounds but the last are full)
+    const int n_active = my_tile >= a.per_round ? 0 : a.rounds - 1 + (my_tile < a.n_tiles - (a.rounds - 1) * a.per_round ? 1 : 0);
     const int total = (s1 - s0) * n_active;
 
     // requests, two stages ahead (past the end the last stage again: the loads in flight are then the same on every path)
@@ -88,10 +95,10 @@ __global__ void __launch_bounds__(TkFmt<FMT>::WAVES * 64) __attribute__((amdgpu_
             ld_k = k;
             ld_b = sb0 + s0 * SBS;
             ld_left = s1 - s0;
-            const int sg = tile >= a.seg[2].tile0 ? 2 : (tile >= a.seg[1].tile0 ? 1 : 0);
-            const uint8_t *W = sg == 0 ? a.seg[0].W : (sg == 1 ? a.seg[1].W : a.seg[2].W);
-            const int64_t n_rows = sg == 0 ? a.seg[0].n_rows : (sg == 1 ? a.seg[1].n_rows : a.seg[2].n_rows);
-            const int first = sg == 0 ? a.seg[0].tile0 : (sg == 1 ? a.seg[1].tile0 : a.seg[2].tile0);
+            const bool one = tile >= first1, two = tile >= first2;
+            const uint8_t *W = W0 + ((one ? W1 : 0) + (two ? W2 : 0));
+            const int64_t n_rows = rows0 + (one ? rows1 : 0) + (two ? rows2 : 0);
+            const int first = two ? first2 : (one ? first1 : 0);
             tk_tile<FMT>(src, W, n_rows, nb, static_cast<int64_t>(tile - first) * 16, lane);
         } else {
             ld_b -= ld_step;
@@ -266,6 +273,7 @@ __device__ __forceinline__ tk_f4 merge_records(const float *rec, int nsplit, int
 template <int NT>
 __global__ void __launch_bounds__(64 * ADD_WAVES) tok_prepare_kernel(TokPrepare a)
 {
+    request_args<sizeof(a)>();
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int pi = blockIdx.x * ADD_WAVES + wave, t = pi & (NT - 1), b = pi / NT; // (pairs: a multiple of four)
     const int64_t col = static_cast<int64_t>(b) * 256 + lane * 4, K = static_cast<int64_t>(a.nb) * 256;
@@ -310,15 +318,20 @@ __global__ void __launch_bounds__(64 * ADD_WAVES) tok_prepare_kernel(TokPrepare 
 // y[t][row] = 1/rms * sum of the shares (+ residual) of up to three vectors of their own lengths, 256 rows a wave
 __global__ void __launch_bounds__(64 * ADD_WAVES) tok_sum_kernel(TokSum a)
 {
+    request_args<sizeof(a)>();
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int t = blockIdx.y;
     int64_t first = (static_cast<int64_t>(blockIdx.x) * ADD_WAVES + wave) * 256;
-    int i = 0;
-    while (i < a.n && first >= (a.rows[i] + 255) / 256 * 256) { first -= (a.rows[i] + 255) / 256 * 256; ++i; }
-    if (i >= a.n) return;
-    const TokPart &p = i == 0 ? a.p[0] : (i == 1 ? a.p[1] : a.p[2]);
-    const int64_t rows = i == 0 ? a.rows[0] : (i == 1 ? a.rows[1] : a.rows[2]);
-    float *const y = i == 0 ? a.y[0] : (i == 1 ? a.y[1] : a.y[2]);
+    // which vector: fields as those of the one before and what it has more (picked by a number they are fetched through a picked address)
+    const int64_t r0 = (a.rows[0] + 255) / 256 * 256, r1 = r0 + (a.rows[1] + 255) / 256 * 256, r2 = r1 + (a.rows[2] + 255) / 256 * 256;
+    const bool one = first >= r0, two = first >= r1;
+    if (first >= (a.n == 3 ? r2 : (a.n == 2 ? r1 : r0))) return;
+    first -= two ? r1 : (one ? r0 : 0);
+    auto pick = [&](auto x, auto y, auto z) { return x + ((one ? y - x : 0) + (two ? z - y : 0)); };
+    const TokPart p{pick(a.p[0].part, a.p[1].part, a.p[2].part), pick(a.p[0].n_parts, a.p[1].n_parts, a.p[2].n_parts),
+                    pick(a.p[0].rows, a.p[1].rows, a.p[2].rows), pick(a.p[0].row0, a.p[1].row0, a.p[2].row0)};
+    const int64_t rows = pick(a.rows[0], a.rows[1], a.rows[2]);
+    float *const y = pick(a.y[0], a.y[1], a.y[2]);
     const bool mine = first + lane * 4 < rows; // (rows are a multiple of 16)
     const int64_t row = mine ? first + lane * 4 : 0; // (else a valid address, not stored)
     tk_f4 v = {0.f, 0.f, 0.f, 0.f}, r = v;
@@ -384,6 +397,8 @@ prima_status launch_nt(StreamArgs &a, const StreamPlan &p, hipStream_t st)
         attr_set = true;
     }
     const int grid = std::min<int64_t>(TK_CUS, static_cast<int64_t>(a.n_tiles) * a.n_slabs);
+    a.wg_slab = grid / a.n_slabs; a.wg_more = grid % a.n_slabs;
+    a.slab_magic = static_cast<unsigned>((uint64_t{1} << 32) / a.n_slabs + 1); // exact: a workgroup's number times n_slabs is far below 2^32
     hipLaunchKernelGGL((tok_stream_kernel<FMT, NT>), dim3(grid), dim3(TkFmt<FMT>::WAVES * 64), p.lds, st, a);
     return last_launch_status();
 }
