@@ -246,7 +246,6 @@ __global__ void __launch_bounds__(ATT_THREADS, 4) attn_decode_kernel(AttnArgs a)
             }
         }
         __syncthreads(); // the new rows are in LDS
-        if (key0 < p_end) patch_k(key0, kb);
     }
 
     float m_run = -INFINITY, l_run = 0.f; // of this lane's query (the same in its four lanes)
@@ -258,7 +257,8 @@ __global__ void __launch_bounds__(ATT_THREADS, 4) attn_decode_kernel(AttnArgs a)
     while (key0 < p_end) {
         const int next = key0 + tile_stride;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // this tile's V is in LDS (its K is waited for by the compiler)
-        if (has_new && key0 + 16 > arg_n_past) {
+        if (has_new && key0 + 16 > arg_n_past) { // (uniform)
+            patch_k(key0, kb);
             // rows of this step in the tile, and the rows past the last one (which repeat it): what the cache
             // held for them is replaced, so that nothing undefined meets a zero probability
             for (int r = max(0, arg_n_past - key0); r < 16; ++r)
@@ -296,7 +296,6 @@ __global__ void __launch_bounds__(ATT_THREADS, 4) attn_decode_kernel(AttnArgs a)
         // the next tile: its K replaces the one just consumed, its V goes to the other buffer
         if (next < p_end) {
             load_k(next, kb);
-            patch_k(next, kb);
             request_v(next, buf ^ 1);
         }
         // rescale what has been accumulated (rows of the accumulators are queries 4g..4g+3: their factors come
