@@ -104,6 +104,30 @@ prima_status launch_zero_arrivals(void *ws, size_t bytes, hipStream_t st);
 // host only: whether every pass of this launch finds a plan and fits the scratch (nothing is launched)
 prima_status gemv_plan_status(const GemvArgs &a, void *ws, size_t ws_bytes, size_t arrivals_region);
 
+// RoPE table [T][D/2] of (cos, sin) for the positions n_past .. n_past + T - 1 (any T)
+struct RopeTable {
+    float2 *tab; // null: none
+    int64_t n;   // T * half
+    int half, n_past;
+    double theta;
+};
+inline RopeTable rope_table(float *tab, int T, int D, int n_past, float theta)
+{
+    return RopeTable{reinterpret_cast<float2 *>(tab), static_cast<int64_t>(T) * (D / 2), D / 2, n_past, static_cast<double>(theta)};
+}
+// What a window step needs before its first layer: the RoPE table of up to PRIMA_MAX_TOK positions, counters zeroed
+struct RopePositions {
+    int pos[PRIMA_MAX_TOK];
+};
+struct StepInit {
+    float2 *tab;
+    int T, half;
+    RopePositions p;
+    double theta;
+    unsigned *zero;
+    unsigned n_zero;
+};
+
 // ---- many tokens (gemm_prepare.hip, q4k_gemm.hip, fmt_gemm.hip) ----
 // The activations of a product: split and laid out for the matrix cores (gemm_common.h) by launch_gemm_prepare(), without 1/rms: that multiplies the
 // finished sums, from the sums of squares ss[super-block][ld] of the tokens (ss null: no norm).
@@ -137,7 +161,8 @@ struct GemmPrepare {
     uint8_t *A; // null: not laid out
     int waves;  // of a workgroup (filled in by the launch)
 };
-prima_status launch_gemm_prepare(GemmPrepare a, hipStream_t st);
+// table: beside GEMM_PLAIN, the prompt's RoPE table too (tab null: not)
+prima_status launch_gemm_prepare(GemmPrepare a, const RopeTable &table, hipStream_t st);
 size_t gemm_acts_bytes(int T, int64_t n_cols); // A
 size_t gemm_ss_bytes(int T, int64_t n_cols);   // ss
 // y = 1/rms * the shares of one matrix (+ resid)
@@ -179,14 +204,14 @@ struct RopeAppend {
     int Hq, Hkv, D, mode, block; // (filled in by the launch)
 };
 prima_status launch_rope_append(RopeAppend a, const prima_dims &d, int T, hipStream_t st);
-// RoPE table [T][D/2] of (cos, sin) for the positions n_past .. n_past + T - 1 (any T)
-prima_status launch_rope_table(float *tab, int T, int D, int n_past, float theta, hipStream_t st);
+prima_status launch_rope_table(const RopeTable &r, hipStream_t st);
 
 prima_status launch_stream_read(const void *src, size_t bytes, void *sink, hipStream_t st, bool nt);
 prima_status launch_swiglu(float *a, const float *u, int64_t n, hipStream_t st);
-// the RoPE table [T][D/2] of (cos, sin), and `zero` cleared, in one launch.
+// the RoPE table [T][D/2] of (cos, sin), and `zero` cleared, in one launch (or at the end of a window's first, tok_stream.h).
 // positions: null (token t sits at n_past + t) or T positions, one per token (a batch of sequences)
-prima_status launch_step_init(float *tab, int T, int D, int n_past, float theta, const int *positions, void *zero, size_t zero_bytes, hipStream_t st);
+StepInit step_init_args(float *tab, int T, int D, int n_past, float theta, const int *positions, void *zero, size_t zero_bytes);
+prima_status launch_step_init(const StepInit &s, hipStream_t st);
 prima_status launch_fill_words(void *a, size_t a_bytes, unsigned a_word, void *b, size_t b_bytes, unsigned b_word, hipStream_t st);
 size_t attn_ws_bytes(const prima_dims &d, int kv_cap, int T);
 // The attention scratch: attn_counter_bytes() whose first word is the flag a bounded wait raises when it gives up
@@ -220,6 +245,34 @@ AttnRecords attn_records(const prima_dims &d, int n_past, int T, void *ws, const
 // a prompt: rotated K / V rows already in the caches, q rotated; pieces of PRIMA_MAX_TOK tokens in one launch
 prima_status launch_attn_prompt(const prima_dims &d, const float *q, __half *K, __half *V, int kv_cap, int n_past, int T,
                                 float *o, hipStream_t st);
+// (cos, sin) of pos * theta^(-2i/D), in fp64: at positions of several thousand an fp32 angle would already be off by ~1e-4 rad
+__device__ __forceinline__ float2 rope_angle(int64_t pos, int i, int half, double theta)
+{
+    const double ang = static_cast<double>(pos) * pow(theta, -static_cast<double>(i) / static_cast<double>(half));
+    return make_float2(static_cast<float>(cos(ang)), static_cast<float>(sin(ang)));
+}
+__device__ __forceinline__ void rope_table_entry(const RopeTable &r, int64_t idx)
+{
+    if (idx >= r.n) return;
+    const int t = static_cast<int>(idx / r.half), i = static_cast<int>(idx - static_cast<int64_t>(t) * r.half);
+    r.tab[idx] = rope_angle(static_cast<int64_t>(r.n_past) + t, i, r.half, r.theta);
+}
+__device__ __forceinline__ void step_init_entry(const StepInit &s, unsigned idx)
+{
+    if (idx < s.n_zero) s.zero[idx] = 0u;
+    if (idx >= static_cast<unsigned>(s.T * s.half)) return;
+    const int t = idx / s.half, i = idx - t * s.half;
+    int pos = 0;
+#pragma unroll
+    for (int k = 0; k < PRIMA_MAX_TOK; ++k) pos = (k == t) ? s.p.pos[k] : pos; // no run-time index into the arguments
+    s.tab[idx] = rope_angle(pos, i, s.half, s.theta);
+}
+inline unsigned step_init_blocks(const StepInit &s) // of 256 threads
+{
+    const unsigned n = static_cast<unsigned>(s.T * s.half) > s.n_zero ? static_cast<unsigned>(s.T * s.half) : s.n_zero;
+    return (n + 255) / 256;
+}
+
 // Requests every line of a kernel's `bytes` of arguments at once, as its first thing.  A launch starts with cold scalar caches, and the
 // compiler fetches an argument where it is first needed: two to five trips through memory one after the other (half a microsecond and more
 // each) before the first load of data went out.  With this and the streams' matrices picked without fetches of their own, us, before / now: four 32B layers,

@@ -6,35 +6,21 @@
 
 namespace prima {
 
-struct RopePositions {
-    int pos[PRIMA_MAX_TOK];
-};
-
 // Everything a window step needs before its first layer, in one launch: the mat-vec's counters zeroed and the RoPE table,
-// tab[t][i] = (cos, sin) of pos_t * theta^(-2i/D) with pos_t = n_past + t (or the token's own position in
-// a batch of sequences), evaluated in fp64: at positions of several thousand an fp32 angle would already be off
-// by ~1e-4 rad.
-__global__ void step_init_kernel(float2 *tab, int T, int half, RopePositions p, double theta, unsigned *zero, unsigned n_zero)
+// tab[t][i] = (cos, sin) of pos_t * theta^(-2i/D) with pos_t = n_past + t (or the token's own position in a batch of sequences)
+__global__ void __launch_bounds__(256) step_init_kernel(StepInit s) { step_init_entry(s, blockIdx.x * 256 + threadIdx.x); }
+
+StepInit step_init_args(float *tab, int T, int D, int n_past, float theta, const int *positions, void *zero, size_t zero_bytes)
 {
-    const unsigned idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx < n_zero) zero[idx] = 0u;
-    if (idx >= static_cast<unsigned>(T * half)) return;
-    const int t = idx / half, i = idx - t * half;
-    int pos = 0;
-#pragma unroll
-    for (int k = 0; k < PRIMA_MAX_TOK; ++k) pos = (k == t) ? p.pos[k] : pos; // no run-time index into the arguments
-    const double ang = static_cast<double>(pos) * pow(theta, -static_cast<double>(i) / static_cast<double>(half));
-    tab[idx] = make_float2(static_cast<float>(cos(ang)), static_cast<float>(sin(ang)));
+    StepInit s{reinterpret_cast<float2 *>(tab), T, D / 2, {}, static_cast<double>(theta), static_cast<unsigned *>(zero),
+               static_cast<unsigned>(zero_bytes / sizeof(unsigned))};
+    for (int t = 0; t < T && t < PRIMA_MAX_TOK; ++t) s.p.pos[t] = positions ? positions[t] : n_past + t;
+    return s;
 }
 
-prima_status launch_step_init(float *tab, int T, int D, int n_past, float theta, const int *positions, void *zero, size_t zero_bytes, hipStream_t st)
+prima_status launch_step_init(const StepInit &s, hipStream_t st)
 {
-    RopePositions p{};
-    for (int t = 0; t < T && t < PRIMA_MAX_TOK; ++t) p.pos[t] = positions ? positions[t] : n_past + t;
-    const unsigned n_zero = static_cast<unsigned>(zero_bytes / sizeof(unsigned));
-    const unsigned n = std::max(static_cast<unsigned>(T * (D / 2)), n_zero);
-    hipLaunchKernelGGL(step_init_kernel, dim3((n + 255) / 256), dim3(256), 0, st,
-                       reinterpret_cast<float2 *>(tab), T, D / 2, p, static_cast<double>(theta), static_cast<unsigned *>(zero), n_zero);
+    hipLaunchKernelGGL(step_init_kernel, dim3(step_init_blocks(s)), dim3(256), 0, st, s);
     return last_launch_status();
 }
 
@@ -56,22 +42,13 @@ prima_status launch_fill_words(void *a, size_t a_bytes, unsigned a_word, void *b
     return last_launch_status();
 }
 
-// the same table for any number of consecutive positions (prompt processing)
-__global__ void __launch_bounds__(256) rope_table_kernel(float2 *tab, int64_t n, int half, int n_past, double theta)
-{
-    const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (idx >= n) return;
-    const int t = static_cast<int>(idx / half), i = static_cast<int>(idx - static_cast<int64_t>(t) * half);
-    const double ang = static_cast<double>(n_past + t) * pow(theta, -static_cast<double>(i) / static_cast<double>(half));
-    tab[idx] = make_float2(static_cast<float>(cos(ang)), static_cast<float>(sin(ang)));
-}
+// the same table for any number of consecutive positions (prompt processing; usually beside the first layer's activations, gemm_prepare.hip)
+__global__ void __launch_bounds__(256) rope_table_kernel(RopeTable r) { rope_table_entry(r, static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x); }
 
-prima_status launch_rope_table(float *tab, int T, int D, int n_past, float theta, hipStream_t st)
+prima_status launch_rope_table(const RopeTable &r, hipStream_t st)
 {
-    const int64_t n = static_cast<int64_t>(T) * (D / 2);
-    if (n <= 0) return PRIMA_OK;
-    hipLaunchKernelGGL(rope_table_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, st,
-                       reinterpret_cast<float2 *>(tab), n, D / 2, n_past, static_cast<double>(theta));
+    if (r.n <= 0) return PRIMA_OK;
+    hipLaunchKernelGGL(rope_table_kernel, dim3(static_cast<unsigned>((r.n + 255) / 256)), dim3(256), 0, st, r);
     return last_launch_status();
 }
 

@@ -57,7 +57,7 @@ __device__ __forceinline__ void add_shares(const float *p, const int *off, int64
 // A wave takes four tokens of a super-block: lane (m, j) the columns 64 i + 4 j .. + 3 of token m, a row of 16 lanes per token, so that the
 // sums over a super-block stay in the row and nothing goes through LDS.  Everything is requested in front of the first use.
 template <int MODE>
-__global__ void __launch_bounds__(256) gemm_prepare_kernel(GemmPrepare a)
+__device__ __forceinline__ void prepare_unit(const GemmPrepare &a)
 {
     const int lane = threadIdx.x & 63, m = lane >> 4, j = lane & 15;
     // every argument that the launch will look at, requested at once
@@ -185,6 +185,16 @@ __global__ void __launch_bounds__(256) gemm_prepare_kernel(GemmPrepare a)
     if (j == 2) *reinterpret_cast<float *>(dst + 16 * 1024 + GM_SCALES + m16 * 4) = ldexpf(1.0f, -p);
 }
 
+template <int MODE>
+__global__ void __launch_bounds__(256) gemm_prepare_kernel(GemmPrepare a) { prepare_unit<MODE>(a); }
+
+// A prompt's first launch: the first layer's activations, and behind them its RoPE table (a launch of 4.7 us by itself).
+__global__ void __launch_bounds__(256) gemm_first_kernel(GemmPrepare a, RopeTable r, unsigned blocks)
+{
+    if (blockIdx.x < blocks) prepare_unit<GEMM_PLAIN>(a);
+    else rope_table_entry(r, static_cast<int64_t>(blockIdx.x - blocks) * blockDim.x + threadIdx.x);
+}
+
 // y[t][row] = 1/rms * the shares of K of a number added in order (+ residual)
 __global__ void __launch_bounds__(256) gemm_sum_kernel(GemmShares p, GemmNorm norm, const float *resid, int64_t ldr, float *y, int64_t ldy, int64_t n_rows)
 {
@@ -255,7 +265,7 @@ __global__ void __launch_bounds__(256) rope_append_kernel(RopeAppend a)
 
 } // namespace
 
-prima_status launch_gemm_prepare(GemmPrepare a, hipStream_t st)
+prima_status launch_gemm_prepare(GemmPrepare a, const RopeTable &table, hipStream_t st)
 {
     a.n_tiles = (a.T + 15) / 16;
     const int64_t units = static_cast<int64_t>(a.n_tiles) * 4 * a.nb;
@@ -263,7 +273,11 @@ prima_status launch_gemm_prepare(GemmPrepare a, hipStream_t st)
     // a wave a workgroup while that spreads them over more compute units
     a.waves = units <= 8 * GM_CUS ? 1 : 4;
     const dim3 grid(static_cast<unsigned>((units + a.waves - 1) / a.waves)), block(64 * a.waves);
-    if (a.mode == GEMM_PLAIN) hipLaunchKernelGGL(gemm_prepare_kernel<GEMM_PLAIN>, grid, block, 0, st, a);
+    if (table.tab) {
+        const int64_t more = (table.n + block.x - 1) / block.x;
+        if (a.mode != GEMM_PLAIN || grid.x + more >= (int64_t{1} << 31)) return PRIMA_E_SHAPE;
+        hipLaunchKernelGGL(gemm_first_kernel, dim3(grid.x + static_cast<unsigned>(more)), block, 0, st, a, table, grid.x);
+    } else if (a.mode == GEMM_PLAIN) hipLaunchKernelGGL(gemm_prepare_kernel<GEMM_PLAIN>, grid, block, 0, st, a);
     else if (a.mode == GEMM_RESIDUAL) hipLaunchKernelGGL(gemm_prepare_kernel<GEMM_RESIDUAL>, grid, block, 0, st, a);
     else hipLaunchKernelGGL(gemm_prepare_kernel<GEMM_SWIGLU>, grid, block, 0, st, a);
     return last_launch_status();

@@ -52,7 +52,8 @@ prima_status launch_tok_stream(int fmt, const TokMat *mats, int n_mats, int64_t 
                                TokPart *out, hipStream_t st);
 // host only: whether matrices of n_rows rows in all find a plan whose shares fit
 prima_status tok_stream_plan_status(int fmt, int64_t n_rows, int64_t n_cols, int T, size_t part_floats);
-prima_status launch_tok_prepare(const TokPrepare &a, hipStream_t st);
+// init: a window's first launch does what a step needs in front of it too (tab null: not)
+prima_status launch_tok_prepare(const TokPrepare &a, const StepInit &init, hipStream_t st);
 prima_status launch_tok_sum(const TokSum &a, hipStream_t st);
 
 } // namespace prima

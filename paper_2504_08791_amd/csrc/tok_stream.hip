@@ -271,9 +271,8 @@ __device__ __forceinline__ tk_f4 merge_records(const float *rec, int nsplit, int
 
 // A (token, super-block) pair a wave.  Token slots past T: zeros.
 template <int NT>
-__global__ void __launch_bounds__(64 * ADD_WAVES) tok_prepare_kernel(TokPrepare a)
+__device__ __forceinline__ void prepare_pair(const TokPrepare &a)
 {
-    request_args<sizeof(a)>();
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int pi = blockIdx.x * ADD_WAVES + wave, t = pi & (NT - 1), b = pi / NT; // (pairs: a multiple of four)
     const int64_t col = static_cast<int64_t>(b) * 256 + lane * 4, K = static_cast<int64_t>(a.nb) * 256;
@@ -313,6 +312,22 @@ __global__ void __launch_bounds__(64 * ADD_WAVES) tok_prepare_kernel(TokPrepare 
     const float o[4] = {v[0], v[1], v[2], v[3]};
     if (a.rec[0]) tk_split_wave<NT, 0, false>(o, lane, t, a.rec[0] + static_cast<int64_t>(b) * tk_rec(NT));
     if (a.rec[1]) tk_split_wave<NT, 1, true>(o, lane, t, a.rec[1] + static_cast<int64_t>(b) * tk_rec(NT));
+}
+
+template <int NT>
+__global__ void __launch_bounds__(64 * ADD_WAVES) tok_prepare_kernel(TokPrepare a)
+{
+    request_args<sizeof(a)>();
+    prepare_pair<NT>(a);
+}
+
+// A step's first launch: the first layer's activations, and behind them the RoPE table and the counters (3 to 4 us as a launch in front)
+template <int NT>
+__global__ void __launch_bounds__(64 * ADD_WAVES) tok_first_kernel(TokPrepare a, StepInit s)
+{
+    const int blocks = a.nb * NT / ADD_WAVES;
+    if (static_cast<int>(blockIdx.x) < blocks) prepare_pair<NT>(a);
+    else step_init_entry(s, (blockIdx.x - blocks) * (64 * ADD_WAVES) + threadIdx.x);
 }
 
 // y[t][row] = 1/rms * sum of the shares (+ residual) of up to three vectors of their own lengths, 256 rows a wave
@@ -474,9 +489,20 @@ prima_status launch_tok_stream(int fmt, const TokMat *mats, int n_mats, int64_t 
     return s;
 }
 
-prima_status launch_tok_prepare(const TokPrepare &a, hipStream_t st)
+prima_status launch_tok_prepare(const TokPrepare &a, const StepInit &init, hipStream_t st)
 {
-    const int nt = tok_slots(a.T), grid = a.nb * nt / 4;
+    const int nt = tok_slots(a.T), grid = a.nb * nt / ADD_WAVES;
+    static_assert(ADD_WAVES == 4, "step_init_blocks() counts blocks of 256 threads");
+    if (init.tab) {
+        const dim3 more(grid + step_init_blocks(init));
+        switch (nt) {
+        case 4: hipLaunchKernelGGL((tok_first_kernel<4>), more, dim3(64 * ADD_WAVES), 0, st, a, init); break;
+        case 8: hipLaunchKernelGGL((tok_first_kernel<8>), more, dim3(64 * ADD_WAVES), 0, st, a, init); break;
+        case 16: hipLaunchKernelGGL((tok_first_kernel<16>), more, dim3(64 * ADD_WAVES), 0, st, a, init); break;
+        default: return PRIMA_E_SHAPE;
+        }
+        return last_launch_status();
+    }
     switch (nt) {
     case 4: hipLaunchKernelGGL((tok_prepare_kernel<4>), dim3(grid), dim3(64 * ADD_WAVES), 0, st, a); break;
     case 8: hipLaunchKernelGGL((tok_prepare_kernel<8>), dim3(grid), dim3(64 * ADD_WAVES), 0, st, a); break;

@@ -253,7 +253,7 @@ prima_status run_layer(const prima_dims &d, const prima_layer &L, int kv_cap, in
         TokPrepare a{};
         a.mode = TOK_PLAIN; a.T = T; a.nb = static_cast<int>(cols / QK); a.x = xin; a.gain = gain; a.ss = at<float>(ws, w.tok_ss);
         a.rec[1] = at<uint8_t>(ws, w.tok_rec[1]);
-        prima_status ps = launch_tok_prepare(a, st);
+        prima_status ps = launch_tok_prepare(a, StepInit{}, st);
         if (ps != PRIMA_OK) return ps;
         ps = tok_streams(mats, fmts, n_tok, cols, T, ws, w, sum.p, st);
         if (ps != PRIMA_OK) return ps;
@@ -341,11 +341,12 @@ prima_status run_layer(const prima_dims &d, const prima_layer &L, int kv_cap, in
 // One decoder layer for several tokens (tok_stream.hip), x -> y.  Launches: the weight streams (one per format in a group), and
 // between them one that adds their shares, finishes the vector and lays it out for the next stream.  prepared: the layer
 // before this one has laid out x for the Q/K/V streams; next: the layer after it, whose Q/K/V activations the last launch
-// lays out (null: none).  Every matrix in a format that the streams take.
+// lays out (null: none); init: done by the first launch (tab null: done before; not with prepared).  Every matrix in a format that the streams take.
 prima_status run_layer_tok(const prima_dims &d, const prima_layer &L, int kv_cap, int n_past, int T,
                            const float *x, float *y, void *ws, const WindowWs &w, hipStream_t st,
                            float *tap_q, float *tap_o, float *tap_h, float *tap_a, int only, const AttnSeqs *seq,
-                           const prima_layer_formats *fm, bool prepared, const prima_layer *next, const prima_layer_formats *next_fm)
+                           const prima_layer_formats *fm, bool prepared, const prima_layer *next, const prima_layer_formats *next_fm,
+                           const StepInit &init = StepInit{})
 {
     static constexpr prima_layer_formats ALL_Q4_K = {0, 0, 0, 0, 0, 0, 0};
     const prima_layer_formats &f = fm ? *fm : ALL_Q4_K, &nf = next_fm ? *next_fm : ALL_Q4_K;
@@ -369,7 +370,7 @@ prima_status run_layer_tok(const prima_dims &d, const prima_layer &L, int kv_cap
         if (!prepared) {
             TokPrepare a = prepare(TOK_PLAIN, e, L.g_attn, {f.wq, f.wk, f.wv});
             a.x = x;
-            PRIMA_TRY(launch_tok_prepare(a, st));
+            PRIMA_TRY(launch_tok_prepare(a, init, st));
         }
         const TokMat m[3] = {{W(L.wq), qd}, {W(L.wk), kvd}, {W(L.wv), kvd}};
         const int fmts[3] = {f.wq, f.wk, f.wv};
@@ -387,14 +388,14 @@ prima_status run_layer_tok(const prima_dims &d, const prima_layer &L, int kv_cap
         a.att = rec;
         a.D = d.head_dim;
         a.out = tap_o && rec.nsplit != 1 ? o : nullptr;
-        PRIMA_TRY(launch_tok_prepare(a, st));
+        PRIMA_TRY(launch_tok_prepare(a, StepInit{}, st));
         if (tap_o && hipMemcpyAsync(tap_o, o, T * qd * sizeof(float), hipMemcpyDeviceToDevice, st) != hipSuccess) return PRIMA_E_DEVICE;
         const TokMat m{W(L.wo), e};
         a = prepare(TOK_RESIDUAL, e, L.g_ffn, {f.wgate, f.wup});
         PRIMA_TRY(streams(&m, &f.wo, 1, qd, a.p));
         a.x = x;
         a.out = h;
-        PRIMA_TRY(launch_tok_prepare(a, st));
+        PRIMA_TRY(launch_tok_prepare(a, StepInit{}, st));
     }
     if (tap_h && hipMemcpyAsync(tap_h, h, T * e * sizeof(float), hipMemcpyDeviceToDevice, st) != hipSuccess) return PRIMA_E_DEVICE;
     if (PRIMA_WANT(PRIMA_K_GATE_UP)) {
@@ -404,7 +405,7 @@ prima_status run_layer_tok(const prima_dims &d, const prima_layer &L, int kv_cap
         PRIMA_TRY(streams(m, fmts, 2, e, a.p));
         a.norm = norm;
         a.out = tap_a ? at<float>(ws, w.a) : nullptr;
-        PRIMA_TRY(launch_tok_prepare(a, st));
+        PRIMA_TRY(launch_tok_prepare(a, StepInit{}, st));
     }
     if (tap_a && hipMemcpyAsync(tap_a, at<char>(ws, w.a), T * F * sizeof(float), hipMemcpyDeviceToDevice, st) != hipSuccess) return PRIMA_E_DEVICE;
     if (PRIMA_WANT(PRIMA_K_DOWN)) {
@@ -414,7 +415,7 @@ prima_status run_layer_tok(const prima_dims &d, const prima_layer &L, int kv_cap
             PRIMA_TRY(streams(&m, &f.wdown, 1, F, a.p));
             a.x = h;
             a.out = y;
-            PRIMA_TRY(launch_tok_prepare(a, st));
+            PRIMA_TRY(launch_tok_prepare(a, StepInit{}, st));
         } else {
             TokSum a{1, T, tok_slots(T), {}, {e, 0, 0}, {y, nullptr, nullptr}, TokNorm{nullptr, 0, 0.f}, h};
             PRIMA_TRY(streams(&m, &f.wdown, 1, F, a.p));
@@ -446,10 +447,17 @@ bool layer_is_tok(const prima_dims &d, const WindowWs &w, int T, int n_past, con
 // all layers of a step; caches(i, seq): a batch's caches of layer i
 template <class Caches>
 prima_status run_layers(const prima_dims &d, const prima_layer *layers, const prima_layer_formats *formats, int L, int kv_cap, int n_past, int T,
-                        const float *x_in, float *x_out, void *ws, const WindowWs &w, hipStream_t st, Caches caches)
+                        const float *x_in, float *x_out, void *ws, const WindowWs &w, hipStream_t st, Caches caches, const int *positions = nullptr)
 {
     const float *cur = x_in;
     bool prepared = false;
+    // before the first layer: RoPE table, the counters of the mat-vec zeroed; in the first layer's first launch where that is a small one
+    StepInit init = step_init_args(at<float>(ws, w.rope), T, d.head_dim, n_past, d.rope_theta, positions, at<char>(ws, w.gemv), w.arrivals_bytes);
+    if (!layer_is_tok(d, w, T, n_past, caches(0), formats)) {
+        const prima_status s = launch_step_init(init, st);
+        if (s != PRIMA_OK) return s;
+        init = StepInit{};
+    }
     for (int i = 0; i < L; ++i) {
         float *dst = (i == L - 1) ? x_out : at<float>(ws, (i & 1) ? w.xb1 : w.xb0);
         const prima_layer_formats *f = formats ? &formats[i] : nullptr, *nf = formats && i + 1 < L ? &formats[i + 1] : nullptr;
@@ -458,7 +466,8 @@ prima_status run_layers(const prima_dims &d, const prima_layer *layers, const pr
         if (layer_is_tok(d, w, T, n_past, seq, f)) {
             const bool chain = i + 1 < L && layer_is_tok(d, w, T, n_past, seq, nf);
             s = run_layer_tok(d, layers[i], kv_cap, n_past, T, cur, dst, ws, w, st, nullptr, nullptr, nullptr, nullptr, -1, seq, f, prepared,
-                              chain ? &layers[i + 1] : nullptr, nf);
+                              chain ? &layers[i + 1] : nullptr, nf, init);
+            init = StepInit{};
             prepared = chain;
         } else {
             s = run_layer(d, layers[i], kv_cap, n_past, T, cur, dst, ws, w, st, nullptr, nullptr, nullptr, nullptr, -1, seq, f);
@@ -468,12 +477,6 @@ prima_status run_layers(const prima_dims &d, const prima_layer *layers, const pr
         cur = dst;
     }
     return PRIMA_OK;
-}
-
-// before the first layer of a step: RoPE table, the counters of the mat-vec zeroed; one launch
-prima_status step_init(const prima_dims &d, void *ws, const WindowWs &w, int T, int n_past, const int *positions, hipStream_t st)
-{
-    return launch_step_init(at<float>(ws, w.rope), T, d.head_dim, n_past, d.rope_theta, positions, at<char>(ws, w.gemv), w.arrivals_bytes, st);
 }
 
 prima_status check_window_args(const prima_dims *d, int32_t kv_cap, int32_t n_past, int32_t T,
@@ -537,12 +540,12 @@ PrefillWs carve_prefill(const prima_dims &d, int kv_cap, int T)
 // One decoder layer for T prompt tokens: the projections as matrix products over all tokens, attention for pieces of PRIMA_MAX_TOK tokens (each sees
 // the rows cached before it and, causally, its own), all pieces in one launch; between them the launches of gemm_prepare.hip.  prepared: the layer
 // before this one has laid out x for this one's Q/K/V; next: the layer after it, whose Q/K/V activations the last launch may lay out (null: none), and
-// then sets next_prepared.
+// then sets next_prepared; table: the RoPE table to be filled in by the layer's first launch or one in front (tab null: done before).
 // fm: formats of the seven matrices (null: all Q4_K).  Each goes through the matrix product of its format; FP32 (whose
 // weights are not exact in the product's binary16 operands) through the format mat-vec, PRIMA_MAX_TOK tokens a launch
 prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv_cap, int n_past, int T, const float *x, float *y, void *ws,
                                const PrefillWs &w, hipStream_t st, const prima_layer_formats *fm, bool prepared, const prima_layer *next,
-                               const prima_layer_formats *next_fm, bool *next_prepared)
+                               const prima_layer_formats *next_fm, bool *next_prepared, const RopeTable &table)
 {
     static constexpr prima_layer_formats ALL_Q4_K = {0, 0, 0, 0, 0, 0, 0};
     const prima_layer_formats &f = fm ? *fm : ALL_Q4_K, &nf = next_fm ? *next_fm : ALL_Q4_K;
@@ -576,12 +579,13 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
         return PRIMA_OK;
     };
     // v (x, or the shares + x, or SwiGLU of the shares), stored to out and laid out as activations (lay), its gain applied
-    auto prepare = [&](int mode, int64_t cols, const float *xin, const GemmShares &p, float *out, const float *gain, bool lay) -> prima_status {
+    auto prepare = [&](int mode, int64_t cols, const float *xin, const GemmShares &p, float *out, const float *gain, bool lay,
+                       const RopeTable &tab = RopeTable{}) -> prima_status {
         if (!lay && !out) return PRIMA_OK;
         GemmPrepare a{};
         a.mode = mode; a.T = T; a.nb = static_cast<int>(cols / QK); a.x = xin; a.ldx = cols; a.p = p; a.norm = normed.norm;
         a.out = out; a.ldo = cols; a.gain = gain; a.ss = ss; a.A = lay ? acts : nullptr;
-        return launch_gemm_prepare(a, st);
+        return launch_gemm_prepare(a, tab, st);
     };
     const float *g_attn = static_cast<const float *>(L.g_attn), *g_ffn = static_cast<const float *>(L.g_ffn);
 
@@ -590,8 +594,10 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
         const GemmMat m[3] = {mat(L.wq, q, qd), mat(L.wk, k, kvd), mat(L.wv, v, kvd)};
         RopeAppend r{};
         if (takes(f.wq) || takes(f.wk) || takes(f.wv)) {
-            if (!prepared) PRIMA_TRY(prepare(GEMM_PLAIN, e, x, GemmShares{}, nullptr, g_attn, true));
+            if (!prepared) PRIMA_TRY(prepare(GEMM_PLAIN, e, x, GemmShares{}, nullptr, g_attn, true, table));
             r.norm = normed.norm;
+        } else if (table.tab) {
+            PRIMA_TRY(launch_rope_table(table, st));
         }
         size_t used = 0;
         auto used_by = [&](const GemmShares &p) { used += round_up(static_cast<size_t>(p.n) * static_cast<size_t>(p.stride) * sizeof(float), 256); };
@@ -835,7 +841,7 @@ prima_status prima_q4k_gemm(const void *W, int64_t n_rows, int64_t n_cols, const
     a.ss = static_cast<float *>(workspace);
     a.A = static_cast<uint8_t *>(workspace) + gemm_ss_bytes(T, n_cols);
     if (n_cols / QK >= (int64_t{1} << 31)) return PRIMA_E_SHAPE;
-    const prima_status s = launch_gemm_prepare(a, st);
+    const prima_status s = launch_gemm_prepare(a, RopeTable{}, st);
     if (s != PRIMA_OK) return s;
     GemmActs acts{a.A, GemmNorm{}};
     if (gain) acts.norm = GemmNorm{a.ss, a.nb, (T + 15) / 16 * 16, eps};
@@ -970,8 +976,6 @@ prima_status prima_layer_window_decode(const prima_dims *d, const prima_layer *l
         if ((s = check_layer(layers[i])) != PRIMA_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const WindowWs w = carve(*d, kv_cap, T);
-    s = step_init(*d, workspace, w, T, n_past, nullptr, st);
-    if (s != PRIMA_OK) return s;
     return run_layers(*d, layers, nullptr, L, kv_cap, n_past, T, x_in, x_out, workspace, w, st, [](int) { return static_cast<const AttnSeqs *>(nullptr); });
 }
 
@@ -992,8 +996,6 @@ prima_status prima_layer_window_decode_mixed(const prima_dims *d, const prima_la
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const WindowWs w = carve(*d, kv_cap, T);
-    s = step_init(*d, workspace, w, T, n_past, nullptr, st);
-    if (s != PRIMA_OK) return s;
     return run_layers(*d, layers, formats, L, kv_cap, n_past, T, x_in, x_out, workspace, w, st, [](int) { return static_cast<const AttnSeqs *>(nullptr); });
 }
 
@@ -1034,8 +1036,6 @@ prima_status prima_layer_window_decode_batch_mixed(const prima_dims *d, const pr
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const WindowWs w = carve(*d, kv_cap, B);
-    s = step_init(*d, workspace, w, B, 0, n_past, st);
-    if (s != PRIMA_OK) return s;
     __half *kc[PRIMA_MAX_TOK], *vc[PRIMA_MAX_TOK];
     const AttnSeqs seq{n_past, kc, vc};
     return run_layers(*d, layers, formats, L, kv_cap, 0, B, x_in, x_out, workspace, w, st, [&](int i) {
@@ -1044,7 +1044,7 @@ prima_status prima_layer_window_decode_batch_mixed(const prima_dims *d, const pr
             vc[b] = static_cast<__half *>(v_caches[static_cast<size_t>(i) * B + b]);
         }
         return &seq;
-    });
+    }, n_past);
 }
 
 void prima_set_prefill_small_tokens(int32_t n) { g_prefill_small_tokens = n < 0 ? 0 : n; }
@@ -1088,16 +1088,13 @@ prima_status prima_layer_window_prefill_mixed(const prima_dims *d, const prima_l
         void *dws = at<char>(workspace, w.dec_base);
         for (int t0 = 0; t0 < T; t0 += PRIMA_MAX_TOK) {
             const int Tc = std::min<int>(PRIMA_MAX_TOK, T - t0);
-            prima_status cs = step_init(*d, dws, w.dec, Tc, n_past + t0, nullptr, st);
-            if (cs != PRIMA_OK) return cs;
-            cs = run_layers(*d, layers, formats, L, kv_cap, n_past + t0, Tc, x_in + static_cast<int64_t>(t0) * d->e, x_out + static_cast<int64_t>(t0) * d->e,
+            const prima_status cs = run_layers(*d, layers, formats, L, kv_cap, n_past + t0, Tc, x_in + static_cast<int64_t>(t0) * d->e, x_out + static_cast<int64_t>(t0) * d->e,
                             dws, w.dec, st, [](int) { return static_cast<const AttnSeqs *>(nullptr); });
             if (cs != PRIMA_OK) return cs;
         }
         return PRIMA_OK;
     }
-    prima_status s = launch_rope_table(at<float>(workspace, w.rope), T, d->head_dim, n_past, d->rope_theta, st);
-    if (s != PRIMA_OK) return s;
+    prima_status s = PRIMA_OK;
     if (T < PRIMA_MAX_TOK) { // the attention launch then merges its key ranges inside: its records marked "not written"
         char *const attn = at<char>(workspace, w.attn);
         const size_t head_bytes = attn_counter_bytes(*d, T); // the records start behind it
@@ -1110,7 +1107,8 @@ prima_status prima_layer_window_prefill_mixed(const prima_dims *d, const prima_l
         float *dst = (i == L - 1) ? x_out : at<float>(workspace, (i & 1) ? w.xb1 : w.xb0);
         const bool more = i + 1 < L;
         s = run_layer_prefill(*d, layers[i], kv_cap, n_past, T, cur, dst, workspace, w, st, formats ? &formats[i] : nullptr, prepared,
-                              more ? &layers[i + 1] : nullptr, formats && more ? &formats[i + 1] : nullptr, &prepared);
+                              more ? &layers[i + 1] : nullptr, formats && more ? &formats[i + 1] : nullptr, &prepared,
+                              i == 0 ? rope_table(at<float>(workspace, w.rope), T, d->head_dim, n_past, d->rope_theta) : RopeTable{});
         if (s != PRIMA_OK) return s;
         cur = dst;
     }
@@ -1142,10 +1140,7 @@ prima_status prima_layer_window_decode_profiled(const prima_dims *d, const prima
     const WindowWs w = carve(*d, kv_cap, T);
     // one ordinary step first: every intermediate buffer then holds this step's values
     auto ordinary_step = [&]() {
-        prima_status os = step_init(*d, workspace, w, T, n_past, nullptr, st);
-        if (os == PRIMA_OK)
-            os = run_layers(*d, layers, nullptr, L, kv_cap, n_past, T, x_in, x_out, workspace, w, st, [](int) { return static_cast<const AttnSeqs *>(nullptr); });
-        return os;
+        return run_layers(*d, layers, nullptr, L, kv_cap, n_past, T, x_in, x_out, workspace, w, st, [](int) { return static_cast<const AttnSeqs *>(nullptr); });
     };
     s = ordinary_step();
     // then each kind of launch on its own, once per layer (L different weight sets, so nothing is
@@ -1197,7 +1192,7 @@ prima_status prima_layer_decode_taps(const prima_dims *d, const prima_layer *lay
     if ((s = check_layer(*layer)) != PRIMA_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const WindowWs w = carve(*d, kv_cap, T);
-    s = step_init(*d, workspace, w, T, n_past, nullptr, st);
+    s = launch_step_init(step_init_args(at<float>(workspace, w.rope), T, d->head_dim, n_past, d->rope_theta, nullptr, at<char>(workspace, w.gemv), w.arrivals_bytes), st);
     if (s != PRIMA_OK) return s;
     if (layer_is_tok(*d, w, T, n_past, nullptr, nullptr))
         return run_layer_tok(*d, *layer, kv_cap, n_past, T, x_in, x_out, workspace, w, st, tap_q, tap_o, tap_h, tap_a, -1, nullptr, nullptr, false, nullptr, nullptr);
