@@ -426,20 +426,22 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
     for (int rt = 0; rt < FM_RT; ++rt) {
         const int64_t row = static_cast<int64_t>(rb) * FM_ROWS + wr * 64 + rt * 16 + n;
         if (row >= a.n_rows) continue;
+        float add[WT][4] = {}; // the residual, requested at once (as in q4k_gemm.hip)
+        if (a.resid && a.ksplit == 1) {
+#pragma unroll
+            for (int tt = 0; tt < WT; ++tt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) add[tt][i] = a.resid[min((tile0 + 2 * tt + wt) * 16 + 4 * g + i, a.T - 1) * a.ldr + row];
+        }
 #pragma unroll
         for (int tt = 0; tt < WT; ++tt)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int t = (tile0 + 2 * tt + wt) * 16 + 4 * g + i;
                 if ((FULL || tt < my_tiles) && t < a.T) {
-                    float v = ysum[tt][rt][i];
-                    if (a.ksplit > 1) {
-                        a.part[(static_cast<int64_t>(share) * a.T + t) * a.ldp + row] = v;
-                    } else {
-                        if (inv) v *= inv[16 * (2 * tt + wt) + 4 * g + i];
-                        if (a.resid) v += a.resid[t * a.ldr + row];
-                        a.y[t * a.ldy + row] = v;
-                    }
+                    const float v = ysum[tt][rt][i];
+                    if (a.ksplit > 1) a.part[(static_cast<int64_t>(share) * a.T + t) * a.ldp + row] = v;
+                    else a.y[t * a.ldy + row] = v * (inv ? inv[16 * (2 * tt + wt) + 4 * g + i] : 1.f) + add[tt][i];
                 }
             }
     }

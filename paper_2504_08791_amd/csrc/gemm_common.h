@@ -69,9 +69,16 @@ template <int NT>
 __device__ __forceinline__ void gemm_inv_rms_tokens(const GemmNorm &n, int t0, float *red, float *inv)
 {
     constexpr int P = 256 / NT;
+    constexpr int AT = 8; // requested at a time
     const int k = threadIdx.x % NT, t = min(t0 + k, n.ld - 1);
     float s = 0.f;
-    for (int b = threadIdx.x / NT; b < n.nb; b += P) s += n.ss[static_cast<int64_t>(b) * n.ld + t];
+    for (int b = threadIdx.x / NT; b < n.nb; b += AT * P) {
+        float v[AT];
+#pragma unroll
+        for (int j = 0; j < AT; ++j) v[j] = n.ss[static_cast<int64_t>(min(b + j * P, n.nb - 1)) * n.ld + t];
+#pragma unroll
+        for (int j = 0; j < AT; ++j) s += b + j * P < n.nb ? v[j] : 0.f;
+    }
     red[threadIdx.x] = s;
     __syncthreads();
     if (threadIdx.x < NT) {

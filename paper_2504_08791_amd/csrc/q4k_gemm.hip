@@ -485,6 +485,25 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
         }
         return;
     }
+    // The residual is requested at once: number by number, each between the stores of the ones before, a trip through memory each (4096 x 4096,
+    // 1024 tokens, K undivided, 110 us, now 99).
+    float add[GM_RT][TT][4];
+    if (a.resid) {
+#pragma unroll
+        for (int rt = 0; rt < GM_RT; ++rt)
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    add[rt][tt][i] = a.resid[min((tile0 + tt) * 16 + 4 * g + i, a.T - 1) * a.ldr + min<int64_t>(row0 + 16 * rt + n, my.n_rows - 1)];
+    } else {
+#pragma unroll
+        for (int rt = 0; rt < GM_RT; ++rt)
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) add[rt][tt][i] = 0.f;
+    }
 #pragma unroll
     for (int rt = 0; rt < GM_RT; ++rt) {
         const int64_t out_row = row0 + 16 * rt + n;
@@ -494,11 +513,7 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int t = (tile0 + tt) * 16 + 4 * g + i;
-                if (t < a.T) {
-                    float v = yacc[tt][rt][i] * of(tt, i);
-                    if (a.resid) v += a.resid[t * a.ldr + out_row];
-                    my.y[t * my.ldy + out_row] = v;
-                }
+                if (t < a.T) my.y[t * my.ldy + out_row] = yacc[tt][rt][i] * of(tt, i) + add[rt][tt][i];
             }
     }
 }
@@ -528,28 +543,42 @@ int ksplit_for(int64_t n_rb, int64_t n_tb, int64_t nb)
     const int64_t s = std::min<int64_t>({slots / wgs, nb / GM_MIN_SHARE, GM_MAX_KSPLIT});
     return s < 2 ? 1 : static_cast<int>(s);
 }
-// Shares that the caller's next launch adds on its way: they cost no launch, so that it takes them for less.  By rounds of workgroups times a
-// share's super-blocks (us each, a token tile a workgroup: 1.7 alone on a compute unit, 2.5 with another), and the shares' way to memory and back.
-// Two layers, us, shares by ksplit_for() (four super-blocks at the least, none from half a device of workgroups on) / here: 8B 17 tokens 248 / 217, 64 332 / 303,
-// 128 424 / 406, 333 865 / 860, 700 1606 / 1508; 14B 48 340 / 308, 333 1032 / 1025; 70B 17 475 / 461, 96 910 / 909, 333 2749 / 2611, 700 5273 / 4996.
-int shares_for(int64_t n_rb, int n_tiles, int64_t nb, int T)
+// Token blocks and shares of K, `least` to `most` of these, by the time of the rounds of workgroups.  A super-block of t token tiles takes a workgroup that
+// has its compute unit to itself 2.0 + 0.75 t us, two that share one 2.7 + 1.35 t (tiles of unequal blocks count mostly by their mean: the
+// blocks of one compute unit even out); an undivided product has 4 us at its end that shares leave to the launch behind, shares go to memory and back.
+// So the tokens are cut into more blocks than they need where the last round is better filled by it: 21 tiles (333 tokens) into seven blocks of three instead of
+// six, the output projection of 8B 50.7 -> 45 us with its shares.  A block more costs what the unpacking of the weights once more costs: 5 % of
+// its part, in long launches, which run at the card's power limit, 30 % (70B, 400 tokens, gate and up in eight blocks or nine 40 us slower than in seven, two shares).
+// Fitted to single launches (16 prompts of 17 to 1500 tokens, 8B to 70B, up to 4 more blocks and 14 shares) and to whole calls back to back.
+// Whole calls, one layer, us, the fewest blocks and the shares by rounds times tiles / this: 8B 180 tokens 264 / 258, 800 831 / 816, 14B 333 520 / 498, 1500 1962 / 1926, 70B 1024
+// 3601 / 3561; 28 others (8B to 70B, 17 to 1500 tokens) between 0.98 and 1.004 of what they were.
+struct GemmPlan {
+    int n_tb, shares;
+};
+GemmPlan plan_gemm(int64_t n_rb, int n_tiles, int64_t nb, int T, int64_t least, int64_t most)
 {
-    const int n_tb = (n_tiles + GM_TT - 1) / GM_TT;
-    const int64_t wgs = n_rb * n_tb, slots = 2 * GM_CUS;
-    const double tiles = (n_tiles + n_tb - 1) / n_tb;
-    double best = 0.;
-    int best_ks = 1;
-    for (int64_t ks = 1; ks <= std::min<int64_t>(GM_MAX_KSPLIT, nb); ++ks) {
-        const int64_t units = wgs * ks, full = units / slots, rest = units - full * slots;
-        const double rounds = full * 2.5 + (rest == 0 ? 0. : (rest <= GM_CUS ? 1.7 : 2.5));
-        const double us = rounds * tiles * static_cast<double>((nb + ks - 1) / ks) +
-                          (ks > 1 ? 1. + static_cast<double>(ks) * T * static_cast<double>(n_rb) * GM_ROWS * 8. / 4e6 : 0.);
-        if (ks == 1 || us < best) {
-            best = us;
-            best_ks = static_cast<int>(ks);
+    constexpr int64_t slots = 2 * GM_CUS;
+    constexpr int MORE = 4; // blocks beyond the fewest
+    const int fewest = (n_tiles + GM_TT - 1) / GM_TT;
+    most = std::max(least, std::min<int64_t>({most, GM_MAX_KSPLIT, nb}));
+    GemmPlan best{fewest, static_cast<int>(least)};
+    double best_us = 0.;
+    for (int n_tb = fewest; n_tb <= std::min(n_tiles, fewest + MORE); ++n_tb) {
+        const double t = 0.2 * ((n_tiles + n_tb - 1) / n_tb) + 0.8 * n_tiles / n_tb, alone = 2. + 0.75 * t, both = 2.7 + 1.35 * t;
+        for (int64_t ks = least; ks <= most; ++ks) {
+            const int64_t units = n_rb * n_tb * ks, rest = units % slots;
+            if (n_tb > fewest && units >= (int64_t{1} << 31) - GM_XCDS) break;
+            const double rounds = static_cast<double>(units / slots) * both + (rest == 0 ? 0. : (rest <= GM_CUS ? alone : both));
+            double us = rounds * static_cast<double>((nb + ks - 1) / ks) +
+                        (ks == 1 ? 4. : 1. + static_cast<double>(ks) * T * static_cast<double>(n_rb) * GM_ROWS * 1.2e-6);
+            us *= 1. + (us > 300. ? 0.3 : 0.05) * (n_tb - fewest) / fewest;
+            if (best_us == 0. || us < best_us) {
+                best_us = us;
+                best = GemmPlan{n_tb, static_cast<int>(ks)};
+            }
         }
     }
-    return best_ks;
+    return best;
 }
 // row blocks of one matrix; of a (gate, up) pair of n_rows each: 128 rows of both per block
 int64_t row_blocks(int64_t n_rows, bool pair = false) { return pair ? (n_rows + GM_ROWS / 2 - 1) / (GM_ROWS / 2) : (n_rows + GM_ROWS - 1) / GM_ROWS; }
@@ -577,7 +606,7 @@ size_t gemm_later_bytes(int T, const int64_t *n_rows, int n_mats, int64_t n_cols
 {
     int64_t n_rb = 0;
     for (int i = 0; i < (pair ? 1 : n_mats); ++i) n_rb += row_blocks(n_rows[i], pair);
-    const int s = shares_for(n_rb, (T + 15) / 16, n_cols / QK, T);
+    const int s = plan_gemm(n_rb, (T + 15) / 16, n_cols / QK, T, 1, GM_MAX_KSPLIT).shares;
     return s == 1 ? 0 : static_cast<size_t>(s) * static_cast<size_t>(T) * static_cast<size_t>(n_rb) * GM_ROWS * sizeof(float);
 }
 
@@ -605,9 +634,8 @@ prima_status launch_q4k_gemm(const GemmMat *mats, int n_mats, bool pair, int64_t
     if (n_rb == 0) return PRIMA_OK;
     const int64_t nb = n_cols / QK;
     const int n_tiles = (T + 15) / 16;
-    const int n_tb = (n_tiles + GM_TT - 1) / GM_TT;
     if (nb >= (int64_t{1} << 32) / 144) return PRIMA_E_SHAPE; // (a row of 4 GiB: its activations laid out would be 500)
-    if (n_rb * n_tb >= (int64_t{1} << 31) - GM_XCDS || n_tiles > 65535 || nb >= (int64_t{1} << 31)) return PRIMA_E_SHAPE;
+    if (n_rb * token_blocks(T) >= (int64_t{1} << 31) - GM_XCDS || n_tiles > 65535 || nb >= (int64_t{1} << 31)) return PRIMA_E_SHAPE;
     static std::atomic<bool> attr_set{false}; // set twice by two threads at worst: the attribute call is idempotent
     if (!attr_set) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(q4k_gemm_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, GM_LDS_BYTES) != hipSuccess)
@@ -616,24 +644,30 @@ prima_status launch_q4k_gemm(const GemmMat *mats, int n_mats, bool pair, int64_t
     }
     a.pair = pair ? 1 : 0;
     a.n_cols = n_cols; a.A = x.A; a.norm = x.norm; a.resid = resid; a.ldr = ldr;
-    a.T = T; a.n_tiles = n_tiles; a.n_rb = static_cast<int>(n_rb); a.n_tb = n_tb; a.band = gemm_band(n_tb);
-    // K is divided when that fills the device and the caller's scratch holds the shares
-    a.ksplit = part && T <= 65535 && (later || (n_mats == 1 && !pair)) ? (later ? shares_for(n_rb, n_tiles, nb, T) : ksplit_for(n_rb, n_tb, nb)) : 1; // (shares: T a grid dimension of the launch that adds them)
+    a.T = T; a.n_tiles = n_tiles; a.n_rb = static_cast<int>(n_rb);
     a.ldp = n_rb * GM_ROWS;
-    const size_t share_bytes = static_cast<size_t>(T) * static_cast<size_t>(a.ldp) * sizeof(float);
-    if (later && a.ksplit > 1) a.ksplit = static_cast<int>(std::max<size_t>(1, std::min<size_t>(a.ksplit, part_bytes / share_bytes)));
-    if (a.ksplit > 1 && part_bytes < a.ksplit * share_bytes) a.ksplit = 1;
+    // K is divided when that fills the device and the caller's scratch holds the shares (T: a grid dimension of the launch that adds them)
+    const int64_t share_bytes = static_cast<int64_t>(T) * a.ldp * static_cast<int64_t>(sizeof(float));
+    const int64_t held = part && T <= 65535 ? static_cast<int64_t>(part_bytes / static_cast<size_t>(share_bytes)) : 0;
+    GemmPlan p{};
+    if (later) {
+        p = plan_gemm(n_rb, n_tiles, nb, T, 1, std::max<int64_t>(1, held));
+    } else {
+        const int ks = n_mats == 1 && !pair ? ksplit_for(n_rb, token_blocks(T), nb) : 1, divided = held >= ks ? ks : 1;
+        p = plan_gemm(n_rb, n_tiles, nb, T, divided, divided);
+    }
+    a.n_tb = p.n_tb; a.ksplit = p.shares; a.band = gemm_band(a.n_tb);
     a.share_q = static_cast<int>(nb / a.ksplit); a.share_r = static_cast<int>(nb % a.ksplit);
-    a.tile_q = n_tiles / n_tb; a.tile_r = n_tiles % n_tb;
+    a.tile_q = n_tiles / a.n_tb; a.tile_r = n_tiles % a.n_tb;
     a.part = a.ksplit > 1 ? static_cast<float *>(part) : nullptr;
-    hipLaunchKernelGGL(q4k_gemm_kernel, dim3(gemm_grid(n_rb * n_tb * a.ksplit)), dim3(GM_THREADS), GM_LDS_BYTES, st, a);
+    hipLaunchKernelGGL(q4k_gemm_kernel, dim3(gemm_grid(n_rb * a.n_tb * a.ksplit)), dim3(GM_THREADS), GM_LDS_BYTES, st, a);
     const prima_status ps = last_launch_status();
     if (ps != PRIMA_OK || a.ksplit == 1) return ps;
-    GemmShares p{a.part, a.ksplit, static_cast<int64_t>(T) * a.ldp, a.ldp, {0, 0, 0}};
+    GemmShares sh{a.part, a.ksplit, static_cast<int64_t>(T) * a.ldp, a.ldp, {0, 0, 0}};
     for (int i = 0; i < 3; ++i)
-        if (a.seg[i].rb0 != 0x7fffffff) p.col[i] = static_cast<int64_t>(a.seg[i].rb0) * GM_ROWS;
-    if (!later) return launch_gemm_sum(p, x.norm, resid, ldr, mats[0].y, mats[0].ldy, mats[0].n_rows, T, st);
-    *later = p;
+        if (a.seg[i].rb0 != 0x7fffffff) sh.col[i] = static_cast<int64_t>(a.seg[i].rb0) * GM_ROWS;
+    if (!later) return launch_gemm_sum(sh, x.norm, resid, ldr, mats[0].y, mats[0].ldy, mats[0].n_rows, T, st);
+    *later = sh;
     return PRIMA_OK;
 }
 
