@@ -515,7 +515,7 @@ def bench_prefill(args, cfg):
         "window_tflops": round(flops_step / (ms * 1e-3) / 1e12, 1),
         "roofline": {
             "bound": "mfma",
-            "kernel": "prima_q4k_gemm as called for the gate projection (token scales, activation split and q4k_gemm_kernel; RMSNorm in front)",
+            "kernel": "prima_q4k_gemm as called for the gate projection (gemm_prepare_kernel, which lays out the activations, and q4k_gemm_kernel; RMSNorm in front)",
             "achieved": round(achieved, 1), "peak": 2500.0, "unit": "TFLOP/s", "frac": round(achieved / 2500.0, 4),
             "flops_per_launch": gate_flops, "avg_launch_us": round(gate_us, 1),
             "mfma_passes": 2,   # every activation enters as hi + lo: the matrix cores do twice the algorithmic work

@@ -27,7 +27,7 @@
 // decodes 16 weights of one row for the next position into LDS, where both row halves of the workgroup's waves read them
 // as operands: a weight is decoded once per workgroup, not once per wave.  Activations come by 16-byte global->LDS loads.  Both
 // are double-buffered with one barrier per position; 33 to 65 KiB of LDS by format and tokens, so that two workgroups share a compute unit and one's
-// waits run under the other's matrix instructions.
+// waits run under the other's matrix instructions.  Registers held to 168 at 64 tokens, so that three share one: between 1 % faster and 2.5 % slower (a few spills).
 #include <algorithm>
 #include <atomic>
 

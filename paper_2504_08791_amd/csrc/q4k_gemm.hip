@@ -15,12 +15,12 @@
 //     then  y += d * acc - dmin * acc_m  in fp32.
 // gemm_prepare.hip splits the activations and lays them out in A-operand order per (16-token tile, super-block): 17 slabs of 1 KiB
 // (8 sub-blocks x (hi, lo), and the sums), so that the product kernel moves them into LDS with 16-byte global->LDS loads and no
-// arithmetic; the split is done once, not once per row block.  The product: a workgroup of 4 waves owns 256 rows x 64 tokens,
+// arithmetic; the split is done once, not once per row block.  The product: a workgroup of 4 waves owns 256 rows x up to 64 tokens,
 // a wave 64 rows (four B tiles in registers: every A tile read from LDS feeds four MFMAs per part); two workgroups
 // share a compute unit, so that one's VALU and LDS phases run under the other's MFMAs.  The super-block is walked
 // sub-block by sub-block; global->LDS loads fill a ring of activation slots two positions ahead and, per wave,
-// two buffers with half a super-block of its rows' quants each (the comment at the kernel has the details).  Workgroups are numbered so
-// that those running on one XCD (one L2) at a time are patches of 4 row blocks x 8 token blocks.  Up to three
+// two buffers with half a super-block of its rows' quants each (the comment at the kernel has the details).  Every XCD takes an equal run of
+// (row block, token block, share of K) units in which neighbours share operands in its L2 (gemm_unit).  Up to three
 // matrices with the same columns share a launch (Q / K / V), and so do a gate and an up matrix, with SwiGLU behind.
 // The weights stay exact: dequantised to binary16 (one accumulator for all of K) they would be off by ~1e-3 per
 // product, measured in the metric of the tests.

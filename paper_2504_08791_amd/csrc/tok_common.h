@@ -79,7 +79,7 @@ __device__ __forceinline__ void tk_split(const float (&v)[16], int i, int t, uin
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
         float sv = v[k] * S;
-        asm volatile("" : "+v"(sv)); // one rounded number for hi and lo (see gemm_split_kernel)
+        asm volatile("" : "+v"(sv)); // one rounded number for hi and lo (else the compiler folds the product into what uses it)
         hh[k] = static_cast<_Float16>(sv);
         float r = sv - static_cast<float>(hh[k]);
         if constexpr (INF) r = fmaxf(r, -1024.f); // (in a NaN's place: inf - inf; any other is smaller)
