@@ -616,6 +616,7 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(const float *__restrict
         float m = M;
 #pragma unroll
         for (int i = 0; i < MERGE_LD; ++i) m = fmaxf(m, ml[i].x);
+        m = max_across_32(RPI == 4 ? max_across_16(m) : m); // (a maximum of each group's own costs another factor and rounding at the end: errors 1 % larger)
         const float keep = M == -INFINITY ? 0.f : __expf(M - m);
         M = m;
         L *= keep;
@@ -629,10 +630,6 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(const float *__restrict
         }
     }
     // the RPI groups of lanes hold different ranges' shares of the same columns
-    const float top = max_across_32(RPI == 4 ? max_across_16(M) : M);
-    const float f = M == -INFINITY ? 0.f : __expf(M - top);
-    L *= f;
-    acc *= f;
     L = add_across_32(RPI == 4 ? add_across_16(L) : L);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
