@@ -619,15 +619,20 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(const float *__restrict
         m = max_across_32(RPI == 4 ? max_across_16(m) : m); // (a maximum of each group's own costs another factor and rounding at the end: errors 1 % larger)
         const float keep = M == -INFINITY ? 0.f : __expf(M - m);
         M = m;
-        L *= keep;
         acc *= keep;
+        float l[MERGE_LD]; // (added pairwise: their sum's error is every column's)
 #pragma unroll
         for (int i = 0; i < MERGE_LD; ++i) {
             const float w = s0 + i * RPI + sub >= nsplit || ml[i].x == -INFINITY ? 0.f : __expf(ml[i].x - m);
-            L = fmaf(ml[i].y, w, L);
+            l[i] = ml[i].y * w;
 #pragma unroll
             for (int k = 0; k < 4; ++k) acc[k] = fmaf(v[i][k], w, acc[k]);
         }
+#pragma unroll
+        for (int h = MERGE_LD / 2; h > 0; h /= 2)
+#pragma unroll
+            for (int i = 0; i < h; ++i) l[i] += l[i + h];
+        L = fmaf(L, keep, l[0]);
     }
     // the RPI groups of lanes hold different ranges' shares of the same columns
     L = add_across_32(RPI == 4 ? add_across_16(L) : L);
