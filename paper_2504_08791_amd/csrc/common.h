@@ -174,8 +174,9 @@ prima_status launch_gemm_sum(const GemmShares &p, const GemmNorm &norm, const fl
 // that much.
 int gemm_ksplit(int T, const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair = false);
 size_t gemm_part_bytes(int T, const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair = false);
-// the same where the shares are left to the caller's next launch
-size_t gemm_later_bytes(int T, const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair = false);
+// Where the shares are left to the caller's next launch: room for the most numbers a token that they take, whatever T (prompts of a few tokens of
+// very tall matrices excepted)
+int64_t gemm_most_shares(const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair = false);
 // up to three matrices with the same columns against the same activations (Q / K / V), or, with pair set, two of equal
 // shape (gate, up) with silu(gate) * up stored to mats[0].y; the residual only with one matrix.  later: the shares of K, if there are any, are left to
 // the caller's next launch (resid and y then unused); null: one matrix, they are added here.
@@ -189,7 +190,7 @@ prima_status launch_q4k_gemm(const GemmMat *mats, int n_mats, bool pair, int64_t
 // the same for one matrix in another format (fmt_gemm.hip), where fmt_gemm_takes(fmt) (all of them but FP32, whose weights
 // are not exact in binary16)
 bool fmt_gemm_takes(int fmt);
-size_t fmt_gemm_part_bytes(int T, int64_t n_rows, int64_t n_cols); // what its shares take where the scratch does not limit them
+int64_t fmt_gemm_most_shares(int64_t n_rows, int64_t n_cols); // as gemm_most_shares()
 prima_status launch_fmt_gemm(int fmt, const GemmMat &m, int64_t n_cols, const GemmActs &x, int T, const float *resid, int64_t ldr, void *part,
                              size_t part_bytes, GemmShares *later, hipStream_t st);
 // RoPE on q and k, k and v appended to the caches as rows n_past .. n_past + T - 1; p: shares of q, k, v (n 0: complete, at part); q: where the rotated

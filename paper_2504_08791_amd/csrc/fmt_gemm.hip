@@ -519,10 +519,10 @@ prima_status launch_fm(FmtGemmArgs a, const FmPlan &p, hipStream_t st)
 
 bool fmt_gemm_takes(int fmt) { return fmt == PRIMA_FMT_Q5_K || fmt == PRIMA_FMT_Q6_K || fmt == PRIMA_FMT_Q8_0 || fmt == PRIMA_FMT_F16; }
 
-size_t fmt_gemm_part_bytes(int T, int64_t n_rows, int64_t n_cols)
+int64_t fmt_gemm_most_shares(int64_t n_rows, int64_t n_cols)
 {
-    const int ks = plan_fm(T, n_rows, n_cols, int64_t{1} << 62).ksplit;
-    return ks == 1 ? 0 : static_cast<size_t>(ks) * static_cast<size_t>(T) * static_cast<size_t>(n_rows) * sizeof(float);
+    const int64_t n_rb = (n_rows + FM_ROWS - 1) / FM_ROWS;
+    return std::max<int64_t>(1, std::min<int64_t>({16, n_cols / QK, 2 * GM_CUS / n_rb})) * n_rows;
 }
 
 prima_status launch_fmt_gemm(int fmt, const GemmMat &m, int64_t n_cols, const GemmActs &x, int T, const float *resid, int64_t ldr, void *part,

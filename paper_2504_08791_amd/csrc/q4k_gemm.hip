@@ -602,12 +602,13 @@ size_t gemm_part_bytes(int T, const int64_t *n_rows, int n_mats, int64_t n_cols,
     return static_cast<size_t>(s) * static_cast<size_t>(T) * static_cast<size_t>(n_rb) * GM_ROWS * sizeof(float);
 }
 
-size_t gemm_later_bytes(int T, const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair)
+// plan_gemm() takes no more shares than the first of them that fills the device with one token block, or four (its plans for 10 shapes of 1B to 70B widths, 20 to
+// 8192 tokens)
+int64_t gemm_most_shares(const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair)
 {
     int64_t n_rb = 0;
     for (int i = 0; i < (pair ? 1 : n_mats); ++i) n_rb += row_blocks(n_rows[i], pair);
-    const int s = plan_gemm(n_rb, (T + 15) / 16, n_cols / QK, T, 1, GM_MAX_KSPLIT).shares;
-    return s == 1 ? 0 : static_cast<size_t>(s) * static_cast<size_t>(T) * static_cast<size_t>(n_rb) * GM_ROWS * sizeof(float);
+    return std::min<int64_t>({GM_MAX_KSPLIT, n_cols / QK, std::max<int64_t>(4, (2 * GM_CUS + n_rb - 1) / n_rb)}) * n_rb * GM_ROWS;
 }
 
 size_t gemm_acts_bytes(int T, int64_t n_cols) { return (static_cast<size_t>(T) + 15) / 16 * static_cast<size_t>(n_cols / QK) * GM_TILE_BYTES; }

@@ -490,50 +490,69 @@ prima_status check_window_args(const prima_dims *d, int32_t kv_cap, int32_t n_pa
     return PRIMA_OK;
 }
 
+struct Span {
+    size_t at, bytes;
+};
 struct PrefillWs {
-    size_t q, k, v, o, h, a, u, xb0, xb1, rope, attn, ss, acts, part, part_bytes, total;
-    size_t dec_base; // short prompts: the scratch of a decode call of PRIMA_MAX_TOK tokens, carved from here
-    WindowWs dec;
+    size_t q, k, v, o, h, a, u, xb0, xb1, rope, attn, ss, acts, total;
+    // where the shares of K of a product lie: Q/K/V; output projection and down; gate and up sharing a launch (`pair_act`: the launch behind it
+    // stores the activations); gate and up one by one
+    Span s_qkv, s_out, s_pair, s_pair_act, s_gate, s_up;
+    WindowWs dec; // short prompts: the scratch of a decode call of PRIMA_MAX_TOK tokens, in place of all this
 };
 
-// scratch of a prompt-processing call: the layer's intermediate activations for all T tokens, the RoPE table, the
-// matrix product's scratch (sized for the widest matrix), and the attention scratch of one 16-token call
+// Scratch of a prompt-processing call: the layer's intermediate activations for all T tokens, the RoPE table, the
+// matrix product's scratch (sized for the widest matrix), and the attention scratch of one 16-token call.  Every part grows with T, so that
+// scratch for more tokens holds what fewer need.
+// The shares of K lie in what the layer does not use at that time, around a region of their own:
+//   a, u, the region, o, q, k, v, xb0, xb1
+// Q/K/V leave them in a .. o (RoPE writes q, k and v while others still read shares), output projection and down in a .. v (the layer's input or
+// output may be in xb0 or xb1), gate and up in all but what they write (the layer's input has been added by then).  The region holds what the most
+// shares need beyond that (for prompts of a few tokens up to LEAST, their plans follow no such rule), and no more than MOST: from some T on what lies around is
+// nearly enough.  A region that held the shares of just this T alone rose and fell with T.
+// MB with 8192 cache rows, that / this (a decode call's scratch in the same place instead of behind): 8B 17 tokens 68 / 54, 276 255 / 226, 333 187 / 240, 1024 394 / 424;
+// 70B 151 / 79, 381 / 315, 436 / 344, 729 / 705.
 PrefillWs carve_prefill(const prima_dims &d, int kv_cap, int T)
 {
+    constexpr size_t LEAST = size_t{32} << 20, MOST = size_t{128} << 20;
     PrefillWs w{};
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += round_up(bytes, 256); return o; };
     const size_t qd = static_cast<size_t>(d.n_q_heads) * d.head_dim, kvd = static_cast<size_t>(d.n_kv_heads) * d.head_dim;
     const size_t f = sizeof(float), t = static_cast<size_t>(T);
+    w.a = take(t * static_cast<size_t>(d.ffn) * f);
+    w.u = take(t * static_cast<size_t>(d.ffn) * f); // up projection, when gate / up are not both Q4_K
+    size_t part;
+    {
+        const int64_t e = d.e, F = d.ffn, Q = static_cast<int64_t>(qd), KV = static_cast<int64_t>(kvd), rows[3] = {Q, KV, KV};
+        auto most = [](int64_t n_rows, int64_t n_cols) { return std::max(gemm_most_shares(&n_rows, 1, n_cols), fmt_gemm_most_shares(n_rows, n_cols)); };
+        const int64_t beyond = std::max<int64_t>({
+            gemm_most_shares(rows, 3, e) - (2 * F + Q),
+            most(Q, e) + 2 * most(KV, e) - (2 * F + Q), // one by one when the formats differ, all there until the launch behind them
+            most(e, Q) - 2 * (F + Q + KV), most(e, F) - 2 * (F + Q + KV),
+            gemm_most_shares(&F, 1, e, true) - (F + 2 * (Q + KV + e)), most(F, e) - 2 * (Q + KV + e), 0});
+        const size_t widest = static_cast<size_t>(std::max<int64_t>({Q + 2 * KV, e, 2 * F}));
+        part = take(std::min(MOST, std::max(t * static_cast<size_t>(beyond) * f, std::min(LEAST, 16 * t * widest * f))));
+    }
+    w.o = take(t * qd * f);
     w.q = take(t * qd * f);
     w.k = take(t * kvd * f);
     w.v = take(t * kvd * f);
-    w.o = take(t * qd * f);
-    w.h = take(t * static_cast<size_t>(d.e) * f);
-    w.a = take(t * static_cast<size_t>(d.ffn) * f);
-    w.u = take(t * static_cast<size_t>(d.ffn) * f); // up projection, when gate / up are not both Q4_K
     w.xb0 = take(t * static_cast<size_t>(d.e) * f);
     w.xb1 = take(t * static_cast<size_t>(d.e) * f);
+    w.h = take(t * static_cast<size_t>(d.e) * f);
+    auto span = [](size_t from, size_t to) { return Span{from, to - from}; };
+    w.s_qkv = span(w.a, w.q);
+    w.s_out = span(w.a, w.xb0);
+    w.s_pair = span(w.a, w.h);
+    w.s_pair_act = w.s_gate = span(w.u, w.h);
+    w.s_up = span(part, w.h);
     w.rope = take(t * static_cast<size_t>(d.head_dim) * f);
     w.attn = take(attn_ws_bytes(d, kv_cap, PRIMA_MAX_TOK));
     w.ss = take(gemm_ss_bytes(T, d.e));
     w.acts = take(gemm_acts_bytes(T, std::max<int64_t>({d.e, static_cast<int64_t>(qd), d.ffn})));
-    {
-        // the shares of K of the launches that divide it (few rows, few tokens): the largest of the layer's products
-        const int64_t r_qkv[3] = {static_cast<int64_t>(qd), static_cast<int64_t>(kvd), static_cast<int64_t>(kvd)}, r_e[1] = {d.e}, r_f[1] = {d.ffn};
-        size_t pb = std::max(gemm_part_bytes(T, r_f, 1, d.e), gemm_later_bytes(T, r_qkv, 3, d.e)), apart = 0;
-        for (int i = 0; i < 3; ++i) // one by one when the formats differ, all there until the launch behind them
-            apart += round_up(std::max(gemm_later_bytes(T, r_qkv + i, 1, d.e), fmt_gemm_part_bytes(T, r_qkv[i], d.e)), 256);
-        pb = std::max(pb, apart);
-        for (const int64_t cols : {static_cast<int64_t>(qd), static_cast<int64_t>(d.ffn)})
-            pb = std::max({pb, gemm_later_bytes(T, r_e, 1, cols), fmt_gemm_part_bytes(T, d.e, cols)});
-        pb = std::max(pb, gemm_later_bytes(T, r_f, 1, d.e, true));
-        w.part_bytes = pb;
-        w.part = take(pb);
-    }
     w.dec = carve(d, kv_cap, PRIMA_MAX_TOK);
-    w.dec_base = take(w.dec.total);
-    w.total = off;
+    w.total = std::max(off, w.dec.total);
     return w;
 }
 
@@ -553,7 +572,7 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
     float *q = at<float>(ws, w.q), *k = at<float>(ws, w.k), *v = at<float>(ws, w.v);
     float *o = at<float>(ws, w.o), *h = at<float>(ws, w.h), *act = at<float>(ws, w.a), *ss = at<float>(ws, w.ss);
     uint8_t *const acts = at<uint8_t>(ws, w.acts);
-    char *const part = at<char>(ws, w.part);
+    auto part = [&](const Span &p) { return at<char>(ws, p.at); };
     prima_status s;
 #define PRIMA_TRY(call) do { s = (call); if (s != PRIMA_OK) return s; } while (0)
     const GemmActs plain{acts, GemmNorm{}};
@@ -566,9 +585,9 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
         return fmt == PRIMA_FMT_Q4_K || (fmt_gemm_takes(fmt) && !(T <= 2 * PRIMA_MAX_TOK && rows * cols < (int64_t{1} << 20)));
     };
     // one matrix: out = W a (+ resid); its shares of K left to the next launch, or added
-    auto product = [&](int fmt, const GemmMat &m, int64_t cols, const GemmActs &a, const float *resid, char *to, size_t to_bytes, GemmShares *later) {
-        return fmt == PRIMA_FMT_Q4_K ? launch_q4k_gemm(&m, 1, false, cols, a, T, resid, m.n_rows, to, to_bytes, later, st)
-                                     : launch_fmt_gemm(fmt, m, cols, a, T, resid, m.n_rows, to, to_bytes, later, st);
+    auto product = [&](int fmt, const GemmMat &m, int64_t cols, const GemmActs &a, const float *resid, const Span &to, GemmShares *later) {
+        return fmt == PRIMA_FMT_Q4_K ? launch_q4k_gemm(&m, 1, false, cols, a, T, resid, m.n_rows, part(to), to.bytes, later, st)
+                                     : launch_fmt_gemm(fmt, m, cols, a, T, resid, m.n_rows, part(to), to.bytes, later, st);
     };
     auto mat_vecs = [&](int fmt, const GemmMat &m, int64_t cols, const float *xin, const float *gain, const float *resid) -> prima_status {
         for (int t0 = 0; t0 < T; t0 += PRIMA_MAX_TOK) {
@@ -599,15 +618,18 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
         } else if (table.tab) {
             PRIMA_TRY(launch_rope_table(table, st));
         }
-        size_t used = 0;
-        auto used_by = [&](const GemmShares &p) { used += round_up(static_cast<size_t>(p.n) * static_cast<size_t>(p.stride) * sizeof(float), 256); };
+        Span to = w.s_qkv;
+        auto used_by = [&](const GemmShares &p) {
+            const size_t n = std::min(to.bytes, round_up(static_cast<size_t>(p.n) * static_cast<size_t>(p.stride) * sizeof(float), 256));
+            to = Span{to.at + n, to.bytes - n};
+        };
         GemmMat q4[3];
         int at_q4[3], n_q4 = 0;
         for (int i = 0; i < 3; ++i)
             if (fmts[i] == PRIMA_FMT_Q4_K) { at_q4[n_q4] = i; q4[n_q4++] = m[i]; }
         if (n_q4) {
             GemmShares p;
-            PRIMA_TRY(launch_q4k_gemm(q4, n_q4, false, e, normed, T, nullptr, 0, part, w.part_bytes, &p, st));
+            PRIMA_TRY(launch_q4k_gemm(q4, n_q4, false, e, normed, T, nullptr, 0, part(to), to.bytes, &p, st));
             used_by(p);
             for (int i = 0; i < n_q4; ++i) {
                 r.p[at_q4[i]] = p;
@@ -620,7 +642,7 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
                 PRIMA_TRY(mat_vecs(fmts[i], m[i], e, x, g_attn, nullptr));
                 continue;
             }
-            PRIMA_TRY(product(fmts[i], m[i], e, normed, nullptr, part + used, w.part_bytes > used ? w.part_bytes - used : 0, &r.p[i]));
+            PRIMA_TRY(product(fmts[i], m[i], e, normed, nullptr, to, &r.p[i]));
             used_by(r.p[i]);
         }
         for (int i = 0; i < 3; ++i)
@@ -639,7 +661,7 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
         const bool lay = takes(f.wgate) || takes(f.wup);
         if (takes_alone(f.wo, e, qd)) {
             PRIMA_TRY(prepare(GEMM_PLAIN, qd, o, GemmShares{}, nullptr, nullptr, true));
-            PRIMA_TRY(product(f.wo, mat(L.wo, h, e), qd, plain, x, part, w.part_bytes, &p));
+            PRIMA_TRY(product(f.wo, mat(L.wo, h, e), qd, plain, x, w.s_out, &p));
         } else {
             PRIMA_TRY(mat_vecs(f.wo, mat(L.wo, h, e), qd, o, nullptr, x));
         }
@@ -650,7 +672,8 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
     if (f.wgate == PRIMA_FMT_Q4_K && f.wup == PRIMA_FMT_Q4_K) {
         const GemmMat gate_up[2] = {mat(L.wgate, act, F), mat(L.wup, nullptr, F)};
         GemmShares p;
-        PRIMA_TRY(launch_q4k_gemm(gate_up, 2, true, e, normed, T, nullptr, 0, part, w.part_bytes, &p, st));
+        const Span &to = down ? w.s_pair : w.s_pair_act;
+        PRIMA_TRY(launch_q4k_gemm(gate_up, 2, true, e, normed, T, nullptr, 0, part(to), to.bytes, &p, st));
         if (p.n) PRIMA_TRY(prepare(GEMM_SWIGLU, F, nullptr, p, down ? nullptr : act, nullptr, down));
         else PRIMA_TRY(prepare(GEMM_PLAIN, F, act, p, nullptr, nullptr, down));
     } else {
@@ -658,7 +681,7 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
         const GemmMat m[2] = {mat(L.wgate, act, F), mat(L.wup, up, F)};
         const int fmts[2] = {f.wgate, f.wup};
         for (int i = 0; i < 2; ++i) {
-            if (takes(fmts[i])) PRIMA_TRY(product(fmts[i], m[i], e, normed, nullptr, part, w.part_bytes, nullptr));
+            if (takes(fmts[i])) PRIMA_TRY(product(fmts[i], m[i], e, normed, nullptr, i == 0 ? w.s_gate : w.s_up, nullptr));
             else PRIMA_TRY(mat_vecs(fmts[i], m[i], e, h, g_ffn, nullptr));
         }
         PRIMA_TRY(launch_swiglu(act, up, static_cast<int64_t>(T) * F, st));
@@ -669,7 +692,7 @@ prima_status run_layer_prefill(const prima_dims &d, const prima_layer &L, int kv
         PRIMA_TRY(mat_vecs(f.wdown, mat(L.wdown, y, e), F, act, nullptr, h));
     } else {
         GemmShares p;
-        PRIMA_TRY(product(f.wdown, mat(L.wdown, y, e), F, plain, h, part, w.part_bytes, &p));
+        PRIMA_TRY(product(f.wdown, mat(L.wdown, y, e), F, plain, h, w.s_out, &p));
         if (p.n && next && (takes(nf.wq) || takes(nf.wk) || takes(nf.wv))) {
             PRIMA_TRY(prepare(GEMM_RESIDUAL, e, h, p, y, static_cast<const float *>(next->g_attn), true));
             *next_prepared = true;
@@ -1085,11 +1108,10 @@ prima_status prima_layer_window_prefill_mixed(const prima_dims *d, const prima_l
     if (T <= g_prefill_small_tokens) {
         // a short prompt: a matrix-product workgroup does the work of 64 tokens whatever their number; up to one decode call's
         // worth of tokens the decode kernels are faster
-        void *dws = at<char>(workspace, w.dec_base);
         for (int t0 = 0; t0 < T; t0 += PRIMA_MAX_TOK) {
             const int Tc = std::min<int>(PRIMA_MAX_TOK, T - t0);
             const prima_status cs = run_layers(*d, layers, formats, L, kv_cap, n_past + t0, Tc, x_in + static_cast<int64_t>(t0) * d->e, x_out + static_cast<int64_t>(t0) * d->e,
-                            dws, w.dec, st, [](int) { return static_cast<const AttnSeqs *>(nullptr); });
+                            workspace, w.dec, st, [](int) { return static_cast<const AttnSeqs *>(nullptr); });
             if (cs != PRIMA_OK) return cs;
         }
         return PRIMA_OK;

@@ -172,6 +172,20 @@ def test_matrix_product_k_division_policy():
     assert L.prima_gemm_workspace_bytes_ksplit(0, 8, 256) == 0 and L.prima_gemm_workspace_bytes_ksplit(4, 8, 300) == 0
 
 
+@pytest.mark.parametrize("e,heads,kv_heads,head_dim,ffn", [(4096, 32, 8, 128, 14336), (5120, 40, 8, 128, 13824), (8192, 64, 8, 128, 28672),
+                                                           (512, 8, 2, 64, 1536), (8448, 8, 2, 128, 512)])
+def test_scratch_of_a_prompt_serves_every_shorter_one(e, heads, kv_heads, head_dim, ffn):
+    """Scratch for T tokens is enough for fewer, at the widths of real models: the shares of K, which come and go with T, lie in a part that grows with T."""
+    L = _ffi.lib()
+    d = _dims(e=e, n_q_heads=heads, n_kv_heads=kv_heads, head_dim=head_dim, ffn=ffn)
+    need = [L.prima_prefill_workspace_bytes(C.byref(d), 8192, T) for T in range(1, 8193)]
+    assert need[0] > 0
+    down = [T for T in range(1, 8192) if need[T] < need[T - 1]]
+    assert not down, down[:9]
+    # a decode call's scratch is part of it (short prompts take that route)
+    assert need[0] >= L.prima_workspace_bytes(C.byref(d), 8192, 16)
+
+
 def test_batch_window_argument_errors():
     L = _ffi.lib()
     d = _dims()

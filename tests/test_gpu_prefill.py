@@ -6,6 +6,7 @@ The oracle advances at most 64 tokens a call; a prompt goes through it in such p
 Bar: hidden states max relative error <= 2e-3 (tests/metrics.rel_err), appended cache rows within one fp16 step.
 """
 import copy
+import ctypes
 
 import numpy as np
 import pytest
@@ -309,6 +310,30 @@ def test_the_launches_between_the_products(gpu_lib, matrix_product_route, mode, 
     assert torch.equal(y, win.prefill(_dev(x), n_past))
     ref = _oracle_prompt(d, host, x, n_past, formats)
     check_hidden(f"launches between mode={mode} T={T}", rel_err(y.cpu().numpy(), ref), d, host, x.astype(np.float64), n_past, formats=formats, eps=EPS_FP32)
+
+
+@pytest.mark.parametrize("T", [17, 130])
+def test_shares_of_k_leave_what_is_still_needed(gpu_lib, matrix_product_route, T):
+    """The shares of a product lie in what the layer does not use at that time: three layers (either vector between layers is input and output once), Q, K, V and gate, up
+    launched one by one, a gate and up pair whose activations are stored beside the shares (down in FP32) or laid out (down in Q6_K)."""
+    d = ModelDims(1024, 8, 2, 128, 2048, 1e4)
+    cfg = WindowConfig("shares", 82, d, 3, T, 9)
+    formats = [{"wq": "q5_k", "wk": "q8_0", "wv": "q6_k", "wo": "f16", "wgate": "q6_k", "wup": "q8_0", "wdown": "q5_k"}, {"wup": "q5_k", "wdown": "f32"},
+               {"wdown": "f32"}]
+    for fm in (formats, [{"wdown": "q6_k"}, formats[0], {}]):
+        cap = 9 + T
+        host = [synth.layer_tensors(cfg, l, kv_cap=cap, formats=fm[l]) for l in range(3)]
+        win = gpu_lib.Window(d, [{k: _dev(v) for k, v in t.items()} for t in host], cap, T_max=16, formats=fm)
+        x = synth.window_input(cfg)
+        print("case", T, fm, flush=True)
+        y = win.prefill(_dev(x), 9)
+        ref = _oracle_prompt(d, host, x, 9, fm)
+        check_hidden(f"shares T={T}", rel_err(y.cpu().numpy(), ref), d, host, x.astype(np.float64), 9, formats=fm, eps=EPS_FP32)
+        # a scratch made for a longer prompt gives the same bits
+        need = gpu_lib._ffi.lib().prima_prefill_workspace_bytes
+        longer = max(need(ctypes.byref(win.dims), win.kv_cap, t) for t in (T, 600))
+        win._prefill_ws = torch.empty(longer, dtype=torch.uint8, device="cuda")
+        assert torch.equal(y, win.prefill(_dev(x), 9))
 
 
 def test_prefill_at_the_largest_token_count(gpu_lib):
