@@ -370,6 +370,21 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (s == 7) { // the super-block's term is formed at its own magnitude and added in one step
+                // The sums slabs were requested a position ago by all waves and have landed before this position's barrier.  What the fold needs of them is
+                // read in front of it where the registers hold it (read where it is used, each read waited for: Q6_K, 64 tokens a workgroup, 4 % slower).
+                constexpr bool FRONT = !Q5 || WT == 2;
+                gm_v4f scale[FRONT ? WT : 1]; // of this lane's tokens: powers of two
+                half8 ax[Q5 && FRONT ? WT : 1];
+                auto read_sums = [&](int tt, int to) __attribute__((always_inline)) {
+                    const uint8_t *const sums = l_xs + (2 * tt + wt) * 1024;
+                    const int l = lane_anew(); // (kept, it spills)
+                    scale[to] = *reinterpret_cast<const gm_v4f *>(sums + GM_SCALES + (l >> 4) * 16);
+                    if constexpr (Q5) ax[to] = gemm_sums_operand(*reinterpret_cast<const half8 *>(sums + l * 16), g);
+                };
+                if constexpr (FRONT) {
+#pragma unroll
+                    for (int tt = 0; tt < WT; ++tt) read_sums(tt, tt);
+                }
 #pragma unroll
                 for (int rt = 0; rt < FM_RT; ++rt) {
                     const int r = wr * 64 + rt * 16 + n;
@@ -383,22 +398,19 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
                     }
 #pragma unroll
                     for (int tt = 0; tt < WT; ++tt) {
+                        if constexpr (!FRONT) read_sums(tt, 0);
+                        const int at = FRONT ? tt : 0;
                         gm_v4f am = zero, t = acc[tt][rt];
-                        // the sums slabs were requested a position ago by all waves and have landed before this position's barrier
-                        const uint8_t *const sums = l_xs + (2 * tt + wt) * 1024;
-                        const int l = lane_anew(); // (read again for every tile of rows: kept, they spill)
-                        const gm_v4f scale = *reinterpret_cast<const gm_v4f *>(sums + GM_SCALES + (l >> 4) * 16); // of this lane's tokens: powers of two
                         if constexpr (Q5) {
-                            const half8 ax = gemm_sums_operand(*reinterpret_cast<const half8 *>(sums + l * 16), g);
-                            am = __builtin_amdgcn_mfma_f32_16x16x32_f16(ax, m, zero, 0, 0, 0);
-                            t = __builtin_amdgcn_mfma_f32_16x16x32_f16(ax, sc16, t, 0, 0, 0);
+                            am = __builtin_amdgcn_mfma_f32_16x16x32_f16(ax[at], m, zero, 0, 0, 0);
+                            t = __builtin_amdgcn_mfma_f32_16x16x32_f16(ax[at], sc16, t, 0, 0, 0);
                         }
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             if constexpr (Q6) {
-                                ysum[tt][rt][i] = fmaf(d * scale[i], t[i], ysum[tt][rt][i]);
+                                ysum[tt][rt][i] = fmaf(d * scale[at][i], t[i], ysum[tt][rt][i]);
                             } else {
-                                const float term = (Q5 ? fmaf(d, t[i], -(dm * am[i])) : t[i]) * scale[i];
+                                const float term = (Q5 ? fmaf(d, t[i], -(dm * am[i])) : t[i]) * scale[at][i];
                                 unsigned &cw = comp[tt][rt][i >> 1];
                                 const float c0 = __builtin_bit_cast(float, i & 1 ? cw & 0xffff0000u : cw << 16);
                                 const float v = term - c0, yn = ysum[tt][rt][i] + v;
