@@ -478,7 +478,8 @@ struct FmPlan {
     bool narrow;
     int n_tb, ksplit;
 };
-FmPlan plan_fm(int T, int64_t n_rows, int64_t n_cols, int64_t part_bytes)
+// own_sum: a launch of their own adds the shares (else the caller's next one, which there is anyway)
+FmPlan plan_fm(int T, int64_t n_rows, int64_t n_cols, int64_t part_bytes, bool own_sum)
 {
     const int64_t n_rb = (n_rows + FM_ROWS - 1) / FM_ROWS, nb = n_cols / QK;
     const int n_tiles = (T + 15) / 16;
@@ -497,11 +498,18 @@ FmPlan plan_fm(int T, int64_t n_rows, int64_t n_cols, int64_t part_bytes)
     if (part_bytes > 0 && T <= 65535) {
         const int64_t share_bytes = static_cast<int64_t>(T) * n_rows * static_cast<int64_t>(sizeof(float));
         const int64_t most = std::min<int64_t>({nb, 16, part_bytes / share_bytes});
+        // Where a launch of its own adds them (a gate and an up matrix one by one), a last round that leaves half of the slots empty counts four fifths (a
+        // workgroup alone on its compute unit is faster), and more shares have to save 2 %.  One layer, every matrix in one format, us, without these two / with: 14B 700 tokens
+        // (two shares / one) Q8_0 1497 / 1433, FP16 1523 / 1448, 70B 450 (four / one) FP16 2978 / 2861, Q8_0 3007 / 2911.  Over 28 shapes of 8B to 70B widths and 100 to
+        // 1400 tokens 0.8 % above the best of one to six shares on average.
+        const double alone = own_sum ? 0.8 : 1., least_gain = own_sum ? 0.98 : 1.;
         double best = 0.;
         for (int64_t ks = 1; ks <= std::max<int64_t>(1, most); ++ks) {
-            const double us = static_cast<double>((wgs * ks + slots - 1) / slots) * static_cast<double>((nb + ks - 1) / ks) * (p.narrow ? 7. : 14.) +
+            const int64_t full = wgs * ks / slots, rest = wgs * ks % slots;
+            const double rounds = static_cast<double>(full) + (rest == 0 ? 0. : (rest <= GM_CUS ? alone : 1.));
+            const double us = rounds * static_cast<double>((nb + ks - 1) / ks) * (p.narrow ? 7. : 14.) +
                               (ks > 1 ? 4. + static_cast<double>(ks * share_bytes) * 2. / 4e6 : 0.);
-            if (ks == 1 || us < best) {
+            if (ks == 1 || us < best * least_gain) {
                 best = us;
                 p.ksplit = static_cast<int>(ks);
             }
@@ -545,7 +553,7 @@ prima_status launch_fmt_gemm(int fmt, const GemmMat &m, int64_t n_cols, const Ge
     const int64_t n_rb = (m.n_rows + FM_ROWS - 1) / FM_ROWS;
     const int n_tiles = (T + 15) / 16;
     if (n_rb >= (int64_t{1} << 30) || n_tiles > 65535 || n_cols / QK >= (int64_t{1} << 31)) return PRIMA_E_SHAPE;
-    const FmPlan p = plan_fm(T, m.n_rows, n_cols, part ? static_cast<int64_t>(part_bytes) : 0);
+    const FmPlan p = plan_fm(T, m.n_rows, n_cols, part ? static_cast<int64_t>(part_bytes) : 0, !later);
     FmtGemmArgs a{};
     a.W = m.W; a.n_rows = m.n_rows; a.n_cols = n_cols; a.A = x.A; a.norm = x.norm;
     a.resid = resid; a.ldr = ldr; a.y = m.y; a.ldy = m.ldy; a.T = T; a.n_tiles = n_tiles; a.n_rb = static_cast<int>(n_rb);
