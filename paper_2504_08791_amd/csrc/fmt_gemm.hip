@@ -247,17 +247,16 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
 
     // ---- activation requests: 4 WT slabs of 1 KiB per position, WT per wave; a sums slab per token tile and super-block ----
     const uint32_t lds0 = lds_address(smem), lane16 = lane * 16;
-    const uint8_t *abase[WT];
+    // (a base per tile, not per slab: scalar registers short of the 128-token kernels were kept in lanes of vector registers.  With this, one layer,
+    // every matrix in Q5_K, 70B 1024 tokens 5559 -> 5395 us, 8B 1685 -> 1650, Q6_K 14B 700 1777 -> 1750)
+    const uint8_t *abase[WT / 2];
 #pragma unroll
-    for (int j = 0; j < WT; ++j) {
-        const int slab = wave * WT + j, tile = min(tile0 + (slab >> 1), a.n_tiles - 1);
-        abase[j] = a.A + (static_cast<int64_t>(tile) * nb * GM_SLABS + (slab & 1)) * 1024;
-    }
+    for (int j = 0; j < WT / 2; ++j) abase[j] = a.A + static_cast<int64_t>(min(tile0 + wave * (WT / 2) + j, a.n_tiles - 1)) * nb * GM_TILE_BYTES;
     auto issue = [&](int b, int s, int buf) __attribute__((always_inline)) {
         const int64_t off = (static_cast<int64_t>(b) * GM_SLABS + 2 * s) * 1024;
 #pragma unroll
         for (int j = 0; j < WT; ++j)
-            if (FULL || wave * WT + j < 2 * tiles) dma16_base(abase[j] + off, lane16, lds0 + buf * L::A_SLOT + (wave * WT + j) * 1024);
+            if (FULL || wave * WT + j < 2 * tiles) dma16_base(abase[j >> 1] + off + (j & 1) * 1024, lane16, lds0 + buf * L::A_SLOT + (wave * WT + j) * 1024);
     };
     auto issue_sums = [&](int b) __attribute__((always_inline)) {
         {
@@ -387,7 +386,7 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
                 }
 #pragma unroll
                 for (int rt = 0; rt < FM_RT; ++rt) {
-                    const int r = wr * 64 + rt * 16 + n;
+                    const int r = wr * 64 + rt * 16 + (Q5 ? lane_anew() & 15 : n); // (Q5_K: kept, the addresses spill eight registers; 64 tokens: 178 registers, now 164, three workgroups a compute unit)
                     float d = 1.f, dm = 0.f;
                     half8 m = {}, sc16 = {};
                     if constexpr (Q5 || Q6) d = l_d[r];
@@ -500,7 +499,7 @@ FmPlan plan_fm(int T, int64_t n_rows, int64_t n_cols, int64_t part_bytes, bool o
         const int64_t most = std::min<int64_t>({nb, 16, part_bytes / share_bytes});
         // Where a launch of its own adds them (a gate and an up matrix one by one), a last round that leaves half of the slots empty counts four fifths (a
         // workgroup alone on its compute unit is faster), and more shares have to save 2 %.  One layer, every matrix in one format, us, without these two / with: 14B 700 tokens
-        // (two shares / one) Q8_0 1497 / 1433, FP16 1523 / 1448, 70B 450 (four / one) FP16 2978 / 2861, Q8_0 3007 / 2911.  Over 28 shapes of 8B to 70B widths and 100 to
+        // (two shares / one) Q8_0 1497 / 1433, FP16 1523 / 1448, 70B 450 FP16 2922 / 2861, Q8_0 2968 / 2911.  Over 28 shapes of 8B to 70B widths and 100 to
         // 1400 tokens 0.8 % above the best of one to six shares on average.
         const double alone = own_sum ? 0.8 : 1., least_gain = own_sum ? 0.98 : 1.;
         double best = 0.;
