@@ -91,7 +91,7 @@ struct FmLds {
 };
 
 // FULL: every workgroup does 2 WT token tiles (past the last: the last again, not stored); else the tiles are shared out evenly over the
-// workgroups, which skip those they do not have.  (The branches cost 3 to 5 %; both in one kernel spill.)
+// workgroups, which skip those they do not have.  (The branches, and the unpacking in front of the products, cost 3 to 7 %; both in one kernel spill.)
 template <int FMT, int WT, bool FULL>
 __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
 {
@@ -533,8 +533,10 @@ prima_status launch_fm(FmtGemmArgs a, const FmPlan &p, hipStream_t st)
     a.share_q = static_cast<int>(nb / a.ksplit); a.share_r = static_cast<int>(nb % a.ksplit);
     a.tile_q = a.n_tiles / a.n_tb; a.tile_r = a.n_tiles % a.n_tb;
     const unsigned grid = gemm_grid(wgs * a.ksplit);
-    // full workgroups where that leaves less than a twentieth of padding
-    const bool full = (a.n_tb * (p.narrow ? 4 : 8) - a.n_tiles) * 20 < a.n_tiles;
+    // Full workgroups where that leaves less than a seventh of padding.  (A twentieth before: one layer, every matrix in one format, us, before / now: 70B 450 tokens (29
+    // tiles) Q5_K 3117 / 2983, Q6_K 3152 / 3089, Q8_0 2862 / 2651, FP16 2861 / 2683, 14B 720 (45) Q6_K 1772 / 1736, Q8_0 1606 / 1524, 8B 900 (57) Q5_K 1646 / 1574; 96 of 8B to
+    // 70B and 200 to 1170 tokens 0.926 to 1.005 of before.  At a seventh, 21 tiles, 70B 333 in Q8_0 full 2101, not full 2018.)
+    const bool full = (a.n_tb * (p.narrow ? 4 : 8) - a.n_tiles) * 7 < a.n_tiles;
     if (p.narrow) return full ? launch_wt<FMT, 2, true>(a, grid, st) : launch_wt<FMT, 2, false>(a, grid, st);
     return full ? launch_wt<FMT, 4, true>(a, grid, st) : launch_wt<FMT, 4, false>(a, grid, st);
 }
