@@ -405,6 +405,10 @@ prima_status prima_layer_window_prefill_mixed(const prima_dims *d, const prima_l
                                               const float *x_in, float *x_out,
                                               void *workspace, size_t workspace_bytes, void *hip_stream);
 size_t prima_prefill_workspace_bytes(const prima_dims *d, int32_t kv_cap, int32_t T);
+/* Host only: how the prompt call's matrix product for Q5_K, Q6_K, Q8_0 and FP16 shares T tokens out: tokens of a workgroup (64 or 128), such blocks, and
+ * whether every workgroup does all of its tokens (full = 1; past the last they are thrown away) or the blocks share the 16-token tiles out evenly (0).
+ * PRIMA_E_SHAPE for a format that goes another way. */
+prima_status prima_fmt_gemm_plan(int32_t fmt, int32_t T, int64_t n_rows, int64_t n_cols, int32_t *tokens, int32_t *blocks, int32_t *full);
 /* Prompts of up to n tokens are advanced by the decode kernels, PRIMA_MAX_TOK tokens at a time, inside the prompt call
  * (default 16, one decode call: from 17 tokens on the matrix product is faster).  0: always the matrix product (tests).  Process-wide; not to be changed while a call is being enqueued. */
 void prima_set_prefill_small_tokens(int32_t n);

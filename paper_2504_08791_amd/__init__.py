@@ -83,6 +83,13 @@ def gemm_ksplit(T, rows, cols):
     return _ffi.lib().prima_gemm_ksplit(T, rows, cols)
 
 
+def fmt_gemm_plan(fmt, T, rows, cols):
+    """How the prompt call's matrix product for the other formats shares T tokens out: (tokens of a workgroup, blocks, full)."""
+    out = [C.c_int32() for _ in range(3)]
+    _ffi.check(_ffi.lib().prima_fmt_gemm_plan(_ffi.FORMATS[fmt], T, rows, cols, *(C.byref(o) for o in out)), "prima_fmt_gemm_plan")
+    return out[0].value, out[1].value, bool(out[2].value)
+
+
 def gemm_workspace_bytes(T, rows, cols, ksplit=True):
     """Workspace of q4k_gemm: the minimum, or (ksplit) the size with which few rows x few tokens divide K."""
     if ksplit:

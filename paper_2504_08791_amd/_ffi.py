@@ -18,7 +18,7 @@ EXPORTS = ["prima_q4k_gemv", "prima_gemv_workspace_bytes", "prima_q4k_dequant", 
            "prima_fmt_tensor_bytes", "prima_fmt_dequant", "prima_fmt_gemv", "prima_lm_head_fmt", "prima_layer_window_decode_mixed", "prima_window_plan_status", "prima_gemv_plan_status", "prima_layer_window_decode_batch_mixed",
            "prima_q4k_gemm", "prima_gemm_workspace_bytes", "prima_gemm_workspace_bytes_ksplit", "prima_gemm_ksplit", "prima_layer_window_prefill", "prima_prefill_workspace_bytes",
            "prima_layer_window_prefill_mixed", "prima_set_prefill_small_tokens", "prima_q4k_gemv_noalloc",
-           "prima_gguf_tensor_bytes", "prima_repack_gguf"]
+           "prima_gguf_tensor_bytes", "prima_repack_gguf", "prima_fmt_gemm_plan"]
 FORMATS = {"q4_k": 0, "q5_k": 1, "q6_k": 2, "q8_0": 3, "f16": 4, "f32": 5}
 
 
@@ -68,6 +68,8 @@ def lib():
         L.prima_gemm_workspace_bytes_ksplit.restype = sz
         L.prima_gemm_ksplit.argtypes = [i32, i64, i64]
         L.prima_gemm_ksplit.restype = i32
+        L.prima_fmt_gemm_plan.argtypes = [i32, i32, i64, i64] + [C.POINTER(i32)] * 3
+        L.prima_fmt_gemm_plan.restype = C.c_int
         L.prima_layer_window_prefill.argtypes = [dp, lp, i32, i32, i32, i32, vp, vp, vp, sz, vp]
         L.prima_layer_window_prefill.restype = C.c_int
         L.prima_prefill_workspace_bytes.argtypes = [dp, i32, i32]

@@ -191,6 +191,11 @@ prima_status launch_q4k_gemm(const GemmMat *mats, int n_mats, bool pair, int64_t
 // are not exact in binary16)
 bool fmt_gemm_takes(int fmt);
 int64_t fmt_gemm_most_shares(int64_t n_rows, int64_t n_cols); // as gemm_most_shares()
+struct FmtGemmBlocks {
+    int tokens, blocks; // of a workgroup, and of these in a row block
+    bool full;          // every workgroup does all of its tokens; else the blocks share the 16-token tiles out evenly
+};
+FmtGemmBlocks fmt_gemm_blocks(int T, int64_t n_rows, int64_t n_cols);
 prima_status launch_fmt_gemm(int fmt, const GemmMat &m, int64_t n_cols, const GemmActs &x, int T, const float *resid, int64_t ldr, void *part,
                              size_t part_bytes, GemmShares *later, hipStream_t st);
 // RoPE on q and k, k and v appended to the caches as rows n_past .. n_past + T - 1; p: shares of q, k, v (n 0: complete, at part); q: where the rotated

@@ -479,7 +479,7 @@ prima_status launch_wt(const FmtGemmArgs &a, unsigned grid, hipStream_t st)
 
 // Token blocks and shares of K
 struct FmPlan {
-    bool narrow;
+    bool narrow, full;
     int n_tb, ksplit;
 };
 // own_sum: a launch of their own adds the shares (else the caller's next one, which there is anyway)
@@ -491,6 +491,10 @@ FmPlan plan_fm(int T, int64_t n_rows, int64_t n_cols, int64_t part_bytes, bool o
     // 128 tokens per workgroup, 64 where that leaves fewer tokens of padding or twice the workgroups on an idle device
     p.narrow = (n_tiles + 3) / 4 * 4 < (n_tiles + 7) / 8 * 8 || n_rb * ((n_tiles + 7) / 8) * 2 <= 2 * GM_CUS;
     p.n_tb = p.narrow ? (n_tiles + 3) / 4 : (n_tiles + 7) / 8;
+    // Full workgroups where that leaves less than a seventh of padding.  (A twentieth before: one layer, every matrix in one format, us, before / now: 70B 450 tokens (29
+    // tiles) Q5_K 3117 / 2983, Q6_K 3152 / 3089, Q8_0 2862 / 2651, FP16 2861 / 2683, 14B 720 (45) Q6_K 1772 / 1736, Q8_0 1606 / 1524, 8B 900 (57) Q5_K 1646 / 1574; 96 of 8B to
+    // 70B and 200 to 1170 tokens 0.926 to 1.005 of before.  At a seventh, 21 tiles, 70B 333 in Q8_0 full 2101, not full 2018.)
+    p.full = (p.n_tb * (p.narrow ? 4 : 8) - n_tiles) * 7 < n_tiles;
     const int64_t wgs = n_rb * p.n_tb, slots = 2 * GM_CUS;
     // Shares of K (as far as the scratch holds them; with four super-blocks of each at the least, two 8B layers with V and down in Q6_K took 293 us at 17 tokens, 248 without): rounds of workgroups times a share's super-blocks, about
     // 7 us each at 64 tokens and 14 at 128, against the shares' way to memory and back (4 TB/s).  (As many as fit the device at once
@@ -533,17 +537,19 @@ prima_status launch_fm(FmtGemmArgs a, const FmPlan &p, hipStream_t st)
     a.share_q = static_cast<int>(nb / a.ksplit); a.share_r = static_cast<int>(nb % a.ksplit);
     a.tile_q = a.n_tiles / a.n_tb; a.tile_r = a.n_tiles % a.n_tb;
     const unsigned grid = gemm_grid(wgs * a.ksplit);
-    // Full workgroups where that leaves less than a seventh of padding.  (A twentieth before: one layer, every matrix in one format, us, before / now: 70B 450 tokens (29
-    // tiles) Q5_K 3117 / 2983, Q6_K 3152 / 3089, Q8_0 2862 / 2651, FP16 2861 / 2683, 14B 720 (45) Q6_K 1772 / 1736, Q8_0 1606 / 1524, 8B 900 (57) Q5_K 1646 / 1574; 96 of 8B to
-    // 70B and 200 to 1170 tokens 0.926 to 1.005 of before.  At a seventh, 21 tiles, 70B 333 in Q8_0 full 2101, not full 2018.)
-    const bool full = (a.n_tb * (p.narrow ? 4 : 8) - a.n_tiles) * 7 < a.n_tiles;
-    if (p.narrow) return full ? launch_wt<FMT, 2, true>(a, grid, st) : launch_wt<FMT, 2, false>(a, grid, st);
-    return full ? launch_wt<FMT, 4, true>(a, grid, st) : launch_wt<FMT, 4, false>(a, grid, st);
+    if (p.narrow) return p.full ? launch_wt<FMT, 2, true>(a, grid, st) : launch_wt<FMT, 2, false>(a, grid, st);
+    return p.full ? launch_wt<FMT, 4, true>(a, grid, st) : launch_wt<FMT, 4, false>(a, grid, st);
 }
 
 } // namespace
 
 bool fmt_gemm_takes(int fmt) { return fmt == PRIMA_FMT_Q5_K || fmt == PRIMA_FMT_Q6_K || fmt == PRIMA_FMT_Q8_0 || fmt == PRIMA_FMT_F16; }
+
+FmtGemmBlocks fmt_gemm_blocks(int T, int64_t n_rows, int64_t n_cols)
+{
+    const FmPlan p = plan_fm(T, n_rows, n_cols, 0, false);
+    return FmtGemmBlocks{p.narrow ? 64 : 128, p.n_tb, p.full};
+}
 
 int64_t fmt_gemm_most_shares(int64_t n_rows, int64_t n_cols)
 {

@@ -843,6 +843,16 @@ size_t prima_gemm_workspace_bytes_ksplit(int32_t T, int64_t n_rows, int64_t n_co
     return round_up(gemm_ws_bytes(T, n_cols), 256) + gemm_part_bytes(T, &n_rows, 1, n_cols);
 }
 
+prima_status prima_fmt_gemm_plan(int32_t fmt, int32_t T, int64_t n_rows, int64_t n_cols, int32_t *tokens, int32_t *blocks, int32_t *full)
+{
+    if (!tokens || !blocks || !full) return PRIMA_E_NULL;
+    if (!fmt_gemm_takes(fmt) || n_rows < 1 || n_cols <= 0 || n_cols % QK) return PRIMA_E_SHAPE;
+    if (T < 1 || T > PRIMA_PREFILL_MAX_TOK) return PRIMA_E_RANGE;
+    const FmtGemmBlocks p = fmt_gemm_blocks(T, n_rows, n_cols);
+    *tokens = p.tokens; *blocks = p.blocks; *full = p.full ? 1 : 0;
+    return PRIMA_OK;
+}
+
 prima_status prima_q4k_gemm(const void *W, int64_t n_rows, int64_t n_cols, const float *x, int64_t ldx, int32_t T,
                             const float *gain, float eps, const float *resid, int64_t ldr, float *y, int64_t ldy,
                             void *workspace, size_t workspace_bytes, void *hip_stream)

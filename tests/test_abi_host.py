@@ -172,6 +172,28 @@ def test_matrix_product_k_division_policy():
     assert L.prima_gemm_workspace_bytes_ksplit(0, 8, 256) == 0 and L.prima_gemm_workspace_bytes_ksplit(4, 8, 300) == 0
 
 
+def test_products_of_the_other_formats_share_the_tokens_out():
+    """Host logic, no GPU: 64 or 128 tokens a workgroup, as many blocks as these need; all of them full where that leaves less than a seventh of padding; 128
+    where that leaves no more padding than 64 and at least half of the 512 workgroup slots are filled."""
+    L = _ffi.lib()
+    out = [C.c_int32() for _ in range(3)]
+    f = lambda fmt=2, T=40, rows=4096, cols=4096: L.prima_fmt_gemm_plan(fmt, T, rows, cols, *(C.byref(o) for o in out))
+    seen = set()
+    for T in list(range(1, 700, 7)) + [1024, 8192]:
+        for rows in (1, 128, 4096, 11264, 16640, 57344):
+            assert f(T=T, rows=rows) == 0
+            tokens, blocks, full = (o.value for o in out)
+            tiles, rb = -(-T // 16), -(-rows // 128)
+            per = tokens // 16
+            assert blocks == -(-tiles // per)
+            assert full == ((blocks * per - tiles) * 7 < tiles)
+            assert (tokens == 64) == (-(-tiles // 4) * 4 < -(-tiles // 8) * 8 or rb * -(-tiles // 8) * 2 <= 512)
+            seen.add((tokens, full))
+    assert len(seen) == 4
+    assert f(fmt=0) == 2 and f(fmt=5) == 2 and f(rows=0) == 2 and f(cols=300) == 2 and f(T=0) == 4 and f(T=8193) == 4
+    assert L.prima_fmt_gemm_plan(2, 40, 4096, 4096, None, C.byref(out[1]), C.byref(out[2])) == 1
+
+
 @pytest.mark.parametrize("e,heads,kv_heads,head_dim,ffn", [(4096, 32, 8, 128, 14336), (5120, 40, 8, 128, 13824), (8192, 64, 8, 128, 28672),
                                                            (512, 8, 2, 64, 1536), (8448, 8, 2, 128, 512)])
 def test_scratch_of_a_prompt_serves_every_shorter_one(e, heads, kv_heads, head_dim, ffn):

@@ -206,10 +206,17 @@ def test_products_of_the_other_formats_are_no_less_exact_than_the_mat_vec(gpu_li
     """One layer with all seven matrices in one format, as one prompt call (matrix product: 64- and 128-token workgroups, ragged
     last ones, rows ragged against 128, K divided and whole) and as decode calls of 3 tokens (the fp32 mat-vec), each against
     64 bits: the prompt's error no larger, both below 1e-6 of what the layer adds.  spread: magnitudes over six decades within a
-    token, whose activations share one power of two; what is added is then small beside the token and its rounding
+    token, whose activations share a power of two in a super-block; what is added is then small beside the token and its rounding
     (2^-24 of the token's largest values) is most of the error."""
-    from workloads.configs import ModelDims
     d = ModelDims(2560, 20, 5, 128, 8448, 1e5)
+    # the tall matrices go through 128-token workgroups from 449 tokens on, all others through 64-token ones; 17, 65 and 129 tokens leave workgroups without tiles
+    plan = {n: gpu_lib.fmt_gemm_plan(fmt, T, r, c)[::2] for n, (r, c) in _shapes(d).items()}
+    full = T in (64, 490)
+    assert plan == {n: (128 if T == 490 and n in ("wgate", "wup") else 64, full) for n in plan}, plan
+    _no_less_exact_than_the_mat_vec(gpu_lib, fmt, T, dist, d)
+
+
+def _no_less_exact_than_the_mat_vec(gpu_lib, fmt, T, dist, d):
     rng = np.random.default_rng(T)
     t = {k: _dev(_centred(rng, fmt, *s)) for k, s in _shapes(d).items()}
     n_past, cap = 64, 64 + T
@@ -232,10 +239,14 @@ def test_products_of_the_other_formats_are_no_less_exact_than_the_mat_vec(gpu_li
     assert err[0] <= 1.02 * err[1] and (dist == "spread" or err[1] < 1e-6), err
 
 
+@pytest.mark.parametrize("T,ffn,blocks", [(333, 11264, 3), (208, 16640, 2)])
 @pytest.mark.parametrize("fmt", ["q5_k", "q6_k", "q8_0", "f16"])
-def test_workgroups_of_128_tokens_that_lack_some(gpu_lib, fmt):
-    """22 token tiles: three workgroups of 128 tokens with seven or eight tiles each, the absent ones skipped."""
-    test_products_of_the_other_formats_are_no_less_exact_than_the_mat_vec(gpu_lib, fmt, 350, "normal")
+def test_workgroups_of_128_tokens_that_lack_some(gpu_lib, fmt, T, ffn, blocks):
+    """21 and 13 token tiles of a tall matrix: workgroups of 128 tokens with seven tiles each, or seven and six, the absent ones skipped (waves with
+    four tiles beside waves with three, or two groups of three)."""
+    d = ModelDims(1024, 8, 2, 128, ffn, 1e5)
+    assert gpu_lib.fmt_gemm_plan(fmt, T, ffn, 1024) == (128, blocks, False)
+    _no_less_exact_than_the_mat_vec(gpu_lib, fmt, T, "normal", d)
 
 
 def test_prefill_then_decode_continues(gpu_lib, route):
@@ -310,6 +321,22 @@ def test_the_launches_between_the_products(gpu_lib, matrix_product_route, mode, 
     assert torch.equal(y, win.prefill(_dev(x), n_past))
     ref = _oracle_prompt(d, host, x, n_past, formats)
     check_hidden(f"launches between mode={mode} T={T}", rel_err(y.cpu().numpy(), ref), d, host, x.astype(np.float64), n_past, formats=formats, eps=EPS_FP32)
+
+
+@pytest.mark.parametrize("e,formats", [(8448, {}), (33024, {}), (33024, {"wgate": "q6_k"})])
+def test_prompt_of_a_very_wide_model(gpu_lib, matrix_product_route, e, formats):
+    """33 and 129 super-blocks a token: more than the 32 and 128 whose sums of squares the launches behind divided products request at first (SwiGLU: 16 lanes a
+    token; RoPE, and the sum of a product on its own: a wave)."""
+    d = ModelDims(e, 2, 1, 128, 512, 1e4)
+    cfg = WindowConfig("wide", 83, d, 1, 17, 5)
+    host = [synth.layer_tensors(cfg, 0, kv_cap=22, formats=formats)]
+    win = gpu_lib.Window(d, [{k: _dev(v) for k, v in t.items()} for t in host], 22, T_max=16, formats=[formats])
+    x = synth.window_input(cfg)
+    x[:, -256:] *= 30   # the last super-block's share of the sum of squares is most of it
+    print("case", e, formats, flush=True)
+    y = win.prefill(_dev(x), 5).cpu().numpy()
+    ref = _oracle_prompt(d, host, x, 5, [formats])
+    check_hidden(f"wide e={e}", rel_err(y, ref), d, host, x.astype(np.float64), 5, formats=[formats], eps=EPS_GEMM)
 
 
 @pytest.mark.parametrize("T", [17, 130])
