@@ -168,12 +168,11 @@ size_t gemm_ss_bytes(int T, int64_t n_cols);   // ss
 // y = 1/rms * the shares of one matrix (+ resid)
 prima_status launch_gemm_sum(const GemmShares &p, const GemmNorm &norm, const float *resid, int64_t ldr, float *y, int64_t ldy, int64_t n_rows, int T,
                              hipStream_t st);
-// K divided among workgroups (a launch whose rows and tokens alone would leave most of the device idle): the number of
-// shares for T tokens and n_mats matrices of these rows sharing a launch, or (pair) a gate and an up matrix of n_rows[0]
-// each (1: none), and the bytes of `part` that hold the shares' sums (0: none).  A launch divides K only if it is given
-// that much.
-int gemm_ksplit(int T, const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair = false);
-size_t gemm_part_bytes(int T, const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair = false);
+// K divided among workgroups (a launch whose rows and tokens alone would leave most of the device idle) where the product itself has its shares added:
+// the number of shares for T tokens and one matrix (1: none), and the bytes of `part` that hold their sums (0: none).  A launch divides K only if it
+// is given that much.
+int gemm_ksplit(int T, int64_t n_rows, int64_t n_cols);
+size_t gemm_part_bytes(int T, int64_t n_rows, int64_t n_cols);
 // Where the shares are left to the caller's next launch: room for the most numbers a token that they take, whatever T (prompts of a few tokens of
 // very tall matrices excepted)
 int64_t gemm_most_shares(const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair = false);

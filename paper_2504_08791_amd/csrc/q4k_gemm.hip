@@ -70,7 +70,7 @@ struct GemmArgs {
     GemmNorm norm;
     const float *resid; // null: none (added to every stored row; launches with a residual have one matrix)
     int64_t ldr;
-    int T, n_tiles, n_rb, n_tb; // 16-token tiles, row blocks, token blocks
+    int T, n_rb, n_tb; // row blocks, token blocks
     int band;                   // gemm_band()
     // K divided among ksplit workgroups per (row block, token block): each walks its share of the
     // super-blocks and stores its sums to part[split][token][ldp] (column: row block * GM_ROWS + row in the block); a
@@ -586,20 +586,12 @@ int token_blocks(int T) { return ((T + 15) / 16 + GM_TT - 1) / GM_TT; }
 
 } // namespace
 
-int gemm_ksplit(int T, const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair)
-{
-    int64_t n_rb = 0;
-    for (int i = 0; i < (pair ? 1 : n_mats); ++i) n_rb += row_blocks(n_rows[i], pair);
-    return ksplit_for(n_rb, token_blocks(T), n_cols / QK);
-}
+int gemm_ksplit(int T, int64_t n_rows, int64_t n_cols) { return ksplit_for(row_blocks(n_rows), token_blocks(T), n_cols / QK); }
 
-size_t gemm_part_bytes(int T, const int64_t *n_rows, int n_mats, int64_t n_cols, bool pair)
+size_t gemm_part_bytes(int T, int64_t n_rows, int64_t n_cols)
 {
-    const int s = gemm_ksplit(T, n_rows, n_mats, n_cols, pair);
-    if (s == 1) return 0;
-    int64_t n_rb = 0;
-    for (int i = 0; i < (pair ? 1 : n_mats); ++i) n_rb += row_blocks(n_rows[i], pair);
-    return static_cast<size_t>(s) * static_cast<size_t>(T) * static_cast<size_t>(n_rb) * GM_ROWS * sizeof(float);
+    const int s = gemm_ksplit(T, n_rows, n_cols);
+    return s == 1 ? 0 : static_cast<size_t>(s) * static_cast<size_t>(T) * static_cast<size_t>(row_blocks(n_rows)) * GM_ROWS * sizeof(float);
 }
 
 // plan_gemm() takes no more shares than the first of them that fills the device with one token block, or four (its plans for 10 shapes of 1B to 70B widths, 20 to
@@ -618,7 +610,8 @@ prima_status launch_q4k_gemm(const GemmMat *mats, int n_mats, bool pair, int64_t
                              void *part, size_t part_bytes, GemmShares *later, hipStream_t st)
 {
     if (later) *later = GemmShares{};
-    if (n_mats < 1 || n_mats > 3 || (pair && (n_mats != 2 || mats[0].n_rows != mats[1].n_rows || resid))) return PRIMA_E_SHAPE;
+    if (n_mats < 1 || n_mats > 3 || (pair && (n_mats != 2 || mats[0].n_rows != mats[1].n_rows || resid)) || (n_mats > 1 && !later))
+        return PRIMA_E_SHAPE;
     if (T == 0) return PRIMA_OK;
     GemmArgs a{};
     int64_t n_rb = 0;
@@ -645,7 +638,7 @@ prima_status launch_q4k_gemm(const GemmMat *mats, int n_mats, bool pair, int64_t
     }
     a.pair = pair ? 1 : 0;
     a.n_cols = n_cols; a.A = x.A; a.norm = x.norm; a.resid = resid; a.ldr = ldr;
-    a.T = T; a.n_tiles = n_tiles; a.n_rb = static_cast<int>(n_rb);
+    a.T = T; a.n_rb = static_cast<int>(n_rb);
     a.ldp = n_rb * GM_ROWS;
     // K is divided when that fills the device and the caller's scratch holds the shares (T: a grid dimension of the launch that adds them)
     const int64_t share_bytes = static_cast<int64_t>(T) * a.ldp * static_cast<int64_t>(sizeof(float));
@@ -654,7 +647,7 @@ prima_status launch_q4k_gemm(const GemmMat *mats, int n_mats, bool pair, int64_t
     if (later) {
         p = plan_gemm(n_rb, n_tiles, nb, T, 1, std::max<int64_t>(1, held));
     } else {
-        const int ks = n_mats == 1 && !pair ? ksplit_for(n_rb, token_blocks(T), nb) : 1, divided = held >= ks ? ks : 1;
+        const int ks = ksplit_for(n_rb, token_blocks(T), nb), divided = held >= ks ? ks : 1;
         p = plan_gemm(n_rb, n_tiles, nb, T, divided, divided);
     }
     a.n_tb = p.n_tb; a.ksplit = p.shares; a.band = gemm_band(a.n_tb);

@@ -834,13 +834,13 @@ size_t prima_gemm_workspace_bytes(int32_t T, int64_t n_cols) { return (T < 1 || 
 
 int32_t prima_gemm_ksplit(int32_t T, int64_t n_rows, int64_t n_cols)
 {
-    return (T < 1 || n_rows < 0 || n_cols <= 0 || n_cols % QK) ? 0 : gemm_ksplit(T, &n_rows, 1, n_cols);
+    return (T < 1 || n_rows < 0 || n_cols <= 0 || n_cols % QK) ? 0 : gemm_ksplit(T, n_rows, n_cols);
 }
 
 size_t prima_gemm_workspace_bytes_ksplit(int32_t T, int64_t n_rows, int64_t n_cols)
 {
     if (T < 1 || n_rows < 0 || n_cols <= 0 || n_cols % QK) return 0;
-    return round_up(gemm_ws_bytes(T, n_cols), 256) + gemm_part_bytes(T, &n_rows, 1, n_cols);
+    return round_up(gemm_ws_bytes(T, n_cols), 256) + gemm_part_bytes(T, n_rows, n_cols);
 }
 
 prima_status prima_fmt_gemm_plan(int32_t fmt, int32_t T, int64_t n_rows, int64_t n_cols, int32_t *tokens, int32_t *blocks, int32_t *full)
