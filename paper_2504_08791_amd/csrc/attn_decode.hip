@@ -590,8 +590,9 @@ __global__ void __launch_bounds__(ATT_THREADS, 4) attn_decode_kernel(AttnArgs a)
     }
 }
 
-// The merge as a launch of its own: a wave per query, the same sums in the same order.  Without the wait inside the launch the scratch need
-// not be marked "not written" first.
+// The merge as a launch of its own: a wave per query.  Without the wait inside the launch the scratch need not be marked "not written" first.
+// The same sums as in the merge inside, not the same bits: the weights are exp(m_i - M) without the 1/L, which divides the finished columns; the ranges' sums are added
+// pairwise; M and the sums are carried from one pass of ranges to the next.
 template <int D>
 __global__ void __launch_bounds__(256) attn_merge_kernel(const float *__restrict__ part, float *__restrict__ o, int heads, int nsplit)
 {

@@ -26,8 +26,9 @@
 // A workgroup of 4 waves owns 128 rows x 32 WT tokens, a wave 64 rows x 16 WT tokens.  Per position (sub-block) a thread
 // decodes 16 weights of one row for the next position into LDS, where both row halves of the workgroup's waves read them
 // as operands: a weight is decoded once per workgroup, not once per wave.  Activations come by 16-byte global->LDS loads.  Both
-// are double-buffered with one barrier per position; 33 to 65 KiB of LDS by format and tokens, so that two workgroups share a compute unit and one's
-// waits run under the other's matrix instructions.  Registers held to 168 at 64 tokens, so that three share one: between 1 % faster and 2.5 % slower (a few spills).
+// are double-buffered with one barrier per position; 37 to 73 KiB of LDS by format and tokens, so that two workgroups share a compute unit and one's
+// waits run under the other's matrix instructions.  At 64 tokens three share one in Q5_K, Q8_0 and FP16 (41 KiB and 168 registers at the most; Q5_K, 14B 700 tokens, every matrix,
+// 178 registers 1638 us, 164 1527); Q6_K has 53 KiB.
 #include <algorithm>
 #include <atomic>
 

@@ -195,7 +195,7 @@ __global__ void __launch_bounds__(256) gemm_first_kernel(GemmPrepare a, RopeTabl
     else rope_table_entry(r, static_cast<int64_t>(blockIdx.x - blocks) * blockDim.x + threadIdx.x);
 }
 
-// y[t][row] = 1/rms * the shares of K of a number added in order (+ residual)
+// y[t][row] = 1/rms * the shares of K of a number (+ residual)
 __global__ void __launch_bounds__(256) gemm_sum_kernel(GemmShares p, GemmNorm norm, const float *resid, int64_t ldr, float *y, int64_t ldy, int64_t n_rows)
 {
     const int64_t row = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;

@@ -116,7 +116,7 @@ static_assert(GM_AHEAD >= 2 && GM_AHEAD <= 4, "the weight requests at s == 3, 4,
 //   quants: per wave two buffers of 4 KiB, sub-blocks 0-3 and 4-7 of its 64 rows, each filled by four requests of 64
 //     bytes x 16 rows as soon as the B tiles of the half super-block before have been built from it;
 //   headers: 64 rows x 16 bytes per wave and super-block, decoded into LDS of the wave.
-// Per position: wait until everything this wave requested four positions ago or earlier has landed (requests complete
+// Per position: wait until everything this wave requested two positions ago or earlier has landed (requests complete
 // in order; the wait names the number of requests made since, which the schedule fixes), barrier (everyone's share of
 // the activations is there, and everyone has finished reading the slot of the position before, which is the slot
 // requested next), the position's requests, and then, token tile by token tile, the MFMAs of this position with,
@@ -124,7 +124,7 @@ static_assert(GM_AHEAD >= 2 && GM_AHEAD <= 4, "the weight requests at s == 3, 4,
 // to wait on.  Measured with parts of the work switched off (8192 x 28672 weights, 1024 tokens): the LDS reads of the
 // activations cost 30 % of the time, the requests 12 %, the B tiles 10 %, the barrier 3 %: a wave reads every
 // activation of its 64 tokens once per position, whatever the tiling, so LDS bandwidth is met before the MFMA rate.
-// TT: the token tiles of this workgroup.  The tiles are shared out evenly, so that one of 21 tiles (333 tokens) is three workgroups
+// TT: the token tiles of this workgroup.  The tiles are shared out evenly, so that 21 tiles (333 tokens) in six blocks are three workgroups
 // of four and three of three; a tile past the last one was multiplied and thrown away.
 template <int TT>
 __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem, int rb, int share, int tile0)
@@ -286,7 +286,7 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
         return *reinterpret_cast<const float2 *>(dec + GM_SC + GM_M + (bb & 1) * GM_D + (16 * rt + (l & 15)) * 8);
     };
 
-    // The wave is alone on its SIMD and issues in order: an MFMA occupies the matrix pipe for 16 cycles, during which
+    // A wave issues in order: an MFMA occupies the matrix pipe for 16 cycles, during which
     // the same wave can issue three or four other instructions for free, and only then.  So the B tiles of position
     // p + 1 are built (VALU) between the MFMAs of position p, in the order the scheduling groups below prescribe;
     // built in front of their own MFMAs they would cost their full issue time with the matrix pipe idle.  The quants
@@ -310,11 +310,11 @@ __device__ __forceinline__ void q4k_gemm_block(const GemmArgs &a, uint8_t *smem,
             constexpr int slot = s % GM_NS; // ring slot of this position
             static_assert(9 % GM_NS == 0, "a position's slot must not depend on the super-block");
             const int p = 9 * b + s;
-            // Everything requested at position p - 4 or before has landed (this wave's share of position p's
-            // activations; the quants and headers that the B tiles built during this position need are older) once at
-            // most the requests of positions p - 3 .. p - 1 are out: their activation requests (DM each, DMS where the
-            // target is a sums position) and, where they fall on s == 3, 4, 7 of a super-block that has a successor,
-            // 4, 1, 4 weight requests.  The last three positions wait for everything.
+            // Everything requested at position p - GM_AHEAD or before has landed (this wave's share of position p's
+            // activations; the quants and headers that the B tiles built during this position need are no younger) once at
+            // most the requests of the positions behind it are out (requests_behind: activations, DM or, where the target is a sums position,
+            // one, and, where they fall on s == 3, 4, 7 of a super-block that has a successor, 4, 1, 4 weight requests).
+            // The last position waits for everything.
             if (p + GM_AHEAD - 1 >= total) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             else if (b + 1 < nbl) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(requests_behind(s, true, DM)) : "memory");
             else asm volatile("s_waitcnt vmcnt(%0)" : : "n"(requests_behind(s, false, DM)) : "memory"); // the last super-block requests no weights
@@ -549,6 +549,8 @@ int ksplit_for(int64_t n_rb, int64_t n_tb, int64_t nb)
 // So the tokens are cut into more blocks than they need where the last round is better filled by it: 21 tiles (333 tokens) into seven blocks of three instead of
 // six, the output projection of 8B 50.7 -> 45 us with its shares.  A block more costs what the unpacking of the weights once more costs: 5 % of
 // its part, in long launches, which run at the card's power limit, 30 % (70B, 400 tokens, gate and up in eight blocks or nine 40 us slower than in seven, two shares).
+// Where the step between the two lies does not matter from 150 to 700 us: with blocks and shares of each of 32 products (8 prompts of 8B to 70B) forced in turn, the choices
+// are the same; without a step, 30 % or 5 % for all, they cost 0.1 % of a call on average and up to 46 us (70B, 400 tokens).
 // Fitted to single launches (16 prompts of 17 to 1500 tokens, 8B to 70B, up to 4 more blocks and 14 shares) and to whole calls back to back.
 // Whole calls, one layer, us, the fewest blocks and the shares by rounds times tiles / this: 8B 180 tokens 264 / 258, 800 831 / 816, 14B 333 520 / 498, 1500 1962 / 1926, 70B 1024
 // 3601 / 3561; 28 others (8B to 70B, 17 to 1500 tokens) between 0.98 and 1.004 of what they were.
