@@ -248,16 +248,20 @@ __global__ void __launch_bounds__(FM_THREADS, 2) fmt_gemm_kernel(FmtGemmArgs a)
 
     // ---- activation requests: 4 WT slabs of 1 KiB per position, WT per wave; a sums slab per token tile and super-block ----
     const uint32_t lds0 = lds_address(smem), lane16 = lane * 16;
-    // (a base per tile, not per slab: scalar registers short of the 128-token kernels were kept in lanes of vector registers.  With this, one layer,
-    // every matrix in Q5_K, 70B 1024 tokens 5559 -> 5395 us, 8B 1685 -> 1650, Q6_K 14B 700 1777 -> 1750)
-    const uint8_t *abase[WT / 2];
+    // A base per tile, not per slab: scalar registers short of the 128-token kernels were kept in lanes of vector registers.  (One layer,
+    // every matrix in Q5_K, 70B 1024 tokens 5559 -> 5395 us, 8B 1685 -> 1650, Q6_K 14B 700 1777 -> 1750; FP16, which has them free: 8B 128 tokens a base per tile 327, per slab 320, before 325.)
+    constexpr int PER_BASE = H ? 1 : 2;
+    const uint8_t *abase[WT / PER_BASE];
 #pragma unroll
-    for (int j = 0; j < WT / 2; ++j) abase[j] = a.A + static_cast<int64_t>(min(tile0 + wave * (WT / 2) + j, a.n_tiles - 1)) * nb * GM_TILE_BYTES;
+    for (int j = 0; j < WT / PER_BASE; ++j) {
+        const int slab = wave * WT + j * PER_BASE;
+        abase[j] = a.A + (static_cast<int64_t>(min(tile0 + (slab >> 1), a.n_tiles - 1)) * nb * GM_SLABS + (slab & 1)) * 1024;
+    }
     auto issue = [&](int b, int s, int buf) __attribute__((always_inline)) {
         const int64_t off = (static_cast<int64_t>(b) * GM_SLABS + 2 * s) * 1024;
 #pragma unroll
         for (int j = 0; j < WT; ++j)
-            if (FULL || wave * WT + j < 2 * tiles) dma16_base(abase[j >> 1] + off + (j & 1) * 1024, lane16, lds0 + buf * L::A_SLOT + (wave * WT + j) * 1024);
+            if (FULL || wave * WT + j < 2 * tiles) dma16_base(abase[j / PER_BASE] + off + j % PER_BASE * 1024, lane16, lds0 + buf * L::A_SLOT + (wave * WT + j) * 1024);
     };
     auto issue_sums = [&](int b) __attribute__((always_inline)) {
         {
