@@ -389,7 +389,7 @@ int32_t prima_gemm_ksplit(int32_t T, int64_t n_rows, int64_t n_cols);
  * prima_layer_window_prefill_mixed for the other formats).
  * 1 <= T <= PRIMA_PREFILL_MAX_TOK, n_past + T <= kv_cap, L >= 1.  x_in, x_out: fp32 [T][e], device, 16-byte
  * aligned (x_out may be x_in).  workspace: device, 256-byte aligned, prima_prefill_workspace_bytes(d, kv_cap, T)
- * bytes, contents need not be kept.  Asynchronous on hip_stream; nothing is allocated.  Errors as for the decode call
+ * bytes (no fewer than for any shorter prompt), contents need not be kept.  Asynchronous on hip_stream; nothing is allocated.  Errors as for the decode call
  * (PRIMA_E_NULL, _SHAPE, _RANGE, _ALIGN, _WORKSPACE before anything is enqueued; PRIMA_E_DEVICE for a failed launch).
  */
 #define PRIMA_PREFILL_MAX_TOK 8192

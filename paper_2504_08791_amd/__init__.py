@@ -285,7 +285,7 @@ class Window:
 
     def prefill(self, x_in, n_past, x_out=None):
         """Prompt processing: all layers for the T = x_in.shape[0] consecutive tokens that follow the n_past cached
-        ones; returns x_out float32 [T, e].  The scratch is kept for the next call of this size."""
+        ones; returns x_out float32 [T, e].  The scratch is kept for the next call of no more tokens."""
         _need(x_in, torch.float32, "x_in")
         T = x_in.shape[0]
         need = _ffi.lib().prima_prefill_workspace_bytes(C.byref(self.dims), self.kv_cap, T)
